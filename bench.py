@@ -306,8 +306,8 @@ def phi_kernel_section(dev):
 def sdf_build_counts(ctx, part, params, build_ms):
     """Node-sample pairs of one sdf_build, counted by the library's counting
     variant (a separate, untimed build): pass 1 (nearest sample), pass 2
-    (kernel sum, samples of the visited tiles) and pairs inside the contact
-    ball, with their rates over the timed build."""
+    (evaluated for the kernel sum, interpolation points included) and pairs
+    inside the contact ball, with their rates over the timed build."""
     import torch
     ctx.set_option("sdf_stats", 1)
     ctx.sdf_build(part.samples.q, part.samples.n, part.samples.w, part.grid, params)
@@ -316,12 +316,13 @@ def sdf_build_counts(ctx, part, params, build_ms):
     ctx.set_option("sdf_stats", 0)
     dense = float(part.samples.count) * part.grid.size
     sec = build_ms * 1e-3
-    # VALU issue bound: the FP32 kernel's inner loops issue about 8 VALU
-    # instructions per pass-1 pair (FP64 distance and compares), 9 per pass-2
-    # pair (distance and ball test) and 18 more per pair inside the ball; the
-    # chip issues 256 CUs x 64 lanes x 2.4 GHz lane instructions per second
+    # VALU issue bound: the FP32 kernel's inner loops issue about 10 VALU
+    # instructions per pass-1 pair (FP64 distance and compares) and 16 per
+    # evaluated pass-2 pair (14 for the term, the rest its share of the ball
+    # test; distances and projections come from the matrix cores); the chip
+    # issues 256 CUs x 64 lanes x 2.4 GHz lane instructions per second
     lanes_per_s = 256 * 64 * 2.4e9
-    bound_ms = 1e3 * (8.0 * c["nearest"] + 9.0 * c["sum"] + 18.0 * c["in_ball"]) / lanes_per_s
+    bound_ms = 1e3 * (10.0 * c["nearest"] + 16.0 * c["sum"]) / lanes_per_s
     return {"build_ms": round(build_ms, 3), "samples": part.samples.count, "nodes": part.grid.size,
             "pairs_nearest": c["nearest"], "pairs_sum": c["sum"], "pairs_in_ball": c["in_ball"],
             "frac_of_dense": {k: round(v / dense, 4) for k, v in c.items()},

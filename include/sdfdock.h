@@ -116,11 +116,12 @@ const char *sdf_last_error(sdf_ctx ctx);
  *                   parity probe (for testing the failure path; default 0)
  *   "sdf_stats"     1: sdf_build (skeletal kernel) runs a counting variant that adds its
  *                   node-sample pairs to three counters (setting the option clears them):
- *                   "sdf_pairs_nearest" (pass 1: valid nodes x samples of the tiles
- *                   visited for the nearest sample), "sdf_pairs_sum" (pass 2: live nodes x
- *                   samples of the tiles visited for the kernel sum) and "sdf_pairs_in_ball"
- *                   (pairs inside the contact ball), read with sdf_ctx_get_option (which
- *                   synchronises the device).  For measurement, not for timed builds.
+ *                   "sdf_pairs_nearest" (pass 1: pairs evaluated for the nearest sample),
+ *                   "sdf_pairs_sum" (pass 2: pairs evaluated for the kernel sum, the
+ *                   interpolation points of far clusters among them) and "sdf_pairs_in_ball"
+ *                   (pairs inside the contact ball, those that interpolation points stand
+ *                   for included), read with sdf_ctx_get_option (which synchronises the
+ *                   device).  For measurement, not for timed builds.
  * With "graph" = 1 the fused launch sequence of a score_rotations call is
  * captured once and replayed while the buffers, shapes and stream stay the
  * same; the null stream cannot be captured and runs without a graph.
@@ -157,11 +158,15 @@ int sdf_ctx_stats_reset(sdf_ctx ctx);
  * q, nrm: n x 3 FP64 (positions, outward unit normals); w: n FP64 weights
  * (area elements; arc lengths in 2D) - FP64 in both precisions.  The
  * discrete decisions (nearest sample, membership, distance floor, and the
- * contact-ball test of samples within 1e-4 of its radius) are taken in FP64;
- * the kernel sum runs in the context's precision.  rho_out: complex,
+ * contact-ball test of samples near its radius) are taken in FP64; the kernel
+ * sum runs in the context's precision.  FP32 contexts replace clusters of
+ * samples that are small and far from a node by Chebyshev interpolation points
+ * (to 1e-6 of a cluster's terms); FP64 contexts sum every pair.  rho_out: complex,
  * g->n[0]*n[1]*n[2].  g, p: host structs.  Any grid shape is accepted.
- * The samples are put in Morton order in the context's workspace (about
+ * The samples are put in Hilbert order in the context's workspace (about
  * 70 bytes per sample), which the next call of any entry point may reuse.
+ * The FP32 sum uses about 200 bytes per sample more where the workspace cap
+ * allows; below that it sums pair by pair.
  * Errors: SDF_EINVAL (null pointer, n <= 0 or n > 2^30, bad grid, invalid
  * params), SDF_ENOMEM (workspace). */
 int sdf_build(sdf_ctx ctx, const void *q, const void *nrm, const void *w, int64_t n,
@@ -229,7 +234,7 @@ int sdf_build_phi(sdf_ctx ctx, const void *q, const void *nrm, const void *w, in
  *   d rho / d xi = -(2 rho + A sum_j w_j c_j K'(r_j) r_j) / xi.
  * Computed in FP64 in both precisions; sums across node bricks use FP64
  * atomics, so the last bits may vary between runs.  Same inputs and
- * constraints as sdf_build; the samples' Morton order lives in the context's
+ * constraints as sdf_build; the samples' Hilbert order lives in the context's
  * workspace.
  * Errors: as sdf_build. */
 int sdf_build_adjoint(sdf_ctx ctx, const void *q, const void *nrm, const void *w, int64_t n,

@@ -290,6 +290,16 @@ sdf::GridDesc desc(const sdf_grid* g) {
 
 int64_t gsize(const sdf_grid* g) { return int64_t(g->n[0]) * g->n[1] * g->n[2]; }
 
+// workspace of one sdf_build: with the FP32 sum's records and interpolation
+// points where they apply and fit the cap, else the least that it needs
+size_t build_ws_bytes(sdf_ctx ctx, int64_t ns, int kind) {
+    if (ctx->dtype == SDF_F32 && (kind == sdf::kPhiSkeletal || kind == sdf::kPhiInverseSquare)) {
+        const size_t fast = sdf::sdf_build_fast_bytes(ns);
+        if (!ctx->cap || fast <= ctx->cap) return fast;
+    }
+    return sdf::sdf_build_workspace_bytes(ns, kind);
+}
+
 void drop_graph(sdf_ctx ctx) {
     if (ctx->graph.exec) (void)hipGraphExecDestroy(ctx->graph.exec);
     if (ctx->graph.graph) (void)hipGraphDestroy(ctx->graph.graph);
@@ -764,7 +774,7 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
     const int nm = gm->n[0];
     const int64_t K = gsize(gm), G = gsize(gf);
     const int nparts = sdf::peak_parts<T>(N, planar);
-    const size_t sdf_ws = sdf::sdf_build_workspace_bytes(ns);
+    size_t sdf_ws = build_ws_bytes(ctx, ns, sdf::kPhiSkeletal);
     Carve cv{nullptr};
     cv.take(sizeof(double) * 4 * n_rot);
     cv.take(sizeof(double) * 9 * n_rot);
@@ -775,6 +785,7 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
     cv.take(2 * sizeof(T) * G);
     cv.take(sizeof(T) * nparts);
     cv.take(sizeof(int) * nparts);
+    if (ctx->cap && cv.off + sdf_ws > ctx->cap) sdf_ws = sdf::sdf_build_workspace_bytes(ns);
     cv.take(sdf_ws);
     int rc = ensure_ws(ctx, cv.off);
     if (rc) return rc;
@@ -797,7 +808,7 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
     SDF_TRY_HIP(ctx, sdf::launch_quat_to_rot<T>(qd, n_rot, r64, RT, s), "rotations");
     for (int64_t r = 0; r < n_rot; ++r) {
         SDF_TRY_HIP(ctx, sdf::launch_rotate_samples(q, nrm, ns, r64 + 9 * r, c, qr, nr, s), "rotate samples");
-        SDF_TRY_HIP(ctx, sdf::launch_sdf_build<T>(qr, nr, w, ns, desc(gm), pd, sdf::kPhiSkeletal, rho, wsb, s),
+        SDF_TRY_HIP(ctx, sdf::launch_sdf_build<T>(qr, nr, w, ns, desc(gm), pd, sdf::kPhiSkeletal, rho, wsb, sdf_ws, s),
                     "box sdf");
         SDF_TRY_HIP(ctx, sdf::launch_zero<T>(grid, G, s), "zero");
         SDF_TRY_HIP(ctx, sdf::launch_place_direct<T>(rho, nm, planar, T(w_node), N, grid, s), "place");
@@ -1073,8 +1084,9 @@ static int sdf_build_impl(sdf_ctx ctx, const void* q, const void* nrm, const voi
     const double* qd = static_cast<const double*>(q);
     const double* nd = static_cast<const double*>(nrm);
     const double* wd = static_cast<const double*>(w);
-    ctx->fused_cache_valid = false;  // the Morton-ordered samples share the workspace
-    rc = ensure_ws(ctx, sdf::sdf_build_workspace_bytes(n, kind));
+    ctx->fused_cache_valid = false;  // the ordered samples share the workspace
+    const size_t ws_bytes = build_ws_bytes(ctx, n, kind);
+    rc = ensure_ws(ctx, ws_bytes);
     if (rc) return rc;
     unsigned long long* stats = nullptr;
     if (ctx->opt_sdf_stats && kind == SDF_PHI_SKELETAL) {
@@ -1087,8 +1099,10 @@ static int sdf_build_impl(sdf_ctx ctx, const void* q, const void* nrm, const voi
         stats = ctx->stats_dev;
     }
     hipError_t e = ctx->dtype == SDF_F64
-                       ? sdf::launch_sdf_build<double>(qd, nd, wd, n, desc(g), pd, kind, rho_out, ctx->ws, s, stats)
-                       : sdf::launch_sdf_build<float>(qd, nd, wd, n, desc(g), pd, kind, rho_out, ctx->ws, s, stats);
+                       ? sdf::launch_sdf_build<double>(qd, nd, wd, n, desc(g), pd, kind, rho_out, ctx->ws, ws_bytes, s,
+                                                       stats)
+                       : sdf::launch_sdf_build<float>(qd, nd, wd, n, desc(g), pd, kind, rho_out, ctx->ws, ws_bytes, s,
+                                                       stats);
     if (e != hipSuccess) return hip_fail(ctx, e, "sdf_build");
     return SDF_OK;
 }
@@ -1120,7 +1134,7 @@ int sdf_build_adjoint(sdf_ctx ctx, const void* q, const void* nrm, const void* w
     const double* qd = static_cast<const double*>(q);
     const double* nd = static_cast<const double*>(nrm);
     const double* wd = static_cast<const double*>(w);
-    ctx->fused_cache_valid = false;  // the Morton-ordered samples share the workspace
+    ctx->fused_cache_valid = false;  // the ordered samples share the workspace
     rc = ensure_ws(ctx, sdf::sdf_build_workspace_bytes(n));
     if (rc) return rc;
     hipError_t e = ctx->dtype == SDF_F64

@@ -27,6 +27,7 @@ namespace {
 constexpr int kScanBlock = 256;
 constexpr int kScanPer = 8;
 constexpr int kScanTile = kScanBlock * kScanPer;  // values per block
+constexpr int kScanOneTiles = 8;
 constexpr int kSortBlock = 256;
 constexpr int kSortRounds = 16;
 constexpr int kSortTile = kSortBlock * kSortRounds;  // keys per block
@@ -74,8 +75,8 @@ __global__ __launch_bounds__(kScanBlock) void scan_tiles_kernel(const int* __res
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// one block: exclusive scan of the nb block totals in place, kScanTile at a time
-__global__ __launch_bounds__(kScanBlock) void scan_sums_kernel(int* __restrict__ sums, int64_t nb) {
+// one block: exclusive scan of nb values, kScanTile at a time (out may be in)
+__global__ __launch_bounds__(kScanBlock) void scan_one_kernel(const int* in, int* out, int64_t nb) {
     __shared__ int sh[kScanBlock / 64];
     int carry = 0;
     for (int64_t b0 = 0; b0 < nb; b0 += kScanTile) {
@@ -84,14 +85,14 @@ __global__ __launch_bounds__(kScanBlock) void scan_sums_kernel(int* __restrict__
         int s = 0;
 #pragma unroll
         for (int k = 0; k < kScanPer; ++k) {
-            v[k] = base + k < nb ? sums[base + k] : 0;
+            v[k] = base + k < nb ? in[base + k] : 0;
             s += v[k];
         }
         int total;
         int run = carry + block_exclusive(s, sh, &total);
 #pragma unroll
         for (int k = 0; k < kScanPer; ++k) {
-            if (base + k < nb) sums[base + k] = run;
+            if (base + k < nb) out[base + k] = run;
             run += v[k];
         }
         carry += total;
@@ -187,8 +188,13 @@ hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, void* temp,
     if (n <= 0) return hipSuccess;
     int* sums = static_cast<int*>(temp);
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
+    // a few tiles: one block walks them in less time than two more launches take
+    if (nb <= kScanOneTiles) {
+        hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(kScanBlock), 0, s, in, out, n);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(scan_tiles_kernel, dim3(unsigned(nb)), dim3(kScanBlock), 0, s, in, out, n, sums);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanBlock), 0, s, sums, nb);
+    hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(kScanBlock), 0, s, sums, sums, nb);
     hipLaunchKernelGGL(scan_add_kernel, dim3(unsigned(nb)), dim3(kScanBlock), 0, s, out, n, sums);
     return hipGetLastError();
 }

@@ -1,36 +1,54 @@
 // Skeletal density function on a grid (eq. 10A, 11, 12a, 13, 15, 16c, 17t).
 //
-// One thread per grid node; a block covers a compact 8 x 8 x 4 brick of
-// nodes (16 x 16 in the plane) so that positions relative to the brick's
-// corner are small.  Boundary samples stream through LDS in tiles of 256
-// that every thread reads by broadcast.
+// The boundary samples are put in Hilbert order (a stable sort of their
+// quantised positions) and cut into leaves of 64 consecutive samples, four
+// leaves to a parent, four parents to a grandparent and so on, every tree node
+// with the FP64 bounding box of its samples.  Runs of a Hilbert curve are
+// connected, so the boxes are compact at every level.
 //
-// The samples are first put in Morton order (a stable radix sort of their
-// quantised positions), so a tile of 256 consecutive samples covers a
-// compact patch of the boundary, and every tile gets an FP64 bounding box.
-// A brick then visits only the tiles that can matter to it:
-//   pass 1: tiles whose box lies within U of the brick, where U is the least,
-//           over all tiles, of the largest brick-to-tile-box distance (every
-//           node of the brick has a sample within U);
-//   pass 2: tiles whose box lies within (1 + eps) max xi_abs of the brick.
-// Both bounds are conservative, so the nodes see exactly the samples they
-// would see in a scan of all samples.
+// One wave owns a brick of 16 grid nodes (4 x 2 x 2, 4 x 4 in the plane): lane
+// = 16 g + n handles node n and, of every four samples, the g-th.  The wave
+// walks the tree depth first, the four lane groups testing four siblings at a
+// time, so it sees only what can matter to its own 16 nodes.
 //
-// Pass 1 finds the nearest sample (lowest original index on exact ties),
-// its membership sign and the distance floor test.  These are discrete
-// decisions, taken in FP64 from FP64 sample positions in both precisions,
-// so the classification of every node is the one an FP64 evaluation makes.
+// Pass 1 finds each node's nearest sample (lowest original index on exact
+// ties), its membership sign and the distance floor test.  These are discrete
+// decisions, taken in FP64 from FP64 sample positions in both precisions, so
+// the classification of every node is the one an FP64 evaluation makes.
 //
-// Pass 2 sums the kernel over the samples inside the eps-approximate contact
-// ball, in the context's precision T, on brick-relative coordinates, in
-// Morton order.  A sample whose squared distance lies within 1e-4 (relative)
-// of the ball's squared radius is re-tested in FP64.
+// Pass 2 sums the kernel over the eps-approximate contact ball in the
+// context's precision T.  Tree nodes outside every node's ball are dropped;
+// a sample whose squared distance lies within 4e-6 (relative) of the ball's
+// squared radius is re-tested in FP64.
 //
 // With r = eta / |xi| the kernel of eq. 15 on zeta = xi + i eta reduces to
 //   phi = lambda / (2 pi sigma xi^2) * G(r) * P(r) / (1 + r^2)^2,
 //   G = exp(-(r - 1)^2 / (2 sigma^2)),  P = (1 - i r)^2 outside, (1 + i r)^2 inside,
 // so a pair costs one reciprocal square root, one exponential and one
 // reciprocal, with no trigonometric calls.
+//
+// Two things make the FP32 sum cheap (FP64 contexts sum every pair):
+//   - Far clusters by interpolation.  Seen from a node, a cluster that lies
+//     wholly inside its ball and is small against its distance and against xi
+//     contributes a smooth function of the sample position, so its samples
+//     are replaced by a tensor grid of Chebyshev points over its box carrying
+//     sum_j L_m(q_j) w_j n_j (L_m the Lagrange polynomials): the same pair
+//     term over fewer points.  The orders follow the ellipse of analyticity
+//     (error rho^-p below kInterpEps per cluster), one per axis, so flat
+//     clusters get flat grids.
+//   - Distances and projections on the matrix cores.  With both positions
+//     relative to the cluster's centre, |p - q|^2 = |p|^2 + (-2 q, |q|^2).(p, 1) and
+//     (p - q).wn = (wn, -q.wn).(p, 1): two 16 x 16 x 4 FP32 MFMAs give 16 nodes x 16
+//     samples of each, 9 of the 23 vector instructions of a pair.  Clusters
+//     closer than their own radius cancel too much and take differences.
+// Bound by VALU issue (88% busy): about 60 instructions per 16 x 16 pairs beyond
+// the 14 of each pair's term.  Measured, whole builds on 128^3 nodes: 242k samples
+// of a union of 2000 spheres 322 -> 64 ms, 15.7k samples of a box with a bore 23.0
+// -> 10.3 ms (from one 256-node brick per block with LDS tiles of 256 samples,
+// every pair of the visited tiles summed); error against 64 bits of the latter
+// 6.9e-7 -> 2.2e-7 (2-norm).
+#include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -41,11 +59,33 @@ namespace {
 
 constexpr int kSdfBlock = 256;
 constexpr int kSdfTile = 256;
+constexpr int kLeaf = 64;       // samples per leaf
+constexpr int kFan = 4;         // children per tree node
+constexpr int kMaxLevels = 14;  // 64 * 4^13 > 2^30 samples
+constexpr int kBrick = 16;      // grid nodes per wave
+static_assert(kSdfTile == kLeaf * kFan, "a 256-sample tile is a first-level tree node");
+
+// interpolation of far clusters: error target of one cluster, largest order
+// per axis, largest share of a cluster's samples worth replacing, and the
+// factor of xi that bounds the accepted size (at sigma = 0.5, the Gaussian's
+// width in r)
+constexpr double kInterpEps = 1e-6;
+constexpr int kInterpMax = 12;
+constexpr double kInterpShare = 0.4;
+constexpr double kInterpXi = 1.2;
+constexpr int kInterpSplit = 2048;  // samples per block of the weight sums
+
+// relative half-width of the band around the ball's squared radius that is
+// decided in FP64.  FP32 squared distances are nearer than that: differences
+// give them to 4e-7; the matrix form sums |p|^2, -2 p.q and |q|^2, at most (|p| + |q|)^2
+// <= 9 d^2 where it is used (|q| <= d), in five roundings of 6e-8.
+constexpr double kBallBand = 4e-6;
 
 template <typename T>
 struct __align__(4 * sizeof(T)) v4 {
     T x, y, z, w;
 };
+using f32x4 = float __attribute__((ext_vector_type(4)));
 
 // FP32 uses the hardware approximations directly (about 1 ulp each):
 // v_rsq_f32 (live pairs have d^2 >= xi_floor^2, far from denormals),
@@ -72,6 +112,449 @@ __device__ __forceinline__ float dev_rcp<float>(float x) { return __builtin_amdg
 template <>
 __device__ __forceinline__ double dev_rcp<double>(double x) { return 1.0 / x; }
 
+// ---- sample tree
+struct TreeNode {
+    double lo[3], hi[3];  // box of the node's samples (infinite if one is not finite)
+    double c[3];          // grid-lattice point nearest the box centre: origin of the node's FP32 records
+    float reach2;         // square of the distance and xi from which its interpolation points stand in; < 0: none
+    float qmax2;          // leaves: largest squared sample distance from c
+    int px;               // first 16-point record group of the interpolation points
+    int order;            // their orders per axis, 4 bits each
+};
+struct SampleTree {
+    const TreeNode* node;
+    int levels;            // level 0: leaves; the top level has at most kFan nodes
+    int off[kMaxLevels];   // first node of each level
+    int cnt[kMaxLevels];
+};
+
+__host__ __device__ inline int order_count(int o) { return (o & 15) * ((o >> 4) & 15) * ((o >> 8) & 15); }
+
+// most interpolation points of a cluster of `size` samples, in whole groups of 16
+__host__ __device__ inline int interp_cap(int64_t size) {
+    const int64_t m = int64_t(kInterpShare * double(size));
+    const int64_t top = int64_t(kInterpMax) * kInterpMax * kInterpMax;
+    return int(((m < top ? m : top) + 15) / 16 * 16);
+}
+
+__device__ __forceinline__ double dist2(double dx, double dy, double dz) {
+    return __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+}
+// least and largest squared distance from p to a node's box
+__device__ __forceinline__ double node_dmin2(const TreeNode& t, double px, double py, double pz) {
+    const double dx = fmax(0.0, fmax(t.lo[0] - px, px - t.hi[0]));
+    const double dy = fmax(0.0, fmax(t.lo[1] - py, py - t.hi[1]));
+    const double dz = fmax(0.0, fmax(t.lo[2] - pz, pz - t.hi[2]));
+    return dist2(dx, dy, dz);
+}
+__device__ __forceinline__ double node_dmax2(const TreeNode& t, double px, double py, double pz) {
+    const double dx = fmax(t.hi[0] - px, px - t.lo[0]);
+    const double dy = fmax(t.hi[1] - py, py - t.lo[1]);
+    const double dz = fmax(t.hi[2] - pz, pz - t.lo[2]);
+    return dist2(dx, dy, dz);
+}
+
+// Sibling groups of a depth-first walk: a level, the first of its (up to
+// four) siblings, and per level the siblings still to visit, 4 bits each.
+struct Walk {
+    int l, base;
+    uint64_t pend;
+    __device__ __forceinline__ int take() {  // next sibling of the current group (there is one)
+        const int m = int(pend >> (4 * l)) & 15;
+        pend &= ~(uint64_t(m & -m) << (4 * l));
+        return base + __builtin_ctz(unsigned(m));
+    }
+    __device__ __forceinline__ void down(int i) {
+        --l;
+        base = kFan * i;
+    }
+    // climbs to the nearest level with siblings left; false at the end
+    __device__ __forceinline__ bool climb(int levels) {
+        while (((pend >> (4 * l)) & 15) == 0) {
+            if (++l >= levels) return false;
+            base = (base >> 2) & ~3;
+        }
+        return true;
+    }
+};
+// bit g set if any lane of lane group g has its bit in m
+__device__ __forceinline__ int group_any(uint64_t m) {
+    return (m & 0xffffull ? 1 : 0) | (m & 0xffff0000ull ? 2 : 0) | (m & 0xffff00000000ull ? 4 : 0) |
+           (m >> 48 ? 8 : 0);
+}
+
+// bricks of kBrick nodes
+struct BrickGrid {
+    int sx, sy, sz, nx, ny, nz;
+};
+__host__ __device__ inline BrickGrid wave_bricks(int gx, int gy, int gz) {
+    BrickGrid b{4, gz == 1 ? 4 : 2, gz == 1 ? 1 : 2, 0, 0, 0};
+    b.nx = (gx + b.sx - 1) / b.sx;
+    b.ny = (gy + b.sy - 1) / b.sy;
+    b.nz = (gz + b.sz - 1) / b.sz;
+    return b;
+}
+
+// the nearer of two candidates (Hilbert positions): lower squared distance,
+// then lower original index
+__device__ __forceinline__ void nearer(double d2, int s, const int* __restrict__ js, double& best, int& sbest) {
+    if (d2 < best || (d2 == best && sbest >= 0 && s >= 0 && js[s] < js[sbest])) {
+        best = d2;
+        sbest = s;
+    }
+}
+
+// PHI: the kernel of eq. 13 (kPhi* in launch.hpp): skeletal (eq. 15),
+// inverse-square (eq. 15 with the medial Gaussian at its peak: the pair
+// term without the exponential), or the double skin layer of eq. 3a, which
+// needs only the signed distance of pass 1.
+// FAST (FP32): pass 2 over the FP32 records with interpolated far clusters and
+// MFMA distances; otherwise over the FP64 samples, pair by pair.
+// WPB: waves per brick.  4 waves share the samples of a brick (and meet in
+// LDS after each pass) where a grid has too few bricks to fill the chip.
+// STATS (measurement builds only): adds to stats[0..2] the node-sample pairs
+// evaluated in pass 1, the pairs (and interpolation points) evaluated in pass
+// 2, and the pairs inside the contact ball, represented ones included.
+template <typename T, int PHI, bool FAST, int WPB, bool STATS = false>
+__global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_build_kernel(const double* __restrict__ q,
+                                                              const double* __restrict__ nrm,
+                                                              const double* __restrict__ qs,
+                                                              const double* __restrict__ wn,
+                                                              const int* __restrict__ js,
+                                                              const TreeNode* __restrict__ nodes, SampleTree tr,
+                                                              const float* __restrict__ rec1,
+                                                              const float* __restrict__ rec2, int64_t ns, GridDesc g,
+                                                              ParamDesc prm, cplx<T>* __restrict__ out,
+                                                              unsigned long long* __restrict__ stats) {
+    static_assert(WPB == 1 || WPB == 4, "waves per brick");
+    __shared__ double sh_best[WPB == 4 ? 256 : 1];
+    __shared__ __align__(8) int sh_idx[WPB == 4 ? 256 : 2];
+    const int lane = int(threadIdx.x) & 63, sub = WPB == 1 ? 0 : uniform(int(threadIdx.x) >> 6);
+    const int n = lane & 15, gq = lane >> 4;
+    const int64_t brick = blockIdx.x;
+    const BrickGrid bg = wave_bricks(g.nx, g.ny, g.nz);
+    // Consecutive blocks go to the XCDs and their shader engines in turn, so a
+    // row of bricks as long as a multiple of their number would give each
+    // engine one column of the grid, whose work differs several times over:
+    // every row starts at another column.
+    const int by = int((brick / bg.nx) % bg.ny), bz = int(brick / (int64_t(bg.nx) * bg.ny));
+    const int bx = int((brick + 5 * by + 11 * bz) % bg.nx);
+    const int i = bx * bg.sx + (n & 3), j = by * bg.sy + ((n >> 2) & (bg.sy - 1)),
+              k = bz * bg.sz + (n >> 2) / bg.sy;
+    const bool valid = i < g.nx && j < g.ny && k < g.nz;
+    const double px = g.ox + g.h * i, py = g.oy + g.h * j, pz = g.oz + g.h * k;
+    unsigned long long vis1 = 0, vis2 = 0, inball = 0;
+
+    // ---- pass 1 (FP64): nearest sample, lowest original index on exact ties
+    double best = INFINITY;  // over the samples this lane has seen
+    double bound = INFINITY;  // over those its node's four lanes have seen
+    int sbest = -1;
+    auto leaf_nearest = [&](int leaf) {
+        const int64_t s0 = int64_t(leaf) * kLeaf;
+        const int cnt = int(ns - s0 < kLeaf ? ns - s0 : kLeaf);
+        if (STATS && valid)
+            for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) ++vis1;
+#pragma unroll 4
+        for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) {
+            const int64_t s = s0 + a;
+            nearer(dist2(px - qs[3 * s], py - qs[3 * s + 1], pz - qs[3 * s + 2]), int(s), js, best, sbest);
+        }
+        bound = fmin(best, __shfl_xor(best, 16));
+        bound = fmin(bound, __shfl_xor(bound, 32));
+    };
+    {
+        // a first bound from the leaf found by going down towards the brick
+        // (its first node), the nearest sibling at every level
+        const double ax = __shfl(px, 0), ay = __shfl(py, 0), az = __shfl(pz, 0);
+        int at = 0;
+        for (int l = tr.levels - 1; l >= 0; --l) {
+            const int c = at + gq;
+            double d = c < tr.cnt[l] ? node_dmin2(nodes[tr.off[l] + c], ax, ay, az) : INFINITY;
+            int id = c;
+#pragma unroll
+            for (int off = 16; off <= 32; off <<= 1) {
+                const double d1 = __shfl_xor(d, off);
+                const int i1 = __shfl_xor(id, off);
+                if (d1 < d || (d1 == d && i1 < id)) {
+                    d = d1;
+                    id = i1;
+                }
+            }
+            id = __builtin_amdgcn_readfirstlane(id);
+            if (l == 0) leaf_nearest(id);
+            else at = kFan * id;
+        }
+    }
+    {
+        Walk w{tr.levels - 1, 0, 0};
+        auto test = [&]() {
+            const int c = w.base + gq;
+            // prune only beyond rounding of either side; NaN bounds (no finite sample yet) keep walking
+            const bool hit = valid && c < tr.cnt[w.l] &&
+                             !(node_dmin2(nodes[tr.off[w.l] + c], px, py, pz) > bound * (1.0 + 1e-9));
+            w.pend |= uint64_t(group_any(__ballot(hit))) << (4 * w.l);
+        };
+        test();
+        while (w.climb(tr.levels)) {
+            const int c = w.take();
+            if (w.l == 0) {
+                leaf_nearest(c);
+            } else {
+                w.down(c);
+                test();
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+        const double d1 = __shfl_xor(best, off);
+        const int s1 = __shfl_xor(sbest, off);
+        nearer(d1, s1, js, best, sbest);
+    }
+    if constexpr (WPB == 4) {
+        sh_best[threadIdx.x] = best;
+        sh_idx[threadIdx.x] = sbest;
+        __syncthreads();
+#pragma unroll
+        for (int wv = 0; wv < 4; ++wv) nearer(sh_best[64 * wv + n], sh_idx[64 * wv + n], js, best, sbest);
+        __syncthreads();
+    }
+    const int64_t jb = sbest >= 0 ? js[sbest] : 0;
+    const double dot = (px - q[3 * jb]) * nrm[3 * jb] + (py - q[3 * jb + 1]) * nrm[3 * jb + 1] +
+                       (pz - q[3 * jb + 2]) * nrm[3 * jb + 2];
+    const int pmc = dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
+    const double xi_abs64 = sqrt(best);
+    const bool writer = valid && gq == 0 && sub == 0;
+    cplx<T>* dst = out + (int64_t(k) * g.ny + j) * g.nx + i;
+    if constexpr (PHI == kPhiDsl) {
+        // eq. 3a: lambda1 gb(xi / R - 1) + i lambda2 gb(xi / R + 1), FP64, defined
+        // on the boundary too (no floor); gb truncates at |x| > eps
+        if (writer) {
+            const double xi = pmc * xi_abs64;
+            const double x1 = xi / prm.radius - 1.0, x2 = xi / prm.radius + 1.0;
+            const double c = 1.0 / (2.5066282746310002 * prm.sigma);
+            const double h = -0.5 / (prm.sigma * prm.sigma);
+            const double re = fabs(x1) <= prm.eps ? prm.lambda1 * c * exp(h * x1 * x1) : 0.0;
+            const double im = fabs(x2) <= prm.eps ? prm.lambda2 * c * exp(h * x2 * x2) : 0.0;
+            *dst = mk(T(re), T(im));
+        }
+        return;
+    }
+    const bool live = valid && pmc != 0 && xi_abs64 >= prm.xi_floor;
+
+    // ---- pass 2 (T): truncated kernel sum over the contact ball
+    const double r2max64 = (1.0 + prm.eps) * (1.0 + prm.eps) * best;
+    const T r2lo = T(r2max64 * (1.0 - kBallBand)), r2hi = T(r2max64 * (1.0 + kBallBand));
+    const float r2mid = float(r2max64), r2gap = float(r2max64 * kBallBand), r2above = r2mid * (1.f + 2.4e-7f);
+    const T inv_xi = T(1.0 / xi_abs64), inv_xi2 = T(1.0 / best);
+    // exp(-(r - 1)^2 / (2 sigma^2)) = 2^(-u^2) with u = (r - 1) gs,
+    // gs = sqrt(log2(e) / 2) / sigma, and u = eta (gs / xi) - gs
+    const double gs64 = std::sqrt(0.5 * 1.4426950408889634) / prm.sigma;
+    const T gs = T(gs64), inv_xi_gs = T(gs64 / xi_abs64);
+    T acc_re = T(0), acc_im = T(0);  // sums of coef (1 - r^2) and of coef eta
+    auto pair_term = [&](T d2, T wdot) {
+        const T inv_eta = fast_rsqrt(d2);
+        const T eta = d2 * inv_eta;
+        T coef = wdot * inv_eta;
+        if constexpr (PHI == kPhiSkeletal) {
+            const T u = eta * inv_xi_gs - gs;
+            coef *= dev_exp2(-u * u);
+        }
+        const T den = T(1) + d2 * inv_xi2;
+        coef *= dev_rcp(den * den);
+        acc_re += coef * (T(1) - d2 * inv_xi2);
+        acc_im += coef * eta;
+    };
+    auto edge_in = [&](int64_t s) {  // the ball test of sample s in FP64
+        return dist2(px - qs[3 * s], py - qs[3 * s + 1], pz - qs[3 * s + 2]) <= r2max64;
+    };
+    // 16 samples (or interpolation points) per group from group `grp0` on, with
+    // positions relative to c; s0: Hilbert position of the first sample.  A node
+    // that the item does not concern takes d^2 = 1 and w.d = 0: no lane is masked.
+    auto matrix_item = [&](auto cut_tag, const double c[3], int grp0, int ngrp, bool mine, int64_t s0) {
+        constexpr bool cut = decltype(cut_tag)::value;
+        const float fx = float(px - c[0]), fy = float(py - c[1]), fz = float(pz - c[2]);
+        const float b = !mine ? 0.f : (gq == 0 ? fx : (gq == 1 ? fy : (gq == 2 ? fz : 1.f)));
+        const float p2 = mine ? fx * fx + fy * fy + fz * fz : 1.f;
+        const f32x4 cc = {p2, p2, p2, p2}, zero = {0.f, 0.f, 0.f, 0.f};
+        // a group's operands through buffer descriptors: scalar offsets, no vector address arithmetic
+        const int last = ngrp - 1;
+        const auto d1 = buffer_rsrc(rec1 + 64 * int64_t(grp0), uint32_t(ngrp) * 256);
+        const auto d2r = buffer_rsrc(rec2 + 64 * int64_t(grp0), uint32_t(ngrp) * 256);
+        auto load1 = [&](int gr) {
+            return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(d1, 4 * lane, 256 * min(gr, last), 0));
+        };
+        auto load2 = [&](int gr) {
+            return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(d2r, 4 * lane, 256 * min(gr, last), 0));
+        };
+        auto terms = [&](f32x4 d2, f32x4 wd, int gr) {
+            if constexpr (cut) {
+                const float gap = fminf(fminf(fabsf(d2[0] - r2mid), fabsf(d2[1] - r2mid)),
+                                        fminf(fabsf(d2[2] - r2mid), fabsf(d2[3] - r2mid)));
+                if (gap <= r2gap) {  // near the sphere: FP64 decides, and d^2 is moved to its side
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int64_t sr = s0 + 16 * gr + 4 * gq + r;
+                        if (fabsf(d2[r] - r2mid) <= r2gap && sr < ns)
+                            d2[r] = edge_in(sr) ? fminf(d2[r], r2mid) : fmaxf(d2[r], r2above);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (STATS && mine && d2[r] <= r2mid && s0 + 16 * gr + 4 * gq + r < ns) ++inball;
+                    wd[r] = d2[r] <= r2mid ? wd[r] : 0.f;
+                }
+            }
+            if (STATS && mine) vis2 += 4;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pair_term(T(d2[r]), T(wd[r]));
+        };
+        // the next group's operands load under this group's terms; seven waves per SIMD hide the rest
+        float u0 = load1(sub), v0 = load2(sub);
+        for (int gr = sub; gr < ngrp; gr += WPB) {
+            const f32x4 da = __builtin_amdgcn_mfma_f32_16x16x4f32(u0, b, cc, 0, 0, 0);
+            const f32x4 wa = __builtin_amdgcn_mfma_f32_16x16x4f32(v0, b, zero, 0, 0, 0);
+            u0 = load1(gr + WPB);
+            v0 = load2(gr + WPB);
+            terms(da, wa, gr);
+        }
+    };
+    // the pairs of a leaf by differences
+    auto plain_leaf = [&](const double c[3], int leaf) {
+        const int64_t s0 = int64_t(leaf) * kLeaf;
+        const int cnt = int(ns - s0 < kLeaf ? ns - s0 : kLeaf);
+        if (!live) return;
+        const T cx = T(px - c[0]), cy = T(py - c[1]), cz = T(pz - c[2]);
+        for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) {
+            const int64_t s = s0 + a;
+            T dx, dy, dz, wx, wy, wz;
+            if constexpr (FAST) {
+                const int64_t o = (s >> 4) * 64 + (s & 15);
+                dx = cx + T(0.5f * rec1[o]);
+                dy = cy + T(0.5f * rec1[o + 16]);
+                dz = cz + T(0.5f * rec1[o + 32]);
+                wx = T(rec2[o]);
+                wy = T(rec2[o + 16]);
+                wz = T(rec2[o + 32]);
+            } else {
+                dx = T(px - qs[3 * s]);
+                dy = T(py - qs[3 * s + 1]);
+                dz = T(pz - qs[3 * s + 2]);
+                wx = T(wn[3 * s]);
+                wy = T(wn[3 * s + 1]);
+                wz = T(wn[3 * s + 2]);
+            }
+            const T d2 = dx * dx + dy * dy + dz * dz;
+            if (STATS) ++vis2;
+            if (d2 <= r2hi) {
+                const bool in = d2 <= r2lo || edge_in(s);
+                if (in) {
+                    if (STATS) ++inball;
+                    pair_term(d2, dx * wx + dy * wy + dz * wz);
+                }
+            }
+        }
+    };
+    {
+        // accepted sizes: within kInterpXi of xi at sigma >= 0.5, less for narrower Gaussians
+        const double fs = kInterpXi * fmin(1.0, 2.0 * prm.sigma);
+        const double xi2 = fs * fs * best;
+        const double r2out = r2max64 * (1.0 + 1e-9), r2in = r2max64 * (1.0 - 1e-9);
+        Walk w{tr.levels - 1, 0, 0};
+        auto visit = [&]() {  // tests four siblings, sums those that need no descent
+            const int cnt = tr.cnt[w.l], off = tr.off[w.l];
+            const int c = w.base + gq;
+            const TreeNode& t = nodes[off + (c < cnt ? c : w.base)];
+            const double dmin2 = node_dmin2(t, px, py, pz);
+            const bool reach = live && c < cnt && !(dmin2 > r2out);
+            const bool cut = reach && !(node_dmax2(t, px, py, pz) <= r2in);
+            bool far = false;
+            if constexpr (FAST)
+                far = t.reach2 >= 0.f &&
+                      double(t.reach2) <= fmin(xi2, dist2(px - 0.5 * (t.lo[0] + t.hi[0]), py - 0.5 * (t.lo[1] + t.hi[1]),
+                                                          pz - 0.5 * (t.lo[2] + t.hi[2])));
+            const uint64_t m_reach = __ballot(reach), m_cut = __ballot(cut);
+            const uint64_t m_fail = FAST ? __ballot(reach && (cut || !far)) : m_reach;
+            const uint64_t m_near = __ballot(reach && (w.l > 0 || dmin2 < double(t.qmax2)));
+            int open = group_any(m_reach);
+            const int cuts = group_any(m_cut), fails = group_any(m_fail), nears = group_any(m_near);
+            int later = 0;
+            while (open) {
+                const int e = __builtin_ctz(unsigned(open));
+                open &= open - 1;
+                const TreeNode& te = nodes[off + w.base + e];
+                const bool mine = (m_reach >> (16 * e + n)) & 1;
+                if (FAST && !((fails >> e) & 1)) {
+                    matrix_item(std::false_type{}, te.c, uniform(te.px), uniform((order_count(te.order) + 15) >> 4), mine,
+                                0);
+                    if (STATS && mine && gq == 0 && sub == 0) {
+                        const int64_t size = int64_t(kLeaf) << (2 * w.l), s0 = size * (w.base + e);
+                        inball += ns - s0 < size ? ns - s0 : size;
+                    }
+                } else if (w.l > 0) {
+                    later |= 1 << e;
+                } else if (FAST && !((nears >> e) & 1)) {
+                    const bool ce = (cuts >> e) & 1;
+                    const int64_t s0 = int64_t(w.base + e) * kLeaf;
+                    const int cnt_s = int(ns - s0 < kLeaf ? ns - s0 : kLeaf);
+                    if (ce) matrix_item(std::true_type{}, te.c, int(s0 >> 4), (cnt_s + 15) >> 4, mine, s0);
+                    else matrix_item(std::false_type{}, te.c, int(s0 >> 4), (cnt_s + 15) >> 4, mine, s0);
+                    if (STATS && !ce && mine)
+                        for (int a = 4 * sub + gq; a < cnt_s; a += 4 * WPB) ++inball;
+                } else {
+                    plain_leaf(te.c, w.base + e);
+                }
+            }
+            w.pend |= uint64_t(later) << (4 * w.l);
+        };
+        if (__ballot(live)) {
+            visit();
+            while (w.climb(tr.levels)) {
+                w.down(w.take());
+                visit();
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+        acc_re += __shfl_xor(acc_re, off);
+        acc_im += __shfl_xor(acc_im, off);
+    }
+    if constexpr (WPB == 4) {
+        double* sh_im = reinterpret_cast<double*>(sh_idx);  // 64 sums fit
+        if (gq == 0) {
+            sh_best[16 * sub + n] = double(acc_re);
+            sh_im[16 * sub + n] = double(acc_im);
+        }
+        __syncthreads();
+        acc_re = T(sh_best[n]);
+        acc_im = T(sh_im[n]);
+#pragma unroll
+        for (int wv = 1; wv < 4; ++wv) {
+            acc_re += T(sh_best[16 * wv + n]);
+            acc_im += T(sh_im[16 * wv + n]);
+        }
+    }
+    if constexpr (STATS) {
+        unsigned long long c[3] = {vis1, vis2, inball};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            for (int off = 32; off > 0; off >>= 1) c[a] += __shfl_xor(c[a], off);
+            if (lane == 0) atomicAdd(stats + a, c[a]);
+        }
+    }
+    if (writer) {
+        cplx<T> res = mk(T(0), T(0));
+        if (live) {
+            const double lam = pmc > 0 ? prm.lambda1 : -prm.lambda2;
+            const T scale = T(lam / (2.0 * 3.14159265358979323846 * prm.sigma * best));
+            const T im_sign = pmc > 0 ? T(-2) : T(2);  // P = (1 - r^2) -+ 2 i r, applied once per node
+            res = mk(acc_re * scale, acc_im * (im_sign * (inv_xi * scale)));
+        }
+        *dst = res;
+    }
+}
+
 // brick of nodes handled by one block
 struct Brick {
     int bx, by, bz;
@@ -88,7 +571,7 @@ __device__ __forceinline__ int opaque_zero() {
     return z;
 }
 
-// Samples in Morton order with per-tile bounding boxes.
+// Samples in Hilbert order with per-tile bounding boxes.
 struct SampleTiles {
     const double* qs;   // positions, n x 3
     const double* wn;   // w_j n_j, n x 3
@@ -176,162 +659,6 @@ __device__ __forceinline__ void nearest_pass(const SampleTiles& st, int64_t ns, 
                 }
             }
         }
-    }
-}
-
-// PHI: the kernel of eq. 13 (kPhi* in launch.hpp): skeletal (eq. 15),
-// inverse-square (eq. 15 with the medial Gaussian at its peak: the pair
-// term without the exponential), or the double skin layer of eq. 3a, which
-// needs only the signed distance of pass 1.
-// STATS (measurement builds only): the block adds to stats[0..2] the
-// node-sample pairs of pass 1 (valid nodes x samples of the visited tiles),
-// of pass 2 (live nodes x samples of the visited tiles) and the pass-2 pairs
-// inside the contact ball.
-template <typename T, int PHI, bool STATS = false>
-__global__ __launch_bounds__(kSdfBlock) void sdf_build_kernel(const double* __restrict__ q,
-                                                              const double* __restrict__ nrm, SampleTiles st,
-                                                              int64_t ns, GridDesc g, ParamDesc prm,
-                                                              cplx<T>* __restrict__ out,
-                                                              unsigned long long* __restrict__ stats = nullptr) {
-    __shared__ v4<double> sq[2 * kSdfTile];  // pass 1: (qx, qy, qz, -); pass 2: reused as two T tiles
-    __shared__ int sidx[kSdfTile];           // pass 1: original index; pass 2: Morton index
-    __shared__ int tflag[kSdfBlock];         // tiles of the current chunk that the brick visits
-    __shared__ double red[kSdfBlock / 64];
-    v4<T>* sq2 = reinterpret_cast<v4<T>*>(sq);             // (qx, qy, qz, -) relative to the brick
-    v4<T>* sn2 = reinterpret_cast<v4<T>*>(sq) + kSdfTile;  // w (nx, ny, nz), -
-
-    const Brick br = brick_shape(g.nz);
-    const int nbx = (g.nx + br.bx - 1) / br.bx, nby = (g.ny + br.by - 1) / br.by;
-    const int blk = blockIdx.x;
-    const int i0 = (blk % nbx) * br.bx, j0 = ((blk / nbx) % nby) * br.by, k0 = (blk / (nbx * nby)) * br.bz;
-    const int li = threadIdx.x % br.bx, lj = (threadIdx.x / br.bx) % br.by, lk = threadIdx.x / (br.bx * br.by);
-    const int i = i0 + li, j = j0 + lj, k = k0 + lk;
-    const bool valid = i < g.nx && j < g.ny && k < g.nz;
-    // brick corner (FP64) and this node relative to it
-    const double cx = g.ox + g.h * i0, cy = g.oy + g.h * j0, cz = g.oz + g.h * k0;
-    const double rx = g.h * li, ry = g.h * lj, rz = g.h * lk;
-    const double px = cx + rx, py = cy + ry, pz = cz + rz;
-    // box of the brick's nodes inside the grid
-    const double bl[3] = {cx, cy, cz};
-    const double bh[3] = {cx + g.h * (min(br.bx, g.nx - i0) - 1), cy + g.h * (min(br.by, g.ny - j0) - 1),
-                          cz + g.h * (min(br.bz, g.nz - k0) - 1)};
-
-    // ---- pass 1 (FP64): nearest sample, lowest original index on exact ties
-    double best;
-    int jbest;
-    int64_t vis1 = 0, vis2 = 0, inball = 0;
-    nearest_pass(st, ns, bl, bh, px, py, pz, sq, sidx, tflag, red, best, jbest, STATS ? &vis1 : nullptr);
-    const int64_t jb = jbest;
-    const double dot = (px - q[3 * jb]) * nrm[3 * jb] + (py - q[3 * jb + 1]) * nrm[3 * jb + 1] +
-                       (pz - q[3 * jb + 2]) * nrm[3 * jb + 2];
-    const int pmc = dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
-    const double xi_abs64 = sqrt(best);
-    if constexpr (PHI == kPhiDsl) {
-        // eq. 3a: lambda1 gb(xi / R - 1) + i lambda2 gb(xi / R + 1), FP64, defined
-        // on the boundary too (no floor); gb truncates at |x| > eps
-        if (valid) {
-            const double xi = pmc * xi_abs64;
-            const double x1 = xi / prm.radius - 1.0, x2 = xi / prm.radius + 1.0;
-            const double c = 1.0 / (2.5066282746310002 * prm.sigma);
-            const double h = -0.5 / (prm.sigma * prm.sigma);
-            const double re = fabs(x1) <= prm.eps ? prm.lambda1 * c * exp(h * x1 * x1) : 0.0;
-            const double im = fabs(x2) <= prm.eps ? prm.lambda2 * c * exp(h * x2 * x2) : 0.0;
-            out[(int64_t(k) * g.ny + j) * g.nx + i] = mk(T(re), T(im));
-        }
-        return;
-    }
-    const bool live = valid && pmc != 0 && xi_abs64 >= prm.xi_floor;
-
-    // ---- pass 2 (T): truncated kernel sum over the contact ball
-    const double r2max64 = (1.0 + prm.eps) * (1.0 + prm.eps) * best;
-    const double r2brick = block_reduce<true>(live ? r2max64 : -1.0, red) * (1.0 + 1e-9);
-    const T r2lo = T(r2max64 * (1.0 - 1e-4)), r2hi = T(r2max64 * (1.0 + 1e-4));
-    const T inv_xi = T(1.0 / xi_abs64);
-    // exp(-(r - 1)^2 / (2 sigma^2)) = 2^(-u^2) with u = (r - 1) gs,
-    // gs = sqrt(log2(e) / 2) / sigma, and u = eta (gs / xi) - gs
-    const double gs64 = std::sqrt(0.5 * 1.4426950408889634) / prm.sigma;
-    const T gs = T(gs64), inv_xi_gs = T(gs64 / xi_abs64);
-    const T im_sign = pmc > 0 ? T(-2) : T(2);  // P = (1 - r^2) -+ 2 i r, applied once per node
-    const T prx = T(rx), pry = T(ry), prz = T(rz);
-    T acc_re = T(0), acc_im = T(0);
-    if (r2brick >= 0.0) {  // uniform: some node of the brick is live
-        for (int64_t c0 = 0; c0 < st.ntile; c0 += kSdfBlock) {
-            const int64_t tc = c0 + threadIdx.x;
-            __syncthreads();
-            tflag[threadIdx.x] = tc < st.ntile && box_dmin2(bl, bh, st.box + 6 * tc) <= r2brick;
-            __syncthreads();
-            const int nchunk = int(st.ntile - c0 < kSdfBlock ? st.ntile - c0 : kSdfBlock);
-            for (int kk = 0; kk < nchunk; ++kk) {
-                if (!tflag[kk]) continue;  // uniform across the block
-                const int64_t t0 = (c0 + kk) * kSdfTile;
-                const int cnt = int(ns - t0 < kSdfTile ? ns - t0 : kSdfTile);
-                if (STATS && live) vis2 += cnt;
-                __syncthreads();
-                for (int a = threadIdx.x; a < cnt; a += kSdfBlock) {
-                    const int64_t s = t0 + a;
-                    sq2[a] = v4<T>{T(st.qs[3 * s] - cx), T(st.qs[3 * s + 1] - cy), T(st.qs[3 * s + 2] - cz), T(0)};
-                    sn2[a] = v4<T>{T(st.wn[3 * s]), T(st.wn[3 * s + 1]), T(st.wn[3 * s + 2]), T(0)};
-                    sidx[a] = int(s);
-                }
-                __syncthreads();
-                if (live) {
-                    const int z0 = opaque_zero();
-                    const v4<T>* sqb = sq2 + z0;
-                    const v4<T>* snb = sn2 + z0;
-#pragma unroll 4
-                    for (int a = 0; a < cnt; ++a) {
-                        const v4<T> s = sqb[a];
-                        const T dx = prx - s.x, dy = pry - s.y, dz = prz - s.z;
-                        const T d2 = dx * dx + dy * dy + dz * dz;
-                        bool in = d2 <= r2lo;
-                        if (!in && d2 <= r2hi) {  // near the sphere: decide in FP64
-                            const int64_t sj = sidx[a];
-                            const double ex = px - st.qs[3 * sj], ey = py - st.qs[3 * sj + 1],
-                                         ez = pz - st.qs[3 * sj + 2];
-                            in = ex * ex + ey * ey + ez * ez <= r2max64;
-                        }
-                        if (in) {
-                            if (STATS) ++inball;
-                            const v4<T> nv = snb[a];
-                            const T inv_eta = fast_rsqrt(d2);
-                            const T eta = d2 * inv_eta;
-                            const T r = eta * inv_xi;
-                            const T wcos = (dx * nv.x + dy * nv.y + dz * nv.z) * inv_eta;
-                            T G = T(1);  // inverse-square: the medial Gaussian at its peak
-                            if constexpr (PHI == kPhiSkeletal) {
-                                const T u = eta * inv_xi_gs - gs;
-                                G = dev_exp2(-u * u);
-                            }
-                            const T rr = r * r;
-                            const T den = T(1) + rr;
-                            const T coef = wcos * G * dev_rcp(den * den);
-                            acc_re += coef * (T(1) - rr);
-                            acc_im += coef * r;
-                        }
-                    }
-                }
-            }
-        }
-    }
-    if constexpr (STATS) {
-        // every thread walked the block's tiles: its pass-1 pairs are vis1
-        // when its node is valid, its pass-2 pairs vis2 when live
-        unsigned long long c[3] = {valid ? (unsigned long long)vis1 : 0ull, (unsigned long long)vis2,
-                                   (unsigned long long)inball};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            for (int off = 32; off > 0; off >>= 1) c[a] += __shfl_xor(c[a], off);
-            if ((threadIdx.x & 63) == 0) atomicAdd(stats + a, c[a]);
-        }
-    }
-    if (valid) {
-        cplx<T> res = mk(T(0), T(0));
-        if (live) {
-            const double lam = pmc > 0 ? prm.lambda1 : -prm.lambda2;
-            const T scale = T(lam / (2.0 * 3.14159265358979323846 * prm.sigma * best));
-            res = mk(acc_re * scale, acc_im * (im_sign * scale));
-        }
-        out[(int64_t(k) * g.ny + j) * g.nx + i] = res;
     }
 }
 
@@ -639,126 +966,548 @@ __global__ __launch_bounds__(kSdfBlock) void sdf_adjoint_kernel(const double* __
     }
 }
 
-// ---- Morton order and tile boxes
-__device__ __forceinline__ unsigned spread10(unsigned x) {
-    x &= 0x3ffu;
-    x = (x | (x << 16)) & 0x030000ffu;
-    x = (x | (x << 8)) & 0x0300f00fu;
-    x = (x | (x << 4)) & 0x030c30c3u;
-    x = (x | (x << 2)) & 0x09249249u;
-    return x;
+// ---- Hilbert order and the sample tree
+// 30-bit Hilbert index of a cell given by 10 bits per axis (Skilling's
+// transpose algorithm, 2004)
+__device__ __forceinline__ unsigned hilbert30(unsigned x, unsigned y, unsigned z) {
+    unsigned X[3] = {x, y, z};
+#pragma unroll
+    for (unsigned Q = 512; Q > 1; Q >>= 1) {
+        const unsigned P = Q - 1;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (X[a] & Q) {
+                X[0] ^= P;
+            } else {
+                const unsigned t = (X[0] ^ X[a]) & P;
+                X[0] ^= t;
+                X[a] ^= t;
+            }
+        }
+    }
+    X[1] ^= X[0];
+    X[2] ^= X[1];
+    unsigned t = 0;
+#pragma unroll
+    for (unsigned Q = 512; Q > 1; Q >>= 1)
+        if (X[2] & Q) t ^= Q - 1;
+    unsigned key = 0;
+#pragma unroll
+    for (int b = 9; b >= 0; --b)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) key = (key << 1) | (((X[a] ^ t) >> b) & 1u);
+    return key;
 }
 
 // 10 bits per axis over the grid's box widened by 4 h (outside samples clamp)
-__global__ void morton_key_kernel(const double* __restrict__ q, int64_t n, double ox, double oy, double oz,
-                                  double inv_cell, unsigned* __restrict__ key, int* __restrict__ val) {
-    const int64_t jx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (jx >= n) return;
+__device__ __forceinline__ unsigned sample_key(const double* __restrict__ q, int64_t j, double ox, double oy,
+                                               double oz, double inv_cell) {
     const double o[3] = {ox, oy, oz};
     unsigned c[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double f = (q[3 * jx + a] - o[a]) * inv_cell;
+        const double f = (q[3 * j + a] - o[a]) * inv_cell;
         c[a] = !(f > 0.0) ? 0u : (f >= 1023.0 ? 1023u : unsigned(f));
     }
-    key[jx] = spread10(c[0]) | (spread10(c[1]) << 1) | (spread10(c[2]) << 2);
-    val[jx] = int(jx);
+    return hilbert30(c[0], c[1], c[2]);
 }
 
-__global__ void sample_gather_kernel(const double* __restrict__ q, const double* __restrict__ nrm,
-                                     const double* __restrict__ w, const int* __restrict__ order, int64_t n,
-                                     double* __restrict__ qs, double* __restrict__ wn) {
-    const int64_t ix = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (ix >= n) return;
-    const int64_t s = order[ix];
+__global__ void hilbert_key_kernel(const double* __restrict__ q, int64_t n, double ox, double oy, double oz,
+                                   double inv_cell, unsigned* __restrict__ key, int* __restrict__ val) {
+    const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (j >= n) return;
+    key[j] = sample_key(q, j, ox, oy, oz, inv_cell);
+    val[j] = int(j);
+}
+
+// Up to kSmallSort samples: keys and order in one block, a bitonic sort in
+// LDS of (key, index) words, which are distinct, so equal keys keep their
+// input order.  Bound by its barriers; replaces the key kernel and the twelve
+// to twenty launches of the radix sort, which is latency-bound at these sizes.
+constexpr int kSmallSort = 4096;
+__global__ __launch_bounds__(1024) void small_order_kernel(const double* __restrict__ q, int n, int n2, double ox,
+                                                           double oy, double oz, double inv_cell,
+                                                           int* __restrict__ order) {
+    __shared__ unsigned long long e[kSmallSort];
+    for (int j = int(threadIdx.x); j < n2; j += 1024)
+        e[j] = j < n ? (uint64_t(sample_key(q, j, ox, oy, oz, inv_cell)) << 32) | unsigned(j) : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= n2; k <<= 1)
+        for (int st = k >> 1; st > 0; st >>= 1) {
+            for (int p = int(threadIdx.x); p < n2 / 2; p += 1024) {
+                const int lo = 2 * p - (p & (st - 1)), hi = lo + st;
+                const unsigned long long a = e[lo], b = e[hi];
+                if ((a > b) == ((lo & k) == 0)) {
+                    e[lo] = b;
+                    e[hi] = a;
+                }
+            }
+            __syncthreads();
+        }
+    for (int j = int(threadIdx.x); j < n; j += 1024) order[j] = int(unsigned(e[j]));
+}
+
+__device__ __forceinline__ double wave_min(double v) {
+    for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off));
+    return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+    return v;
+}
+
+// grid-lattice point nearest v (node differences from it are exact for h a
+// power of two)
+__device__ __forceinline__ double lattice(double v, double o, double h) { return o + h * rint((v - o) / h); }
+
+// MFMA records of a point: rec1 = (-2 q, |q|^2), rec2 = (w, -q.w), stored per
+// 16 points component by component, so a wave's operand is one 256-byte load
+__device__ __forceinline__ void put_record(float* __restrict__ rec1, float* __restrict__ rec2, int64_t at, float x,
+                                           float y, float z, float wx, float wy, float wz) {
+    const int64_t o = (at >> 4) * 64 + (at & 15);
+    rec1[o] = -2.f * x;
+    rec1[o + 16] = -2.f * y;
+    rec1[o + 32] = -2.f * z;
+    rec1[o + 48] = float(double(x) * x + double(y) * y + double(z) * z);
+    rec2[o] = wx;
+    rec2[o + 16] = wy;
+    rec2[o + 32] = wz;
+    rec2[o + 48] = -float(double(x) * wx + double(y) * wy + double(z) * wz);
+}
+
+// One wave per leaf: samples gathered in Hilbert order, the leaf's box, and
+// its FP32 records relative to the lattice point nearest the box centre.
+template <bool FAST>
+__global__ __launch_bounds__(kSdfBlock) void leaf_kernel(const double* __restrict__ q,
+                                                         const double* __restrict__ nrm,
+                                                         const double* __restrict__ w,
+                                                         const int* __restrict__ order, int64_t n, int64_t nleaf,
+                                                         GridDesc g, double* __restrict__ qs,
+                                                         double* __restrict__ wn, TreeNode* __restrict__ node,
+                                                         float* __restrict__ rec1, float* __restrict__ rec2) {
+    const int64_t leaf = int64_t(blockIdx.x) * (kSdfBlock / 64) + (threadIdx.x >> 6);
+    const int lane = int(threadIdx.x) & 63;
+    if (leaf >= nleaf) return;
+    const int64_t ix = leaf * kLeaf + lane;
+    const bool own = ix < n;
+    const int64_t s = order[own ? ix : leaf * kLeaf];  // lanes past the end repeat the first sample, weight 0
+    double p[3], v[3], c[3];
+    TreeNode t;
+    bool finite = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        qs[3 * ix + a] = q[3 * s + a];
-        wn[3 * ix + a] = w[s] * nrm[3 * s + a];
+        p[a] = q[3 * s + a];
+        v[a] = own ? w[s] * nrm[3 * s + a] : 0.0;
+        finite &= fabs(p[a]) < INFINITY;
+        if (own) {
+            qs[3 * ix + a] = p[a];
+            wn[3 * ix + a] = v[a];
+        }
+    }
+    const bool all = __ballot(!finite) == 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double lo = wave_min(finite ? p[a] : INFINITY), hi = wave_max(finite ? p[a] : -INFINITY);
+        const double mid = 0.5 * (lo + hi);
+        const double o = a == 0 ? g.ox : (a == 1 ? g.oy : g.oz);
+        c[a] = fabs(mid) < INFINITY ? lattice(mid, o, g.h) : 0.0;
+        // a sample that is not finite never counts: the leaf is then always visited and tested pair by pair
+        t.lo[a] = all ? lo : -INFINITY;
+        t.hi[a] = all ? hi : INFINITY;
+        t.c[a] = c[a];
+    }
+    const float x = float(p[0] - c[0]), y = float(p[1] - c[1]), z = float(p[2] - c[2]);
+    if constexpr (FAST)
+        put_record(rec1, rec2, ix, x, y, z, float(v[0]), float(v[1]), float(v[2]));
+    const double m2 = wave_max(finite ? double(x) * x + double(y) * y + double(z) * z : 0.0);
+    if (lane == 0) {
+        t.reach2 = -1.f;
+        t.qmax2 = float(m2 * 1.0001);
+        t.px = 0;
+        t.order = 0x111;
+        node[leaf] = t;
     }
 }
 
-__global__ void tile_box_kernel(const double* __restrict__ qs, int64_t n, int64_t ntile, double* __restrict__ box) {
+// 256-sample tile boxes (lo, hi) from the leaves
+__global__ void tile_box_kernel(const TreeNode* __restrict__ node, int64_t nleaf, int64_t ntile,
+                                double* __restrict__ box) {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t >= ntile) return;
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    const int64_t e = (t + 1) * kSdfTile < n ? (t + 1) * kSdfTile : n;
-    for (int64_t s = t * kSdfTile; s < e; ++s)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = fmin(lo[a], qs[3 * s + a]);
-            hi[a] = fmax(hi[a], qs[3 * s + a]);
-        }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        box[6 * t + a] = lo[a];
-        box[6 * t + 3 + a] = hi[a];
+        double lo = INFINITY, hi = -INFINITY;
+        for (int64_t c = kFan * t; c < kFan * (t + 1) && c < nleaf; ++c) {
+            lo = fmin(lo, node[c].lo[a]);
+            hi = fmax(hi, node[c].hi[a]);
+        }
+        box[6 * t + a] = lo;
+        box[6 * t + 3 + a] = hi;
     }
 }
 
-// workspace carve-up (256-byte aligned pieces)
+// Layout of the interpolation points: per level 1 and up, every node has room
+// for cap points; `at` is the level's first record group, `part` its first
+// partial sum, `blk` its first block of the weight kernel.
+struct InterpLayout {
+    int cap[kMaxLevels];
+    int split[kMaxLevels];
+    int64_t at[kMaxLevels];
+    int64_t part[kMaxLevels];
+    int64_t blk[kMaxLevels + 1];
+};
+
+// smallest order whose Chebyshev interpolation error rho^-p over half-width
+// tau (in units of the distance to the nearest singularity) is below kInterpEps
+__device__ int interp_order(double tau) {
+    if (tau < 1e-7) return 1;
+    const double d = 1.0 / tau;
+    const double lr = log(d + sqrt(fmax(d * d - 1.0, 0.0)));
+    if (!(lr > 0.0)) return 99;
+    const int p = int(ceil(-log(kInterpEps) / lr));
+    return p < 2 ? 2 : p;
+}
+
+// Nodes of one or more levels from their children (one block per launch runs
+// the levels [l0, l1), or many blocks one level).  With FAST, the smallest
+// reach = half-width / tau whose tensor grid stays within `share` of the
+// node's samples.
+template <bool FAST>
+__global__ __launch_bounds__(kSdfBlock) void tree_up_kernel(TreeNode* __restrict__ node, SampleTree tr, int l0,
+                                                            int l1, int64_t n, GridDesc g, InterpLayout lay,
+                                                            double share) {
+    for (int l = l0; l < l1; ++l) {
+        if (l > l0) __syncthreads();  // one block: the level below is complete
+        for (int i = int(blockIdx.x) * kSdfBlock + int(threadIdx.x); i < tr.cnt[l]; i += int(gridDim.x) * kSdfBlock) {
+            TreeNode t;
+            double half[3], hmax = 0.0;
+            bool ok = true;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                double lo = INFINITY, hi = -INFINITY;
+                for (int c = kFan * i; c < kFan * (i + 1) && c < tr.cnt[l - 1]; ++c) {
+                    lo = fmin(lo, node[tr.off[l - 1] + c].lo[a]);
+                    hi = fmax(hi, node[tr.off[l - 1] + c].hi[a]);
+                }
+                t.lo[a] = lo;
+                t.hi[a] = hi;
+                const double mid = 0.5 * (lo + hi);
+                const double o = a == 0 ? g.ox : (a == 1 ? g.oy : g.oz);
+                t.c[a] = fabs(mid) < INFINITY ? lattice(mid, o, g.h) : 0.0;
+                half[a] = 0.5 * (hi - lo);
+                ok &= half[a] < INFINITY;
+                hmax = fmax(hmax, half[a]);
+            }
+            t.reach2 = -1.f;
+            t.qmax2 = 0.f;
+            t.px = 0;
+            t.order = 0x111;
+            if constexpr (FAST) {
+                const int64_t size = int64_t(kLeaf) << (2 * l);
+                const double have = double(n - size * i < size ? n - size * i : size);
+                t.px = int(lay.at[l] + int64_t(i) * (lay.cap[l] / 16));
+                for (int k = 0; ok && k < 14; ++k) {
+                    const double tau = 0.6 * pow(0.87, double(k));
+                    const double reach = hmax / tau;
+                    int p[3], most = 1;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        p[a] = hmax > 0.0 ? interp_order(half[a] / reach) : 1;
+                        most = p[a] > most ? p[a] : most;
+                    }
+                    const double m = double(p[0]) * p[1] * p[2];
+                    if (most <= kInterpMax && m <= share * have) {
+                        t.reach2 = float(reach * reach * 1.0001);
+                        t.order = p[0] | (p[1] << 4) | (p[2] << 8);
+                        ok = false;
+                    }
+                }
+            }
+            node[tr.off[l] + i] = t;
+        }
+        if (l + 1 < l1) __threadfence_block();
+    }
+}
+
+// Sums sum_j L_m(q_j) w_j n_j of 64 interpolation points of one node over up to
+// kInterpSplit of its samples, FP64.  Lanes own points, the block's waves a
+// quarter of the samples each; a wave tabulates the Lagrange factors of 16
+// samples at a time in LDS.
+__global__ __launch_bounds__(kSdfBlock) void interp_sum_kernel(const TreeNode* __restrict__ node, SampleTree tr,
+                                                               InterpLayout lay, const double* __restrict__ qs,
+                                                               const double* __restrict__ wn, int64_t n,
+                                                               double* __restrict__ part) {
+    __shared__ double tab[4][16][3][kInterpMax];
+    __shared__ double sums[4][64][3];
+    int l = 1;
+    while (l + 1 < tr.levels && int64_t(blockIdx.x) >= lay.blk[l + 1]) ++l;
+    const int chunks = (lay.cap[l] + 63) / 64;
+    const int64_t b = int64_t(blockIdx.x) - lay.blk[l];
+    const int chunk = int(b % chunks), split = int((b / chunks) % lay.split[l]);
+    const int i = int(b / (int64_t(chunks) * lay.split[l]));
+    const TreeNode t = node[tr.off[l] + i];
+    const int count = t.reach2 < 0.f ? 0 : order_count(t.order);
+    if (64 * chunk >= count) return;  // uniform across the block
+    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+    const int p0 = t.order & 15, p1 = (t.order >> 4) & 15, p2 = (t.order >> 8) & 15;
+    const int m = 64 * chunk + lane;
+    const bool own = m < count;
+    const int m0 = own ? m % p0 : 0, m1 = own ? (m / p0) % p1 : 0, m2 = own ? m / (p0 * p1) : 0;
+    const int64_t size = int64_t(kLeaf) << (2 * l);
+    const int64_t first = size * i + int64_t(split) * kInterpSplit;
+    int64_t last = size * i + size < n ? size * i + size : n;
+    if (last > first + kInterpSplit) last = first + kInterpSplit;
+    // this lane's role in the tables: axis la of sample lane % 16
+    const int la = lane >> 4;
+    const int pl = la == 0 ? p0 : (la == 1 ? p1 : p2);
+    const double lo = la == 0 ? t.lo[0] : (la == 1 ? t.lo[1] : t.lo[2]);
+    const double hi = la == 0 ? t.hi[0] : (la == 1 ? t.hi[1] : t.hi[2]);
+    const double mid = 0.5 * (lo + hi), inv = hi > lo ? 2.0 / (hi - lo) : 0.0;
+    double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
+    for (int64_t s0 = first + 16 * wave; s0 < first + kInterpSplit; s0 += 64) {
+        __syncthreads();
+        if (la < 3 && s0 + (lane & 15) < last) {
+            const double x = (qs[3 * (s0 + (lane & 15)) + la] - mid) * inv;
+            double* L = tab[wave][lane & 15][la];
+            // L_m(x) = w_m prod_{k != m} (x - x_k), x_k = cos((2k + 1) pi / 2p),
+            // w_m = (-1)^m 2^(p - 1) sin((2m + 1) pi / 2p) / p
+            const double sc = exp2(double(pl - 1)) / pl;
+            double run = 1.0;
+            for (int k = 0; k < pl; ++k) {
+                L[k] = run;
+                run *= x - cospi((2 * k + 1) / (2.0 * pl));
+            }
+            run = sc;
+            for (int k = pl - 1; k >= 0; --k) {
+                const double a = (2 * k + 1) / (2.0 * pl);
+                L[k] *= run * ((k & 1) ? -sinpi(a) : sinpi(a));
+                run *= x - cospi(a);
+            }
+        }
+        __syncthreads();
+        const int cnt = int(last - s0 < 16 ? last - s0 : 16);
+        for (int a = 0; a < cnt; ++a) {
+            const double f = tab[wave][a][0][m0] * tab[wave][a][1][m1] * tab[wave][a][2][m2];
+            const int64_t s = s0 + a;
+            acc0 += f * wn[3 * s];
+            acc1 += f * wn[3 * s + 1];
+            acc2 += f * wn[3 * s + 2];
+        }
+    }
+    sums[wave][lane][0] = acc0;
+    sums[wave][lane][1] = acc1;
+    sums[wave][lane][2] = acc2;
+    __syncthreads();
+    if (wave == 0 && own) {
+        double* o = part + (lay.part[l] + (int64_t(i) * lay.split[l] + split) * lay.cap[l] + m) * 3;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) o[a] = (sums[0][lane][a] + sums[1][lane][a]) + (sums[2][lane][a] + sums[3][lane][a]);
+    }
+}
+
+// Records of the interpolation points of level 1 + blockIdx.y: position, and
+// the splits' sums; points past the count repeat the first with weight 0.
+__global__ __launch_bounds__(kSdfBlock) void interp_record_kernel(const TreeNode* __restrict__ node, SampleTree tr,
+                                                                  InterpLayout lay,
+                                                                  const double* __restrict__ part,
+                                                                  float* __restrict__ rec1,
+                                                                  float* __restrict__ rec2) {
+    const int l = 1 + int(blockIdx.y);
+    const int64_t id = int64_t(blockIdx.x) * kSdfBlock + threadIdx.x;
+    const int i = int(id / lay.cap[l]), m = int(id % lay.cap[l]);
+    if (i >= tr.cnt[l]) return;
+    const TreeNode t = node[tr.off[l] + i];
+    const int count = t.reach2 < 0.f ? 0 : order_count(t.order);
+    if (m >= (count + 15) / 16 * 16) return;
+    const int mm = m < count ? m : 0;
+    const int p[3] = {t.order & 15, (t.order >> 4) & 15, (t.order >> 8) & 15};
+    const int at[3] = {mm % p[0], (mm / p[0]) % p[1], mm / (p[0] * p[1])};
+    float x[3], w[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double node_x = 0.5 * (t.lo[a] + t.hi[a]) +
+                              (p[a] > 1 ? 0.5 * (t.hi[a] - t.lo[a]) * cospi((2 * at[a] + 1) / (2.0 * p[a])) : 0.0);
+        x[a] = float(node_x - t.c[a]);
+        double v = 0.0;
+        if (m < count)
+            for (int sp = 0; sp < lay.split[l]; ++sp)
+                v += part[(lay.part[l] + (int64_t(i) * lay.split[l] + sp) * lay.cap[l] + m) * 3 + a];
+        w[a] = float(v);
+    }
+    put_record(rec1, rec2, int64_t(t.px) * 16 + m, x[0], x[1], x[2], w[0], w[1], w[2]);
+}
+
+SampleTree tree_layout(int64_t n, int64_t* nodes) {
+    SampleTree tr{};
+    int64_t c = (n + kLeaf - 1) / kLeaf, off = 0;
+    for (;;) {
+        tr.off[tr.levels] = int(off);
+        tr.cnt[tr.levels] = int(c);
+        ++tr.levels;
+        off += c;
+        if (c <= kFan) break;
+        c = (c + kFan - 1) / kFan;
+    }
+    *nodes = off;
+    return tr;
+}
+
+// Workspace carve-up (256-byte aligned pieces).  The sort's buffers are free
+// once the samples are gathered: the tree and the tile boxes reuse them.  The
+// second part, for the FP32 kernels' fast pass 2, is optional.
 struct SdfWs {
-    size_t keys_in, vals_in, keys_out, vals_out, qs, wn, box, temp, temp_bytes, total;
+    size_t keys_in, vals_in, qs, wn, keys_out, vals_out, temp, tree, box, total;
+    size_t rec1, rec2, part, fast_total;
+    InterpLayout lay;
 };
 inline size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 inline SdfWs sdf_ws_layout(int64_t n) {
     SdfWs L{};
-    const size_t temp_bytes = sort_temp_bytes(n);
     const int64_t ntile = (n + kSdfTile - 1) / kSdfTile;
     size_t off = 0;
-    L.keys_in = off;
-    off += al256(size_t(n) * 4);
-    L.vals_in = off;
-    off += al256(size_t(n) * 4);
-    L.keys_out = off;
-    off += al256(size_t(n) * 4);
-    L.vals_out = off;
-    off += al256(size_t(n) * 4);
-    L.qs = off;
-    off += al256(size_t(n) * 24);
-    L.wn = off;
-    off += al256(size_t(n) * 24);
-    L.box = off;
-    off += al256(size_t(ntile) * 48);
-    L.temp = off;
-    L.temp_bytes = temp_bytes;
-    off += al256(temp_bytes);
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off += al256(bytes);
+        return at;
+    };
+    L.vals_in = take(size_t(n) * 4);
+    L.qs = take(size_t(n) * 24);
+    L.wn = take(size_t(n) * 24);
+    const size_t reuse = off;
+    L.keys_in = take(size_t(n) * 4);
+    L.keys_out = take(size_t(n) * 4);
+    L.vals_out = take(size_t(n) * 4);
+    L.temp = take(sort_temp_bytes(n));
+    const size_t sort_end = off;
+    off = reuse;
+    int64_t nodes = 0;
+    const SampleTree tr = tree_layout(n, &nodes);
+    L.tree = take(size_t(nodes) * sizeof(TreeNode));
+    L.box = take(size_t(ntile) * 48);
+    off = std::max(off, sort_end);
     L.total = off;
+    int64_t groups = int64_t(tr.cnt[0]) * (kLeaf / 16), parts = 0, blocks = 0;
+    for (int l = 1; l < tr.levels; ++l) {
+        const int64_t size = int64_t(kLeaf) << (2 * l);
+        L.lay.cap[l] = interp_cap(size);
+        L.lay.split[l] = int((size + kInterpSplit - 1) / kInterpSplit);
+        L.lay.at[l] = groups;
+        L.lay.part[l] = parts;
+        L.lay.blk[l] = blocks;
+        groups += int64_t(tr.cnt[l]) * (L.lay.cap[l] / 16);
+        parts += int64_t(tr.cnt[l]) * L.lay.split[l] * L.lay.cap[l];
+        blocks += int64_t(tr.cnt[l]) * L.lay.split[l] * ((L.lay.cap[l] + 63) / 64);
+    }
+    L.lay.blk[tr.levels] = blocks;
+    L.rec1 = take(size_t(groups) * 256);
+    L.rec2 = take(size_t(groups) * 256);
+    L.part = take(size_t(parts) * 24);
+    L.fast_total = off;
     return L;
 }
 
-// Morton order, sorted copies and tile boxes in the workspace
-hipError_t prepare_tiles(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g, void* ws,
-                         hipStream_t s, SampleTiles* st) {
+struct Prepared {
+    SampleTiles st;       // 256-sample tiles (radial and adjoint kernels)
+    SampleTree tr;
+    const TreeNode* node;
+    const float *rec1, *rec2;
+};
+
+// Hilbert order, sorted copies, sample tree; with `fast` the records of the FP32
+// sum, with `interp` its interpolation points, with `tiles` the 256-sample tile boxes
+hipError_t prepare_samples(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g, void* ws,
+                           bool fast, bool interp, bool tiles, hipStream_t s, Prepared* out) {
     const SdfWs L = sdf_ws_layout(ns);
     char* base = static_cast<char*>(ws);
-    auto* keys_in = reinterpret_cast<unsigned*>(base + L.keys_in);
-    auto* vals_in = reinterpret_cast<int*>(base + L.vals_in);
-    auto* keys_out = reinterpret_cast<unsigned*>(base + L.keys_out);
-    auto* vals_out = reinterpret_cast<int*>(base + L.vals_out);
     auto* qs = reinterpret_cast<double*>(base + L.qs);
     auto* wn = reinterpret_cast<double*>(base + L.wn);
+    auto* node = reinterpret_cast<TreeNode*>(base + L.tree);
     auto* box = reinterpret_cast<double*>(base + L.box);
-    const int64_t ntile = (ns + kSdfTile - 1) / kSdfTile;
-    const unsigned gb = unsigned((ns + 255) / 256);
+    auto* rec1 = reinterpret_cast<float*>(base + L.rec1);
+    auto* rec2 = reinterpret_cast<float*>(base + L.rec2);
+    auto* part = reinterpret_cast<double*>(base + L.part);
+    auto* vals_in = reinterpret_cast<int*>(base + L.vals_in);
     const double ext = g.h * (std::max(g.nx, std::max(g.ny, g.nz)) + 8);
-    hipLaunchKernelGGL(morton_key_kernel, dim3(gb), dim3(256), 0, s, q, ns, g.ox - 4 * g.h, g.oy - 4 * g.h,
-                       g.oz - 4 * g.h, 1024.0 / ext, keys_in, vals_in);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    unsigned* keys_sorted = nullptr;
-    int* order = nullptr;
-    e = launch_sort_pairs(keys_in, vals_in, keys_out, vals_out, ns, 30, base + L.temp, s, &keys_sorted, &order);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sample_gather_kernel, dim3(gb), dim3(256), 0, s, q, n, w, order, ns, qs, wn);
-    hipLaunchKernelGGL(tile_box_kernel, dim3(unsigned((ntile + 63) / 64)), dim3(64), 0, s, qs, ns, ntile, box);
-    *st = SampleTiles{qs, wn, order, box, ntile};
+    const double ox = g.ox - 4 * g.h, oy = g.oy - 4 * g.h, oz = g.oz - 4 * g.h, inv_cell = 1024.0 / ext;
+    int* order = vals_in;
+    if (ns <= kSmallSort) {
+        int n2 = 2;
+        while (n2 < ns) n2 *= 2;
+        hipLaunchKernelGGL(small_order_kernel, dim3(1), dim3(1024), 0, s, q, int(ns), n2, ox, oy, oz, inv_cell, order);
+    } else {
+        auto* keys_in = reinterpret_cast<unsigned*>(base + L.keys_in);
+        auto* keys_out = reinterpret_cast<unsigned*>(base + L.keys_out);
+        auto* vals_out = reinterpret_cast<int*>(base + L.vals_out);
+        hipLaunchKernelGGL(hilbert_key_kernel, dim3(unsigned((ns + 255) / 256)), dim3(256), 0, s, q, ns, ox, oy, oz,
+                           inv_cell, keys_in, vals_in);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        unsigned* keys_sorted = nullptr;
+        // four passes of 8 bits: the result is back in the first pair of buffers
+        e = launch_sort_pairs(keys_in, vals_in, keys_out, vals_out, ns, 30, base + L.temp, s, &keys_sorted, &order);
+        if (e != hipSuccess) return e;
+        if (order != vals_in) return hipErrorUnknown;
+    }
+    int64_t nodes = 0;
+    const SampleTree tr = tree_layout(ns, &nodes);
+    const int64_t nleaf = tr.cnt[0], ntile = (ns + kSdfTile - 1) / kSdfTile;
+    const dim3 lg(unsigned((nleaf + 3) / 4));
+    if (fast)
+        hipLaunchKernelGGL(leaf_kernel<true>, lg, dim3(kSdfBlock), 0, s, q, n, w, order, ns, nleaf, g, qs, wn, node,
+                           rec1, rec2);
+    else
+        hipLaunchKernelGGL(leaf_kernel<false>, lg, dim3(kSdfBlock), 0, s, q, n, w, order, ns, nleaf, g, qs, wn, node,
+                           nullptr, nullptr);
+    // levels of many nodes by a launch each, the rest by one block
+    int l = 1;
+    while (l < tr.levels) {
+        const bool many = tr.cnt[l] > 2048;
+        const int l1 = many ? l + 1 : tr.levels;
+        const dim3 ug(many ? unsigned((tr.cnt[l] + kSdfBlock - 1) / kSdfBlock) : 1u);
+        if (fast)
+            hipLaunchKernelGGL(tree_up_kernel<true>, ug, dim3(kSdfBlock), 0, s, node, tr, l, l1, ns, g, L.lay,
+                               interp ? kInterpShare : 0.0);
+        else
+            hipLaunchKernelGGL(tree_up_kernel<false>, ug, dim3(kSdfBlock), 0, s, node, tr, l, l1, ns, g, L.lay, 0.0);
+        l = l1;
+    }
+    if (fast && interp && tr.levels > 1) {
+        hipLaunchKernelGGL(interp_sum_kernel, dim3(unsigned(L.lay.blk[tr.levels])), dim3(kSdfBlock), 0, s, node, tr,
+                           L.lay, qs, wn, ns, part);
+        int64_t pts = 0;
+        for (int lv = 1; lv < tr.levels; ++lv) pts = std::max(pts, int64_t(tr.cnt[lv]) * L.lay.cap[lv]);
+        const dim3 rg{unsigned((pts + kSdfBlock - 1) / kSdfBlock), unsigned(tr.levels - 1), 1u};
+        hipLaunchKernelGGL(interp_record_kernel, rg, dim3(kSdfBlock), 0, s, node, tr, L.lay, part, rec1, rec2);
+    }
+    if (tiles)
+        hipLaunchKernelGGL(tile_box_kernel, dim3(unsigned((ntile + 63) / 64)), dim3(64), 0, s, node, nleaf, ntile,
+                           box);
+    *out = Prepared{SampleTiles{qs, wn, order, box, ntile}, tr, node, rec1, rec2};
     return hipGetLastError();
 }
+
+// node-sample pairs from which interpolation repays its own launches
+constexpr double kInterpPairs = 1e8;
+// grids of at most this many bricks give each brick's samples to four waves:
+// one wave per brick would leave most of the 1024 SIMDs with fewer than 16
+constexpr int64_t kShareBricks = 16384;
 
 int64_t brick_count(const GridDesc& g) {
     const Brick br = brick_shape(g.nz);
     return int64_t((g.nx + br.bx - 1) / br.bx) * ((g.ny + br.by - 1) / br.by) * ((g.nz + br.bz - 1) / br.bz);
+}
+
+template <typename T, int PHI, bool FAST, bool STATS = false>
+void enqueue_build(const double* q, const double* n, const Prepared& P, int64_t ns, const GridDesc& g,
+                   const ParamDesc& p, cplx<T>* out, unsigned long long* stats, hipStream_t s) {
+    const BrickGrid bg = wave_bricks(g.nx, g.ny, g.nz);
+    const int64_t bricks = int64_t(bg.nx) * bg.ny * bg.nz;
+    if (bricks <= kShareBricks)
+        hipLaunchKernelGGL((sdf_build_kernel<T, PHI, FAST, 4, STATS>), dim3(unsigned(bricks)), dim3(kSdfBlock), 0, s, q,
+                           n, P.st.qs, P.st.wn, P.st.js, P.node, P.tr, P.rec1, P.rec2, ns, g, p, out, stats);
+    else
+        hipLaunchKernelGGL((sdf_build_kernel<T, PHI, FAST, 1, STATS>), dim3(unsigned(bricks)), dim3(64), 0, s, q, n, P.st.qs, P.st.wn, P.st.js, P.node, P.tr, P.rec1, P.rec2, ns, g,
+                           p, out, stats);
 }
 
 }  // namespace
@@ -770,12 +1519,13 @@ size_t sdf_build_workspace_bytes(int64_t ns, int phi) {
     return sdf_ws_layout(ns).total;
 }
 
+size_t sdf_build_fast_bytes(int64_t ns) { return sdf_ws_layout(ns).fast_total; }
+
 template <typename T>
 hipError_t launch_sdf_build(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g,
-                            const ParamDesc& p, int phi, void* rho_out, void* ws, hipStream_t s,
+                            const ParamDesc& p, int phi, void* rho_out, void* ws, size_t ws_bytes, hipStream_t s,
                             unsigned long long* stats) {
-    SampleTiles st{};
-    const dim3 grid(unsigned(brick_count(g))), block(kSdfBlock);
+    Prepared P{};
     auto* out = static_cast<cplx<T>*>(rho_out);
     if (phi == kPhiRadial) {
         double* q2 = static_cast<double*>(ws);
@@ -784,24 +1534,29 @@ hipError_t launch_sdf_build(const double* q, const double* n, const double* w, i
         hipLaunchKernelGGL(offset_points_kernel, dim3(unsigned((ns + 255) / 256)), dim3(256), 0, s, q, n, w, ns,
                            p.radius, p.lambda1, p.lambda2, q2, c2, w2);
         void* ws2 = static_cast<char*>(ws) + al256(size_t(ns) * 2 * 7 * sizeof(double));
-        hipError_t e = prepare_tiles(q2, c2, w2, 2 * ns, g, ws2, s, &st);
+        hipError_t e = prepare_samples(q2, c2, w2, 2 * ns, g, ws2, false, false, true, s, &P);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(sdf_radial_kernel<T>, grid, block, 0, s, st, 2 * ns, g, p, out);
+        hipLaunchKernelGGL(sdf_radial_kernel<T>, dim3(unsigned(brick_count(g))), dim3(kSdfBlock), 0, s, P.st, 2 * ns,
+                           g, p, out);
         return hipGetLastError();
     }
-    hipError_t e = prepare_tiles(q, n, w, ns, g, ws, s, &st);
+    const bool sums = phi == kPhiSkeletal || phi == kPhiInverseSquare;
+    const bool fast = std::is_same<T, float>::value && sums && ws_bytes >= sdf_build_fast_bytes(ns);
+    const bool interp = fast && double(ns) * g.nx * g.ny * g.nz >= kInterpPairs;
+    hipError_t e = prepare_samples(q, n, w, ns, g, ws, fast, interp, false, s, &P);
     if (e != hipSuccess) return e;
-    if (stats) {
-        hipLaunchKernelGGL((sdf_build_kernel<T, kPhiSkeletal, true>), grid, block, 0, s, q, n, st, ns, g, p, out,
-                           stats);
-        return hipGetLastError();
+    if constexpr (std::is_same<T, float>::value) {
+        if (fast) {
+            if (stats) enqueue_build<T, kPhiSkeletal, true, true>(q, n, P, ns, g, p, out, stats, s);
+            else if (phi == kPhiSkeletal) enqueue_build<T, kPhiSkeletal, true>(q, n, P, ns, g, p, out, nullptr, s);
+            else enqueue_build<T, kPhiInverseSquare, true>(q, n, P, ns, g, p, out, nullptr, s);
+            return hipGetLastError();
+        }
     }
-    if (phi == kPhiDsl)
-        hipLaunchKernelGGL((sdf_build_kernel<T, kPhiDsl>), grid, block, 0, s, q, n, st, ns, g, p, out);
-    else if (phi == kPhiInverseSquare)
-        hipLaunchKernelGGL((sdf_build_kernel<T, kPhiInverseSquare>), grid, block, 0, s, q, n, st, ns, g, p, out);
-    else
-        hipLaunchKernelGGL((sdf_build_kernel<T, kPhiSkeletal>), grid, block, 0, s, q, n, st, ns, g, p, out);
+    if (stats) enqueue_build<T, kPhiSkeletal, false, true>(q, n, P, ns, g, p, out, stats, s);
+    else if (phi == kPhiDsl) enqueue_build<T, kPhiDsl, false>(q, n, P, ns, g, p, out, nullptr, s);
+    else if (phi == kPhiInverseSquare) enqueue_build<T, kPhiInverseSquare, false>(q, n, P, ns, g, p, out, nullptr, s);
+    else enqueue_build<T, kPhiSkeletal, false>(q, n, P, ns, g, p, out, nullptr, s);
     return hipGetLastError();
 }
 
@@ -814,10 +1569,10 @@ hipError_t launch_sdf_adjoint(const double* q, const double* n, const double* w,
     if (e == hipSuccess) e = launch_zero_f64(grad_n, 3 * ns, s);
     if (e == hipSuccess) e = launch_zero_f64(grad_w, ns, s);
     if (e != hipSuccess) return e;
-    SampleTiles st{};
-    e = prepare_tiles(q, n, w, ns, g, ws, s, &st);
+    Prepared P{};
+    e = prepare_samples(q, n, w, ns, g, ws, false, false, true, s, &P);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sdf_adjoint_kernel<T>, dim3(unsigned(brick_count(g))), dim3(kSdfBlock), 0, s, q, n, w, st,
+    hipLaunchKernelGGL(sdf_adjoint_kernel<T>, dim3(unsigned(brick_count(g))), dim3(kSdfBlock), 0, s, q, n, w, P.st,
                        ns, g, p, static_cast<const cplx<T>*>(cot), grad_q, grad_n, grad_w);
     return hipGetLastError();
 }
@@ -829,8 +1584,10 @@ template hipError_t launch_sdf_adjoint<double>(const double*, const double*, con
                                                const GridDesc&, const ParamDesc&, const void*, double*, double*,
                                                double*, void*, hipStream_t);
 template hipError_t launch_sdf_build<float>(const double*, const double*, const double*, int64_t, const GridDesc&,
-                                            const ParamDesc&, int, void*, void*, hipStream_t, unsigned long long*);
+                                            const ParamDesc&, int, void*, void*, size_t, hipStream_t,
+                                            unsigned long long*);
 template hipError_t launch_sdf_build<double>(const double*, const double*, const double*, int64_t, const GridDesc&,
-                                             const ParamDesc&, int, void*, void*, hipStream_t, unsigned long long*);
+                                             const ParamDesc&, int, void*, void*, size_t, hipStream_t,
+                                             unsigned long long*);
 
 }  // namespace sdf

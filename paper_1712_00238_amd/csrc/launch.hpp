@@ -23,11 +23,14 @@ constexpr int kPhiSkeletal = 0, kPhiInverseSquare = 1, kPhiRadial = 2, kPhiDsl =
 
 // ---- skeletal density (sdf_build): FP64 samples, output in T
 size_t sdf_build_workspace_bytes(int64_t ns, int phi = kPhiSkeletal);
+// workspace with which the FP32 skeletal and inverse-square builds interpolate
+// far clusters (ws_bytes below it: the same sums pair by pair)
+size_t sdf_build_fast_bytes(int64_t ns);
 // stats (may be null; skeletal kernel only): three device counters that the
 // build adds its pass-1 pairs, pass-2 pairs and in-ball pairs to
 template <typename T>
 hipError_t launch_sdf_build(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g,
-                            const ParamDesc& p, int phi, void* rho_out, void* ws, hipStream_t s,
+                            const ParamDesc& p, int phi, void* rho_out, void* ws, size_t ws_bytes, hipStream_t s,
                             unsigned long long* stats = nullptr);
 // adjoint of sdf_build: gradients (FP64, zeroed here) of Re sum_p cot(p) rho(p)
 // with respect to the sample positions, normals and weights
