@@ -324,7 +324,10 @@ struct PairIn {
 
 enum class Mode { Peaks, Volume };
 
-// Plain path for one pair: one rotation per launch sequence.
+// Plain path for one pair: rotations in batches of about kPlainBatch bytes of
+// grids, which stay in the 256 MB last-level cache between the passes.
+constexpr size_t kPlainBatch = size_t(192) << 20;
+
 template <typename T>
 int plain_pair(sdf_ctx ctx, const PairIn& pr, Mode mode, void* vol_out, hipStream_t s) {
     ctx->fused_cache_valid = false;
@@ -333,45 +336,49 @@ int plain_pair(sdf_ctx ctx, const PairIn& pr, Mode mode, void* vol_out, hipStrea
     const int nm = pr.gm->n[0];
     const int64_t K = gsize(pr.gm), G = gsize(pr.gf);
     const int64_t n_rot = pr.n_rot;
-    const int nparts = sdf::peak_parts<T>(N, planar);
-    Carve cv{nullptr};
-    cv.take(sizeof(double) * 4 * n_rot);
-    cv.take(sizeof(double) * 9 * n_rot);
-    cv.take(sizeof(T) * 9 * n_rot);
-    cv.take(2 * sizeof(T) * K);
-    cv.take(2 * sizeof(T) * G);
-    cv.take(sizeof(T) * nparts);
-    cv.take(sizeof(int) * nparts);
-    int rc = ensure_ws(ctx, cv.off);
+    auto carve = [&](char* base, int64_t B, double** qd, T** RT, unsigned long long** cmax, void** c, void** grid) {
+        Carve cv{base};
+        *qd = static_cast<double*>(cv.take(sizeof(double) * 4 * n_rot));
+        *RT = static_cast<T*>(cv.take(sizeof(T) * 9 * n_rot));
+        *cmax = static_cast<unsigned long long*>(cv.take(sizeof(unsigned long long)));
+        *c = cv.take(2 * sizeof(T) * K);
+        *grid = cv.take(2 * sizeof(T) * G * B);
+        return cv.off;
+    };
+    double* qd;
+    T* RT;
+    unsigned long long* cmax;
+    void *c, *grid;
+    const size_t per = 2 * sizeof(T) * size_t(G);
+    int64_t B = std::min<int64_t>(std::min<int64_t>(n_rot, 4096), std::max<int64_t>(1, int64_t(kPlainBatch / per)));
+    if (ctx->cap) {  // as many rotations as the cap holds
+        const size_t one = carve(nullptr, 1, &qd, &RT, &cmax, &c, &grid);
+        const size_t room = ctx->cap > one ? (ctx->cap - one) / per : 0;
+        B = std::max<int64_t>(1, std::min<int64_t>(B, 1 + int64_t(room)));
+    }
+    int rc = ensure_ws(ctx, carve(nullptr, B, &qd, &RT, &cmax, &c, &grid));
+    if (rc && B > 1) {
+        B = 1;
+        rc = ensure_ws(ctx, carve(nullptr, B, &qd, &RT, &cmax, &c, &grid));
+    }
     if (rc) return rc;
-    Carve c2{static_cast<char*>(ctx->ws)};
-    double* qd = static_cast<double*>(c2.take(sizeof(double) * 4 * n_rot));
-    double* r64 = static_cast<double*>(c2.take(sizeof(double) * 9 * n_rot));
-    T* RT = static_cast<T*>(c2.take(sizeof(T) * 9 * n_rot));
-    void* c = c2.take(2 * sizeof(T) * K);
-    void* grid = c2.take(2 * sizeof(T) * G);
-    T* pval = static_cast<T*>(c2.take(sizeof(T) * nparts));
-    int* pidx = static_cast<int*>(c2.take(sizeof(int) * nparts));
+    carve(static_cast<char*>(ctx->ws), B, &qd, &RT, &cmax, &c, &grid);
     SDF_TRY_HIP(ctx, hipMemcpyAsync(qd, pr.quats, sizeof(double) * 4 * n_rot, hipMemcpyHostToDevice, s),
                 "quaternion upload");
-    SDF_TRY_HIP(ctx, sdf::launch_quat_to_rot<T>(qd, n_rot, r64, RT, s), "rotations");
-    SDF_TRY_HIP(ctx, sdf::launch_coef<T>(pr.rho_m, static_cast<const T*>(pr.w_m), K, c, s), "coefficients");
-    for (int64_t r = 0; r < n_rot; ++r) {
-        SDF_TRY_HIP(ctx, sdf::launch_zero<T>(grid, G, s), "zero");
-        SDF_TRY_HIP(ctx, sdf::launch_spread_atomic<T>(c, nm, planar, RT + 9 * r, 1, T(-1), N, grid, s), "spread");
-        SDF_TRY_HIP(ctx, sdf::launch_fft3<T>(grid, N, planar, 1, -1, 1.0, s), "forward fft");
-        SDF_TRY_HIP(ctx, sdf::launch_mul_spec<T>(grid, pr.spec, G, 1, s), "spectral product");
-        SDF_TRY_HIP(ctx, sdf::launch_fft3<T>(grid, N, planar, 1, +1, 1.0, s), "inverse fft");
-        if (mode == Mode::Volume) {
-            SDF_TRY_HIP(ctx, sdf::launch_real_part<T>(grid, static_cast<T*>(vol_out) + r * G, G, s), "real part");
-        } else {
-            SDF_TRY_HIP(ctx,
-                        sdf::launch_peak<T>(grid, true, N, planar, 1, pval, pidx, nparts,
-                                            static_cast<T*>(pr.score) + r, pr.t + 3 * r,
-                                            pr.nbhd ? static_cast<T*>(pr.nbhd) + 27 * r : nullptr,
-                                            pr.refined ? pr.refined + 3 * r : nullptr, s),
-                        "peak");
-        }
+    SDF_TRY_HIP(ctx, sdf::launch_quat_to_rot<T>(qd, n_rot, nullptr, RT, s, cmax), "rotations");
+    SDF_TRY_HIP(ctx, sdf::launch_coef_max<T>(pr.rho_m, static_cast<const T*>(pr.w_m), K, c, cmax, s), "coefficients");
+    for (int64_t r = 0; r < n_rot; r += B) {
+        const int nb = int(std::min<int64_t>(B, n_rot - r));
+        SDF_TRY_HIP(ctx, sdf::launch_spread_tiles<T>(c, nm, planar, RT + 9 * r, nb, T(-1), N, cmax, grid, s), "spread");
+        const bool peaks = mode == Mode::Peaks;
+        SDF_TRY_HIP(ctx,
+                    sdf::launch_correlate<T>(grid, pr.spec, N, planar, nb,
+                                             peaks ? nullptr : static_cast<T*>(vol_out) + r * G,
+                                             peaks ? static_cast<T*>(pr.score) + r : nullptr,
+                                             peaks ? pr.t + 3 * r : nullptr,
+                                             peaks && pr.nbhd ? static_cast<T*>(pr.nbhd) + 27 * r : nullptr,
+                                             peaks && pr.refined ? pr.refined + 3 * r : nullptr, s),
+                    "correlation");
     }
     return SDF_OK;
 }
@@ -773,7 +780,6 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
     const bool planar = gf->n[2] == 1;
     const int nm = gm->n[0];
     const int64_t K = gsize(gm), G = gsize(gf);
-    const int nparts = sdf::peak_parts<T>(N, planar);
     size_t sdf_ws = build_ws_bytes(ctx, ns, sdf::kPhiSkeletal);
     Carve cv{nullptr};
     cv.take(sizeof(double) * 4 * n_rot);
@@ -783,8 +789,6 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
     cv.take(sizeof(double) * 3 * ns);
     cv.take(2 * sizeof(T) * K);
     cv.take(2 * sizeof(T) * G);
-    cv.take(sizeof(T) * nparts);
-    cv.take(sizeof(int) * nparts);
     if (ctx->cap && cv.off + sdf_ws > ctx->cap) sdf_ws = sdf::sdf_build_workspace_bytes(ns);
     cv.take(sdf_ws);
     int rc = ensure_ws(ctx, cv.off);
@@ -797,8 +801,6 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
     double* nr = static_cast<double*>(c2.take(sizeof(double) * 3 * ns));
     void* rho = c2.take(2 * sizeof(T) * K);
     void* grid = c2.take(2 * sizeof(T) * G);
-    T* pval = static_cast<T*>(c2.take(sizeof(T) * nparts));
-    int* pidx = static_cast<int*>(c2.take(sizeof(int) * nparts));
     void* wsb = c2.take(sdf_ws);
     const double c[3] = {gm->origin[0] + 0.5 * gm->h * nm, gm->origin[1] + 0.5 * gm->h * nm,
                          planar ? gm->origin[2] : gm->origin[2] + 0.5 * gm->h * nm};
@@ -812,14 +814,11 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
                     "box sdf");
         SDF_TRY_HIP(ctx, sdf::launch_zero<T>(grid, G, s), "zero");
         SDF_TRY_HIP(ctx, sdf::launch_place_direct<T>(rho, nm, planar, T(w_node), N, grid, s), "place");
-        SDF_TRY_HIP(ctx, sdf::launch_fft3<T>(grid, N, planar, 1, -1, 1.0, s), "forward fft");
-        SDF_TRY_HIP(ctx, sdf::launch_mul_spec<T>(grid, spec, G, 1, s), "spectral product");
-        SDF_TRY_HIP(ctx, sdf::launch_fft3<T>(grid, N, planar, 1, +1, 1.0, s), "inverse fft");
         SDF_TRY_HIP(ctx,
-                    sdf::launch_peak<T>(grid, true, N, planar, 1, pval, pidx, nparts, static_cast<T*>(score) + r,
-                                        t + 3 * r, nbhd ? static_cast<T*>(nbhd) + 27 * r : nullptr,
-                                        refined ? refined + 3 * r : nullptr, s),
-                    "peak");
+                    sdf::launch_correlate<T>(grid, spec, N, planar, 1, nullptr, static_cast<T*>(score) + r, t + 3 * r,
+                                             nbhd ? static_cast<T*>(nbhd) + 27 * r : nullptr,
+                                             refined ? refined + 3 * r : nullptr, s),
+                    "correlation");
     }
     return SDF_OK;
 }
@@ -897,7 +896,7 @@ int nfft_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const void* pos
                         "real part");
         } else {
             SDF_TRY_HIP(ctx,
-                        sdf::launch_peak<T>(grid, true, N, planar, nb, pval, pidx, nparts,
+                        sdf::launch_peak<T>(grid, N, planar, nb, pval, pidx, nparts,
                                             static_cast<T*>(score) + r0, t + 3 * r0,
                                             nbhd ? static_cast<T*>(nbhd) + 27 * r0 : nullptr,
                                             refined ? refined + 3 * r0 : nullptr, s),

@@ -1,13 +1,19 @@
-// Plain multi-pass correlation path, one template for FP32 and FP64:
-//   quaternions -> rotation matrices (FP64), c_k = w_k rho_M(x_k),
-//   spread with global atomics, per-axis LDS FFT passes, pointwise product
-//   with the fixed spectrum, inverse passes, Re + peak reduction.
-// Every step is a separate launch over whole grids; this is the
-// straightforward baseline the fused FP32 kernels are measured against.
+// Plain multi-pass correlation path, one template for FP32 and FP64, every
+// launch over a batch of rotations:
+//   quaternions -> rotation matrices (FP64), c_k = w_k rho_M(x_k) and max |c_k|,
+//   spread tile by tile in LDS (integers), x and y FFT passes, the z pass
+//   forward, times the fixed spectrum and back in one kernel, the inverse y
+//   pass, and the inverse x pass with the peak of its rows (planar grids: x,
+//   then y with the product, then x).
+// The FP64 search, full score volumes and the windowless reference run here;
+// it is also what the fused FP32 kernels are compared with.
+#include <type_traits>
+
 #include "common.hpp"
 #include "fft.hpp"
 #include "fft256.hpp"
 #include "launch.hpp"
+#include "twiddles.hpp"
 
 namespace sdf {
 
@@ -16,8 +22,9 @@ namespace {
 // ------------------------------------------------------------------ rotations
 template <typename T>
 __global__ void quat_to_rot_kernel(const double* __restrict__ quats, int64_t n, double* __restrict__ r64,
-                                   T* __restrict__ rT) {
+                                   T* __restrict__ rT, unsigned long long* __restrict__ cmax) {
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (cmax && i == 0) *cmax = 0;  // for coef_max_kernel
     if (i >= n) return;
     double w = quats[4 * i], x = quats[4 * i + 1], y = quats[4 * i + 2], z = quats[4 * i + 3];
     double inv = 1.0 / sqrt(w * w + x * x + y * y + z * z);
@@ -40,6 +47,27 @@ __global__ void coef_kernel(const cplx<T>* __restrict__ rho, const T* __restrict
                             cplx<T>* __restrict__ c) {
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) c[i] = rho[i] * w[i];
+}
+
+// the same, and the largest |Re c| or |Im c| as the bits of a non-negative double
+// (which order like integers; infinities and NaN above every number)
+template <typename T>
+__global__ __launch_bounds__(256) void coef_max_kernel(const cplx<T>* __restrict__ rho, const T* __restrict__ w,
+                                                       int64_t n, cplx<T>* __restrict__ c,
+                                                       unsigned long long* __restrict__ cmax) {
+    __shared__ unsigned long long wave_max[4];
+    unsigned long long m = 0;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
+        const cplx<T> v = rho[i] * w[i];
+        c[i] = v;
+        const unsigned long long a = __double_as_longlong(fabs(double(v.re))),
+                                 b = __double_as_longlong(fabs(double(v.im)));
+        m = max(m, max(a, b));
+    }
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned long long)__shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(cmax, max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3])));
 }
 
 template <typename T>
@@ -108,6 +136,197 @@ __global__ void spread_atomic_kernel(const cplx<T>* __restrict__ c, int n_m, int
     }
 }
 
+// ------------------------------------------------------------------ tile spread
+// The search's spread: a block owns a tile of grid nodes of one rotation and
+// gathers every body sample whose stencil reaches it, so each node is stored
+// once, with no zero pass and no global atomics (FP64 global atomics took four
+// fifths of the FP64 search: 17 million adds per rotation at 64^3 samples).
+//   1. The tile's support turned back into the body box gives an axis-aligned
+//      range of samples; the block tests them 256 at a time and appends the
+//      ones that reach the tile to a list, so that
+//   2. the scatter runs with full waves: each lane takes a listed sample, forms
+//      its weights and adds its taps that lie in the tile to LDS.
+// Sums are integers (their order does not matter, runs repeat bit for bit):
+// 64 bits for FP64, in units of at most 16 max|c| / 2^60, finer than the rounding of an
+// FP64 sum; 32 bits for FP32, in units of at most 16 max|c| / 2^31.  The weights at a node of a unit-density lattice sum to about 1, so
+// no sum leaves the range.  Nodes are centred coordinates [-N/2, N/2): the fit
+// rule keeps every stencil inside, so no index wraps before the store.
+// Bound by VALU issue and LDS adds (7 + 1 instructions per FP64 sum).  FP64,
+// 8 rotations of 96^3 / 48^3: the whole search 6212 -> 535 us; 36 rotations of
+// 128^2 / 64^2: 1930 -> 73 us (with the batched and fused transform passes).
+constexpr int kTileBlock = 256;
+constexpr int kTileList = 1024;
+// 3D 16 x 16 x 8 nodes (33 KiB of FP64 sums: four blocks per CU; a sample is
+// visited 1.9 times on average), planar 32 x 32
+template <bool PLANAR>
+struct SpreadTile {
+    static constexpr int X = PLANAR ? 32 : 16, Y = PLANAR ? 32 : 16, Z = PLANAR ? 1 : 8;
+    static constexpr int PITCH = X + 1;
+};
+template <typename T>
+struct TileSum;
+template <>
+struct TileSum<float> {
+    using type = int;
+    static constexpr double top = 2147483648.0;  // 2^31
+    static __device__ __forceinline__ int fixed(float v) { return __float2int_rn(v); }
+};
+template <>
+struct TileSum<double> {
+    using type = unsigned long long;
+    static constexpr double top = 1152921504606846976.0;  // 2^60
+    // round to nearest in two exact steps: adding m = 1.5 2^52 leaves an integer in the low words
+    static __device__ __forceinline__ unsigned long long fixed(double v) {
+        constexpr double m = 6755399441055744.0;
+        const double hm = __builtin_fma(v, 2.3283064365386963e-10, m);
+        const double l = __builtin_fma(hm - m, -4294967296.0, v);
+        const double lm = l + m;  // m + l, l in [-2^31, 2^31]: the words of the signed integer l, plus m's high word
+        const unsigned hi = unsigned(__double2loint(hm)) + unsigned(__double2hiint(lm)) - 0x43380000u;
+        return (static_cast<unsigned long long>(hi) << 32) | unsigned(__double2loint(lm));
+    }
+};
+
+template <typename T>
+__device__ __forceinline__ void tile_position(const T* __restrict__ r, T sign, T bx, T by, T bz, T y[3]) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) y[a] = sign * (r[3 * a] * bx + r[3 * a + 1] * by + r[3 * a + 2] * bz);
+}
+
+template <typename T, bool PLANAR>
+__global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* __restrict__ c, int n_m,
+                                                                 const T* __restrict__ R, T sign, int N,
+                                                                 const unsigned long long* __restrict__ cmax,
+                                                                 cplx<T>* __restrict__ out) {
+    using S = SpreadTile<PLANAR>;
+    using A = typename TileSum<T>::type;
+    __shared__ A acc[S::Z * S::Y * S::PITCH * 2];
+    __shared__ int list[kTileList];
+    __shared__ int count;
+    const int sx = min(S::X, N), sy = min(S::Y, N), sz = PLANAR ? 1 : min(S::Z, N);
+    const int ntx = N / sx, nty = N / sy;
+    const int tile = int(blockIdx.x);
+    const int t0[3] = {(tile % ntx) * sx - N / 2, ((tile / ntx) % nty) * sy - N / 2,
+                       PLANAR ? 0 : (tile / (ntx * nty)) * sz - N / 2};
+    const int dim[3] = {sx, sy, sz};
+    const int64_t G = PLANAR ? int64_t(N) * N : int64_t(N) * N * N;
+    cplx<T>* g = out + int64_t(blockIdx.y) * G;
+    const T* r = R + 9 * int64_t(blockIdx.y);
+    const double cm = __longlong_as_double((long long)*cmax);
+    const bool finite = cm < INFINITY;
+    // a power of two (the exponent of the quotient alone), so scaling rounds nothing
+    const double quot = fmin(TileSum<T>::top / (8.0 * cm), std::is_same<T, float>::value ? 1e37 : 1e300);
+    const double pow2 = __longlong_as_double(__double_as_longlong(quot) & 0x7ff0000000000000ll);
+    const T scale = cm > 0.0 && finite ? T(pow2) : T(0);
+    const T inv = cm > 0.0 ? T(1.0 / pow2) : T(0);
+    for (int i = int(threadIdx.x); i < S::Z * S::Y * S::PITCH * 2; i += kTileBlock) acc[i] = 0;
+    if (threadIdx.x == 0) count = 0;
+    // samples that can reach the tile: |y - centre| <= half per axis, x = sign R^T y
+    int lo[3], num[3];
+    const T half_box = T(0.5) * T(n_m);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        T mid = T(0), ext = T(1e-2);
+#pragma unroll
+        for (int b = 0; b < (PLANAR ? 2 : 3); ++b) {
+            const T q = r[3 * b + a];
+            mid += sign * q * (T(t0[b]) + T(0.5) * T(dim[b] - 1));
+            ext += (q < T(0) ? -q : q) * (T(0.5) * T(dim[b] - 1) + T(2));
+        }
+        if (PLANAR && a == 2) {
+            lo[a] = 0;
+            num[a] = 1;
+        } else {
+            lo[a] = max(0, int(dev_floor(mid - ext + half_box)));
+            num[a] = max(0, min(n_m, int(dev_floor(mid + ext + half_box)) + 2) - lo[a]);
+        }
+    }
+    const int total = num[0] * num[1] * num[2];
+    __syncthreads();
+    auto scatter = [&]() {  // the listed samples, one per thread and round
+        const int n = count;
+        for (int e = int(threadIdx.x); e < n; e += kTileBlock) {
+            const int k = list[e];
+            cplx<T> v = c[k];
+            v.re *= scale;
+            v.im *= scale;
+            T y[3];
+            tile_position(r, sign, T(k % n_m) - half_box, T((k / n_m) % n_m) - half_box,
+                          PLANAR ? T(0) : T(k / (n_m * n_m)) - half_box, y);
+            T wt[3][4];
+            int b[3];
+#pragma unroll
+            for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
+                const T fl = dev_floor(y[a]);
+                b[a] = int(fl) - 1 - t0[a];
+                bspline3_weights(y[a] - fl, wt[a]);
+            }
+#pragma unroll
+            for (int cz = 0; cz < (PLANAR ? 1 : 4); ++cz) {
+                const int iz = PLANAR ? 0 : b[2] + cz;
+                if (unsigned(iz) >= unsigned(sz)) continue;
+#pragma unroll
+                for (int cy = 0; cy < 4; ++cy) {
+                    const int iy = b[1] + cy;
+                    if (unsigned(iy) >= unsigned(sy)) continue;
+                    const T wyz = PLANAR ? wt[1][cy] : wt[1][cy] * wt[2][cz];
+                    A* row = acc + ((iz * S::Y + iy) * S::PITCH) * 2;
+#pragma unroll
+                    for (int cx = 0; cx < 4; ++cx) {
+                        const int ix = b[0] + cx;
+                        if (unsigned(ix) >= unsigned(sx)) continue;
+                        const T w3 = wt[0][cx] * wyz;
+                        atomicAdd(row + 2 * ix, TileSum<T>::fixed(v.re * w3));
+                        atomicAdd(row + 2 * ix + 1, TileSum<T>::fixed(v.im * w3));
+                    }
+                }
+            }
+        }
+    };
+    for (int e0 = 0; e0 < total; e0 += kTileBlock) {
+        const int e = e0 + int(threadIdx.x);
+        bool hit = false;
+        int k = 0;
+        if (e < total) {
+            const int i = lo[0] + e % num[0], j = lo[1] + (e / num[0]) % num[1], l = lo[2] + e / (num[0] * num[1]);
+            k = (l * n_m + j) * n_m + i;
+            T y[3];
+            tile_position(r, sign, T(i) - half_box, T(j) - half_box, PLANAR ? T(0) : T(l) - half_box, y);
+            hit = true;
+#pragma unroll
+            for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
+                const int b = int(dev_floor(y[a])) - 1 - t0[a];
+                hit &= b >= -3 && b < dim[a];
+            }
+        }
+        const unsigned long long m = __ballot(hit);
+        int at = 0;
+        if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&count, int(__popcll(m)));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (hit) list[at + int(__popcll(m & ((1ull << (threadIdx.x & 63)) - 1)))] = k;
+        __syncthreads();
+        const int n = count;
+        __syncthreads();  // every wave has read it before the next round appends
+        if (n > kTileList - kTileBlock) {  // no room for another round
+            scatter();
+            __syncthreads();
+            if (threadIdx.x == 0) count = 0;
+            __syncthreads();
+        }
+    }
+    scatter();
+    __syncthreads();
+    for (int i = int(threadIdx.x); i < sx * sy * sz; i += kTileBlock) {
+        const int ix = i % sx, iy = (i / sx) % sy, iz = i / (sx * sy);
+        const A* a = acc + ((iz * S::Y + iy) * S::PITCH + ix) * 2;
+        const int ux = (t0[0] + ix + N) % N, uy = (t0[1] + iy + N) % N, uz = PLANAR ? 0 : (t0[2] + iz + N) % N;
+        using I = typename std::conditional<std::is_same<T, double>::value, long long, int>::type;
+        cplx<T> v = mk(T(I(a[0])) * inv, T(I(a[1])) * inv);
+        // a transform of any value that is not finite is NaN everywhere
+        if (!finite) v = mk(T(NAN), T(NAN));
+        g[(int64_t(uz) * N + uy) * N + ux] = v;
+    }
+}
+
 // ------------------------------------------------------------------ direct reference
 // Boundary samples of the moving part turned about its body-box centre c:
 // q' = c + R (q - c), n' = R n (FP64, R row-major).
@@ -152,7 +371,7 @@ __global__ __launch_bounds__(kFftBlock) void fft_rows_kernel(cplx<T>* __restrict
     constexpr int CONC = kFftBlock / TPL;
     __shared__ cplx<T> buf[CONC * N];
     __shared__ cplx<T> tw[N];
-    fill_twiddles<T, N>(tw);
+    table_twiddles<T, N>(tw);
     const int64_t row0 = int64_t(blockIdx.x) * CONC;
     const int nr = int(nrows - row0 < CONC ? nrows - row0 : CONC);
     cplx<T>* src = data + row0 * N;
@@ -179,7 +398,7 @@ __global__ __launch_bounds__(kFftBlock) void fft_cols_kernel(cplx<T>* __restrict
     constexpr int W = cols_width<N>();
     __shared__ cplx<T> buf[N * W];
     __shared__ cplx<T> tw[N];
-    fill_twiddles<T, N>(tw);
+    table_twiddles<T, N>(tw);
     const int x0 = blockIdx.x * W;
     const int o = blockIdx.y;
     cplx<T>* base = data + int64_t(blockIdx.z) * gsz + int64_t(o) * os + x0;
@@ -192,6 +411,94 @@ __global__ __launch_bounds__(kFftBlock) void fft_cols_kernel(cplx<T>* __restrict
     for (int i = threadIdx.x; i < N * W; i += kFftBlock) {
         const int e = i / W, xl = i % W;
         base[e * es + xl] = buf[i] * scale;
+    }
+}
+
+// The last forward axis, the product with the fixed spectrum and the first
+// inverse axis in one pass over the grid: W columns forward, times S, back.
+template <typename T, int N>
+__global__ __launch_bounds__(kFftBlock) void fft_cols_mul_kernel(cplx<T>* __restrict__ data, int64_t es, int64_t os,
+                                                                 int64_t gsz, const cplx<T>* __restrict__ spec) {
+    constexpr int W = cols_width<N>();
+    __shared__ cplx<T> buf[N * W];
+    __shared__ cplx<T> tw[N];
+    table_twiddles<T, N>(tw);
+    const int64_t off = int64_t(blockIdx.y) * os + int64_t(blockIdx.x) * W;
+    cplx<T>* base = data + int64_t(blockIdx.z) * gsz + off;
+    const cplx<T>* sb = spec + off;
+    for (int i = threadIdx.x; i < N * W; i += kFftBlock) buf[i] = base[(i / W) * es + i % W];
+    __syncthreads();
+    lds_fft_lines<T, N, -1, true>(buf, W, 1, W, tw);
+    for (int i = threadIdx.x; i < N * W; i += kFftBlock) buf[i] = buf[i] * sb[(i / W) * es + i % W];
+    __syncthreads();
+    lds_fft_lines<T, N, 1, true>(buf, W, 1, W, tw);
+    for (int i = threadIdx.x; i < N * W; i += kFftBlock) base[(i / W) * es + i % W] = buf[i];
+}
+
+// Peaks kept by the inverse x pass: rows of a rotation store their real parts
+// compactly at their own start (row r at reals 2 N r), and the first row of a
+// block its best (value, flat index) in the free half behind.
+template <typename T>
+struct RowPeak {
+    T v;
+    int i;
+};
+template <typename T>
+__device__ __forceinline__ RowPeak<T>* row_peak(T* rot, int N, int64_t row) {
+    return reinterpret_cast<RowPeak<T>*>(rot + (2 * row + 1) * N);
+}
+
+// Inverse x pass of blockIdx.y's grid, real parts only: to vol (a volume per
+// rotation), or (vol null) in place with the block's best value.
+template <typename T, int N>
+__global__ __launch_bounds__(kFftBlock) void fft_rows_real_kernel(cplx<T>* __restrict__ data, int nrows,
+                                                                  T* __restrict__ vol) {
+    constexpr int TPL = FFTShape<N>::TPL;
+    constexpr int CONC = kFftBlock / TPL;
+    __shared__ cplx<T> buf[CONC * N];
+    __shared__ cplx<T> tw[N];
+    __shared__ RowPeak<T> best[kFftBlock / 64];
+    table_twiddles<T, N>(tw);
+    const int row0 = int(blockIdx.x) * CONC;
+    const int nr = min(CONC, nrows - row0);
+    cplx<T>* rot = data + int64_t(blockIdx.y) * nrows * N;
+    cplx<T>* src = rot + int64_t(row0) * N;
+    for (int i = threadIdx.x; i < nr * N; i += kFftBlock) buf[i] = src[i];
+    __syncthreads();
+    lds_fft_lines<T, N, 1, false>(buf, 1, N, nr, tw);
+    if (vol) {
+        T* dst = vol + (int64_t(blockIdx.y) * nrows + row0) * N;
+        for (int i = threadIdx.x; i < nr * N; i += kFftBlock) dst[i] = buf[i].re;
+        return;
+    }
+    T* real = reinterpret_cast<T*>(rot);
+    T bv = T(-INFINITY);
+    int bi = 0x7fffffff;
+    for (int i = threadIdx.x; i < nr * N; i += kFftBlock) {
+        const T v = buf[i].re;
+        real[(2 * int64_t(row0 + i / N)) * N + i % N] = v;
+        if (v > bv) {  // i grows: the lowest index keeps a tie
+            bv = v;
+            bi = row0 * N + i;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const T ov = __shfl_xor(bv, off);
+        const int oi = __shfl_xor(bi, off);
+        if (ov > bv || (ov == bv && oi < bi)) {
+            bv = ov;
+            bi = oi;
+        }
+    }
+    if ((threadIdx.x & 63) == 0) best[threadIdx.x >> 6] = RowPeak<T>{bv, bi};
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kFftBlock / 64; ++w)
+            if (best[w].v > bv || (best[w].v == bv && best[w].i < bi)) {
+                bv = best[w].v;
+                bi = best[w].i;
+            }
+        *row_peak(real, N, row0) = RowPeak<T>{bv, bi};
     }
 }
 
@@ -237,15 +544,6 @@ hipError_t fft3_impl(void* data, bool planar, int batch, int dir, double scale, 
     return hipGetLastError();
 }
 
-template <typename T>
-__global__ void mul_spec_kernel(cplx<T>* __restrict__ data, const cplx<T>* __restrict__ spec, int64_t count,
-                                int batch) {
-    const int64_t total = count * batch;
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-    for (; i < total; i += stride) data[i] = data[i] * spec[i % count];
-}
-
 // ------------------------------------------------------------------ peak
 constexpr int kPeakBlock = 256;
 
@@ -277,13 +575,15 @@ __device__ __forceinline__ void block_argmax(T& v, int& idx) {
     __syncthreads();
 }
 
-template <typename T, bool CPLX>
-__device__ __forceinline__ T vol_at(const void* vol, int64_t i) {
-    if (CPLX) return static_cast<const cplx<T>*>(vol)[i].re;
-    return static_cast<const T*>(vol)[i];
+// layouts of a volume: complex, or the inverse x pass's compact real rows
+enum { kVolCplx, kVolRows };
+template <typename T, int KIND>
+__device__ __forceinline__ T vol_at(const void* vol, int64_t i, int N) {
+    if (KIND == kVolCplx) return static_cast<const cplx<T>*>(vol)[i].re;
+    return static_cast<const T*>(vol)[(i / N) * (2 * N) + i % N];
 }
 
-template <typename T, bool CPLX>
+template <typename T>
 __global__ __launch_bounds__(kPeakBlock) void peak_partial_kernel(const void* __restrict__ vol, int64_t nvox,
                                                                   int nparts, T* __restrict__ pval,
                                                                   int* __restrict__ pidx) {
@@ -295,7 +595,7 @@ __global__ __launch_bounds__(kPeakBlock) void peak_partial_kernel(const void* __
     T bv = T(-INFINITY);
     int bi = 0x7fffffff;
     for (int64_t i = lo + threadIdx.x; i < hi; i += kPeakBlock) {
-        T v = vol_at<T, CPLX>(vol, off + i);
+        T v = vol_at<T, kVolCplx>(vol, off + i, 1);
         if (better(v, int(i), bv, bi)) {
             bv = v;
             bi = int(i);
@@ -308,9 +608,11 @@ __global__ __launch_bounds__(kPeakBlock) void peak_partial_kernel(const void* __
     }
 }
 
-template <typename T, bool CPLX>
+// part_rows (kVolRows): rows per partial of the inverse x pass
+template <typename T, int KIND>
 __global__ __launch_bounds__(kPeakBlock) void peak_final_kernel(const void* __restrict__ vol, int N, int planar,
-                                                                int nparts, const T* __restrict__ pval,
+                                                                int nparts, int part_rows,
+                                                                const T* __restrict__ pval,
                                                                 const int* __restrict__ pidx, T* __restrict__ score,
                                                                 int32_t* __restrict__ tout, T* __restrict__ nbhd,
                                                                 double* __restrict__ refined) {
@@ -320,8 +622,17 @@ __global__ __launch_bounds__(kPeakBlock) void peak_final_kernel(const void* __re
     T bv = T(-INFINITY);
     int bi = 0x7fffffff;
     for (int i = threadIdx.x; i < nparts; i += kPeakBlock) {
-        T v = pval[int64_t(b) * nparts + i];
-        int id = pidx[int64_t(b) * nparts + i];
+        T v;
+        int id;
+        if constexpr (KIND == kVolRows) {
+            T* rot = const_cast<T*>(static_cast<const T*>(vol)) + int64_t(b) * 2 * nvox;
+            const RowPeak<T> p = *row_peak(rot, N, int64_t(i) * part_rows);
+            v = p.v;
+            id = p.i;
+        } else {
+            v = pval[int64_t(b) * nparts + i];
+            id = pidx[int64_t(b) * nparts + i];
+        }
         if (better(v, id, bv, bi)) {
             bv = v;
             bi = id;
@@ -333,7 +644,7 @@ __global__ __launch_bounds__(kPeakBlock) void peak_final_kernel(const void* __re
     if (threadIdx.x < 27) {
         const int dz = threadIdx.x / 9 - 1, dy = (threadIdx.x / 3) % 3 - 1, dx = threadIdx.x % 3 - 1;
         const int zz = wrap(tz + dz, nz), yy = wrap(ty + dy, N), xx = wrap(tx + dx, N);
-        nb[threadIdx.x] = vol_at<T, CPLX>(vol, int64_t(b) * nvox + (int64_t(zz) * N + yy) * N + xx);
+        nb[threadIdx.x] = vol_at<T, KIND>(vol, int64_t(b) * nvox + (int64_t(zz) * N + yy) * N + xx, N);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -379,8 +690,9 @@ inline unsigned grid_for(int64_t n, int block, int cap = 65535 * 4) {
 }  // namespace
 
 template <typename T>
-hipError_t launch_quat_to_rot(const double* quats, int64_t n, double* r64, T* rT, hipStream_t s) {
-    hipLaunchKernelGGL(quat_to_rot_kernel<T>, dim3(grid_for(n, 64)), dim3(64), 0, s, quats, n, r64, rT);
+hipError_t launch_quat_to_rot(const double* quats, int64_t n, double* r64, T* rT, hipStream_t s,
+                              unsigned long long* cmax) {
+    hipLaunchKernelGGL(quat_to_rot_kernel<T>, dim3(grid_for(n, 64)), dim3(64), 0, s, quats, n, r64, rT, cmax);
     return hipGetLastError();
 }
 
@@ -423,13 +735,6 @@ hipError_t launch_fft3(void* data, int N, bool planar, int batch, int dir, doubl
 }
 
 template <typename T>
-hipError_t launch_mul_spec(void* data, const void* spec, int64_t count, int batch, hipStream_t s) {
-    hipLaunchKernelGGL(mul_spec_kernel<T>, dim3(grid_for(count * batch, 256, 16384)), dim3(256), 0, s,
-                       static_cast<cplx<T>*>(data), static_cast<const cplx<T>*>(spec), count, batch);
-    return hipGetLastError();
-}
-
-template <typename T>
 int peak_parts(int N, bool planar) {
     const int64_t nvox = int64_t(N) * N * (planar ? 1 : N);
     int64_t p = (nvox + 4095) / 4096;
@@ -439,21 +744,87 @@ int peak_parts(int N, bool planar) {
 }
 
 template <typename T>
-hipError_t launch_peak(const void* vol, bool vol_is_complex, int N, bool planar, int batch, T* part_val,
-                       int* part_idx, int nparts, T* score, int32_t* t, T* nbhd, double* refined, hipStream_t s) {
+hipError_t launch_peak(const void* vol, int N, bool planar, int batch, T* part_val, int* part_idx, int nparts,
+                       T* score, int32_t* t, T* nbhd, double* refined, hipStream_t s) {
     const int64_t nvox = int64_t(N) * N * (planar ? 1 : N);
     const dim3 g1{unsigned(nparts), unsigned(batch), 1u};
-    if (vol_is_complex) {
-        hipLaunchKernelGGL((peak_partial_kernel<T, true>), g1, dim3(kPeakBlock), 0, s, vol, nvox, nparts, part_val,
-                           part_idx);
-        hipLaunchKernelGGL((peak_final_kernel<T, true>), dim3(unsigned(batch)), dim3(kPeakBlock), 0, s, vol, N,
-                           planar ? 1 : 0, nparts, part_val, part_idx, score, t, nbhd, refined);
+    hipLaunchKernelGGL(peak_partial_kernel<T>, g1, dim3(kPeakBlock), 0, s, vol, nvox, nparts, part_val, part_idx);
+    hipLaunchKernelGGL((peak_final_kernel<T, kVolCplx>), dim3(unsigned(batch)), dim3(kPeakBlock), 0, s, vol, N,
+                       planar ? 1 : 0, nparts, 0, part_val, part_idx, score, t, nbhd, refined);
+    return hipGetLastError();
+}
+
+namespace {
+template <typename T, int N>
+hipError_t correlate_impl(void* data, const void* spec, bool planar, int batch, T* vol, T* score, int32_t* t, T* nbhd,
+                          double* refined, hipStream_t s) {
+    constexpr int CONC = kFftBlock / FFTShape<N>::TPL;
+    constexpr int W = cols_width<N>();
+    cplx<T>* d = static_cast<cplx<T>*>(data);
+    const auto* sp = static_cast<const cplx<T>*>(spec);
+    const int nz = planar ? 1 : N, rows = N * nz;
+    const int64_t plane = int64_t(N) * N, gsz = plane * nz, all = int64_t(rows) * batch;
+    hipLaunchKernelGGL((fft_rows_kernel<T, N, -1>), dim3(unsigned((all + CONC - 1) / CONC)), dim3(kFftBlock), 0, s, d,
+                       all, T(1));
+    if (planar) {
+        hipLaunchKernelGGL((fft_cols_mul_kernel<T, N>), dim3(N / W, 1, batch), dim3(kFftBlock), 0, s, d, int64_t(N),
+                           plane, gsz, sp);
     } else {
-        hipLaunchKernelGGL((peak_partial_kernel<T, false>), g1, dim3(kPeakBlock), 0, s, vol, nvox, nparts,
-                           part_val, part_idx);
-        hipLaunchKernelGGL((peak_final_kernel<T, false>), dim3(unsigned(batch)), dim3(kPeakBlock), 0, s, vol, N,
-                           planar ? 1 : 0, nparts, part_val, part_idx, score, t, nbhd, refined);
+        const dim3 g(N / W, N, batch);
+        hipLaunchKernelGGL((fft_cols_kernel<T, N, -1>), g, dim3(kFftBlock), 0, s, d, int64_t(N), plane, gsz, T(1));
+        hipLaunchKernelGGL((fft_cols_mul_kernel<T, N>), g, dim3(kFftBlock), 0, s, d, plane, int64_t(N), gsz, sp);
+        hipLaunchKernelGGL((fft_cols_kernel<T, N, 1>), g, dim3(kFftBlock), 0, s, d, int64_t(N), plane, gsz, T(1));
     }
+    const int blocks = (rows + CONC - 1) / CONC;
+    hipLaunchKernelGGL((fft_rows_real_kernel<T, N>), dim3(unsigned(blocks), unsigned(batch)), dim3(kFftBlock), 0, s, d,
+                       rows, vol);
+    if (!vol)
+        hipLaunchKernelGGL((peak_final_kernel<T, kVolRows>), dim3(unsigned(batch)), dim3(kPeakBlock), 0, s, data, N,
+                           planar ? 1 : 0, blocks, CONC, nullptr, nullptr, score, t, nbhd, refined);
+    return hipGetLastError();
+}
+}  // namespace
+
+template <typename T>
+hipError_t launch_correlate(void* grid, const void* spec, int N, bool planar, int batch, T* vol, T* score, int32_t* t,
+                            T* nbhd, double* refined, hipStream_t s) {
+    switch (N) {
+        case 8: return correlate_impl<T, 8>(grid, spec, planar, batch, vol, score, t, nbhd, refined, s);
+        case 16: return correlate_impl<T, 16>(grid, spec, planar, batch, vol, score, t, nbhd, refined, s);
+        case 32: return correlate_impl<T, 32>(grid, spec, planar, batch, vol, score, t, nbhd, refined, s);
+        case 64: return correlate_impl<T, 64>(grid, spec, planar, batch, vol, score, t, nbhd, refined, s);
+        case 96: return correlate_impl<T, 96>(grid, spec, planar, batch, vol, score, t, nbhd, refined, s);
+        case 128: return correlate_impl<T, 128>(grid, spec, planar, batch, vol, score, t, nbhd, refined, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+template <typename T>
+hipError_t launch_spread_tiles(const void* c, int n_m, bool planar, const T* R, int n_rot, T sign, int N,
+                               const unsigned long long* cmax, void* out, hipStream_t s) {
+    const auto* cc = static_cast<const cplx<T>*>(c);
+    auto* o = static_cast<cplx<T>*>(out);
+    if (planar) {
+        using S = SpreadTile<true>;
+        const unsigned tx = unsigned(N / (S::X < N ? S::X : N)), ty = unsigned(N / (S::Y < N ? S::Y : N));
+        hipLaunchKernelGGL((spread_tile_kernel<T, true>), dim3(tx * ty, unsigned(n_rot)), dim3(kTileBlock), 0, s, cc,
+                           n_m, R, sign, N, cmax, o);
+    } else {
+        using S = SpreadTile<false>;
+        const unsigned tx = unsigned(N / (S::X < N ? S::X : N)), ty = unsigned(N / (S::Y < N ? S::Y : N)),
+                       tz = unsigned(N / (S::Z < N ? S::Z : N));
+        hipLaunchKernelGGL((spread_tile_kernel<T, false>), dim3(tx * ty * tz, unsigned(n_rot)), dim3(kTileBlock), 0, s,
+                           cc, n_m, R, sign, N, cmax, o);
+    }
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_coef_max(const void* rho_m, const T* w_m, int64_t count, void* c_out, unsigned long long* cmax,
+                           hipStream_t s) {
+    // at most one block per CU: their maxima meet at one address
+    hipLaunchKernelGGL(coef_max_kernel<T>, dim3(grid_for(count, 256, 256)), dim3(256), 0, s,
+                       static_cast<const cplx<T>*>(rho_m), w_m, count, static_cast<cplx<T>*>(c_out), cmax);
     return hipGetLastError();
 }
 
@@ -480,17 +851,23 @@ hipError_t launch_place_direct(const void* rho, int n_m, bool planar, T w_node, 
 }
 
 #define SDF_INST(T)                                                                                              \
-    template hipError_t launch_quat_to_rot<T>(const double*, int64_t, double*, T*, hipStream_t);                \
+    template hipError_t launch_quat_to_rot<T>(const double*, int64_t, double*, T*, hipStream_t,                 \
+                                              unsigned long long*);                                              \
     template hipError_t launch_coef<T>(const void*, const T*, int64_t, void*, hipStream_t);                      \
+    template hipError_t launch_coef_max<T>(const void*, const T*, int64_t, void*, unsigned long long*,           \
+                                           hipStream_t);                                                         \
     template hipError_t launch_zero<T>(void*, int64_t, hipStream_t);                                             \
     template hipError_t launch_place_direct<T>(const void*, int, bool, T, int, void*, hipStream_t);               \
     template hipError_t launch_spread_atomic<T>(const void*, int, bool, const T*, int, T, int, void*,           \
                                                 hipStream_t);                                                    \
+    template hipError_t launch_spread_tiles<T>(const void*, int, bool, const T*, int, T, int,                    \
+                                               const unsigned long long*, void*, hipStream_t);                   \
+    template hipError_t launch_correlate<T>(void*, const void*, int, bool, int, T*, T*, int32_t*, T*, double*,   \
+                                            hipStream_t);                                                        \
     template hipError_t launch_fft3<T>(void*, int, bool, int, int, double, hipStream_t);                         \
-    template hipError_t launch_mul_spec<T>(void*, const void*, int64_t, int, hipStream_t);                       \
     template int peak_parts<T>(int, bool);                                                                      \
-    template hipError_t launch_peak<T>(const void*, bool, int, bool, int, T*, int*, int, T*, int32_t*, T*,      \
-                                       double*, hipStream_t);                                                    \
+    template hipError_t launch_peak<T>(const void*, int, bool, int, T*, int*, int, T*, int32_t*, T*, double*,   \
+                                       hipStream_t);                                                             \
     template hipError_t launch_real_part<T>(const void*, T*, int64_t, hipStream_t);
 
 SDF_INST(float)

@@ -39,13 +39,19 @@ hipError_t launch_sdf_adjoint(const double* q, const double* n, const double* w,
                               const ParamDesc& p, const void* cot, double* grad_q, double* grad_n, double* grad_w,
                               void* ws, hipStream_t s);
 
-// ---- rotations: quaternions (FP64, device) -> R (FP64 and cast to T), n x 9 row-major
+// ---- rotations: quaternions (FP64, device) -> R (FP64 and cast to T; either may be null), n x 9
+// row-major; cmax (may be null) is cleared for launch_coef_max
 template <typename T>
-hipError_t launch_quat_to_rot(const double* quats, int64_t n, double* r64, T* rT, hipStream_t s);
+hipError_t launch_quat_to_rot(const double* quats, int64_t n, double* r64, T* rT, hipStream_t s,
+                              unsigned long long* cmax = nullptr);
 
 // ---- per-sample coefficients c_k = w_k rho_M(x_k)
 template <typename T>
 hipError_t launch_coef(const void* rho_m, const T* w_m, int64_t count, void* c_out, hipStream_t s);
+// the same, and *cmax = bits of the largest |Re c_k| or |Im c_k| as a double (cleared before)
+template <typename T>
+hipError_t launch_coef_max(const void* rho_m, const T* w_m, int64_t count, void* c_out, unsigned long long* cmax,
+                           hipStream_t s);
 
 // ---- plain multi-pass path (any T)
 // zero `count` complex values
@@ -62,19 +68,27 @@ hipError_t launch_place_direct(const void* rho, int n_m, bool planar, T w_node, 
 template <typename T>
 hipError_t launch_spread_atomic(const void* c, int n_m, bool planar, const T* R, int n_rot, T sign, int N,
                                 void* out, hipStream_t s);
+// the same spread tile by tile through LDS: every node of out[rot] is written
+// (nothing need be zero before); cmax from launch_coef_max.  The rotated box
+// and its stencils must fit the grid (the search's rule).
+template <typename T>
+hipError_t launch_spread_tiles(const void* c, int n_m, bool planar, const T* R, int n_rot, T sign, int N,
+                               const unsigned long long* cmax, void* out, hipStream_t s);
+// correlation of `batch` spread grids (overwritten) with the fixed spectrum:
+// forward FFT, times spec, inverse FFT, then the real volumes (vol, batch grids)
+// or, with vol null, each rotation's peak, neighbourhood and refinement
+template <typename T>
+hipError_t launch_correlate(void* grid, const void* spec, int N, bool planar, int batch, T* vol, T* score, int32_t* t,
+                            T* nbhd, double* refined, hipStream_t s);
 // in-place 3D (or 2D) FFT of `batch` N^3 (N^2) grids; dir -1 forward, +1 inverse;
 // results multiplied by `scale`.
 template <typename T>
 hipError_t launch_fft3(void* data, int N, bool planar, int batch, int dir, double scale, hipStream_t s);
-// data[b] *= spec, elementwise, batch grids of `count`
+// per-rotation peak of complex volumes (Re part); part_val, part_idx: nparts
+// partial peaks per rotation
 template <typename T>
-hipError_t launch_mul_spec(void* data, const void* spec, int64_t count, int batch, hipStream_t s);
-// per-rotation peak from complex volumes (Re part) or real volumes.
-// partial: per block (value, index); final writes score, t, nbhd, refined.
-template <typename T>
-hipError_t launch_peak(const void* vol, bool vol_is_complex, int N, bool planar, int batch, T* part_val,
-                       int* part_idx, int nparts, T* score, int32_t* t, T* nbhd, double* refined,
-                       hipStream_t s);
+hipError_t launch_peak(const void* vol, int N, bool planar, int batch, T* part_val, int* part_idx, int nparts,
+                       T* score, int32_t* t, T* nbhd, double* refined, hipStream_t s);
 template <typename T>
 int peak_parts(int N, bool planar);
 // real part of complex volumes into real output
