@@ -300,6 +300,17 @@ size_t build_ws_bytes(sdf_ctx ctx, int64_t ns, int kind) {
     return sdf::sdf_build_workspace_bytes(ns, kind);
 }
 
+// workspace of one fixed-field cotangent: with partial grids for the pose
+// ranges where the cap allows
+size_t fixed_ws_bytes(sdf_ctx ctx, int64_t B, int N, bool planar) {
+    const bool wide = ctx->dtype == SDF_F64;
+    const size_t split = wide ? sdf::fixed_cotangent_bytes<double>(B, N, planar, true)
+                              : sdf::fixed_cotangent_bytes<float>(B, N, planar, true);
+    if (!ctx->cap || split <= ctx->cap) return split;
+    return wide ? sdf::fixed_cotangent_bytes<double>(B, N, planar, false)
+                : sdf::fixed_cotangent_bytes<float>(B, N, planar, false);
+}
+
 void drop_graph(sdf_ctx ctx) {
     if (ctx->graph.exec) (void)hipGraphExecDestroy(ctx->graph.exec);
     if (ctx->graph.graph) (void)hipGraphDestroy(ctx->graph.graph);
@@ -1456,8 +1467,8 @@ int score_grad_backward(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g_fi
     cv.take(gws);
     cv.take(el * size_t(B));
     cv.take(2 * el * size_t(K));
-    const size_t need = std::max(cv.off, sizeof(double) * 12 * size_t(B) + 256);
-    rc = ensure_ws(ctx, need);
+    const size_t fixed_bytes = grad_rho_fixed ? fixed_ws_bytes(ctx, B, N, planar) : 0;
+    rc = ensure_ws(ctx, std::max(cv.off, fixed_bytes));
     if (rc) return rc;
     Carve c2{static_cast<char*>(ctx->ws)};
     void* gw_ws = c2.take(gws);
@@ -1486,9 +1497,9 @@ int score_grad_backward(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g_fi
     if (grad_rho_fixed) {
         e = ctx->dtype == SDF_F64
                 ? sdf::launch_fixed_cotangent<double>(rho_moving, static_cast<const double*>(w_moving), nm, planar, N,
-                                                      poses, B, grad_score, grad_rho_fixed, ctx->ws, s)
+                                                      poses, B, grad_score, grad_rho_fixed, ctx->ws, fixed_bytes, s)
                 : sdf::launch_fixed_cotangent<float>(rho_moving, static_cast<const float*>(w_moving), nm, planar, N,
-                                                     poses, B, grad_score, grad_rho_fixed, ctx->ws, s);
+                                                     poses, B, grad_score, grad_rho_fixed, ctx->ws, fixed_bytes, s);
         if (e != hipSuccess) return hip_fail(ctx, e, "score_grad_backward");
     }
     return SDF_OK;
@@ -1520,13 +1531,16 @@ int score_grad_fixed(sdf_ctx ctx, const sdf_grid* g_fixed, const void* rho_movin
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool planar = g_fixed->n[2] == 1;
     const int N = g_fixed->n[0], nm = g_moving->n[0];
-    rc = ensure_ws(ctx, sizeof(double) * 12 * size_t(B) + 256);
+    const size_t ws_bytes = fixed_ws_bytes(ctx, B, N, planar);
+    rc = ensure_ws(ctx, ws_bytes);
     if (rc) return rc;
     hipError_t e = ctx->dtype == SDF_F64
                        ? sdf::launch_fixed_cotangent<double>(rho_moving, static_cast<const double*>(w_moving), nm,
-                                                             planar, N, poses, B, grad_scale, grad_f, ctx->ws, s)
+                                                             planar, N, poses, B, grad_scale, grad_f, ctx->ws,
+                                                             ws_bytes, s)
                        : sdf::launch_fixed_cotangent<float>(rho_moving, static_cast<const float*>(w_moving), nm,
-                                                            planar, N, poses, B, grad_scale, grad_f, ctx->ws, s);
+                                                            planar, N, poses, B, grad_scale, grad_f, ctx->ws,
+                                                             ws_bytes, s);
     if (e != hipSuccess) return hip_fail(ctx, e, "score_grad_fixed");
     return SDF_OK;
 }

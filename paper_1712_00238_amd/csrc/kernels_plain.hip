@@ -13,6 +13,7 @@
 #include "fft.hpp"
 #include "fft256.hpp"
 #include "launch.hpp"
+#include "tile_spread.hpp"
 #include "twiddles.hpp"
 
 namespace sdf {
@@ -141,28 +142,18 @@ __global__ void spread_atomic_kernel(const cplx<T>* __restrict__ c, int n_m, int
 // gathers every body sample whose stencil reaches it, so each node is stored
 // once, with no zero pass and no global atomics (FP64 global atomics took four
 // fifths of the FP64 search: 17 million adds per rotation at 64^3 samples).
-//   1. The tile's support turned back into the body box gives an axis-aligned
-//      range of samples; the block tests them 256 at a time and appends the
-//      ones that reach the tile to a list, so that
-//   2. the scatter runs with full waves: each lane takes a listed sample, forms
-//      its weights and adds its taps that lie in the tile to LDS.
+// The samples that reach the tile come wave by wave with full lanes
+// (box_samples): each lane forms its sample's weights and adds the taps that
+// lie in the tile to LDS.
 // Sums are integers (their order does not matter, runs repeat bit for bit):
 // 64 bits for FP64, in units of at most 16 max|c| / 2^60, finer than the rounding of an
 // FP64 sum; 32 bits for FP32, in units of at most 16 max|c| / 2^31.  The weights at a node of a unit-density lattice sum to about 1, so
 // no sum leaves the range.  Nodes are centred coordinates [-N/2, N/2): the fit
 // rule keeps every stencil inside, so no index wraps before the store.
 // Bound by VALU issue and LDS adds (7 + 1 instructions per FP64 sum).  FP64,
-// 8 rotations of 96^3 / 48^3: the whole search 6212 -> 535 us; 36 rotations of
-// 128^2 / 64^2: 1930 -> 73 us (with the batched and fused transform passes).
-constexpr int kTileBlock = 256;
-constexpr int kTileList = 1024;
-// 3D 16 x 16 x 8 nodes (33 KiB of FP64 sums: four blocks per CU; a sample is
-// visited 1.9 times on average), planar 32 x 32
-template <bool PLANAR>
-struct SpreadTile {
-    static constexpr int X = PLANAR ? 32 : 16, Y = PLANAR ? 32 : 16, Z = PLANAR ? 1 : 8;
-    static constexpr int PITCH = X + 1;
-};
+// 8 rotations of 96^3 / 48^3: the whole search 6212 -> 467 us, 216 of them here;
+// 36 rotations of 128^2 / 64^2: 1930 -> 71 us (with the batched and fused
+// transform passes).
 template <typename T>
 struct TileSum;
 template <>
@@ -175,22 +166,8 @@ template <>
 struct TileSum<double> {
     using type = unsigned long long;
     static constexpr double top = 1152921504606846976.0;  // 2^60
-    // round to nearest in two exact steps: adding m = 1.5 2^52 leaves an integer in the low words
-    static __device__ __forceinline__ unsigned long long fixed(double v) {
-        constexpr double m = 6755399441055744.0;
-        const double hm = __builtin_fma(v, 2.3283064365386963e-10, m);
-        const double l = __builtin_fma(hm - m, -4294967296.0, v);
-        const double lm = l + m;  // m + l, l in [-2^31, 2^31]: the words of the signed integer l, plus m's high word
-        const unsigned hi = unsigned(__double2loint(hm)) + unsigned(__double2hiint(lm)) - 0x43380000u;
-        return (static_cast<unsigned long long>(hi) << 32) | unsigned(__double2loint(lm));
-    }
+    static __device__ __forceinline__ unsigned long long fixed(double v) { return fixed64(v); }
 };
-
-template <typename T>
-__device__ __forceinline__ void tile_position(const T* __restrict__ r, T sign, T bx, T by, T bz, T y[3]) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) y[a] = sign * (r[3 * a] * bx + r[3 * a + 1] * by + r[3 * a + 2] * bz);
-}
 
 template <typename T, bool PLANAR>
 __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* __restrict__ c, int n_m,
@@ -199,9 +176,7 @@ __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* 
                                                                  cplx<T>* __restrict__ out) {
     using S = SpreadTile<PLANAR>;
     using A = typename TileSum<T>::type;
-    __shared__ A acc[S::Z * S::Y * S::PITCH * 2];
-    __shared__ int list[kTileList];
-    __shared__ int count;
+    __shared__ A acc[S::WORDS];
     const int sx = min(S::X, N), sy = min(S::Y, N), sz = PLANAR ? 1 : min(S::Z, N);
     const int ntx = N / sx, nty = N / sy;
     const int tile = int(blockIdx.x);
@@ -213,114 +188,62 @@ __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* 
     const T* r = R + 9 * int64_t(blockIdx.y);
     const double cm = __longlong_as_double((long long)*cmax);
     const bool finite = cm < INFINITY;
-    // a power of two (the exponent of the quotient alone), so scaling rounds nothing
-    const double quot = fmin(TileSum<T>::top / (8.0 * cm), std::is_same<T, float>::value ? 1e37 : 1e300);
-    const double pow2 = __longlong_as_double(__double_as_longlong(quot) & 0x7ff0000000000000ll);
+    const double pow2 = pow2_below(fmin(TileSum<T>::top / (8.0 * cm), std::is_same<T, float>::value ? 1e37 : 1e300));
     const T scale = cm > 0.0 && finite ? T(pow2) : T(0);
     const T inv = cm > 0.0 ? T(1.0 / pow2) : T(0);
-    for (int i = int(threadIdx.x); i < S::Z * S::Y * S::PITCH * 2; i += kTileBlock) acc[i] = 0;
-    if (threadIdx.x == 0) count = 0;
-    // samples that can reach the tile: |y - centre| <= half per axis, x = sign R^T y
-    int lo[3], num[3];
+    for (int i = int(threadIdx.x); i < S::WORDS; i += kTileBlock) acc[i] = 0;
+    __syncthreads();
     const T half_box = T(0.5) * T(n_m);
+    float rf[9], lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 9; ++a) rf[a] = float(sign * r[a]);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        T mid = T(0), ext = T(1e-2);
-#pragma unroll
-        for (int b = 0; b < (PLANAR ? 2 : 3); ++b) {
-            const T q = r[3 * b + a];
-            mid += sign * q * (T(t0[b]) + T(0.5) * T(dim[b] - 1));
-            ext += (q < T(0) ? -q : q) * (T(0.5) * T(dim[b] - 1) + T(2));
-        }
-        if (PLANAR && a == 2) {
-            lo[a] = 0;
-            num[a] = 1;
-        } else {
-            lo[a] = max(0, int(dev_floor(mid - ext + half_box)));
-            num[a] = max(0, min(n_m, int(dev_floor(mid + ext + half_box)) + 2) - lo[a]);
-        }
+        lo[a] = float(t0[a] - 2);
+        hi[a] = float(t0[a] + dim[a] + 1);
     }
-    const int total = num[0] * num[1] * num[2];
-    __syncthreads();
-    auto scatter = [&]() {  // the listed samples, one per thread and round
-        const int n = count;
-        for (int e = int(threadIdx.x); e < n; e += kTileBlock) {
-            const int k = list[e];
-            cplx<T> v = c[k];
-            v.re *= scale;
-            v.im *= scale;
-            T y[3];
-            tile_position(r, sign, T(k % n_m) - half_box, T((k / n_m) % n_m) - half_box,
-                          PLANAR ? T(0) : T(k / (n_m * n_m)) - half_box, y);
-            T wt[3][4];
-            int b[3];
+    box_samples<PLANAR>(rf, n_m, lo, hi, uniform(int(threadIdx.x) >> 6), kTileBlock / 64, [&](int i, int j, int k) {
+        cplx<T> v = c[(k * n_m + j) * n_m + i];
+        v.re *= scale;
+        v.im *= scale;
+        const T bx = T(i) - half_box, by = T(j) - half_box, bz = PLANAR ? T(0) : T(k) - half_box;
+        T wt[3][4];
+        int b[3];
 #pragma unroll
-            for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
-                const T fl = dev_floor(y[a]);
-                b[a] = int(fl) - 1 - t0[a];
-                bspline3_weights(y[a] - fl, wt[a]);
-            }
+        for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
+            const T y = sign * (r[3 * a] * bx + r[3 * a + 1] * by + r[3 * a + 2] * bz);
+            const T fl = dev_floor(y);
+            b[a] = int(fl) - 1 - t0[a];
+            bspline3_weights(y - fl, wt[a]);
+        }
 #pragma unroll
-            for (int cz = 0; cz < (PLANAR ? 1 : 4); ++cz) {
-                const int iz = PLANAR ? 0 : b[2] + cz;
-                if (unsigned(iz) >= unsigned(sz)) continue;
+        for (int cz = 0; cz < (PLANAR ? 1 : 4); ++cz) {
+            const int iz = PLANAR ? 0 : b[2] + cz;
+            if (unsigned(iz) >= unsigned(sz)) continue;
 #pragma unroll
-                for (int cy = 0; cy < 4; ++cy) {
-                    const int iy = b[1] + cy;
-                    if (unsigned(iy) >= unsigned(sy)) continue;
-                    const T wyz = PLANAR ? wt[1][cy] : wt[1][cy] * wt[2][cz];
-                    A* row = acc + ((iz * S::Y + iy) * S::PITCH) * 2;
+            for (int cy = 0; cy < 4; ++cy) {
+                const int iy = b[1] + cy;
+                if (unsigned(iy) >= unsigned(sy)) continue;
+                const T wyz = PLANAR ? wt[1][cy] : wt[1][cy] * wt[2][cz];
+                A* row = acc + (iz * S::Y + iy) * S::PITCH;
 #pragma unroll
-                    for (int cx = 0; cx < 4; ++cx) {
-                        const int ix = b[0] + cx;
-                        if (unsigned(ix) >= unsigned(sx)) continue;
-                        const T w3 = wt[0][cx] * wyz;
-                        atomicAdd(row + 2 * ix, TileSum<T>::fixed(v.re * w3));
-                        atomicAdd(row + 2 * ix + 1, TileSum<T>::fixed(v.im * w3));
-                    }
+                for (int cx = 0; cx < 4; ++cx) {
+                    const int ix = b[0] + cx;
+                    if (unsigned(ix) >= unsigned(sx)) continue;
+                    const T w3 = wt[0][cx] * wyz;
+                    atomicAdd(row + ix, TileSum<T>::fixed(v.re * w3));
+                    atomicAdd(row + S::IMAG + ix, TileSum<T>::fixed(v.im * w3));
                 }
             }
         }
-    };
-    for (int e0 = 0; e0 < total; e0 += kTileBlock) {
-        const int e = e0 + int(threadIdx.x);
-        bool hit = false;
-        int k = 0;
-        if (e < total) {
-            const int i = lo[0] + e % num[0], j = lo[1] + (e / num[0]) % num[1], l = lo[2] + e / (num[0] * num[1]);
-            k = (l * n_m + j) * n_m + i;
-            T y[3];
-            tile_position(r, sign, T(i) - half_box, T(j) - half_box, PLANAR ? T(0) : T(l) - half_box, y);
-            hit = true;
-#pragma unroll
-            for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
-                const int b = int(dev_floor(y[a])) - 1 - t0[a];
-                hit &= b >= -3 && b < dim[a];
-            }
-        }
-        const unsigned long long m = __ballot(hit);
-        int at = 0;
-        if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&count, int(__popcll(m)));
-        at = __builtin_amdgcn_readfirstlane(at);
-        if (hit) list[at + int(__popcll(m & ((1ull << (threadIdx.x & 63)) - 1)))] = k;
-        __syncthreads();
-        const int n = count;
-        __syncthreads();  // every wave has read it before the next round appends
-        if (n > kTileList - kTileBlock) {  // no room for another round
-            scatter();
-            __syncthreads();
-            if (threadIdx.x == 0) count = 0;
-            __syncthreads();
-        }
-    }
-    scatter();
+    });
     __syncthreads();
     for (int i = int(threadIdx.x); i < sx * sy * sz; i += kTileBlock) {
         const int ix = i % sx, iy = (i / sx) % sy, iz = i / (sx * sy);
-        const A* a = acc + ((iz * S::Y + iy) * S::PITCH + ix) * 2;
+        const A* a = acc + (iz * S::Y + iy) * S::PITCH + ix;
         const int ux = (t0[0] + ix + N) % N, uy = (t0[1] + iy + N) % N, uz = PLANAR ? 0 : (t0[2] + iz + N) % N;
         using I = typename std::conditional<std::is_same<T, double>::value, long long, int>::type;
-        cplx<T> v = mk(T(I(a[0])) * inv, T(I(a[1])) * inv);
+        cplx<T> v = mk(T(I(a[0])) * inv, T(I(a[S::IMAG])) * inv);
         // a transform of any value that is not finite is NaN everywhere
         if (!finite) v = mk(T(NAN), T(NAN));
         g[(int64_t(uz) * N + uy) * N + ux] = v;

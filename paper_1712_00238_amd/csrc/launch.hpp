@@ -227,11 +227,15 @@ template <typename T>
 size_t grad_workspace_bytes(int64_t B, int N, int n_m, bool planar, int wmode);
 // grad_c (may be NULL): complex per-sample sums of grad_scale_b Phi_b(y_k);
 // grad_w then follows as Re(rho_M grad_c)
-// cotangent of sum_b s_b f_b with respect to rho_F (complex, zeroed here);
-// ws: 12 B doubles
+// cotangent of sum_b s_b f_b with respect to rho_F (complex, every node
+// written); ws: fixed_cotangent_bytes, with `split` so much that grids of few
+// tiles can divide the poses over more blocks
+template <typename T>
+size_t fixed_cotangent_bytes(int64_t B, int N, bool planar, bool split);
 template <typename T>
 hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool planar, int N, const double* poses,
-                                  int64_t B, const double* grad_scale, void* grad_f, void* ws, hipStream_t s);
+                                  int64_t B, const double* grad_scale, void* grad_f, void* ws, size_t ws_bytes,
+                                  hipStream_t s);
 // out[b][j] = gp[b][j] * scale[b], FP64 B x 7 (may be in place)
 hipError_t launch_pose_chain(const double* gp, const double* scale, int64_t B, double* out, hipStream_t s);
 // grad_rho[k] = w_m[k] grad_c[k] (complex, context precision)
