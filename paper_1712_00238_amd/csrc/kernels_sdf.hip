@@ -204,56 +204,24 @@ __device__ __forceinline__ void nearer(double d2, int s, const int* __restrict__
     }
 }
 
-// PHI: the kernel of eq. 13 (kPhi* in launch.hpp): skeletal (eq. 15),
-// inverse-square (eq. 15 with the medial Gaussian at its peak: the pair
-// term without the exponential), or the double skin layer of eq. 3a, which
-// needs only the signed distance of pass 1.
-// FAST (FP32): pass 2 over the FP32 records with interpolated far clusters and
-// MFMA distances; otherwise over the FP64 samples, pair by pair.
-// WPB: waves per brick.  4 waves share the samples of a brick (and meet in
-// LDS after each pass) where a grid has too few bricks to fill the chip.
-// STATS (measurement builds only): adds to stats[0..2] the node-sample pairs
-// evaluated in pass 1, the pairs (and interpolation points) evaluated in pass
-// 2, and the pairs inside the contact ball, represented ones included.
-template <typename T, int PHI, bool FAST, int WPB, bool STATS = false>
-__global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_build_kernel(const double* __restrict__ q,
-                                                              const double* __restrict__ nrm,
-                                                              const double* __restrict__ qs,
-                                                              const double* __restrict__ wn,
-                                                              const int* __restrict__ js,
-                                                              const TreeNode* __restrict__ nodes, SampleTree tr,
-                                                              const float* __restrict__ rec1,
-                                                              const float* __restrict__ rec2, int64_t ns, GridDesc g,
-                                                              ParamDesc prm, cplx<T>* __restrict__ out,
-                                                              unsigned long long* __restrict__ stats) {
-    static_assert(WPB == 1 || WPB == 4, "waves per brick");
-    __shared__ double sh_best[WPB == 4 ? 256 : 1];
-    __shared__ __align__(8) int sh_idx[WPB == 4 ? 256 : 2];
-    const int lane = int(threadIdx.x) & 63, sub = WPB == 1 ? 0 : uniform(int(threadIdx.x) >> 6);
-    const int n = lane & 15, gq = lane >> 4;
-    const int64_t brick = blockIdx.x;
-    const BrickGrid bg = wave_bricks(g.nx, g.ny, g.nz);
-    // Consecutive blocks go to the XCDs and their shader engines in turn, so a
-    // row of bricks as long as a multiple of their number would give each
-    // engine one column of the grid, whose work differs several times over:
-    // every row starts at another column.
-    const int by = int((brick / bg.nx) % bg.ny), bz = int(brick / (int64_t(bg.nx) * bg.ny));
-    const int bx = int((brick + 5 * by + 11 * bz) % bg.nx);
-    const int i = bx * bg.sx + (n & 3), j = by * bg.sy + ((n >> 2) & (bg.sy - 1)),
-              k = bz * bg.sz + (n >> 2) / bg.sy;
-    const bool valid = i < g.nx && j < g.ny && k < g.nz;
-    const double px = g.ox + g.h * i, py = g.oy + g.h * j, pz = g.oz + g.h * k;
-    unsigned long long vis1 = 0, vis2 = 0, inball = 0;
-
-    // ---- pass 1 (FP64): nearest sample, lowest original index on exact ties
-    double best = INFINITY;  // over the samples this lane has seen
+// Pass 1 (FP64) for the wave's 16 nodes: squared distance to the nearest
+// sample and its Hilbert position (-1: no finite sample), the lowest original
+// index on exact ties, in all four lanes of a node.  With WPB = 4 the wave sees
+// the sub-th quarter of every leaf.
+template <int WPB>
+__device__ __forceinline__ void wave_nearest(const double* __restrict__ qs, const int* __restrict__ js,
+                                             const TreeNode* __restrict__ nodes, const SampleTree& tr, int64_t ns,
+                                             double px, double py, double pz, bool valid, int sub, double& best,
+                                             int& sbest, unsigned long long* visited) {
+    const int gq = (int(threadIdx.x) & 63) >> 4;
+    best = INFINITY;          // over the samples this lane has seen
     double bound = INFINITY;  // over those its node's four lanes have seen
-    int sbest = -1;
+    sbest = -1;
     auto leaf_nearest = [&](int leaf) {
         const int64_t s0 = int64_t(leaf) * kLeaf;
         const int cnt = int(ns - s0 < kLeaf ? ns - s0 : kLeaf);
-        if (STATS && valid)
-            for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) ++vis1;
+        if (visited && valid)
+            for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) ++*visited;
 #pragma unroll 4
         for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) {
             const int64_t s = s0 + a;
@@ -311,6 +279,53 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
         const int s1 = __shfl_xor(sbest, off);
         nearer(d1, s1, js, best, sbest);
     }
+}
+
+// PHI: the kernel of eq. 13 (kPhi* in launch.hpp): skeletal (eq. 15),
+// inverse-square (eq. 15 with the medial Gaussian at its peak: the pair
+// term without the exponential), or the double skin layer of eq. 3a, which
+// needs only the signed distance of pass 1.
+// FAST (FP32): pass 2 over the FP32 records with interpolated far clusters and
+// MFMA distances; otherwise over the FP64 samples, pair by pair.
+// WPB: waves per brick.  4 waves share the samples of a brick (and meet in
+// LDS after each pass) where a grid has too few bricks to fill the chip.
+// STATS (measurement builds only): adds to stats[0..2] the node-sample pairs
+// evaluated in pass 1, the pairs (and interpolation points) evaluated in pass
+// 2, and the pairs inside the contact ball, represented ones included.
+template <typename T, int PHI, bool FAST, int WPB, bool STATS = false>
+__global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_build_kernel(const double* __restrict__ q,
+                                                              const double* __restrict__ nrm,
+                                                              const double* __restrict__ qs,
+                                                              const double* __restrict__ wn,
+                                                              const int* __restrict__ js,
+                                                              const TreeNode* __restrict__ nodes, SampleTree tr,
+                                                              const float* __restrict__ rec1,
+                                                              const float* __restrict__ rec2, int64_t ns, GridDesc g,
+                                                              ParamDesc prm, cplx<T>* __restrict__ out,
+                                                              unsigned long long* __restrict__ stats) {
+    static_assert(WPB == 1 || WPB == 4, "waves per brick");
+    __shared__ double sh_best[WPB == 4 ? 256 : 1];
+    __shared__ __align__(8) int sh_idx[WPB == 4 ? 256 : 2];
+    const int lane = int(threadIdx.x) & 63, sub = WPB == 1 ? 0 : uniform(int(threadIdx.x) >> 6);
+    const int n = lane & 15, gq = lane >> 4;
+    const int64_t brick = blockIdx.x;
+    const BrickGrid bg = wave_bricks(g.nx, g.ny, g.nz);
+    // Consecutive blocks go to the XCDs and their shader engines in turn, so a
+    // row of bricks as long as a multiple of their number would give each
+    // engine one column of the grid, whose work differs several times over:
+    // every row starts at another column.
+    const int by = int((brick / bg.nx) % bg.ny), bz = int(brick / (int64_t(bg.nx) * bg.ny));
+    const int bx = int((brick + 5 * by + 11 * bz) % bg.nx);
+    const int i = bx * bg.sx + (n & 3), j = by * bg.sy + ((n >> 2) & (bg.sy - 1)),
+              k = bz * bg.sz + (n >> 2) / bg.sy;
+    const bool valid = i < g.nx && j < g.ny && k < g.nz;
+    const double px = g.ox + g.h * i, py = g.oy + g.h * j, pz = g.oz + g.h * k;
+    unsigned long long vis1 = 0, vis2 = 0, inball = 0;
+
+    // ---- pass 1 (FP64): nearest sample, lowest original index on exact ties
+    double best;
+    int sbest;
+    wave_nearest<WPB>(qs, js, nodes, tr, ns, px, py, pz, valid, sub, best, sbest, STATS ? &vis1 : nullptr);
     if constexpr (WPB == 4) {
         sh_best[threadIdx.x] = best;
         sh_idx[threadIdx.x] = sbest;
@@ -561,16 +576,6 @@ struct Brick {
 };
 __host__ __device__ inline Brick brick_shape(int nz) { return nz == 1 ? Brick{16, 16, 1} : Brick{8, 8, 4}; }
 
-// A zero the compiler cannot see through: LDS addresses offset by it stay in
-// a vector register across a loop, so the broadcast reads of the sample
-// tiles use immediate offsets from it instead of re-copying a scalar base
-// into a vector register for every read.
-__device__ __forceinline__ int opaque_zero() {
-    int z = 0;
-    asm volatile("" : "+v"(z));
-    return z;
-}
-
 // Samples in Hilbert order with per-tile bounding boxes.
 struct SampleTiles {
     const double* qs;   // positions, n x 3
@@ -614,52 +619,15 @@ __device__ __forceinline__ double block_reduce(double v, double* red) {
     return v;
 }
 
-// Pass 1 (FP64) for the node (px, py, pz) of the brick [bl, bh]: squared
-// distance to the nearest sample and its original index (lowest on exact
-// ties), visiting only the tiles within U of the brick.  Block-wide: every
-// thread of the block calls it.
-__device__ __forceinline__ void nearest_pass(const SampleTiles& st, int64_t ns, const double bl[3], const double bh[3],
-                                             double px, double py, double pz, v4<double>* sq, int* sidx, int* tflag,
-                                             double* red, double& best, int& jbest, int64_t* visited = nullptr) {
-    double u2 = INFINITY;
-    for (int64_t t = threadIdx.x; t < st.ntile; t += kSdfBlock) u2 = fmin(u2, box_dmax2(bl, bh, st.box + 6 * t));
-    u2 = block_reduce<false>(u2, red) * (1.0 + 1e-9);
-    best = INFINITY;
-    jbest = 0;
-    for (int64_t c0 = 0; c0 < st.ntile; c0 += kSdfBlock) {
-        const int64_t tc = c0 + threadIdx.x;
-        __syncthreads();  // the previous chunk is done with tflag, sq and sidx
-        tflag[threadIdx.x] = tc < st.ntile && box_dmin2(bl, bh, st.box + 6 * tc) <= u2;
-        __syncthreads();
-        const int nchunk = int(st.ntile - c0 < kSdfBlock ? st.ntile - c0 : kSdfBlock);
-        for (int kk = 0; kk < nchunk; ++kk) {
-            if (!tflag[kk]) continue;  // uniform across the block
-            const int64_t t0 = (c0 + kk) * kSdfTile;
-            const int cnt = int(ns - t0 < kSdfTile ? ns - t0 : kSdfTile);
-            if (visited) *visited += cnt;
-            __syncthreads();
-            for (int a = threadIdx.x; a < cnt; a += kSdfBlock) {
-                const int64_t s = t0 + a;
-                sq[a] = v4<double>{st.qs[3 * s], st.qs[3 * s + 1], st.qs[3 * s + 2], 0.0};
-                sidx[a] = st.js[s];
-            }
-            __syncthreads();
-            const int z0 = opaque_zero();
-            const v4<double>* sqb = sq + z0;
-            const int* sib = sidx + z0;
-#pragma unroll 4
-            for (int a = 0; a < cnt; ++a) {
-                const v4<double> s = sqb[a];
-                const double dx = px - s.x, dy = py - s.y, dz = pz - s.z;
-                const double d2 = dx * dx + dy * dy + dz * dz;
-                const int jj = sib[a];
-                if (d2 < best || (d2 == best && jj < jbest)) {
-                    best = d2;
-                    jbest = jj;
-                }
-            }
-        }
+// least squared distance between a brick's box and a tree node's
+__device__ __forceinline__ double box_gap2(const double bl[3], const double bh[3], const TreeNode& t) {
+    double s = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double d = fmax(0.0, fmax(t.lo[a] - bh[a], bl[a] - t.hi[a]));
+        s += d * d;
     }
+    return s;
 }
 
 // ---- radial-basis affinity (eq. 2, continuum form): Gaussian shells of
@@ -782,187 +750,223 @@ __global__ void offset_points_kernel(const double* __restrict__ q, const double*
 //   d rho / d xi  = -(2 rho + A sum_j w_j c_j K'(r_j) r_j) / xi,   d xi / d q* = -u*,
 // with A = lambda / (2 pi sigma xi^2), K = G P / (1 + r^2)^2 as in the sum and
 //   K' = K (-(r - 1) / sigma^2 - 4 r / (1 + r^2)) + G (-2 r + i s) / (1 + r^2)^2.
-__device__ __forceinline__ void kernel_and_slope(double r, double sig2inv, double s, double& kre, double& kim,
-                                                 double& dre, double& dim) {
-    const double x = r - 1.0;
-    const double G = exp(-0.5 * x * x * sig2inv);
-    const double iden = 1.0 / (1.0 + r * r);
-    const double gi = G * iden * iden;
-    kre = gi * (1.0 - r * r);
-    kim = gi * (s * r);
-    const double f = -x * sig2inv - 4.0 * r * iden;
-    dre = kre * f - 2.0 * r * gi;
-    dim = kim * f + s * gi;
+//
+// The kernels below use FP64 exp, rsqrt and reciprocals of a few instructions
+// (errors of about one unit in the last place): the sums are bound by them.
+
+// exp(t), t <= 0: t = n ln 2 + f with ln 2 in two parts (Cody and Waite), |f| <= ln 2 / 2, Taylor to
+// f^13 / 13! (4e-18)
+__device__ __forceinline__ double exp_neg(double t) {
+    t = fmax(t, -745.0);
+    const double n = rint(t * 1.4426950408889634);
+    const double f = __builtin_fma(n, -1.9082149292705877e-10, __builtin_fma(n, -0.6931471803691238, t));
+    double p = 1.0 / 6227020800.0;
+    p = __builtin_fma(p, f, 1.0 / 479001600.0);
+    p = __builtin_fma(p, f, 1.0 / 39916800.0);
+    p = __builtin_fma(p, f, 1.0 / 3628800.0);
+    p = __builtin_fma(p, f, 1.0 / 362880.0);
+    p = __builtin_fma(p, f, 1.0 / 40320.0);
+    p = __builtin_fma(p, f, 1.0 / 5040.0);
+    p = __builtin_fma(p, f, 1.0 / 720.0);
+    p = __builtin_fma(p, f, 1.0 / 120.0);
+    p = __builtin_fma(p, f, 1.0 / 24.0);
+    p = __builtin_fma(p, f, 1.0 / 6.0);
+    p = __builtin_fma(p, f, 0.5);
+    p = __builtin_fma(p, f, 1.0);
+    p = __builtin_fma(p, f, 1.0);
+    return __builtin_amdgcn_ldexp(p, int(n));
+}
+// x^(-1/2) and 1 / x for normal x > 0: the hardware estimate (about 24 bits) and one cubic Newton step
+__device__ __forceinline__ double rsqrt_step(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-x * y, y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+__device__ __forceinline__ double rcp_step(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, y, 1.0);
+    return __builtin_fma(y, __builtin_fma(e, e, e), y);
 }
 
-// A block per brick.  Pass 1 as in the build; a node pass over the contact
-// ball gives rho and the xi term, added to the nearest sample's position
-// gradient; a sample pass puts the brick's live nodes in LDS, and each
-// thread owns one sample of a visited tile and sums its gradient over those
-// nodes.  Sums across bricks go through FP64 atomics (their order varies, so
-// the last bits of the gradients may vary between runs).
+// sum over each row of 16 lanes, in every lane of the row
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+    v += row_move<0xb1>(v);   // quad_perm [1, 0, 3, 2]
+    v += row_move<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+    v += row_move<0x124>(v);  // row_ror 4
+    v += row_move<0x128>(v);  // row_ror 8
+    return v;
+}
+
+// A block per brick of 256 nodes (16 groups of 16, as the build's waves take
+// them) and range of leaves.  Pass 1 as in the build puts every node's data in
+// LDS; then each wave takes leaves: a lane owns one of the 64 samples and walks
+// the nodes whose ball reaches the leaf, so that one evaluation of a pair's
+// kernel serves both sums: the sample's seven gradient components stay in the
+// lane's registers, and the node's xi term,
+//   Re(g d rho / d xi) = -(1 / xi) sum_j w_j c_j Re(A g (2 K(r_j) + K'(r_j) r_j)),
+// one value per pair, is summed over the lanes.  Samples are added to the
+// gradients once per leaf and block by FP64 atomics (their order varies, so the
+// last bits may vary between runs); blocks start at different leaves, so they
+// do not add to the same addresses at a time.
+// Bound by FP64 VALU issue, about 100 instructions per pair (a pass over the
+// nodes and one over the samples, with the library's exp, took some 220):
+// 3.9k samples on 64^3 nodes 5.2 -> 2.5 ms.
 template <typename T>
 __global__ __launch_bounds__(kSdfBlock) void sdf_adjoint_kernel(const double* __restrict__ q,
                                                                 const double* __restrict__ nrm,
-                                                                const double* __restrict__ w, SampleTiles st,
+                                                                const double* __restrict__ w,
+                                                                const double* __restrict__ qs,
+                                                                const int* __restrict__ js,
+                                                                const TreeNode* __restrict__ nodes, SampleTree tr,
                                                                 int64_t ns, GridDesc g, ParamDesc prm,
                                                                 const cplx<T>* __restrict__ cot,
                                                                 double* __restrict__ gq, double* __restrict__ gn,
                                                                 double* __restrict__ gw) {
-    __shared__ v4<double> sq[2 * kSdfTile];
-    __shared__ int sidx[kSdfTile];
-    __shared__ int tflag[kSdfBlock];
-    __shared__ double red[kSdfBlock / 64];
     __shared__ v4<double> nodep[kSdfBlock];  // (px, py, pz, 1 / xi)
     __shared__ v4<double> nodeg[kSdfBlock];  // (A g.re, A g.im, ball radius^2 or -1, s)
-    static_assert(kSdfTile == kSdfBlock, "one sample per thread in the sample pass");
+    __shared__ double nsum[kSdfBlock];
+    __shared__ int nnear[kSdfBlock];
+    __shared__ double red[kSdfBlock / 64];
 
     const Brick br = brick_shape(g.nz);
     const int nbx = (g.nx + br.bx - 1) / br.bx, nby = (g.ny + br.by - 1) / br.by;
     const int blk = blockIdx.x;
     const int i0 = (blk % nbx) * br.bx, j0 = ((blk / nbx) % nby) * br.by, k0 = (blk / (nbx * nby)) * br.bz;
-    const int li = threadIdx.x % br.bx, lj = (threadIdx.x / br.bx) % br.by, lk = threadIdx.x / (br.bx * br.by);
-    const int i = i0 + li, j = j0 + lj, k = k0 + lk;
-    const bool valid = i < g.nx && j < g.ny && k < g.nz;
-    const double cx = g.ox + g.h * i0, cy = g.oy + g.h * j0, cz = g.oz + g.h * k0;
-    const double px = cx + g.h * li, py = cy + g.h * lj, pz = cz + g.h * lk;
-    const double bl[3] = {cx, cy, cz};
-    const double bh[3] = {cx + g.h * (min(br.bx, g.nx - i0) - 1), cy + g.h * (min(br.by, g.ny - j0) - 1),
-                          cz + g.h * (min(br.bz, g.nz - k0) - 1)};
-
-    double best;
-    int jbest;
-    nearest_pass(st, ns, bl, bh, px, py, pz, sq, sidx, tflag, red, best, jbest);
-    const int64_t jb = jbest;
-    const double ex = px - q[3 * jb], ey = py - q[3 * jb + 1], ez = pz - q[3 * jb + 2];
-    const double dot = ex * nrm[3 * jb] + ey * nrm[3 * jb + 1] + ez * nrm[3 * jb + 2];
-    const int pmc = dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
-    const double xi = sqrt(best);
-    const cplx<T> gt = valid ? cot[(int64_t(k) * g.ny + j) * g.nx + i] : mk(T(0), T(0));
-    const double g_re = double(gt.re), g_im = double(gt.im);
-    const bool act = valid && pmc != 0 && xi >= prm.xi_floor && (g_re != 0.0 || g_im != 0.0);
-    const double r2max = (1.0 + prm.eps) * (1.0 + prm.eps) * best;
-    const double lam = pmc > 0 ? prm.lambda1 : -prm.lambda2;
-    const double sgn = pmc > 0 ? -2.0 : 2.0;
-    const double A = lam / (2.0 * 3.14159265358979323846 * prm.sigma * best);
-    const double inv_xi = 1.0 / xi;
+    const int lane = int(threadIdx.x) & 63, wave = uniform(int(threadIdx.x) >> 6);
     const double sig2inv = 1.0 / (prm.sigma * prm.sigma);
-    const double r2brick = block_reduce<true>(act ? r2max : -1.0, red) * (1.0 + 1e-9);
-    if (r2brick < 0.0) return;  // uniform: no node of the brick contributes
 
-    // ---- node pass: rho / A and sum_j w_j c_j K'(r_j) r_j over the ball
-    double rr = 0.0, ri = 0.0, sr = 0.0, si = 0.0;
-    for (int64_t c0 = 0; c0 < st.ntile; c0 += kSdfBlock) {
-        const int64_t tc = c0 + threadIdx.x;
-        __syncthreads();
-        tflag[threadIdx.x] = tc < st.ntile && box_dmin2(bl, bh, st.box + 6 * tc) <= r2brick;
-        __syncthreads();
-        const int nchunk = int(st.ntile - c0 < kSdfBlock ? st.ntile - c0 : kSdfBlock);
-        for (int kk = 0; kk < nchunk; ++kk) {
-            if (!tflag[kk]) continue;  // uniform across the block
-            const int64_t t0 = (c0 + kk) * kSdfTile;
-            const int cnt = int(ns - t0 < kSdfTile ? ns - t0 : kSdfTile);
-            __syncthreads();
-            for (int a = threadIdx.x; a < cnt; a += kSdfBlock) {
-                const int64_t s = t0 + a;
-                sq[a] = v4<double>{st.qs[3 * s], st.qs[3 * s + 1], st.qs[3 * s + 2], 0.0};
-                sq[kSdfTile + a] = v4<double>{st.wn[3 * s], st.wn[3 * s + 1], st.wn[3 * s + 2], 0.0};
-            }
-            __syncthreads();
-            if (act) {
-                for (int a = 0; a < cnt; ++a) {
-                    const v4<double> sp = sq[a];
-                    const double dx = px - sp.x, dy = py - sp.y, dz = pz - sp.z;
-                    const double d2 = dx * dx + dy * dy + dz * dz;
-                    if (d2 <= r2max) {
-                        const v4<double> wv = sq[kSdfTile + a];
-                        const double ie = rsqrt(d2);
-                        const double eta = d2 * ie;
-                        const double wc = (dx * wv.x + dy * wv.y + dz * wv.z) * ie;  // w_j c_j
-                        const double r = eta * inv_xi;
-                        double kre, kim, dre, dim;
-                        kernel_and_slope(r, sig2inv, sgn, kre, kim, dre, dim);
-                        rr += wc * kre;
-                        ri += wc * kim;
-                        sr += wc * dre * r;
-                        si += wc * dim * r;
-                    }
-                }
-            }
+    for (int grp = 4 * wave; grp < 4 * wave + 4; ++grp) {
+        const int n = lane & 15;
+        const bool planar = g.nz == 1;
+        const int i = i0 + (planar ? 4 * (grp & 3) : 4 * (grp & 1)) + (n & 3);
+        const int j = j0 + (planar ? 4 * (grp >> 2) + (n >> 2) : 2 * ((grp >> 1) & 3) + ((n >> 2) & 1));
+        const int k = k0 + (planar ? 0 : 2 * (grp >> 3) + (n >> 3));
+        const bool valid = i < g.nx && j < g.ny && k < g.nz;
+        const double px = g.ox + g.h * i, py = g.oy + g.h * j, pz = g.oz + g.h * k;
+        double best;
+        int sbest;
+        wave_nearest<1>(qs, js, nodes, tr, ns, px, py, pz, valid, 0, best, sbest, nullptr);
+        if (lane < 16) {
+            const int64_t jb = sbest >= 0 ? js[sbest] : 0;
+            const double dot = (px - q[3 * jb]) * nrm[3 * jb] + (py - q[3 * jb + 1]) * nrm[3 * jb + 1] +
+                               (pz - q[3 * jb + 2]) * nrm[3 * jb + 2];
+            const int pmc = dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
+            const double xi = sqrt(best);
+            const cplx<T> gt = valid ? cot[(int64_t(k) * g.ny + j) * g.nx + i] : mk(T(0), T(0));
+            const double g_re = double(gt.re), g_im = double(gt.im);
+            const bool act = valid && pmc != 0 && xi >= prm.xi_floor && (g_re != 0.0 || g_im != 0.0);
+            const double lam = pmc > 0 ? prm.lambda1 : -prm.lambda2;
+            const double A = lam / (2.0 * 3.14159265358979323846 * prm.sigma * best);
+            const int m = 16 * grp + n;
+            nodep[m] = v4<double>{px, py, pz, 1.0 / xi};
+            nodeg[m] = v4<double>{A * g_re, A * g_im, act ? (1.0 + prm.eps) * (1.0 + prm.eps) * best : -1.0,
+                                  pmc > 0 ? -2.0 : 2.0};
+            nnear[m] = int(jb);
+            nsum[m] = 0.0;
         }
     }
-    if (act) {
-        // d rho / d xi = -(2 A rr + A sr) / xi (complex), then Re(g ...) along -u*
-        const double dre = -A * (2.0 * rr + sr) * inv_xi, dim = -A * (2.0 * ri + si) * inv_xi;
-        const double coef = (g_re * dre - g_im * dim) * inv_xi;
-        atomicAdd(gq + 3 * jb, -coef * ex);
-        atomicAdd(gq + 3 * jb + 1, -coef * ey);
-        atomicAdd(gq + 3 * jb + 2, -coef * ez);
-    }
-
-    // ---- sample pass: the brick's live nodes in LDS, one sample per thread.
-    // Every brick is resident at once, so each starts its walk over the tiles
-    // at its own offset: bricks then add to different samples' gradients at a
-    // time instead of contending for the same addresses.
     __syncthreads();
-    nodep[threadIdx.x] = v4<double>{px, py, pz, inv_xi};
-    nodeg[threadIdx.x] = v4<double>{A * g_re, A * g_im, act ? r2max : -1.0, sgn};
-    const int64_t nchunks = (st.ntile + kSdfBlock - 1) / kSdfBlock;
-    for (int64_t ci = 0; ci < nchunks; ++ci) {
-        const int64_t c0 = ((ci + blk) % nchunks) * kSdfBlock;
-        const int64_t tc = c0 + threadIdx.x;
-        __syncthreads();
-        tflag[threadIdx.x] = tc < st.ntile && box_dmin2(bl, bh, st.box + 6 * tc) <= r2brick;
-        __syncthreads();
-        const int nchunk = int(st.ntile - c0 < kSdfBlock ? st.ntile - c0 : kSdfBlock);
-        for (int k1 = 0; k1 < nchunk; ++k1) {
-            const int kk = (k1 + blk) % nchunk;
-            if (!tflag[kk]) continue;  // uniform across the block
-            const int64_t t0 = (c0 + kk) * kSdfTile;
-            const int cnt = int(ns - t0 < kSdfTile ? ns - t0 : kSdfTile);
-            if (int(threadIdx.x) >= cnt) continue;
-            const int64_t sj = st.js[t0 + threadIdx.x];
+    const double r2brick = block_reduce<true>(nodeg[threadIdx.x].z, red) * (1.0 + 1e-9);
+    if (r2brick < 0.0) return;  // uniform: no node of the brick contributes
+    const double bl[3] = {g.ox + g.h * i0, g.oy + g.h * j0, g.oz + g.h * k0};
+    const double bh[3] = {bl[0] + g.h * (min(br.bx, g.nx - i0) - 1), bl[1] + g.h * (min(br.by, g.ny - j0) - 1),
+                          bl[2] + g.h * (min(br.bz, g.nz - k0) - 1)};
+
+    // this wave's leaves: every (4 splits)-th, walked from an offset of its own
+    const int nleaf = tr.cnt[0], step = 4 * int(gridDim.y), first = 4 * int(blockIdx.y) + wave;
+    const int own = first < nleaf ? (nleaf - first + step - 1) / step : 0;
+    for (int t0 = 0; t0 < own; t0 += 64) {
+        int lf = -1;
+        if (t0 + lane < own) lf = first + step * int((unsigned(t0 + lane) + unsigned(blk)) % unsigned(own));
+        const bool hit = lf >= 0 && box_gap2(bl, bh, nodes[lf]) <= r2brick;
+        unsigned long long todo = __ballot(hit);
+        while (todo) {
+            const int from = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const int leaf = uniform(__shfl(lf, from));
+            const TreeNode& tn = nodes[leaf];
+            const int64_t sidx = int64_t(leaf) * kLeaf + lane;
+            const bool have = sidx < ns;
+            const int64_t sj = js[have ? sidx : int64_t(leaf) * kLeaf];
             const double qx = q[3 * sj], qy = q[3 * sj + 1], qz = q[3 * sj + 2];
             const double nx = nrm[3 * sj], ny = nrm[3 * sj + 1], nz = nrm[3 * sj + 2];
             const double wj = w[sj];
-            double aq0 = 0.0, aq1 = 0.0, aq2 = 0.0, an0 = 0.0, an1 = 0.0, an2 = 0.0, aw = 0.0;
+            // sums of gk u, of e u, of -gk / eta and of c gk (see below)
+            double b0 = 0.0, b1 = 0.0, b2 = 0.0, e0 = 0.0, e1 = 0.0, e2 = 0.0, s1 = 0.0, aw = 0.0;
             bool any = false;
-            for (int nd = 0; nd < kSdfBlock; ++nd) {
-                const v4<double> ng = nodeg[nd];
-                if (ng.z < 0.0) continue;  // the same node for every thread: uniform
-                const v4<double> np = nodep[nd];
-                const double dx = np.x - qx, dy = np.y - qy, dz = np.z - qz;
-                const double d2 = dx * dx + dy * dy + dz * dz;
-                if (d2 > ng.z) continue;
-                any = true;
-                const double ie = rsqrt(d2);
-                const double ux = dx * ie, uy = dy * ie, uz = dz * ie;
-                const double c = ux * nx + uy * ny + uz * nz;
-                const double r = d2 * ie * np.w;
-                double kre, kim, dre, dim;
-                kernel_and_slope(r, sig2inv, ng.w, kre, kim, dre, dim);
-                const double gk = ng.x * kre - ng.y * kim;    // Re(A g K)
-                const double gkp = ng.x * dre - ng.y * dim;   // Re(A g K')
-                aw += c * gk;
-                const double wg = wj * gk;
-                an0 += wg * ux;
-                an1 += wg * uy;
-                an2 += wg * uz;
-                const double t1 = -wg * ie, t2 = -wj * c * gkp * np.w;
-                aq0 += t1 * (nx - c * ux) + t2 * ux;
-                aq1 += t1 * (ny - c * uy) + t2 * uy;
-                aq2 += t1 * (nz - c * uz) + t2 * uz;
+            for (int c0 = 0; c0 < kSdfBlock; c0 += 64) {
+                const v4<double> np0 = nodep[c0 + lane];
+                const unsigned long long reach =
+                    __ballot(node_dmin2(tn, np0.x, np0.y, np0.z) <= nodeg[c0 + lane].z * (1.0 + 1e-9));
+                for (int sg = 0; sg < 64; sg += 16) {
+                    int bits = int(reach >> sg) & 0xffff;
+                    if (!bits) continue;
+                    double nacc = 0.0;
+                    while (bits) {
+                        const int b = __builtin_ctz(unsigned(bits));
+                        bits &= bits - 1;
+                        const v4<double> np = nodep[c0 + sg + b], ng = nodeg[c0 + sg + b];
+                        const double dx = np.x - qx, dy = np.y - qy, dz = np.z - qz;
+                        const double d2 = dist2(dx, dy, dz);
+                        const bool in = have && d2 <= ng.z;
+                        const double ie = rsqrt_step(d2);
+                        const double ux = dx * ie, uy = dy * ie, uz = dz * ie;
+                        const double c = ux * nx + uy * ny + uz * nz;
+                        const double r = d2 * ie * np.w;
+                        const double x = r - 1.0;
+                        const double G = exp_neg(-0.5 * sig2inv * x * x);
+                        const double iden = rcp_step(1.0 + r * r);
+                        const double gi = G * iden * iden;
+                        const double kre = gi * (1.0 - r * r), kim = gi * (ng.w * r);
+                        const double f = -x * sig2inv - 4.0 * r * iden;
+                        const double dre = kre * f - 2.0 * r * gi, dim = kim * f + ng.w * gi;
+                        // Re(A g K), Re(A g K')
+                        const double gk = in ? ng.x * kre - ng.y * kim : 0.0;
+                        const double gkp = in ? ng.x * dre - ng.y * dim : 0.0;
+                        any |= in;
+                        aw += c * gk;
+                        b0 += gk * ux;
+                        b1 += gk * uy;
+                        b2 += gk * uz;
+                        // d rho / d q_j = w [t1 (n - c u) + t2 u] = w [t1 n + e u]
+                        const double t1 = -gk * ie, e = -c * gkp * np.w - t1 * c;
+                        s1 += t1;
+                        e0 += e * ux;
+                        e1 += e * uy;
+                        e2 += e * uz;
+                        const double v = row_sum(in ? wj * c * (2.0 * gk + r * gkp) : 0.0);
+                        if ((lane & 15) == b) nacc = v;
+                    }
+                    if (nacc != 0.0) atomicAdd(nsum + c0 + sg + (lane & 15), nacc);
+                }
             }
             if (any) {
-                atomicAdd(gq + 3 * sj, aq0);
-                atomicAdd(gq + 3 * sj + 1, aq1);
-                atomicAdd(gq + 3 * sj + 2, aq2);
-                atomicAdd(gn + 3 * sj, an0);
-                atomicAdd(gn + 3 * sj + 1, an1);
-                atomicAdd(gn + 3 * sj + 2, an2);
+                atomicAdd(gq + 3 * sj, wj * (s1 * nx + e0));
+                atomicAdd(gq + 3 * sj + 1, wj * (s1 * ny + e1));
+                atomicAdd(gq + 3 * sj + 2, wj * (s1 * nz + e2));
+                atomicAdd(gn + 3 * sj, wj * b0);
+                atomicAdd(gn + 3 * sj + 1, wj * b1);
+                atomicAdd(gn + 3 * sj + 2, wj * b2);
                 atomicAdd(gw + sj, aw);
             }
         }
+    }
+    __syncthreads();
+    const double nv = nsum[threadIdx.x];
+    if (nodeg[threadIdx.x].z >= 0.0 && nv != 0.0) {
+        // xi term of the nearest sample: -(d rho / d xi) u*, u* = e / xi
+        const v4<double> np = nodep[threadIdx.x];
+        const int64_t jb = nnear[threadIdx.x];
+        const double coef = np.w * np.w * nv;
+        atomicAdd(gq + 3 * jb, coef * (np.x - q[3 * jb]));
+        atomicAdd(gq + 3 * jb + 1, coef * (np.y - q[3 * jb + 1]));
+        atomicAdd(gq + 3 * jb + 2, coef * (np.z - q[3 * jb + 2]));
     }
 }
 
@@ -1570,10 +1574,14 @@ hipError_t launch_sdf_adjoint(const double* q, const double* n, const double* w,
     if (e == hipSuccess) e = launch_zero_f64(grad_w, ns, s);
     if (e != hipSuccess) return e;
     Prepared P{};
-    e = prepare_samples(q, n, w, ns, g, ws, false, false, true, s, &P);
+    e = prepare_samples(q, n, w, ns, g, ws, false, false, false, s, &P);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sdf_adjoint_kernel<T>, dim3(unsigned(brick_count(g))), dim3(kSdfBlock), 0, s, q, n, w, P.st,
-                       ns, g, p, static_cast<const cplx<T>*>(cot), grad_q, grad_n, grad_w);
+    // grids of few bricks split the leaves so that about four blocks per CU run
+    const int64_t bricks = brick_count(g);
+    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(1024 / bricks, (P.tr.cnt[0] + 3) / 4));
+    hipLaunchKernelGGL(sdf_adjoint_kernel<T>, dim3(unsigned(bricks), unsigned(splits)), dim3(kSdfBlock), 0, s, q, n, w,
+                       P.st.qs, P.st.js, P.node, P.tr, ns, g, p, static_cast<const cplx<T>*>(cot), grad_q, grad_n,
+                       grad_w);
     return hipGetLastError();
 }
 
