@@ -616,14 +616,6 @@ __global__ void rho_from_c_kernel(const T* __restrict__ w_m, const T* __restrict
     grad_rho[2 * k + 1] = w_m[k] * grad_c[2 * k + 1];
 }
 
-// zero `count` values of type T (a kernel rather than hipMemsetAsync, so that
-// the calls stay valid inside captured graphs)
-template <typename T>
-__global__ void zero_fill_kernel(T* __restrict__ p, int64_t count) {
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < count; i += int64_t(gridDim.x) * blockDim.x)
-        p[i] = T(0);
-}
-
 // ---- cotangent of the scores with respect to rho_F (the adjoint of the
 // gather): G(p) = sum_b s_b sum_k c_k B3(p - y_kb), periodic, y_kb = R_b x_k + t_b.
 // Per pose: R (FP64).  Also clears the maxima of fixed_max_kernel.
@@ -1023,12 +1015,6 @@ hipError_t launch_rho_from_c(const T* w_m, const void* grad_c, int64_t K, void* 
 }
 template hipError_t launch_rho_from_c<float>(const float*, const void*, int64_t, void*, hipStream_t);
 template hipError_t launch_rho_from_c<double>(const double*, const void*, int64_t, void*, hipStream_t);
-
-hipError_t launch_zero_f64(double* p, int64_t count, hipStream_t s) {
-    hipLaunchKernelGGL(zero_fill_kernel<double>, dim3(unsigned(std::min<int64_t>((count + 255) / 256, 4096))),
-                       dim3(256), 0, s, p, count);
-    return hipGetLastError();
-}
 
 template size_t fixed_cotangent_bytes<float>(int64_t, int, bool, bool);
 template size_t fixed_cotangent_bytes<double>(int64_t, int, bool, bool);

@@ -1026,8 +1026,8 @@ __global__ void hilbert_key_kernel(const double* __restrict__ q, int64_t n, doub
 
 // Up to kSmallSort samples: keys and order in one block, a bitonic sort in
 // LDS of (key, index) words, which are distinct, so equal keys keep their
-// input order.  Bound by its barriers; replaces the key kernel and the twelve
-// to twenty launches of the radix sort, which is latency-bound at these sizes.
+// input order.  Bound by its LDS round trips; replaces the key kernel and the
+// twelve to twenty launches of the radix sort, latency-bound at these sizes.
 constexpr int kSmallSort = 4096;
 __global__ __launch_bounds__(1024) void small_order_kernel(const double* __restrict__ q, int n, int n2, double ox,
                                                            double oy, double oz, double inv_cell,
@@ -1046,8 +1046,14 @@ __global__ __launch_bounds__(1024) void small_order_kernel(const double* __restr
                     e[hi] = a;
                 }
             }
-            __syncthreads();
+            // pairs at strides up to 64 stay within the 128 words of one wave, whose LDS operations are in order
+            if (st > 64 || (st == 1 && k >= 128)) __syncthreads();
+            else {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
         }
+    __syncthreads();
     for (int j = int(threadIdx.x); j < n; j += 1024) order[j] = int(unsigned(e[j]));
 }
 
@@ -1173,19 +1179,25 @@ __device__ int interp_order(double tau) {
 }
 
 // Nodes of one or more levels from their children (one block per launch runs
-// the levels [l0, l1), or many blocks one level).  With FAST, the smallest
-// reach = half-width / tau whose tensor grid stays within `share` of the
-// node's samples.
+// the levels [l0, l1), or many blocks one level), 16 lanes a node.  With FAST,
+// lane k tries tau = 0.6 0.87^k, and the node takes the largest (the smallest
+// reach = half-width / tau) whose tensor grid stays within `share` of its
+// samples.
+constexpr int kTauTries = 14;
 template <bool FAST>
 __global__ __launch_bounds__(kSdfBlock) void tree_up_kernel(TreeNode* __restrict__ node, SampleTree tr, int l0,
                                                             int l1, int64_t n, GridDesc g, InterpLayout lay,
                                                             double share) {
+    const int k = int(threadIdx.x) & 15, per = kSdfBlock / 16;
     for (int l = l0; l < l1; ++l) {
         if (l > l0) __syncthreads();  // one block: the level below is complete
-        for (int i = int(blockIdx.x) * kSdfBlock + int(threadIdx.x); i < tr.cnt[l]; i += int(gridDim.x) * kSdfBlock) {
+        // every lane of a wave runs the same rounds: the choice of tau is a ballot
+        for (int i0 = int(blockIdx.x) * per; i0 < tr.cnt[l]; i0 += int(gridDim.x) * per) {
+            const int i = i0 + (int(threadIdx.x) >> 4);
+            const bool own = i < tr.cnt[l];
             TreeNode t;
             double half[3], hmax = 0.0;
-            bool ok = true;
+            bool ok = own;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 double lo = INFINITY, hi = -INFINITY;
@@ -1206,28 +1218,30 @@ __global__ __launch_bounds__(kSdfBlock) void tree_up_kernel(TreeNode* __restrict
             t.qmax2 = 0.f;
             t.px = 0;
             t.order = 0x111;
+            int pick = 0;
             if constexpr (FAST) {
                 const int64_t size = int64_t(kLeaf) << (2 * l);
                 const double have = double(n - size * i < size ? n - size * i : size);
                 t.px = int(lay.at[l] + int64_t(i) * (lay.cap[l] / 16));
-                for (int k = 0; ok && k < 14; ++k) {
-                    const double tau = 0.6 * pow(0.87, double(k));
-                    const double reach = hmax / tau;
-                    int p[3], most = 1;
+                double tau = 0.6;
+                for (int e = 0; e < k; ++e) tau *= 0.87;
+                const double reach = hmax / tau;
+                int p[3], most = 1;
 #pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        p[a] = hmax > 0.0 ? interp_order(half[a] / reach) : 1;
-                        most = p[a] > most ? p[a] : most;
-                    }
-                    const double m = double(p[0]) * p[1] * p[2];
-                    if (most <= kInterpMax && m <= share * have) {
-                        t.reach2 = float(reach * reach * 1.0001);
-                        t.order = p[0] | (p[1] << 4) | (p[2] << 8);
-                        ok = false;
-                    }
+                for (int a = 0; a < 3; ++a) {
+                    p[a] = hmax > 0.0 ? interp_order(half[a] / reach) : 1;
+                    most = p[a] > most ? p[a] : most;
                 }
+                const double m = double(p[0]) * p[1] * p[2];
+                const bool fits = ok && k < kTauTries && most <= kInterpMax && m <= share * have;
+                const int tries = int(__ballot(fits) >> (int(threadIdx.x) & 48)) & 0xffff;
+                if (fits) {
+                    t.reach2 = float(reach * reach * 1.0001);
+                    t.order = p[0] | (p[1] << 4) | (p[2] << 8);
+                }
+                pick = tries ? __builtin_ctz(unsigned(tries)) : 0;
             }
-            node[tr.off[l] + i] = t;
+            if (own && k == pick) node[tr.off[l] + i] = t;
         }
         if (l + 1 < l1) __threadfence_block();
     }
@@ -1465,9 +1479,9 @@ hipError_t prepare_samples(const double* q, const double* n, const double* w, in
     // levels of many nodes by a launch each, the rest by one block
     int l = 1;
     while (l < tr.levels) {
-        const bool many = tr.cnt[l] > 2048;
+        const bool many = tr.cnt[l] > 64;
         const int l1 = many ? l + 1 : tr.levels;
-        const dim3 ug(many ? unsigned((tr.cnt[l] + kSdfBlock - 1) / kSdfBlock) : 1u);
+        const dim3 ug(many ? unsigned((tr.cnt[l] + kSdfBlock / 16 - 1) / (kSdfBlock / 16)) : 1u);
         if (fast)
             hipLaunchKernelGGL(tree_up_kernel<true>, ug, dim3(kSdfBlock), 0, s, node, tr, l, l1, ns, g, L.lay,
                                interp ? kInterpShare : 0.0);
@@ -1492,13 +1506,29 @@ hipError_t prepare_samples(const double* q, const double* n, const double* w, in
 
 // node-sample pairs from which interpolation repays its own launches
 constexpr double kInterpPairs = 1e8;
-// grids of at most this many bricks give each brick's samples to four waves:
-// one wave per brick would leave most of the 1024 SIMDs with fewer than 16
-constexpr int64_t kShareBricks = 16384;
+// Grids of at most this many bricks give each brick's samples to four waves,
+// where one wave per brick would leave the 1024 SIMDs too few waves to hide a
+// walk's loads.  The fast kernel keeps a SIMD busy with two waves and pays the
+// shared walk: 4 waves / 1 wave take 130 / 150 us at 2048 bricks (32^3, 0.9k
+// samples), 211 / 192 us at 4000, 1196 / 773 us at 16384 (64^3, 3.9k).  The
+// FP64 one, bound by the latency of its serial pair loop, crosses later:
+// 386 / 420 us at 4000, 2350 / 2630 us at 16384, 4030 / 3960 us at 23328.
+template <bool FAST>
+constexpr int64_t kShareBricks = FAST ? 2500 : 20000;
 
 int64_t brick_count(const GridDesc& g) {
     const Brick br = brick_shape(g.nz);
     return int64_t((g.nx + br.bx - 1) / br.bx) * ((g.ny + br.by - 1) / br.by) * ((g.nz + br.bz - 1) / br.bz);
+}
+
+// zeroed by a kernel, not hipMemsetAsync, so the call can be captured in a graph
+__global__ void zero_grads_kernel(double* __restrict__ gq, double* __restrict__ gn, double* __restrict__ gw,
+                                  int64_t ns) {
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < 3 * ns; i += int64_t(gridDim.x) * blockDim.x) {
+        gq[i] = 0.0;
+        gn[i] = 0.0;
+        if (i < ns) gw[i] = 0.0;
+    }
 }
 
 template <typename T, int PHI, bool FAST, bool STATS = false>
@@ -1506,12 +1536,12 @@ void enqueue_build(const double* q, const double* n, const Prepared& P, int64_t 
                    const ParamDesc& p, cplx<T>* out, unsigned long long* stats, hipStream_t s) {
     const BrickGrid bg = wave_bricks(g.nx, g.ny, g.nz);
     const int64_t bricks = int64_t(bg.nx) * bg.ny * bg.nz;
-    if (bricks <= kShareBricks)
+    if (bricks <= kShareBricks<FAST>)
         hipLaunchKernelGGL((sdf_build_kernel<T, PHI, FAST, 4, STATS>), dim3(unsigned(bricks)), dim3(kSdfBlock), 0, s, q,
                            n, P.st.qs, P.st.wn, P.st.js, P.node, P.tr, P.rec1, P.rec2, ns, g, p, out, stats);
     else
-        hipLaunchKernelGGL((sdf_build_kernel<T, PHI, FAST, 1, STATS>), dim3(unsigned(bricks)), dim3(64), 0, s, q, n, P.st.qs, P.st.wn, P.st.js, P.node, P.tr, P.rec1, P.rec2, ns, g,
-                           p, out, stats);
+        hipLaunchKernelGGL((sdf_build_kernel<T, PHI, FAST, 1, STATS>), dim3(unsigned(bricks)), dim3(64), 0, s, q, n,
+                           P.st.qs, P.st.wn, P.st.js, P.node, P.tr, P.rec1, P.rec2, ns, g, p, out, stats);
 }
 
 }  // namespace
@@ -1568,13 +1598,10 @@ template <typename T>
 hipError_t launch_sdf_adjoint(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g,
                               const ParamDesc& p, const void* cot, double* grad_q, double* grad_n, double* grad_w,
                               void* ws, hipStream_t s) {
-    // zeroed by a kernel, not hipMemsetAsync, so the call can be captured in a graph
-    hipError_t e = launch_zero_f64(grad_q, 3 * ns, s);
-    if (e == hipSuccess) e = launch_zero_f64(grad_n, 3 * ns, s);
-    if (e == hipSuccess) e = launch_zero_f64(grad_w, ns, s);
-    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(zero_grads_kernel, dim3(unsigned(std::min<int64_t>((3 * ns + 255) / 256, 4096))), dim3(256), 0, s,
+                       grad_q, grad_n, grad_w, ns);
     Prepared P{};
-    e = prepare_samples(q, n, w, ns, g, ws, false, false, false, s, &P);
+    hipError_t e = prepare_samples(q, n, w, ns, g, ws, false, false, false, s, &P);
     if (e != hipSuccess) return e;
     // grids of few bricks split the leaves so that about four blocks per CU run
     const int64_t bricks = brick_count(g);

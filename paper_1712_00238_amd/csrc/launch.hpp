@@ -242,7 +242,6 @@ hipError_t launch_pose_chain(const double* gp, const double* scale, int64_t B, d
 template <typename T>
 hipError_t launch_rho_from_c(const T* w_m, const void* grad_c, int64_t K, void* grad_rho, hipStream_t s);
 // zero `count` doubles with a kernel (valid inside captured graphs)
-hipError_t launch_zero_f64(double* p, int64_t count, hipStream_t s);
 template <typename T>
 hipError_t launch_score_grad(const void* rho_f, int N, bool planar, const void* rho_m, const T* w_m, int n_m,
                              const double* poses, int64_t B, T* score, double* grad_pose, T* grad_w, T* grad_c,
