@@ -311,6 +311,17 @@ size_t fixed_ws_bytes(sdf_ctx ctx, int64_t B, int N, bool planar) {
                 : sdf::fixed_cotangent_bytes<float>(B, N, planar, false);
 }
 
+// workspace of the pose kernels: the finer split's where `limit` (0: none)
+// leaves room for it beside `other` bytes
+size_t pose_ws_bytes(sdf_ctx ctx, int64_t B, int N, int nm, bool planar, int wmode, size_t limit, size_t other) {
+    auto bytes = [&](bool fine) {
+        return ctx->dtype == SDF_F64 ? sdf::grad_workspace_bytes<double>(B, N, nm, planar, wmode, fine)
+                                     : sdf::grad_workspace_bytes<float>(B, N, nm, planar, wmode, fine);
+    };
+    const size_t fine = bytes(true);
+    return !limit || align_up(fine) + other <= limit ? fine : bytes(false);
+}
+
 void drop_graph(sdf_ctx ctx) {
     if (ctx->graph.exec) (void)hipGraphExecDestroy(ctx->graph.exec);
     if (ctx->graph.graph) (void)hipGraphDestroy(ctx->graph.graph);
@@ -1381,8 +1392,8 @@ static int score_grad_impl(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g
     const bool planar = g_fixed->n[2] == 1;
     const int N = g_fixed->n[0], nm = g_moving->n[0];
     const int wmode = grad_c ? 2 : (grad_w ? 1 : 0);
-    size_t need = ctx->dtype == SDF_F64 ? sdf::grad_workspace_bytes<double>(B, N, nm, planar, wmode)
-                                        : sdf::grad_workspace_bytes<float>(B, N, nm, planar, wmode);
+    const size_t need =
+        pose_ws_bytes(ctx, B, N, nm, planar, wmode, scratch_buf ? kScratchBytes : ctx->cap, 0);
     void* ws = scratch_buf;
     if (scratch_buf) {
         if (need > kScratchBytes)
@@ -1400,12 +1411,12 @@ static int score_grad_impl(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g
         e = sdf::launch_score_grad<double>(rho_fixed, N, planar, rho_moving, static_cast<const double*>(w_moving), nm,
                                            poses, B, static_cast<double*>(score), grad_pose,
                                            static_cast<double*>(grad_w), static_cast<double*>(grad_c), grad_scale,
-                                           ws, s);
+                                           ws, need, s);
     else
         e = sdf::launch_score_grad<float>(rho_fixed, N, planar, rho_moving, static_cast<const float*>(w_moving), nm,
                                           poses, B, static_cast<float*>(score), grad_pose,
                                           static_cast<float*>(grad_w), static_cast<float*>(grad_c), grad_scale,
-                                          ws, s);
+                                          ws, need, s);
     if (e != hipSuccess) return hip_fail(ctx, e, "score_grad");
     return SDF_OK;
 }
@@ -1458,8 +1469,8 @@ int score_grad_backward(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g_fi
     const int64_t K = gsize(g_moving);
     const size_t el = esize(ctx);
     const int wmode = grad_rho_moving ? 2 : (grad_w ? 1 : 0);
-    const size_t gws = ctx->dtype == SDF_F64 ? sdf::grad_workspace_bytes<double>(B, N, nm, planar, wmode)
-                                             : sdf::grad_workspace_bytes<float>(B, N, nm, planar, wmode);
+    const size_t gws = pose_ws_bytes(ctx, B, N, nm, planar, wmode, ctx->cap,
+                                     align_up(el * size_t(B)) + align_up(2 * el * size_t(K)));
     // workspace: the gradient kernels' scratch, the per-pose scores (not
     // returned), the moving coefficients' cotangent; the fixed cotangent's
     // pose table reuses the front once those kernels are done (stream order)
@@ -1481,12 +1492,12 @@ int score_grad_backward(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g_fi
             e = sdf::launch_score_grad<double>(rho_fixed, N, planar, rho_moving, static_cast<const double*>(w_moving),
                                                nm, poses, B, static_cast<double*>(score_ws), grad_pose,
                                                static_cast<double*>(grad_w), static_cast<double*>(gcp), grad_score,
-                                               gw_ws, s);
+                                               gw_ws, gws, s);
         else
             e = sdf::launch_score_grad<float>(rho_fixed, N, planar, rho_moving, static_cast<const float*>(w_moving), nm,
                                               poses, B, static_cast<float*>(score_ws), grad_pose,
                                               static_cast<float*>(grad_w), static_cast<float*>(gcp), grad_score,
-                                              gw_ws, s);
+                                              gw_ws, gws, s);
         if (e == hipSuccess && grad_pose) e = sdf::launch_pose_chain(grad_pose, grad_score, B, grad_pose, s);
         if (e == hipSuccess && grad_rho_moving)
             e = ctx->dtype == SDF_F64

@@ -26,9 +26,8 @@ namespace sdf {
 namespace {
 
 constexpr int kGBlock = 256;
-constexpr int kSPT = 4;                        // samples per thread
-constexpr int kSamplesPerBlock = kGBlock * kSPT;
-constexpr int kPosesPerBlock = 16;
+constexpr int kSPT = 4;           // samples per thread of the tile kernel (1 where blocks are few)
+constexpr int kPosesPerBlock = 16;  // at most, in both pose kernels
 constexpr int kNAcc = 7;  // f, dt[3], tau[3]
 
 __device__ __forceinline__ void quat_rot(const double* q, double r[9]) {
@@ -49,32 +48,52 @@ __device__ __forceinline__ void quat_rot(const double* q, double r[9]) {
     r[8] = 1 - 2 * (x * x + y * y);
 }
 
+// Sum of v over each row of 16 lanes, left in every lane of the row (DPP
+// quad permutations and row rotations; no LDS traffic).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row16_sum(double v) {
+    v += dpp_f64<0xb1>(v);   // quad_perm [1, 0, 3, 2]
+    v += dpp_f64<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+    v += dpp_f64<0x124>(v);  // row_ror 4
+    v += dpp_f64<0x128>(v);  // row_ror 8
+    return v;
+}
+
 __device__ __forceinline__ double warp_sum(double v) {
     for (int off = warpSize / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
     return v;
 }
 
-template <typename T, bool GRAD>
+// Bound by the latency of its gathers where a call is small: a block of 1024
+// samples walked 16 poses one after the other, and 25 poses of 4096 planar
+// FP64 samples ran 8 blocks on 256 CUs.  SPT samples a thread and `per` poses
+// a block come from grad_split; that call: 163 -> 8 us with gradients.
+template <typename T, bool GRAD, int SPT>
 __global__ __launch_bounds__(kGBlock) void grad_tile_kernel(const cplx<T>* __restrict__ rho_f, int N, int planar,
                                                             const cplx<T>* __restrict__ rho_m,
                                                             const T* __restrict__ w_m, int n_m,
                                                             const double* __restrict__ poses, int64_t B,
                                                             const double* __restrict__ gscale,
                                                             double* __restrict__ part, int nsb,
-                                                            T* __restrict__ wpart, int want_w, int pb0) {
+                                                            T* __restrict__ wpart, int want_w, int pb0, int per) {
     const int sb = blockIdx.x, pb = pb0 + int(blockIdx.y);
     const int64_t K = planar ? int64_t(n_m) * n_m : int64_t(n_m) * n_m * n_m;
     const int nz = planar ? 1 : N;
     const T half = T(0.5) * T(n_m);
 
     // this thread's samples
-    int64_t ks[kSPT];
-    T xb[kSPT][3];
-    cplx<T> ck[kSPT], rm[kSPT];
-    T gw[kSPT], gwi[kSPT];  // wmode 1: Re(rho_M Phi) sums; 2: Phi sums (re, im)
+    int64_t ks[SPT];
+    T xb[SPT][3];
+    cplx<T> ck[SPT], rm[SPT];
+    T gw[SPT], gwi[SPT];  // wmode 1: Re(rho_M Phi) sums; 2: Phi sums (re, im)
 #pragma unroll
-    for (int s = 0; s < kSPT; ++s) {
-        const int64_t k = int64_t(sb) * kSamplesPerBlock + s * kGBlock + threadIdx.x;
+    for (int s = 0; s < SPT; ++s) {
+        const int64_t k = (int64_t(sb) * SPT + s) * kGBlock + threadIdx.x;
         ks[s] = k;
         const int64_t kk = k < K ? k : 0;
         xb[s][0] = T(int(kk % n_m)) - half;
@@ -86,11 +105,10 @@ __global__ __launch_bounds__(kGBlock) void grad_tile_kernel(const cplx<T>* __res
         gwi[s] = T(0);
     }
 
-    __shared__ double red[kGBlock / 64][kNAcc];
-    const int lane = threadIdx.x % warpSize, wid = threadIdx.x / warpSize;
+    __shared__ double red[kGBlock / 16][kNAcc];
 
-    const int64_t b0 = int64_t(pb) * kPosesPerBlock;
-    for (int pi = 0; pi < kPosesPerBlock; ++pi) {
+    const int64_t b0 = int64_t(pb) * per;
+    for (int pi = 0; pi < per; ++pi) {
         const int64_t b = b0 + pi;
         if (b >= B) break;  // uniform across the block
         const double* pose = poses + 7 * b;
@@ -114,7 +132,7 @@ __global__ __launch_bounds__(kGBlock) void grad_tile_kernel(const cplx<T>* __res
         for (int a = 0; a < kNAcc; ++a) acc[a] = 0.0;
 
 #pragma unroll
-        for (int s = 0; s < kSPT; ++s) {
+        for (int s = 0; s < SPT; ++s) {
             if (ks[s] >= K) continue;
             T y[3];
 #pragma unroll
@@ -178,23 +196,25 @@ __global__ __launch_bounds__(kGBlock) void grad_tile_kernel(const cplx<T>* __res
                 }
             }
         }
-        // block reduction of the per-pose sums (FP64)
-        const int nacc = GRAD ? kNAcc : 1;
+        // block reduction of the per-pose sums (FP64): rows of 16 lanes, then the rows
+        constexpr int nacc = GRAD ? kNAcc : 1;
+#pragma unroll
         for (int a = 0; a < nacc; ++a) {
-            double v = warp_sum(acc[a]);
-            if (lane == 0) red[wid][a] = v;
+            const double v = row16_sum(acc[a]);
+            if ((threadIdx.x & 15) == 0) red[threadIdx.x >> 4][a] = v;
         }
         __syncthreads();
         if (threadIdx.x < nacc) {
             double v = 0.0;
-            for (int wv = 0; wv < kGBlock / 64; ++wv) v += red[wv][threadIdx.x];
+#pragma unroll
+            for (int rw = 0; rw < kGBlock / 16; ++rw) v += red[rw][threadIdx.x];
             part[(b * nsb + sb) * kNAcc + threadIdx.x] = v;
         }
         __syncthreads();
     }
     if (GRAD && want_w) {
 #pragma unroll
-        for (int s = 0; s < kSPT; ++s)
+        for (int s = 0; s < SPT; ++s)
             if (ks[s] < K) {
                 if (want_w == 1) wpart[int64_t(pb) * K + ks[s]] = gw[s];
                 else {
@@ -203,22 +223,6 @@ __global__ __launch_bounds__(kGBlock) void grad_tile_kernel(const cplx<T>* __res
                 }
             }
     }
-}
-
-// Sum of v over each row of 16 lanes, left in every lane of the row (DPP
-// quad permutations and row rotations; no LDS traffic).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double row16_sum(double v) {
-    v += dpp_f64<0xb1>(v);   // quad_perm [1, 0, 3, 2]
-    v += dpp_f64<0x4e>(v);   // quad_perm [2, 3, 0, 1]
-    v += dpp_f64<0x124>(v);  // row_ror 4
-    v += dpp_f64<0x128>(v);  // row_ror 8
-    return v;
 }
 
 // 3D FP32 variant with the fixed field staged in LDS.  Block (8 x 8 x 8
@@ -244,7 +248,6 @@ constexpr int kBoxCells = kBoxPlane * kBoxMax;
 constexpr int kBoxSlotRows = 3;                                            // rows per wave load
 constexpr int kBoxSlots = kBoxMax * ((kBoxMax + kBoxSlotRows - 1) / kBoxSlotRows);
 constexpr int kBoxStage = (kBoxSlots + kBoxWaves - 1) / kBoxWaves;         // loads per lane
-constexpr int kBoxPoses = 16;
 constexpr float kBoxMargin = 1e-3f;
 static_assert(kBoxRow >= kBoxMax && kBoxPlane >= kBoxRow * kBoxMax, "box pitches");
 static_assert(kBoxRow * kBoxSlotRows <= 64, "staging rows per wave");
@@ -302,7 +305,8 @@ __global__ __launch_bounds__(kBoxBlock, 2) void grad_box_kernel(const cplx<float
                                                                 const BoxPose* __restrict__ bpose, int64_t B,
                                                                 const double* __restrict__ gscale,
                                                                 double* __restrict__ part, int nsb,
-                                                                float* __restrict__ wpart, int want_w, int pb0) {
+                                                                float* __restrict__ wpart, int want_w, int pb0,
+                                                                int per) {
     __shared__ cplx<float> box[kBoxCells];
     __shared__ double red[kBoxBlock / 16][kNAcc];
     const int sb = blockIdx.x, pb = pb0 + int(blockIdx.y);
@@ -329,8 +333,8 @@ __global__ __launch_bounds__(kBoxBlock, 2) void grad_box_kernel(const cplx<float
     const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     // staging lane roles: row j_s of a slot of three rows, cell cx_s of the row
     const int js = lane / kBoxRow, cxs = lane - js * kBoxRow;
-    const int64_t b0 = int64_t(pb) * kBoxPoses;
-    for (int pi = 0; pi < kBoxPoses; ++pi) {
+    const int64_t b0 = int64_t(pb) * per;
+    for (int pi = 0; pi < per; ++pi) {
         const int64_t b = b0 + pi;
         if (b >= B) break;  // uniform across the block
         const BoxPose& P = bpose[b];
@@ -860,27 +864,47 @@ bool use_box(bool planar, int N) {
     return std::is_same<T, float>::value && !planar && N >= kBoxMax && N <= 1024;
 }
 
+// Blocks of a pose kernel: nsb sample tiles (of 256 spt samples, or the box
+// kernel's 8^3) x npb groups of `per` poses.  A block that walks 16 poses
+// reuses its samples' registers, which pays while the chip is full; below
+// kFewBlocks blocks the walk is a serial chain on a part of the CUs, so the
+// groups shrink and, at one pose a block, the tile kernel's samples go one to
+// a thread.  Weight gradients hold one partial per group and sample and a last
+// kernel walks them, so they keep to 64 groups.  64 tiles of 32 poses (box
+// kernel, gradients of poses and samples): 90 us in 128 blocks, 35 us in 1024.
+constexpr int64_t kFewBlocks = 1024;
+constexpr int64_t kFewGroups = 64;
+struct GradSplit {
+    int64_t nsb, npb;
+    int spt, per;
+};
 template <typename T>
-void grad_tiles(int64_t B, int N, int n_m, bool planar, int64_t* nsb, int64_t* npb) {
+GradSplit grad_split(int64_t B, int N, int n_m, bool planar, int wmode, bool fine) {
     const int64_t K = planar ? int64_t(n_m) * n_m : int64_t(n_m) * n_m * n_m;
-    if (use_box<T>(planar, N)) {
-        const int64_t nt = (n_m + kBoxTile - 1) / kBoxTile;
-        *nsb = nt * nt * nt;
-        *npb = (B + kBoxPoses - 1) / kBoxPoses;
-    } else {
-        *nsb = (K + kSamplesPerBlock - 1) / kSamplesPerBlock;
-        *npb = (B + kPosesPerBlock - 1) / kPosesPerBlock;
+    const int64_t nt = (n_m + kBoxTile - 1) / kBoxTile;
+    const bool box = use_box<T>(planar, N);
+    auto tiles = [&](int spt) { return box ? nt * nt * nt : (K + kGBlock * spt - 1) / (kGBlock * spt); };
+    GradSplit g{tiles(kSPT), 0, kSPT, kPosesPerBlock};
+    if (fine) {
+        const int64_t least = wmode ? (B + kFewGroups - 1) / kFewGroups : 1;
+        const int64_t per = std::max(g.nsb * B / kFewBlocks, least);
+        if (per < kPosesPerBlock) g.per = int(per);
+        if (g.nsb * ((B + g.per - 1) / g.per) < kFewBlocks) {
+            g.spt = 1;
+            g.nsb = tiles(1);
+        }
     }
+    g.npb = (B + g.per - 1) / g.per;
+    return g;
 }
 
 template <typename T>
-size_t grad_workspace_bytes(int64_t B, int N, int n_m, bool planar, int wmode) {
+size_t grad_workspace_bytes(int64_t B, int N, int n_m, bool planar, int wmode, bool fine) {
     const int64_t K = planar ? int64_t(n_m) * n_m : int64_t(n_m) * n_m * n_m;
-    int64_t nsb, npb;
-    grad_tiles<T>(B, N, n_m, planar, &nsb, &npb);
-    size_t bytes = size_t(B * nsb * kNAcc) * sizeof(double);
+    const GradSplit g = grad_split<T>(B, N, n_m, planar, wmode, fine);
+    size_t bytes = size_t(B * g.nsb * kNAcc) * sizeof(double);
     bytes = (bytes + 255) / 256 * 256;
-    if (wmode) bytes += (size_t(npb * K) * sizeof(T) * size_t(wmode) + 255) / 256 * 256;
+    if (wmode) bytes += (size_t(g.npb * K) * sizeof(T) * size_t(wmode) + 255) / 256 * 256;
     if (use_box<T>(planar, N)) bytes += size_t(B) * sizeof(BoxPose);
     return bytes + 256;
 }
@@ -888,19 +912,19 @@ size_t grad_workspace_bytes(int64_t B, int N, int n_m, bool planar, int wmode) {
 template <typename T>
 hipError_t launch_score_grad(const void* rho_f, int N, bool planar, const void* rho_m, const T* w_m, int n_m,
                              const double* poses, int64_t B, T* score, double* grad_pose, T* grad_w, T* grad_c,
-                             const double* grad_scale, void* ws, hipStream_t s) {
+                             const double* grad_scale, void* ws, size_t ws_bytes, hipStream_t s) {
     const int64_t K = planar ? int64_t(n_m) * n_m : int64_t(n_m) * n_m * n_m;
-    int64_t nsb64, npb64;
-    grad_tiles<T>(B, N, n_m, planar, &nsb64, &npb64);
-    const int nsb = int(nsb64), npb = int(npb64);
+    // weight mode: 2 sums Phi (complex) per sample, from which grad_w follows;
+    // 1 sums Re(rho_M Phi) directly
+    const int ww = grad_c ? 2 : (grad_w ? 1 : 0);
+    const bool fine = ws_bytes >= grad_workspace_bytes<T>(B, N, n_m, planar, ww, true);
+    const GradSplit gs = grad_split<T>(B, N, n_m, planar, ww, fine);
+    const int nsb = int(gs.nsb), npb = int(gs.npb), per = gs.per;
     double* part = static_cast<double*>(ws);
     size_t off = size_t(B * nsb * kNAcc) * sizeof(double);
     off = (off + 255) / 256 * 256;
     T* wpart = reinterpret_cast<T*>(static_cast<char*>(ws) + off);
-    // weight mode: 2 sums Phi (complex) per sample, from which grad_w follows;
-    // 1 sums Re(rho_M Phi) directly
-    const int ww = grad_c ? 2 : (grad_w ? 1 : 0);
-    if (ww) off += (size_t(npb64 * K) * sizeof(T) * size_t(ww) + 255) / 256 * 256;
+    if (ww) off += (size_t(gs.npb * K) * sizeof(T) * size_t(ww) + 255) / 256 * 256;
     BoxPose* bpose = reinterpret_cast<BoxPose*>(static_cast<char*>(ws) + off);
     if (use_box<T>(planar, N)) {
         hipLaunchKernelGGL(box_pose_kernel, dim3(unsigned((B + 127) / 128)), dim3(128), 0, s, poses, B, bpose);
@@ -917,22 +941,27 @@ hipError_t launch_score_grad(const void* rho_f, int N, bool planar, const void* 
             if (use_box<T>(planar, N)) {
                 if (grad && ww == 0)
                     hipLaunchKernelGGL((grad_box_kernel<true, true>), grid, dim3(kBoxBlock), 0, s, rf, N, rm, w_m, n_m,
-                                       bpose, B, grad_scale, part, nsb, wpart, 0, pb0);
+                                       bpose, B, grad_scale, part, nsb, wpart, 0, pb0, per);
                 else if (grad)
                     hipLaunchKernelGGL((grad_box_kernel<true>), grid, dim3(kBoxBlock), 0, s, rf, N, rm, w_m, n_m, bpose,
-                                       B, grad_scale, part, nsb, wpart, ww, pb0);
+                                       B, grad_scale, part, nsb, wpart, ww, pb0, per);
                 else
                     hipLaunchKernelGGL((grad_box_kernel<false>), grid, dim3(kBoxBlock), 0, s, rf, N, rm, w_m, n_m,
-                                       bpose, B, grad_scale, part, nsb, wpart, 0, pb0);
+                                       bpose, B, grad_scale, part, nsb, wpart, 0, pb0, per);
             }
         }
         if (!use_box<T>(planar, N)) {
-            if (grad)
-                hipLaunchKernelGGL((grad_tile_kernel<T, true>), grid, dim3(kGBlock), 0, s, rf, N, planar ? 1 : 0, rm,
-                                   w_m, n_m, poses, B, grad_scale, part, nsb, wpart, ww, pb0);
-            else
-                hipLaunchKernelGGL((grad_tile_kernel<T, false>), grid, dim3(kGBlock), 0, s, rf, N, planar ? 1 : 0, rm,
-                                   w_m, n_m, poses, B, grad_scale, part, nsb, wpart, 0, pb0);
+            auto tile = [&](auto kernel, int want_w) {
+                hipLaunchKernelGGL(kernel, grid, dim3(kGBlock), 0, s, rf, N, planar ? 1 : 0, rm, w_m, n_m, poses, B,
+                                   grad_scale, part, nsb, wpart, want_w, pb0, per);
+            };
+            if (gs.spt == 1) {
+                if (grad) tile(grad_tile_kernel<T, true, 1>, ww);
+                else tile(grad_tile_kernel<T, false, 1>, 0);
+            } else {
+                if (grad) tile(grad_tile_kernel<T, true, kSPT>, ww);
+                else tile(grad_tile_kernel<T, false, kSPT>, 0);
+            }
         }
     }
     hipError_t e = hipGetLastError();
@@ -1022,13 +1051,13 @@ template hipError_t launch_fixed_cotangent<float>(const void*, const float*, int
                                                   const double*, void*, void*, size_t, hipStream_t);
 template hipError_t launch_fixed_cotangent<double>(const void*, const double*, int, bool, int, const double*, int64_t,
                                                    const double*, void*, void*, size_t, hipStream_t);
-template size_t grad_workspace_bytes<float>(int64_t, int, int, bool, int);
-template size_t grad_workspace_bytes<double>(int64_t, int, int, bool, int);
+template size_t grad_workspace_bytes<float>(int64_t, int, int, bool, int, bool);
+template size_t grad_workspace_bytes<double>(int64_t, int, int, bool, int, bool);
 template hipError_t launch_score_grad<float>(const void*, int, bool, const void*, const float*, int, const double*,
-                                             int64_t, float*, double*, float*, float*, const double*, void*,
+                                             int64_t, float*, double*, float*, float*, const double*, void*, size_t,
                                              hipStream_t);
 template hipError_t launch_score_grad<double>(const void*, int, bool, const void*, const double*, int, const double*,
-                                              int64_t, double*, double*, double*, double*, const double*, void*,
+                                              int64_t, double*, double*, double*, double*, const double*, void*, size_t,
                                               hipStream_t);
 
 }  // namespace sdf

@@ -223,10 +223,9 @@ hipError_t launch_topk(const T* scores, int64_t n, int64_t k, void* ws, int32_t*
 size_t topk_workspace_bytes(int64_t n);
 
 // ---- score_grad
+// workspace; with `fine` so much that calls of few blocks can split their poses and samples further
 template <typename T>
-size_t grad_workspace_bytes(int64_t B, int N, int n_m, bool planar, int wmode);
-// grad_c (may be NULL): complex per-sample sums of grad_scale_b Phi_b(y_k);
-// grad_w then follows as Re(rho_M grad_c)
+size_t grad_workspace_bytes(int64_t B, int N, int n_m, bool planar, int wmode, bool fine);
 // cotangent of sum_b s_b f_b with respect to rho_F (complex, every node
 // written); ws: fixed_cotangent_bytes, with `split` so much that grids of few
 // tiles can divide the poses over more blocks
@@ -241,10 +240,11 @@ hipError_t launch_pose_chain(const double* gp, const double* scale, int64_t B, d
 // grad_rho[k] = w_m[k] grad_c[k] (complex, context precision)
 template <typename T>
 hipError_t launch_rho_from_c(const T* w_m, const void* grad_c, int64_t K, void* grad_rho, hipStream_t s);
-// zero `count` doubles with a kernel (valid inside captured graphs)
+// grad_c (may be NULL): complex per-sample sums of grad_scale_b Phi_b(y_k);
+// grad_w then follows as Re(rho_M grad_c)
 template <typename T>
 hipError_t launch_score_grad(const void* rho_f, int N, bool planar, const void* rho_m, const T* w_m, int n_m,
                              const double* poses, int64_t B, T* score, double* grad_pose, T* grad_w, T* grad_c,
-                             const double* grad_scale, void* ws, hipStream_t s);
+                             const double* grad_scale, void* ws, size_t ws_bytes, hipStream_t s);
 
 }  // namespace sdf
