@@ -268,6 +268,16 @@ inline bool fused_x_pass(int nf) { return nf >= 32 && nf <= 256; }
 constexpr int kFusedRowsZ = 4;
 constexpr int kFusedBlock = 512;
 
+// y tile of block `tile` = (row tbz, column): consecutive blocks go to the
+// XCDs and their shader engines in turn, and a row of 32 tiles gave each engine
+// the same y of every row and rotation, the body's middle to a few of them.
+// Rows and rotations start at other columns: with the fused x pass, 2N = 256,
+// 24 rotations of a 64^3 body's octree samples take 1430 us, 2450 before, when a
+// CU held a block two thirds of the time.
+__device__ __forceinline__ int turned_tile(int tile, int tbz, int rot, int nty) {
+    return (tile + 5 * tbz + 11 * rot) % nty;
+}
+
 TileShape tile_shape(int nf, bool planar, bool line) {
     TileShape t{};
     if (line) {
@@ -754,7 +764,7 @@ __global__ __launch_bounds__(kLineBlock) void nfft_line_tile_kernel(const float*
     __shared__ unsigned long long redi[kLineBlock / 64];
     const int nbins = ts.nty * ts.ntz;
     const int tile = int(blockIdx.x), rot = int(blockIdx.y);
-    const int tby = tile % ts.nty, tbz = tile / ts.nty;
+    const int tbz = tile / ts.nty, tby = turned_tile(tile, tbz, rot, ts.nty);
     const int y0 = tby * kLineRows, z0 = tbz * kLineRows;
     const int px = ts.py;
     const int used = kLineRows * kLineRows * px;
@@ -924,7 +934,7 @@ __global__ __launch_bounds__(kFusedBlock) void nfft_line_fft_kernel(const float*
     fill_twiddles<float, NF>(tw);
     const int nbins = ts.nty * ts.ntz;
     const int tile = int(blockIdx.x), rot = int(blockIdx.y);
-    const int tby = tile % ts.nty, tbz = tile / ts.nty;
+    const int tbz = tile / ts.nty, tby = turned_tile(tile, tbz, rot, ts.nty);
     const int y0 = tby * RY, z0 = tbz * RZ;
     const int px = ts.py;
     const float half = float(0.5 * W), beta = float(kEsBetaPerWidth * W), zs = float(2.0 / W);

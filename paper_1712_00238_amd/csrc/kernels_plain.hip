@@ -179,13 +179,18 @@ __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* 
     __shared__ A acc[S::WORDS];
     const int sx = min(S::X, N), sy = min(S::Y, N), sz = PLANAR ? 1 : min(S::Z, N);
     const int ntx = N / sx, nty = N / sy;
-    const int tile = int(blockIdx.x);
-    const int t0[3] = {(tile % ntx) * sx - N / 2, ((tile / ntx) % nty) * sy - N / 2,
-                       PLANAR ? 0 : (tile / (ntx * nty)) * sz - N / 2};
+    // the tiles of the body, which take most of the time, from the middle of
+    // the grid outwards over all rotations: they spread over the CUs evenly
+    // and none is left for the end (FP64, 96^3, 8 rotations of a 48^3 body:
+    // 222 -> 205 us)
+    const int tile = int(blockIdx.y);
+    auto outwards = [](int r, int n) { return n / 2 + ((r & 1) ? -((r + 1) / 2) : r / 2); };
+    const int t0[3] = {outwards(tile % ntx, ntx) * sx - N / 2, outwards((tile / ntx) % nty, nty) * sy - N / 2,
+                       PLANAR ? 0 : outwards(tile / (ntx * nty), N / sz) * sz - N / 2};
     const int dim[3] = {sx, sy, sz};
     const int64_t G = PLANAR ? int64_t(N) * N : int64_t(N) * N * N;
-    cplx<T>* g = out + int64_t(blockIdx.y) * G;
-    const T* r = R + 9 * int64_t(blockIdx.y);
+    cplx<T>* g = out + int64_t(blockIdx.x) * G;
+    const T* r = R + 9 * int64_t(blockIdx.x);
     const double cm = __longlong_as_double((long long)*cmax);
     const bool finite = cm < INFINITY;
     const double pow2 = pow2_below(fmin(TileSum<T>::top / (8.0 * cm), std::is_same<T, float>::value ? 1e37 : 1e300));
@@ -730,13 +735,13 @@ hipError_t launch_spread_tiles(const void* c, int n_m, bool planar, const T* R, 
     if (planar) {
         using S = SpreadTile<true>;
         const unsigned tx = unsigned(N / (S::X < N ? S::X : N)), ty = unsigned(N / (S::Y < N ? S::Y : N));
-        hipLaunchKernelGGL((spread_tile_kernel<T, true>), dim3(tx * ty, unsigned(n_rot)), dim3(kTileBlock), 0, s, cc,
+        hipLaunchKernelGGL((spread_tile_kernel<T, true>), dim3(unsigned(n_rot), tx * ty), dim3(kTileBlock), 0, s, cc,
                            n_m, R, sign, N, cmax, o);
     } else {
         using S = SpreadTile<false>;
         const unsigned tx = unsigned(N / (S::X < N ? S::X : N)), ty = unsigned(N / (S::Y < N ? S::Y : N)),
                        tz = unsigned(N / (S::Z < N ? S::Z : N));
-        hipLaunchKernelGGL((spread_tile_kernel<T, false>), dim3(tx * ty * tz, unsigned(n_rot)), dim3(kTileBlock), 0, s,
+        hipLaunchKernelGGL((spread_tile_kernel<T, false>), dim3(unsigned(n_rot), tx * ty * tz), dim3(kTileBlock), 0, s,
                            cc, n_m, R, sign, N, cmax, o);
     }
     return hipGetLastError();
