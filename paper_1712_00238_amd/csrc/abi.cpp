@@ -1156,13 +1156,15 @@ int sdf_build_adjoint(sdf_ctx ctx, const void* q, const void* nrm, const void* w
     const double* nd = static_cast<const double*>(nrm);
     const double* wd = static_cast<const double*>(w);
     ctx->fused_cache_valid = false;  // the ordered samples share the workspace
-    rc = ensure_ws(ctx, sdf::sdf_build_workspace_bytes(n));
+    size_t bytes = sdf::sdf_adjoint_bytes(n, desc(g));
+    if (ctx->cap && bytes > ctx->cap) bytes = sdf::sdf_build_workspace_bytes(n);
+    rc = ensure_ws(ctx, bytes);
     if (rc) return rc;
     hipError_t e = ctx->dtype == SDF_F64
                        ? sdf::launch_sdf_adjoint<double>(qd, nd, wd, n, desc(g), pd, cot, grad_q, grad_n, grad_w,
-                                                         ctx->ws, s)
+                                                         ctx->ws, bytes, s)
                        : sdf::launch_sdf_adjoint<float>(qd, nd, wd, n, desc(g), pd, cot, grad_q, grad_n, grad_w,
-                                                        ctx->ws, s);
+                                                        ctx->ws, bytes, s);
     if (e != hipSuccess) return hip_fail(ctx, e, "sdf_build_adjoint");
     return SDF_OK;
 }

@@ -803,9 +803,77 @@ __device__ __forceinline__ double row_sum(double v) {
     return v;
 }
 
-// A block per brick of 256 nodes (16 groups of 16, as the build's waves take
-// them) and range of leaves.  Pass 1 as in the build puts every node's data in
-// LDS; then each wave takes leaves: a lane owns one of the 64 samples and walks
+// nearest samples and xi sums of the nodes in brick order
+struct NearData {
+    double* d2;
+    double* sum;
+    int* at;
+};
+
+// Node m of brick blk: 16 groups of 16 nodes, as the build's waves take them.
+struct BrickNode {
+    int i, j, k;
+    bool valid;
+    double x, y, z;
+};
+__device__ __forceinline__ BrickNode brick_node(const GridDesc& g, int64_t blk, int m) {
+    const Brick br = brick_shape(g.nz);
+    const int nbx = (g.nx + br.bx - 1) / br.bx, nby = (g.ny + br.by - 1) / br.by;
+    const int grp = m >> 4, n = m & 15;
+    const bool planar = g.nz == 1;
+    BrickNode o;
+    o.i = int(blk % nbx) * br.bx + (planar ? 4 * (grp & 3) : 4 * (grp & 1)) + (n & 3);
+    o.j = int(blk / nbx % nby) * br.by +
+          (planar ? 4 * (grp >> 2) + (n >> 2) : 2 * ((grp >> 1) & 3) + ((n >> 2) & 1));
+    o.k = planar ? 0 : int(blk / (nbx * nby)) * br.bz + 2 * (grp >> 3) + (n >> 3);
+    o.valid = o.i < g.nx && o.j < g.ny && o.k < g.nz;
+    o.x = g.ox + g.h * o.i;
+    o.y = g.oy + g.h * o.j;
+    o.z = g.oz + g.h * o.k;
+    return o;
+}
+
+// Pass 1 of the adjoint on its own: the nearest sample of every node in brick
+// order (squared distance, place in tree order or -1), one wave per 16 nodes,
+// and the nodes' xi sums cleared.
+__global__ __launch_bounds__(64) void adjoint_nearest_kernel(const double* __restrict__ qs,
+                                                             const int* __restrict__ js,
+                                                             const TreeNode* __restrict__ nodes, SampleTree tr,
+                                                             int64_t ns, GridDesc g, int64_t turn, NearData near) {
+    const int64_t grp = int64_t(blockIdx.x) * turn % gridDim.x;
+    const int lane = int(threadIdx.x);
+    const BrickNode b = brick_node(g, grp >> 4, int(grp & 15) * 16 + (lane & 15));
+    double best;
+    int sbest;
+    wave_nearest<1>(qs, js, nodes, tr, ns, b.x, b.y, b.z, b.valid, 0, best, sbest, nullptr);
+    if (lane < 16) {
+        near.d2[16 * grp + lane] = best;
+        near.at[16 * grp + lane] = sbest;
+        near.sum[16 * grp + lane] = 0.0;
+    }
+}
+
+// xi term of the nearest sample: -(d rho / d xi) u*, u* = e / xi
+__device__ __forceinline__ void add_xi_term(const double* __restrict__ q, int64_t jb, double x, double y, double z,
+                                            double inv_xi, double sum, double* __restrict__ gq) {
+    const double coef = inv_xi * inv_xi * sum;
+    atomicAdd(gq + 3 * jb, coef * (x - q[3 * jb]));
+    atomicAdd(gq + 3 * jb + 1, coef * (y - q[3 * jb + 1]));
+    atomicAdd(gq + 3 * jb + 2, coef * (z - q[3 * jb + 2]));
+}
+__global__ __launch_bounds__(kSdfBlock) void adjoint_xi_kernel(const double* __restrict__ q,
+                                                               const int* __restrict__ js, GridDesc g, NearData near,
+                                                               double* __restrict__ gq) {
+    const int64_t slot = int64_t(blockIdx.x) * kSdfBlock + threadIdx.x;
+    const double sum = near.sum[slot];
+    if (sum == 0.0) return;
+    const BrickNode b = brick_node(g, blockIdx.x, int(threadIdx.x));
+    add_xi_term(q, js[near.at[slot]], b.x, b.y, b.z, 1.0 / sqrt(near.d2[slot]), sum, gq);
+}
+
+// A block per brick of 256 nodes and range of leaves.  Every node's data goes
+// to LDS (NEAR: its nearest sample is known, else pass 1 runs here); then each
+// wave takes leaves: a lane owns one of the 64 samples and walks
 // the nodes whose ball reaches the leaf, so that one evaluation of a pair's
 // kernel serves both sums: the sample's seven gradient components stay in the
 // lane's registers, and the node's xi term,
@@ -815,9 +883,12 @@ __device__ __forceinline__ double row_sum(double v) {
 // last bits may vary between runs); blocks start at different leaves, so they
 // do not add to the same addresses at a time.
 // Bound by FP64 VALU issue, about 100 instructions per pair (a pass over the
-// nodes and one over the samples, with the library's exp, took some 220):
-// 3.9k samples on 64^3 nodes 5.2 -> 2.5 ms.
-template <typename T>
+// nodes and one over the samples, with the library's exp, took some 220), and
+// on small grids by how evenly the pairs fall: bricks at the surface hold many
+// times the mean.  There the leaves are split over more blocks than run at a
+// time, which needs pass 1 done once, by itself: 3.9k samples on 64^3 nodes
+// 2.2 ms with one block a brick, 1.85 so (the three kernels), 5.2 before all of this.
+template <typename T, bool NEAR>
 __global__ __launch_bounds__(kSdfBlock) void sdf_adjoint_kernel(const double* __restrict__ q,
                                                                 const double* __restrict__ nrm,
                                                                 const double* __restrict__ w,
@@ -827,56 +898,56 @@ __global__ __launch_bounds__(kSdfBlock) void sdf_adjoint_kernel(const double* __
                                                                 int64_t ns, GridDesc g, ParamDesc prm,
                                                                 const cplx<T>* __restrict__ cot,
                                                                 double* __restrict__ gq, double* __restrict__ gn,
-                                                                double* __restrict__ gw) {
+                                                                double* __restrict__ gw, int64_t turn,
+                                                                NearData near) {
     __shared__ v4<double> nodep[kSdfBlock];  // (px, py, pz, 1 / xi)
     __shared__ v4<double> nodeg[kSdfBlock];  // (A g.re, A g.im, ball radius^2 or -1, s)
     __shared__ double nsum[kSdfBlock];
     __shared__ int nnear[kSdfBlock];
     __shared__ double red[kSdfBlock / 64];
 
-    const Brick br = brick_shape(g.nz);
-    const int nbx = (g.nx + br.bx - 1) / br.bx, nby = (g.ny + br.by - 1) / br.by;
-    const int blk = blockIdx.x;
-    const int i0 = (blk % nbx) * br.bx, j0 = ((blk / nbx) % nby) * br.by, k0 = (blk / (nbx * nby)) * br.bz;
+    const int64_t blk = int64_t(blockIdx.x) * turn % gridDim.x;
     const int lane = int(threadIdx.x) & 63, wave = uniform(int(threadIdx.x) >> 6);
     const double sig2inv = 1.0 / (prm.sigma * prm.sigma);
 
-    for (int grp = 4 * wave; grp < 4 * wave + 4; ++grp) {
-        const int n = lane & 15;
-        const bool planar = g.nz == 1;
-        const int i = i0 + (planar ? 4 * (grp & 3) : 4 * (grp & 1)) + (n & 3);
-        const int j = j0 + (planar ? 4 * (grp >> 2) + (n >> 2) : 2 * ((grp >> 1) & 3) + ((n >> 2) & 1));
-        const int k = k0 + (planar ? 0 : 2 * (grp >> 3) + (n >> 3));
-        const bool valid = i < g.nx && j < g.ny && k < g.nz;
-        const double px = g.ox + g.h * i, py = g.oy + g.h * j, pz = g.oz + g.h * k;
-        double best;
-        int sbest;
-        wave_nearest<1>(qs, js, nodes, tr, ns, px, py, pz, valid, 0, best, sbest, nullptr);
-        if (lane < 16) {
-            const int64_t jb = sbest >= 0 ? js[sbest] : 0;
-            const double dot = (px - q[3 * jb]) * nrm[3 * jb] + (py - q[3 * jb + 1]) * nrm[3 * jb + 1] +
-                               (pz - q[3 * jb + 2]) * nrm[3 * jb + 2];
-            const int pmc = dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
-            const double xi = sqrt(best);
-            const cplx<T> gt = valid ? cot[(int64_t(k) * g.ny + j) * g.nx + i] : mk(T(0), T(0));
-            const double g_re = double(gt.re), g_im = double(gt.im);
-            const bool act = valid && pmc != 0 && xi >= prm.xi_floor && (g_re != 0.0 || g_im != 0.0);
-            const double lam = pmc > 0 ? prm.lambda1 : -prm.lambda2;
-            const double A = lam / (2.0 * 3.14159265358979323846 * prm.sigma * best);
-            const int m = 16 * grp + n;
-            nodep[m] = v4<double>{px, py, pz, 1.0 / xi};
-            nodeg[m] = v4<double>{A * g_re, A * g_im, act ? (1.0 + prm.eps) * (1.0 + prm.eps) * best : -1.0,
-                                  pmc > 0 ? -2.0 : 2.0};
-            nnear[m] = int(jb);
-            nsum[m] = 0.0;
+    auto put_node = [&](const BrickNode& b, int m, double best, int sbest) {
+        const int64_t jb = sbest >= 0 ? js[sbest] : 0;
+        const double dot = (b.x - q[3 * jb]) * nrm[3 * jb] + (b.y - q[3 * jb + 1]) * nrm[3 * jb + 1] +
+                           (b.z - q[3 * jb + 2]) * nrm[3 * jb + 2];
+        const int pmc = dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
+        const double xi = sqrt(best);
+        const cplx<T> gt = b.valid ? cot[(int64_t(b.k) * g.ny + b.j) * g.nx + b.i] : mk(T(0), T(0));
+        const double g_re = double(gt.re), g_im = double(gt.im);
+        const bool act = b.valid && pmc != 0 && xi >= prm.xi_floor && (g_re != 0.0 || g_im != 0.0);
+        const double lam = pmc > 0 ? prm.lambda1 : -prm.lambda2;
+        const double A = lam / (2.0 * 3.14159265358979323846 * prm.sigma * best);
+        nodep[m] = v4<double>{b.x, b.y, b.z, 1.0 / xi};
+        nodeg[m] = v4<double>{A * g_re, A * g_im, act ? (1.0 + prm.eps) * (1.0 + prm.eps) * best : -1.0,
+                              pmc > 0 ? -2.0 : 2.0};
+        nnear[m] = int(jb);
+        nsum[m] = 0.0;
+    };
+    if constexpr (NEAR) {
+        const int m = int(threadIdx.x);
+        put_node(brick_node(g, blk, m), m, near.d2[blk * kSdfBlock + m], near.at[blk * kSdfBlock + m]);
+    } else {
+        for (int grp = 4 * wave; grp < 4 * wave + 4; ++grp) {
+            const int m = 16 * grp + (lane & 15);
+            const BrickNode b = brick_node(g, blk, m);
+            double best;
+            int sbest;
+            wave_nearest<1>(qs, js, nodes, tr, ns, b.x, b.y, b.z, b.valid, 0, best, sbest, nullptr);
+            if (lane < 16) put_node(b, m, best, sbest);
         }
     }
     __syncthreads();
     const double r2brick = block_reduce<true>(nodeg[threadIdx.x].z, red) * (1.0 + 1e-9);
     if (r2brick < 0.0) return;  // uniform: no node of the brick contributes
-    const double bl[3] = {g.ox + g.h * i0, g.oy + g.h * j0, g.oz + g.h * k0};
-    const double bh[3] = {bl[0] + g.h * (min(br.bx, g.nx - i0) - 1), bl[1] + g.h * (min(br.by, g.ny - j0) - 1),
-                          bl[2] + g.h * (min(br.bz, g.nz - k0) - 1)};
+    const Brick br = brick_shape(g.nz);
+    const BrickNode b0 = brick_node(g, blk, 0);
+    const double bl[3] = {b0.x, b0.y, b0.z};
+    const double bh[3] = {bl[0] + g.h * (min(br.bx, g.nx - b0.i) - 1), bl[1] + g.h * (min(br.by, g.ny - b0.j) - 1),
+                          bl[2] + g.h * (min(br.bz, g.nz - b0.k) - 1)};
 
     // this wave's leaves: every (4 splits)-th, walked from an offset of its own
     const int nleaf = tr.cnt[0], step = 4 * int(gridDim.y), first = 4 * int(blockIdx.y) + wave;
@@ -960,13 +1031,9 @@ __global__ __launch_bounds__(kSdfBlock) void sdf_adjoint_kernel(const double* __
     __syncthreads();
     const double nv = nsum[threadIdx.x];
     if (nodeg[threadIdx.x].z >= 0.0 && nv != 0.0) {
-        // xi term of the nearest sample: -(d rho / d xi) u*, u* = e / xi
         const v4<double> np = nodep[threadIdx.x];
-        const int64_t jb = nnear[threadIdx.x];
-        const double coef = np.w * np.w * nv;
-        atomicAdd(gq + 3 * jb, coef * (np.x - q[3 * jb]));
-        atomicAdd(gq + 3 * jb + 1, coef * (np.y - q[3 * jb + 1]));
-        atomicAdd(gq + 3 * jb + 2, coef * (np.z - q[3 * jb + 2]));
+        if constexpr (NEAR) atomicAdd(near.sum + blk * kSdfBlock + threadIdx.x, nv);
+        else add_xi_term(q, nnear[threadIdx.x], np.x, np.y, np.z, np.w, nv, gq);
     }
 }
 
@@ -1555,6 +1622,26 @@ size_t sdf_build_workspace_bytes(int64_t ns, int phi) {
 
 size_t sdf_build_fast_bytes(int64_t ns) { return sdf_ws_layout(ns).fast_total; }
 
+namespace {
+
+// Leaf ranges per brick of the adjoint: about kAdjointBlocks blocks in all, at
+// least a leaf for each wave.  Larger grids have bricks enough to even out.
+constexpr int64_t kAdjointBlocks = 8192;
+struct AdjointSplit {
+    int64_t bricks, splits;
+};
+AdjointSplit adjoint_split(int64_t ns, const GridDesc& g) {
+    const int64_t bricks = brick_count(g), leaves = (ns + kLeaf - 1) / kLeaf;
+    return {bricks, std::max<int64_t>(1, std::min<int64_t>(kAdjointBlocks / bricks, (leaves + 3) / 4))};
+}
+
+}  // namespace
+
+size_t sdf_adjoint_bytes(int64_t ns, const GridDesc& g) {
+    const AdjointSplit sp = adjoint_split(ns, g);
+    return sdf_ws_layout(ns).total + (sp.splits > 1 ? size_t(sp.bricks) * kSdfBlock * 20 : 0);
+}
+
 template <typename T>
 hipError_t launch_sdf_build(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g,
                             const ParamDesc& p, int phi, void* rho_out, void* ws, size_t ws_bytes, hipStream_t s,
@@ -1597,27 +1684,40 @@ hipError_t launch_sdf_build(const double* q, const double* n, const double* w, i
 template <typename T>
 hipError_t launch_sdf_adjoint(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g,
                               const ParamDesc& p, const void* cot, double* grad_q, double* grad_n, double* grad_w,
-                              void* ws, hipStream_t s) {
+                              void* ws, size_t ws_bytes, hipStream_t s) {
     hipLaunchKernelGGL(zero_grads_kernel, dim3(unsigned(std::min<int64_t>((3 * ns + 255) / 256, 4096))), dim3(256), 0, s,
                        grad_q, grad_n, grad_w, ns);
     Prepared P{};
     hipError_t e = prepare_samples(q, n, w, ns, g, ws, false, false, false, s, &P);
     if (e != hipSuccess) return e;
-    // grids of few bricks split the leaves so that about four blocks per CU run
-    const int64_t bricks = brick_count(g);
-    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(1024 / bricks, (P.tr.cnt[0] + 3) / 4));
-    hipLaunchKernelGGL(sdf_adjoint_kernel<T>, dim3(unsigned(bricks), unsigned(splits)), dim3(kSdfBlock), 0, s, q, n, w,
-                       P.st.qs, P.st.js, P.node, P.tr, ns, g, p, static_cast<const cplx<T>*>(cot), grad_q, grad_n,
-                       grad_w);
+    const AdjointSplit sp = adjoint_split(ns, g);
+    const int64_t turn = tile_step(sp.bricks);
+    auto run = [&](auto kernel, int64_t splits, const NearData& near) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(sp.bricks), unsigned(splits)), dim3(kSdfBlock), 0, s, q, n, w,
+                           P.st.qs, P.st.js, P.node, P.tr, ns, g, p, static_cast<const cplx<T>*>(cot), grad_q, grad_n,
+                           grad_w, turn, near);
+    };
+    const int64_t slots = sp.bricks * kSdfBlock;
+    if (sp.splits > 1 && ws_bytes >= sdf_adjoint_bytes(ns, g)) {
+        auto* d2 = reinterpret_cast<double*>(static_cast<char*>(ws) + sdf_ws_layout(ns).total);
+        const NearData near{d2, d2 + slots, reinterpret_cast<int*>(d2 + 2 * slots)};
+        hipLaunchKernelGGL(adjoint_nearest_kernel, dim3(unsigned(16 * sp.bricks)), dim3(64), 0, s, P.st.qs, P.st.js,
+                           P.node, P.tr, ns, g, tile_step(16 * sp.bricks), near);
+        run(sdf_adjoint_kernel<T, true>, sp.splits, near);
+        hipLaunchKernelGGL(adjoint_xi_kernel, dim3(unsigned(sp.bricks)), dim3(kSdfBlock), 0, s, q, P.st.js, g, near,
+                           grad_q);
+    } else {
+        run(sdf_adjoint_kernel<T, false>, 1, NearData{});
+    }
     return hipGetLastError();
 }
 
 template hipError_t launch_sdf_adjoint<float>(const double*, const double*, const double*, int64_t, const GridDesc&,
                                               const ParamDesc&, const void*, double*, double*, double*, void*,
-                                              hipStream_t);
+                                              size_t, hipStream_t);
 template hipError_t launch_sdf_adjoint<double>(const double*, const double*, const double*, int64_t,
                                                const GridDesc&, const ParamDesc&, const void*, double*, double*,
-                                               double*, void*, hipStream_t);
+                                               double*, void*, size_t, hipStream_t);
 template hipError_t launch_sdf_build<float>(const double*, const double*, const double*, int64_t, const GridDesc&,
                                             const ParamDesc&, int, void*, void*, size_t, hipStream_t,
                                             unsigned long long*);

@@ -37,7 +37,10 @@ hipError_t launch_sdf_build(const double* q, const double* n, const double* w, i
 template <typename T>
 hipError_t launch_sdf_adjoint(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g,
                               const ParamDesc& p, const void* cot, double* grad_q, double* grad_n, double* grad_w,
-                              void* ws, hipStream_t s);
+                              void* ws, size_t ws_bytes, hipStream_t s);
+// workspace with which grids of few bricks search the nearest samples once and
+// split the leaves (below it: a block per brick does both)
+size_t sdf_adjoint_bytes(int64_t ns, const GridDesc& g);
 
 // ---- rotations: quaternions (FP64, device) -> R (FP64 and cast to T; either may be null), n x 9
 // row-major; cmax (may be null) is cleared for launch_coef_max

@@ -67,3 +67,22 @@ def test_sample_that_is_not_finite_gets_and_gives_nothing(ctxs):
     for x, y in zip(a, b):
         assert np.max(np.abs(x - y[:130])) <= 1e-12 * np.abs(x).max()
         assert np.all(y[130] == 0)
+
+
+@pytest.mark.parametrize("n,count", [((40, 37, 33), 1000), ((24, 8, 4), 257), ((70, 45, 1), 700)])
+def test_nearest_samples_found_once_or_per_brick(ctxs, n, count):
+    """Grids of few bricks find the nearest samples in a pass of their own where
+    the workspace allows; under a cap below it a block does both for its brick."""
+    from paper_1712_00238_amd.api import Context
+    s = samples(count, count, n[2] == 1)
+    grid = C.GridSpec(n, tuple(-0.1 * (m - 1) + 0.013 * (m > 1) for m in n), 0.2)
+    params = C.SDFParams(xi_floor=0.05)
+    cot = np.random.default_rng(6).normal(size=n[::-1]) + 1j
+    bricks = -(-n[0] // 16) * -(-n[1] // 16) if n[2] == 1 else -(-n[0] // 8) * -(-n[1] // 8) * -(-n[2] // 4)
+    flush_print("adjoint, nearest pass", n, count)
+    a = [x.cpu().numpy() for x in ctxs["f64"].sdf_build_adjoint(s.q, s.n, s.w, grid, params, cot)]
+    with Context(0, "f64", workspace_cap=max(bricks * 5120, 150 * count)) as capped:
+        b = [x.cpu().numpy() for x in capped.sdf_build_adjoint(s.q, s.n, s.w, grid, params, cot)]
+    # FP64 sums in another order, cancelling a thousandfold at worst
+    for x, y in zip(a, b):
+        assert np.max(np.abs(x - y)) <= 1e-11 * np.abs(y).max()
