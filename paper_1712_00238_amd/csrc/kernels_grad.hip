@@ -65,6 +65,25 @@ __device__ __forceinline__ double row16_sum(double v) {
     return v;
 }
 
+// The sums of v[0 .. 6] over each row of 16 lanes: lane l of a row ends with
+// those of values a and a + 1, a = 4 (l & 1) + (l & 2).  Two exchanges halve
+// the values a lane carries, so 54 instructions do the work of 84.
+__device__ __forceinline__ void row16_sum8(const double v[7], int lane, double out[2]) {
+    const bool b0 = lane & 1, b1 = lane & 2;
+    double h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const double hi = i < 3 ? v[i + 4] : 0.0;
+        h[i] = (b0 ? hi : v[i]) + dpp_f64<0xb1>(b0 ? v[i] : hi);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        double x = (b1 ? h[i + 2] : h[i]) + dpp_f64<0x4e>(b1 ? h[i] : h[i + 2]);
+        x += dpp_f64<0x124>(x);  // the four quads of the row
+        x += dpp_f64<0x128>(x);
+        out[i] = x;
+    }
+}
 __device__ __forceinline__ double warp_sum(double v) {
     for (int off = warpSize / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
     return v;
@@ -236,9 +255,15 @@ __global__ __launch_bounds__(kGBlock) void grad_tile_kernel(const cplx<T>* __res
 // the pitches timed, the best over both uniformly spread and clustered
 // rotations, whose stencil gathers meet different LDS bank conflicts), so the
 // 64 stencil reads of a sample sit at constant offsets from one address.
-// Staging gives each wave three box rows per load instruction (54 lanes, row
-// and plane on the scalar unit) and issues all of a wave's loads before its
-// LDS stores.
+// Staging gives each wave two planes of the box and three rows per load
+// instruction (54 lanes): the lanes' offsets within a plane serve both planes,
+// a plane is a buffer descriptor, and its bounds and kBufferNone stand for the
+// masks.  All of a wave's loads come before its LDS stores.
+// Bound by VALU issue (650 instructions per wave and pose, of which the stencil
+// and its weights need 370) and the gathers' LDS cycles, half of them bank
+// conflicts, each nine tenths of the time.  1024 poses of a 64^3 body: 4.9 ms;
+// 5.6 with row and plane found anew for each load and every sum reduced over
+// the 16 lanes of a row by itself (810 instructions).
 constexpr int kBoxTile = 8;
 constexpr int kBoxBlock = kBoxTile * kBoxTile * kBoxTile;
 constexpr int kBoxWaves = kBoxBlock / 64;
@@ -247,11 +272,11 @@ constexpr int kBoxRow = 18;
 constexpr int kBoxPlane = 312;
 constexpr int kBoxCells = kBoxPlane * kBoxMax;
 constexpr int kBoxSlotRows = 3;                                            // rows per wave load
-constexpr int kBoxSlots = kBoxMax * ((kBoxMax + kBoxSlotRows - 1) / kBoxSlotRows);
-constexpr int kBoxStage = (kBoxSlots + kBoxWaves - 1) / kBoxWaves;         // loads per lane
+constexpr int kBoxSlotsY = (kBoxMax + kBoxSlotRows - 1) / kBoxSlotRows;       // loads per plane
 constexpr float kBoxMargin = 1e-3f;
 static_assert(kBoxRow >= kBoxMax && kBoxPlane >= kBoxRow * kBoxMax, "box pitches");
 static_assert(kBoxRow * kBoxSlotRows <= 64, "staging rows per wave");
+static_assert(kBoxMax == 2 * kBoxWaves + 1 && kBoxSlotsY <= kBoxWaves, "two planes a wave, and one more");
 
 // Per-pose constants of the box kernel, computed once per pose: R in FP32,
 // t split into floor and fraction, and the offsets of the moved 8^3 tile's
@@ -355,40 +380,57 @@ __global__ __launch_bounds__(kBoxBlock, 2) void grad_box_kernel(const cplx<float
             ext[a] = __builtin_amdgcn_readfirstlane(
                 min(int(floorf(y0 + P.dmax[a] + kBoxMargin)) - fmin + 4, kBoxMax));
         }
-        // stage the box: slot s holds rows 3 q .. 3 q + 2 of plane cz, with
-        // s = cz nts + q; lane = kBoxRow j + cx covers row 3 q + j, cell cx
+        // stage the box: a wave takes planes wid and wid + 8, a load rows 3 q .. 3 q + 2
+        // of one (lane = kBoxRow j + cx: row 3 q + j, cell cx)
         {
-            const unsigned Nu = unsigned(N);
-            const unsigned wx = unsigned(wrap(lo[0], N)), wy = __builtin_amdgcn_readfirstlane(wrap(lo[1], N)),
-                           wz = __builtin_amdgcn_readfirstlane(wrap(lo[2], N));
-            const int nts = (ext[1] + kBoxSlotRows - 1) / kBoxSlotRows, nslot = ext[2] * nts;
-            const unsigned inv = 65535u / unsigned(nts) + 1u;  // s / nts = (s inv) >> 16 for s < 2^16 / nts
+            const unsigned Nu = unsigned(N), plane_bytes = Nu * Nu * unsigned(sizeof(cplx<float>));
+            const unsigned wx = unsigned(wrap(lo[0], N)), wy = unsigned(wrap(lo[1], N)), wz = unsigned(wrap(lo[2], N));
             unsigned gx = wx + unsigned(cxs);
             gx = min(gx, gx - Nu);
             const bool lane_ok = js < kBoxSlotRows && cxs < ext[0];
-            cplx<float> v[kBoxStage];
+            auto offset = [&](int q) {  // of this lane's cell within a plane
+                const int cy = q * kBoxSlotRows + js;
+                unsigned gy = wy + unsigned(cy);
+                gy = min(gy, gy - Nu);
+                return lane_ok && cy < ext[1] ? (__umul24(gy, Nu) + gx) * unsigned(sizeof(cplx<float>)) : kBufferNone;
+            };
+            auto plane = [&](int cz) {  // no bytes past the box
+                unsigned gz = wz + unsigned(cz);
+                gz = min(gz, gz - Nu);
+                return buffer_rsrc(rho_f + size_t(gz) * Nu * Nu, cz < ext[2] ? plane_bytes : 0u);
+            };
+            const auto r0 = plane(wid), r1 = plane(wid + kBoxWaves);
+            cplx<float> v0[kBoxSlotsY], v1[kBoxSlotsY];
 #pragma unroll
-            for (int m = 0; m < kBoxStage; ++m) {
-                const int s = wid + m * kBoxWaves;
-                v[m] = mk(0.f, 0.f);
-                if (s < nslot) {
-                    const int cz = int((unsigned(s) * inv) >> 16), q = s - cz * nts;
-                    const int cy = q * kBoxSlotRows + js;
-                    unsigned gz = wz + unsigned(cz);
-                    gz = min(gz, gz - Nu);
-                    unsigned gy = wy + unsigned(cy);
-                    gy = min(gy, gy - Nu);
-                    if (lane_ok && cy < ext[1]) v[m] = rho_f[gz * Nu * Nu + __umul24(gy, Nu) + gx];
+            for (int q = 0; q + 1 < kBoxSlotsY; ++q) {
+                const unsigned at = offset(q);
+                v0[q] = buffer_load_cf(r0, at, 0);
+                v1[q] = buffer_load_cf(r1, at, 0);
+            }
+            const bool tall = ext[1] > (kBoxSlotsY - 1) * kBoxSlotRows;
+            if (tall) {
+                const unsigned at = offset(kBoxSlotsY - 1);
+                v0[kBoxSlotsY - 1] = buffer_load_cf(r0, at, 0);
+                v1[kBoxSlotsY - 1] = buffer_load_cf(r1, at, 0);
+            }
+            cplx<float>* dst = box + wid * kBoxPlane + lane;
+            if (lane < kBoxSlotRows * kBoxRow) {
+#pragma unroll
+                for (int q = 0; q + 1 < kBoxSlotsY; ++q) {
+                    dst[q * (kBoxSlotRows * kBoxRow)] = v0[q];
+                    dst[kBoxWaves * kBoxPlane + q * (kBoxSlotRows * kBoxRow)] = v1[q];
                 }
             }
-#pragma unroll
-            for (int m = 0; m < kBoxStage; ++m) {
-                const int s = wid + m * kBoxWaves;
-                if (s < nslot) {
-                    const int cz = int((unsigned(s) * inv) >> 16), q = s - cz * nts;
-                    if (lane_ok && q * kBoxSlotRows + js < ext[1])
-                        box[cz * kBoxPlane + q * (kBoxSlotRows * kBoxRow) + lane] = v[m];
-                }
+            constexpr int kLastRows = kBoxMax - (kBoxSlotsY - 1) * kBoxSlotRows;
+            if (tall && lane < kLastRows * kBoxRow) {
+                dst[(kBoxSlotsY - 1) * (kBoxSlotRows * kBoxRow)] = v0[kBoxSlotsY - 1];
+                dst[kBoxWaves * kBoxPlane + (kBoxSlotsY - 1) * (kBoxSlotRows * kBoxRow)] = v1[kBoxSlotsY - 1];
+            }
+            // the seventeenth plane: a load for each of the first waves
+            if (ext[2] > 2 * kBoxWaves && wid < kBoxSlotsY) {
+                const cplx<float> v = buffer_load_cf(plane(2 * kBoxWaves), offset(wid), 0);
+                if (lane < (wid + 1 < kBoxSlotsY ? kBoxSlotRows : kLastRows) * kBoxRow)
+                    box[2 * kBoxWaves * kBoxPlane + wid * (kBoxSlotRows * kBoxRow) + lane] = v;
             }
         }
         __syncthreads();
@@ -506,11 +548,18 @@ __global__ __launch_bounds__(kBoxBlock, 2) void grad_box_kernel(const cplx<float
             }
         }
         // block reduction: rows of 16 lanes (DPP), then 32 row sums per value
-        const int nacc = GRAD ? kNAcc : 1;
-#pragma unroll
-        for (int a = 0; a < nacc; ++a) {
-            const double v = row16_sum(acc[a]);
-            if ((lane & 15) == 0) red[wid * 4 + (lane >> 4)][a] = v;
+        constexpr int nacc = GRAD ? kNAcc : 1;
+        if constexpr (GRAD) {
+            double two[2];
+            row16_sum8(acc, lane, two);
+            const int a = 4 * (lane & 1) + (lane & 2);  // this lane holds sums a and a + 1
+            if ((lane & 15) < 4) {
+                red[wid * 4 + (lane >> 4)][a] = two[0];
+                if (a + 1 < nacc) red[wid * 4 + (lane >> 4)][a + 1] = two[1];
+            }
+        } else {
+            const double v = row16_sum(acc[0]);
+            if ((lane & 15) == 0) red[wid * 4 + (lane >> 4)][0] = v;
         }
         __syncthreads();  // also: every thread is done reading the box
         if (threadIdx.x < nacc) {
