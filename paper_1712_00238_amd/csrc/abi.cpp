@@ -552,16 +552,13 @@ int fused_pairs(sdf_ctx ctx, const std::vector<PairIn>& pairs, hipStream_t s) {
         ctx->fused_cache_base = ctx->ws;
         ctx->fused_cache_valid = true;
     }
+    std::vector<sdf::FusedPrepJob> prep_h(nj);
     for (int j = 0; j < nj; ++j)
-        SDF_TRY_HIP(ctx,
-                    sdf::launch_coef<float>(pairs[j].rho_m, static_cast<const float*>(pairs[j].w_m),
-                                            gsize(pairs[j].gm), cptr[j], s),
-                    "coefficients");
-    for (int j = 0; j < nj; ++j)
-        if (xsrc[j] == j)
-            SDF_TRY_HIP(ctx, sdf::launch_spec_pair_group(pairs[j].spec, xptr[j], pairs[j].gf->n[0], s),
-                        "spectrum column order");
-    SDF_TRY_HIP(ctx, sdf::launch_fused_prep(jobs_d, nj, prep, s), "fixed-point scale");
+        prep_h[j] = sdf::FusedPrepJob{pairs[j].rho_m, static_cast<const float*>(pairs[j].w_m), cptr[j],
+                                      gsize(pairs[j].gm), pairs[j].spec, xsrc[j] == j ? xptr[j] : nullptr,
+                                      pairs[j].gf->n[0]};
+    SDF_TRY_HIP(ctx, sdf::launch_fused_prep(prep_h.data(), jobs_d, nj, prep, s),
+                "coefficients, spectrum column order and fixed-point scale");
 
     sdf::KernelTimer* kt = ctx->opt_profile ? &ctx->prof : nullptr;
     auto enqueue = [&]() -> hipError_t {

@@ -83,6 +83,7 @@ constexpr int slab_pitch() { return N + (slab_tpl<N>() < 2 ? 2 : slab_tpl<N>());
 constexpr int kPencilBlock = 512;
 constexpr int kFinishBlock = 256;
 constexpr int kPrepBlocks = 64;
+constexpr int kPrepJobs = 16;  // pairs per preparing launch, in its arguments
 
 template <int N>
 constexpr int pencil_width() {
@@ -175,23 +176,6 @@ __global__ void rot_desc_kernel(const RotInput* __restrict__ in, int64_t n, Fuse
 }
 
 // ------------------------------------------------------------------ K0
-__global__ __launch_bounds__(256) void cmax_partial_kernel(const FusedJob* __restrict__ jobs,
-                                                           float* __restrict__ part) {
-    const FusedJob jb = jobs[blockIdx.y];
-    const cf* c = static_cast<const cf*>(jb.c);
-    const int64_t K = int64_t(jb.n_m) * jb.n_m * (jb.planar ? 1 : jb.n_m);
-    float m = 0.f;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < K; i += int64_t(gridDim.x) * 256) {
-        const cf v = c[i];
-        m = fmaxf(m, fmaxf(fabsf(v.re), fabsf(v.im)));
-    }
-    for (int off = warpSize / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    __shared__ float wm[4];
-    if (threadIdx.x % warpSize == 0) wm[threadIdx.x / warpSize] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
-}
-
 // scale = fixed-point units per unit value: |node sum| <= 8 max|c| maps into 2^31
 __global__ void cmax_final_kernel(const FusedJob* __restrict__ jobs, const float* __restrict__ part, int nparts) {
     float m = 0.f;
@@ -1880,9 +1864,10 @@ size_t fused_prep_scratch_bytes(int n_jobs) { return align256(sizeof(float) * kP
 // the fold's own factor in H(k) = (Y(k) + conj(Y(-k))) / 2 (an exact power of
 // two, so the folded values are the same).
 template <int N>
-__global__ void spec_pair_group_kernel(const cf* __restrict__ in, cf* __restrict__ out) {
+__device__ __forceinline__ void group_spectrum(const cf* __restrict__ in, cf* __restrict__ out, int block,
+                                               int blocks) {
     const int64_t rows = int64_t(N) * N;
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < rows * N; i += int64_t(gridDim.x) * blockDim.x) {
+    for (int64_t i = int64_t(block) * 256 + threadIdx.x; i < rows * N; i += int64_t(blocks) * 256) {
         const int p = int(i % N);
         const int kx = col_kx<N>(p), ky = int((i / N) % N), kz = int(i / rows);
         const cf v = in[i - p + kx];
@@ -1891,16 +1876,38 @@ __global__ void spec_pair_group_kernel(const cf* __restrict__ in, cf* __restrict
     }
 }
 
-hipError_t launch_spec_pair_group(const void* spec, void* out, int N, hipStream_t s) {
-    const cf* in = static_cast<const cf*>(spec);
-    cf* o = static_cast<cf*>(out);
-    if (N == 128)
-        hipLaunchKernelGGL(spec_pair_group_kernel<128>, dim3(2048), dim3(256), 0, s, in, o);
-    else if (N == 64)
-        hipLaunchKernelGGL(spec_pair_group_kernel<64>, dim3(1024), dim3(256), 0, s, in, o);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+// What the pairs of a call need before their rotations, in one launch: blocks
+// [0, kPrepBlocks) of a pair compute its coefficients and their maxima per
+// block, the others its reordered spectrum.  Small searches are a chain of
+// launches: 64^3, 9 rotations took 89 us with a launch for each (and two more
+// per further pair of a batch), 82 so.
+struct PrepArgs {
+    FusedPrepJob job[kPrepJobs];
+};
+__global__ __launch_bounds__(256) void fused_prep_kernel(PrepArgs args, float* __restrict__ part) {
+    const FusedPrepJob jb = args.job[blockIdx.y];
+    if (blockIdx.x >= kPrepBlocks) {
+        const int block = int(blockIdx.x) - kPrepBlocks, blocks = int(gridDim.x) - kPrepBlocks;
+        const cf* in = static_cast<const cf*>(jb.spec);
+        if (jb.grouped && jb.N == 128) group_spectrum<128>(in, static_cast<cf*>(jb.grouped), block, blocks);
+        if (jb.grouped && jb.N == 64) group_spectrum<64>(in, static_cast<cf*>(jb.grouped), block, blocks);
+        return;
+    }
+    const cf* rho = static_cast<const cf*>(jb.rho_m);
+    cf* c = static_cast<cf*>(jb.c);
+    float m = 0.f;
+#pragma unroll 4
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < jb.count; i += kPrepBlocks * 256) {
+        const cf v = rho[i] * jb.w_m[i];
+        c[i] = v;
+        m = fmaxf(m, fmaxf(fabsf(v.re), fabsf(v.im)));
+    }
+    for (int off = warpSize / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    __shared__ float wm[4];
+    if (threadIdx.x % warpSize == 0) wm[threadIdx.x / warpSize] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        part[blockIdx.y * kPrepBlocks + blockIdx.x] = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
 }
 
 hipError_t launch_rot_desc(const RotInput* in, int64_t n, FusedRot* out, hipStream_t s) {
@@ -1908,10 +1915,20 @@ hipError_t launch_rot_desc(const RotInput* in, int64_t n, FusedRot* out, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_fused_prep(const FusedJob* jobs, int n_jobs, void* scratch, hipStream_t s) {
+hipError_t launch_fused_prep(const FusedPrepJob* prep, const FusedJob* jobs, int n_jobs, void* scratch,
+                             hipStream_t s) {
     float* part = static_cast<float*>(scratch);
-    const dim3 g1{unsigned(kPrepBlocks), unsigned(n_jobs), 1u};
-    hipLaunchKernelGGL(cmax_partial_kernel, g1, dim3(256), 0, s, jobs, part);
+    for (int j0 = 0; j0 < n_jobs; j0 += kPrepJobs) {
+        PrepArgs args{};
+        const int n = std::min(kPrepJobs, n_jobs - j0);
+        int N = 0;  // the largest grid whose spectrum is reordered
+        for (int j = 0; j < n; ++j) {
+            args.job[j] = prep[j0 + j];
+            if (prep[j0 + j].grouped) N = std::max(N, prep[j0 + j].N);
+        }
+        hipLaunchKernelGGL(fused_prep_kernel, dim3(unsigned(kPrepBlocks + 16 * N), unsigned(n)), dim3(256), 0, s, args,
+                           part + size_t(j0) * kPrepBlocks);
+    }
     hipLaunchKernelGGL(cmax_final_kernel, dim3(unsigned(n_jobs)), dim3(64), 0, s, jobs, part, kPrepBlocks);
     return hipGetLastError();
 }

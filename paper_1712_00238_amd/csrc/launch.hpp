@@ -160,11 +160,21 @@ void fused_query_occupancy();
 // every kz), and the fixed spectrum is copied into that order and tiling
 // once per call.
 inline bool fused_pair_grouped(int N, bool planar) { return !planar && (N == 64 || N == 128); }
-hipError_t launch_spec_pair_group(const void* spec, void* out, int N, hipStream_t s);
 // quaternions -> FusedRot descriptors (FP64 matrix, cast to FP32)
 hipError_t launch_rot_desc(const RotInput* in, int64_t n, FusedRot* out, hipStream_t s);
-// per pair: max |c_k| and the fixed-point scale (written through jobs[j].scale)
-hipError_t launch_fused_prep(const FusedJob* jobs, int n_jobs, void* scratch, hipStream_t s);
+// what a pair's rotations need first
+struct FusedPrepJob {
+    const void* rho_m;  // complex64, count values
+    const float* w_m;
+    void* c;            // coefficients out
+    int64_t count;
+    const void* spec;   // complex64, N^3
+    void* grouped;      // its reordered copy out (N = 64 or 128), or null
+    int N;
+};
+// per pair: coefficients, reordered spectrum, max |c_k| and the fixed-point
+// scale (written through jobs[j].scale)
+hipError_t launch_fused_prep(const FusedPrepJob* prep, const FusedJob* jobs, int n_jobs, void* scratch, hipStream_t s);
 size_t fused_prep_scratch_bytes(int n_jobs);
 // score rotations rots[0 .. n_rot) (n_rot <= fp.batch) of one grid-size class
 hipError_t launch_fused_batch(const FusedPlan& fp, const FusedRot* rots, int n_rot, const FusedJob* jobs, void* ws,
