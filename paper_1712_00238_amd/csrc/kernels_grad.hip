@@ -768,6 +768,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
         }
         __syncthreads();
     };
+    const Fixed64 fixed;
     const int wave = uniform(int(threadIdx.x) >> 6);
     const T half_box = T(0.5) * T(n_m);
     const int64_t b0 = int64_t(range) * per, b1 = b0 + per < B ? b0 + per : B;
@@ -861,8 +862,8 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                                         const int nd = row * S::X + ix;
                                         atomicOr(bad + nd / 32, 1u << (nd % 32));
                                     } else if constexpr (WIDE) {
-                                        atomicAdd(a, fixed64(cr * wt));
-                                        atomicAdd(a + S::IMAG, fixed64(ci * wt));
+                                        atomicAdd(a, fixed(cr * wt));
+                                        atomicAdd(a + S::IMAG, fixed(ci * wt));
                                     } else {
                                         atomicAdd(a, (unsigned long long)(long long)__float2int_rn(cr * wt));
                                         atomicAdd(a + S::IMAG, (unsigned long long)(long long)__float2int_rn(ci * wt));

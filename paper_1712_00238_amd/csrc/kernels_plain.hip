@@ -150,9 +150,9 @@ __global__ void spread_atomic_kernel(const cplx<T>* __restrict__ c, int n_m, int
 // FP64 sum; 32 bits for FP32, in units of at most 16 max|c| / 2^31.  The weights at a node of a unit-density lattice sum to about 1, so
 // no sum leaves the range.  Nodes are centred coordinates [-N/2, N/2): the fit
 // rule keeps every stencil inside, so no index wraps before the store.
-// Bound by VALU issue and LDS adds (7 + 1 instructions per FP64 sum).  FP64,
-// 8 rotations of 96^3 / 48^3: the whole search 6212 -> 467 us, 216 of them here;
-// 36 rotations of 128^2 / 64^2: 1930 -> 71 us (with the batched and fused
+// Bound by VALU issue (6 instructions per FP64 sum besides its LDS add).  FP64,
+// 8 rotations of 96^3 / 48^3: the whole search 6212 -> 413 us, 180 of them here;
+// 36 rotations of 128^2 / 64^2: 1930 -> 65 us (with the batched and fused
 // transform passes).
 template <typename T>
 struct TileSum;
@@ -160,17 +160,63 @@ template <>
 struct TileSum<float> {
     using type = int;
     static constexpr double top = 2147483648.0;  // 2^31
-    static __device__ __forceinline__ int fixed(float v) { return __float2int_rn(v); }
+    struct Fixed {
+        __device__ __forceinline__ int operator()(float v) const { return __float2int_rn(v); }
+    };
 };
 template <>
 struct TileSum<double> {
     using type = unsigned long long;
     static constexpr double top = 1152921504606846976.0;  // 2^60
-    static __device__ __forceinline__ unsigned long long fixed(double v) { return fixed64(v); }
+    using Fixed = Fixed64;
 };
 
-template <typename T, bool PLANAR>
-__global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* __restrict__ c, int n_m,
+// The r-th tile from the middle of the grid outwards.  The body's tiles take
+// nearly all of the time; launched first, over all rotations, they spread over
+// the CUs evenly and none is left for the end (FP64, 96^3, 8 rotations of a 48^3
+// body: 420 us for the search in row order, 413 so; 12 of 128^3: 1300 and 1215).
+// 3D tiles are half as thick as wide, and
+// shell k of the nested boxes of 2k x 2k x 4k tiles holds its two lowest and two
+// highest layers, then the rings of the layers between; grids of less than two
+// tiles across are taken in order.
+template <bool PLANAR>
+__device__ __forceinline__ void tile_outwards(int r, int nx, int ny, int t[3]) {
+    if (PLANAR) {
+        auto from_middle = [](int i, int n) { return n / 2 + ((i & 1) ? -((i + 1) / 2) : i / 2); };
+        t[0] = from_middle(r % nx, nx);
+        t[1] = from_middle(r / nx, ny);
+        t[2] = 0;
+        return;
+    }
+    if (nx < 2) {
+        t[0] = t[1] = 0;
+        t[2] = r;
+        return;
+    }
+    int k = 1;
+    while (16 * k * k * k <= r) ++k;
+    const int s = 2 * k, area = s * s, ring = 4 * s - 4;
+    int q = r - 16 * (k - 1) * (k - 1) * (k - 1);
+    if (q < 4 * area) {
+        const int layer = q / area;
+        q %= area;
+        t[0] = q % s;
+        t[1] = q / s;
+        t[2] = layer < 2 ? layer : 2 * s - 4 + layer;
+    } else {
+        q -= 4 * area;
+        t[2] = 2 + q / ring;
+        q %= ring;
+        t[0] = q < 2 * s ? q % s : ((q & 1) ? s - 1 : 0);
+        t[1] = q < 2 * s ? (q < s ? 0 : s - 1) : 1 + (q - 2 * s) / 2;
+    }
+    t[0] += nx / 2 - k;
+    t[1] += ny / 2 - k;
+    t[2] += nx - s;
+}
+
+template <typename T, bool PLANAR, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void spread_tile_kernel(const cplx<T>* __restrict__ c, int n_m,
                                                                  const T* __restrict__ R, T sign, int N,
                                                                  const unsigned long long* __restrict__ cmax,
                                                                  cplx<T>* __restrict__ out) {
@@ -179,14 +225,9 @@ __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* 
     __shared__ A acc[S::WORDS];
     const int sx = min(S::X, N), sy = min(S::Y, N), sz = PLANAR ? 1 : min(S::Z, N);
     const int ntx = N / sx, nty = N / sy;
-    // the tiles of the body, which take most of the time, from the middle of
-    // the grid outwards over all rotations: they spread over the CUs evenly
-    // and none is left for the end (FP64, 96^3, 8 rotations of a 48^3 body:
-    // 222 -> 205 us)
-    const int tile = int(blockIdx.y);
-    auto outwards = [](int r, int n) { return n / 2 + ((r & 1) ? -((r + 1) / 2) : r / 2); };
-    const int t0[3] = {outwards(tile % ntx, ntx) * sx - N / 2, outwards((tile / ntx) % nty, nty) * sy - N / 2,
-                       PLANAR ? 0 : outwards(tile / (ntx * nty), N / sz) * sz - N / 2};
+    int tile[3];
+    tile_outwards<PLANAR>(int(blockIdx.y), ntx, nty, tile);
+    const int t0[3] = {tile[0] * sx - N / 2, tile[1] * sy - N / 2, PLANAR ? 0 : tile[2] * sz - N / 2};
     const int dim[3] = {sx, sy, sz};
     const int64_t G = PLANAR ? int64_t(N) * N : int64_t(N) * N * N;
     cplx<T>* g = out + int64_t(blockIdx.x) * G;
@@ -196,9 +237,10 @@ __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* 
     const double pow2 = pow2_below(fmin(TileSum<T>::top / (8.0 * cm), std::is_same<T, float>::value ? 1e37 : 1e300));
     const T scale = cm > 0.0 && finite ? T(pow2) : T(0);
     const T inv = cm > 0.0 ? T(1.0 / pow2) : T(0);
-    for (int i = int(threadIdx.x); i < S::WORDS; i += kTileBlock) acc[i] = 0;
+    for (int i = int(threadIdx.x); i < S::WORDS; i += BLOCK) acc[i] = 0;
     __syncthreads();
     const T half_box = T(0.5) * T(n_m);
+    const typename TileSum<T>::Fixed fixed;
     float rf[9], lo[3], hi[3];
 #pragma unroll
     for (int a = 0; a < 9; ++a) rf[a] = float(sign * r[a]);
@@ -207,7 +249,7 @@ __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* 
         lo[a] = float(t0[a] - 2);
         hi[a] = float(t0[a] + dim[a] + 1);
     }
-    box_samples<PLANAR>(rf, n_m, lo, hi, uniform(int(threadIdx.x) >> 6), kTileBlock / 64, [&](int i, int j, int k) {
+    box_samples<PLANAR>(rf, n_m, lo, hi, uniform(int(threadIdx.x) >> 6), BLOCK / 64, [&](int i, int j, int k) {
         cplx<T> v = c[(k * n_m + j) * n_m + i];
         v.re *= scale;
         v.im *= scale;
@@ -230,20 +272,20 @@ __global__ __launch_bounds__(kTileBlock) void spread_tile_kernel(const cplx<T>* 
                 const int iy = b[1] + cy;
                 if (unsigned(iy) >= unsigned(sy)) continue;
                 const T wyz = PLANAR ? wt[1][cy] : wt[1][cy] * wt[2][cz];
+                const T row_re = v.re * wyz, row_im = v.im * wyz;
                 A* row = acc + (iz * S::Y + iy) * S::PITCH;
 #pragma unroll
                 for (int cx = 0; cx < 4; ++cx) {
                     const int ix = b[0] + cx;
                     if (unsigned(ix) >= unsigned(sx)) continue;
-                    const T w3 = wt[0][cx] * wyz;
-                    atomicAdd(row + ix, TileSum<T>::fixed(v.re * w3));
-                    atomicAdd(row + S::IMAG + ix, TileSum<T>::fixed(v.im * w3));
+                    atomicAdd(row + ix, fixed(row_re * wt[0][cx]));
+                    atomicAdd(row + S::IMAG + ix, fixed(row_im * wt[0][cx]));
                 }
             }
         }
     });
     __syncthreads();
-    for (int i = int(threadIdx.x); i < sx * sy * sz; i += kTileBlock) {
+    for (int i = int(threadIdx.x); i < sx * sy * sz; i += BLOCK) {
         const int ix = i % sx, iy = (i / sx) % sy, iz = i / (sx * sy);
         const A* a = acc + (iz * S::Y + iy) * S::PITCH + ix;
         const int ux = (t0[0] + ix + N) % N, uy = (t0[1] + iy + N) % N, uz = PLANAR ? 0 : (t0[2] + iz + N) % N;
@@ -735,14 +777,23 @@ hipError_t launch_spread_tiles(const void* c, int n_m, bool planar, const T* R, 
     if (planar) {
         using S = SpreadTile<true>;
         const unsigned tx = unsigned(N / (S::X < N ? S::X : N)), ty = unsigned(N / (S::Y < N ? S::Y : N));
-        hipLaunchKernelGGL((spread_tile_kernel<T, true>), dim3(unsigned(n_rot), tx * ty), dim3(kTileBlock), 0, s, cc,
+        hipLaunchKernelGGL((spread_tile_kernel<T, true, kTileBlock>), dim3(unsigned(n_rot), tx * ty), dim3(kTileBlock), 0, s, cc,
                            n_m, R, sign, N, cmax, o);
     } else {
         using S = SpreadTile<false>;
         const unsigned tx = unsigned(N / (S::X < N ? S::X : N)), ty = unsigned(N / (S::Y < N ? S::Y : N)),
                        tz = unsigned(N / (S::Z < N ? S::Z : N));
-        hipLaunchKernelGGL((spread_tile_kernel<T, false>), dim3(unsigned(n_rot), tx * ty * tz), dim3(kTileBlock), 0, s,
-                           cc, n_m, R, sign, N, cmax, o);
+        // A call of few tiles ends with its slowest: eight waves a tile halve
+        // that, where many tiles keep every CU busy with four (FP64: 413 / 455 us
+        // for a search of 8 rotations at 96^3, 3456 tiles; 1214 / 1191 for 12 at
+        // 128^3, 12288).
+        const dim3 grid{unsigned(n_rot), tx * ty * tz, 1u};
+        if (int64_t(n_rot) * tx * ty * tz <= 8192)
+            hipLaunchKernelGGL((spread_tile_kernel<T, false, 2 * kTileBlock>), grid, dim3(2 * kTileBlock), 0, s, cc, n_m,
+                               R, sign, N, cmax, o);
+        else
+            hipLaunchKernelGGL((spread_tile_kernel<T, false, kTileBlock>), grid, dim3(kTileBlock), 0, s, cc, n_m, R,
+                               sign, N, cmax, o);
     }
     return hipGetLastError();
 }

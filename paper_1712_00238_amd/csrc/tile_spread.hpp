@@ -97,15 +97,27 @@ __device__ __forceinline__ void box_samples(const float r[9], int n_m, const flo
 }
 
 // 64-bit integer nearest v, |v| < 2^62, in two exact steps: adding m = 1.5 2^52
-// leaves an integer in the low words
-__device__ __forceinline__ unsigned long long fixed64(double v) {
-    constexpr double m = 6755399441055744.0;
-    const double hm = __builtin_fma(v, 2.3283064365386963e-10, m);
-    const double l = __builtin_fma(hm - m, -4294967296.0, v);
-    const double lm = l + m;  // l in [-2^31, 2^31]: the words of the signed integer l, plus m's high word
-    const unsigned hi = unsigned(__double2loint(hm)) + unsigned(__double2hiint(lm)) - 0x43380000u;
-    return (static_cast<unsigned long long>(hi) << 32) | unsigned(__double2loint(lm));
-}
+// leaves an integer in the low words.  The first step's m is short by the high
+// word that the second leaves above its own, so the words meet in one add.  The
+// constants are a kernel's variables that the compiler cannot see through: as
+// literals they cost five moves a term, more than the arithmetic.
+struct Fixed64 {
+    double mh, ml, up;
+    __device__ __forceinline__ Fixed64()
+        : mh(6755399441055744.0 - 1127743488.0), ml(6755399441055744.0), up(2.3283064365386963e-10) {  // 0x43380000
+        asm("" : "+v"(mh));
+        asm("" : "+v"(ml));
+        asm("" : "+s"(up));
+    }
+    __device__ __forceinline__ unsigned long long operator()(double v) const {
+        const double hm = __builtin_fma(v, up, mh);
+        const double l = __builtin_fma(hm - mh, -4294967296.0, v);
+        const double lm = l + ml;  // l in [-2^31, 2^31]: the words of the signed integer l, plus m's high word
+        unsigned hi = unsigned(__double2loint(hm)) + unsigned(__double2hiint(lm));
+        asm("" : "+v"(hi));
+        return (static_cast<unsigned long long>(hi) << 32) | unsigned(__double2loint(lm));
+    }
+};
 
 // the largest power of two not above v (v > 0, normal): scaling by it rounds nothing
 __device__ __forceinline__ double pow2_below(double v) {

@@ -87,3 +87,20 @@ def test_zero_field_scores_zero():
     with Context(0, "f64") as ctx:
         out = ctx.score_rotations(ctx.spectrum(rho_f, gf), gf, 0 * rho_m, w, gm, quats(False, 2, 1))
         assert bool((out["score"] == 0).all()) and bool((out["t"] == 0).all())
+
+
+@pytest.mark.parametrize("count", [8, 9])
+def test_tiles_of_few_and_of_many_rotations(count):
+    """Up to 8192 tiles (eight rotations of 128^3) take eight waves each, more
+    take four: the integer sums are the same either way."""
+    from paper_1712_00238_amd.api import Context
+    gf, gm, rho_f, rho_m, w = case(128, 13, False, 3)
+    q = quats(False, count, 8)
+    flush_print("plain tiles", count)
+    with Context(0, "f64") as ctx:
+        spec = ctx.spectrum(rho_f, gf)
+        many = ctx.score_rotations(spec, gf, rho_m, w, gm, q)
+        for r in (0, count - 1):
+            one = ctx.score_rotations(spec, gf, rho_m, w, gm, q[r:r + 1])
+            for k in ("score", "t", "nbhd", "refined"):
+                assert np.array_equal(many[k][r].cpu().numpy(), one[k][0].cpu().numpy()), (r, k)
