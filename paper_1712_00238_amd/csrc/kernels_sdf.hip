@@ -866,9 +866,29 @@ __global__ __launch_bounds__(kSdfBlock) void adjoint_xi_kernel(const double* __r
                                                                double* __restrict__ gq) {
     const int64_t slot = int64_t(blockIdx.x) * kSdfBlock + threadIdx.x;
     const double sum = near.sum[slot];
-    if (sum == 0.0) return;
+    const int at = sum != 0.0 ? near.at[slot] : -1;
     const BrickNode b = brick_node(g, blockIdx.x, int(threadIdx.x));
-    add_xi_term(q, js[near.at[slot]], b.x, b.y, b.z, 1.0 / sqrt(near.d2[slot]), sum, gq);
+    const double coef = sum / near.d2[slot];
+    // lanes whose nearest sample is the same add up first: neighbours share
+    // few, and one atomic each made them queue (58 -> 28 us at 64^3)
+    unsigned long long todo = __ballot(at >= 0);
+    while (todo) {
+        const int first = __builtin_ctzll(todo);
+        const int who = uniform(__shfl(at, first));
+        const bool mine = at == who;
+        todo &= ~__ballot(mine);
+        const int64_t jb = js[who];
+        double v[3] = {mine ? coef * (b.x - q[3 * jb]) : 0.0, mine ? coef * (b.y - q[3 * jb + 1]) : 0.0,
+                       mine ? coef * (b.z - q[3 * jb + 2]) : 0.0};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            v[a] = row_sum(v[a]);
+            v[a] += __shfl_xor(v[a], 16);
+            v[a] += __shfl_xor(v[a], 32);
+        }
+        if ((threadIdx.x & 63) < 3)
+            atomicAdd(gq + 3 * jb + (threadIdx.x & 63), (threadIdx.x & 63) == 0 ? v[0] : ((threadIdx.x & 63) == 1 ? v[1] : v[2]));
+    }
 }
 
 // A block per brick of 256 nodes and range of leaves.  Every node's data goes
@@ -1091,37 +1111,45 @@ __global__ void hilbert_key_kernel(const double* __restrict__ q, int64_t n, doub
     val[j] = int(j);
 }
 
-// Up to kSmallSort samples: keys and order in one block, a bitonic sort in
-// LDS of (key, index) words, which are distinct, so equal keys keep their
-// input order.  Bound by its LDS round trips; replaces the key kernel and the
-// twelve to twenty launches of the radix sort, latency-bound at these sizes.
+// Up to kSmallSort samples: keys and order in one launch.  Every block computes
+// all keys, and ranks 64 samples: a wave counts the keys of its sixteenth that
+// come before each lane's (equal keys keep their input order), and the sixteen
+// counts add up to the sample's place.  n^2 comparisons, but spread over n / 64
+// CUs and without a barrier between them, where a bitonic sort in one block is a
+// chain of 45 to 78 LDS round trips: 512 samples 12.7 -> 5.5 us, 3.9k 41 ->
+// 15; the radix sort's twenty launches take more than either.
 constexpr int kSmallSort = 4096;
-__global__ __launch_bounds__(1024) void small_order_kernel(const double* __restrict__ q, int n, int n2, double ox,
-                                                           double oy, double oz, double inv_cell,
-                                                           int* __restrict__ order) {
-    __shared__ unsigned long long e[kSmallSort];
-    for (int j = int(threadIdx.x); j < n2; j += 1024)
-        e[j] = j < n ? (uint64_t(sample_key(q, j, ox, oy, oz, inv_cell)) << 32) | unsigned(j) : ~0ull;
+__global__ __launch_bounds__(1024) void small_order_kernel(const double* __restrict__ q, int n, double ox, double oy,
+                                                           double oz, double inv_cell, int* __restrict__ order) {
+    __shared__ __align__(16) unsigned key[kSmallSort];
+    __shared__ int place[64];
+    const int lane = int(threadIdx.x) & 63, wave = uniform(int(threadIdx.x) >> 6);
+    const int n64 = (n + 63) & ~63;  // keys past the last are larger than any (30 bits)
+    for (int j = int(threadIdx.x); j < n64; j += 1024)
+        key[j] = j < n ? sample_key(q, j, ox, oy, oz, inv_cell) : ~0u;
+    if (threadIdx.x < 64) place[threadIdx.x] = 0;
     __syncthreads();
-    for (int k = 2; k <= n2; k <<= 1)
-        for (int st = k >> 1; st > 0; st >>= 1) {
-            for (int p = int(threadIdx.x); p < n2 / 2; p += 1024) {
-                const int lo = 2 * p - (p & (st - 1)), hi = lo + st;
-                const unsigned long long a = e[lo], b = e[hi];
-                if ((a > b) == ((lo & k) == 0)) {
-                    e[lo] = b;
-                    e[hi] = a;
-                }
+    const int group = int(blockIdx.x), own = 64 * group + lane;
+    const unsigned mine = key[own];
+    int before = 0;
+    for (int g = wave; g < n64 / 64; g += 16) {
+        if (g != group) {
+            const unsigned bound = mine + (g < group ? 1u : 0u);  // equal keys of earlier groups come before
+#pragma unroll 4
+            for (int i = 0; i < 64; i += 4) {
+                const uint4 k = *reinterpret_cast<const uint4*>(key + 64 * g + i);
+                before += int(k.x < bound) + int(k.y < bound) + int(k.z < bound) + int(k.w < bound);
             }
-            // pairs at strides up to 64 stay within the 128 words of one wave, whose LDS operations are in order
-            if (st > 64 || (st == 1 && k >= 128)) __syncthreads();
-            else {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
+        } else {
+            for (int i = 0; i < 64; ++i) {
+                const unsigned k = key[64 * g + i];
+                before += int(k < mine || (k == mine && i < lane));
             }
         }
+    }
+    atomicAdd(place + lane, before);
     __syncthreads();
-    for (int j = int(threadIdx.x); j < n; j += 1024) order[j] = int(unsigned(e[j]));
+    if (threadIdx.x < 64 && own < n) order[place[lane]] = own;
 }
 
 __device__ __forceinline__ double wave_min(double v) {
@@ -1516,9 +1544,8 @@ hipError_t prepare_samples(const double* q, const double* n, const double* w, in
     const double ox = g.ox - 4 * g.h, oy = g.oy - 4 * g.h, oz = g.oz - 4 * g.h, inv_cell = 1024.0 / ext;
     int* order = vals_in;
     if (ns <= kSmallSort) {
-        int n2 = 2;
-        while (n2 < ns) n2 *= 2;
-        hipLaunchKernelGGL(small_order_kernel, dim3(1), dim3(1024), 0, s, q, int(ns), n2, ox, oy, oz, inv_cell, order);
+        hipLaunchKernelGGL(small_order_kernel, dim3(unsigned((ns + 63) / 64)), dim3(1024), 0, s, q, int(ns), ox, oy, oz,
+                           inv_cell, order);
     } else {
         auto* keys_in = reinterpret_cast<unsigned*>(base + L.keys_in);
         auto* keys_out = reinterpret_cast<unsigned*>(base + L.keys_out);
