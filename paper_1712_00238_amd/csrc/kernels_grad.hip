@@ -15,9 +15,9 @@
 // quaternion chain rule in FP64.  Per-sample weight gradients stay in
 // registers across the pose tile and are written once per tile.
 #include <algorithm>
-#include <numeric>
 #include <type_traits>
 
+#include "block_order.hpp"
 #include "common.hpp"
 #include "launch.hpp"
 #include "tile_spread.hpp"
@@ -742,7 +742,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
     __shared__ unsigned bad[S::X * S::Y * S::Z / 32];
     const int ntx = (N + S::X - 1) / S::X, nty = (N + S::Y - 1) / S::Y;
     const int range = int(blockIdx.x % unsigned(ranges));
-    const int tile = int(int64_t(blockIdx.x / unsigned(ranges)) * step % tiles);
+    const int tile = int(scattered_tile(int64_t(blockIdx.x / unsigned(ranges)), tiles, step));
     const int t0[3] = {(tile % ntx) * S::X, ((tile / ntx) % nty) * S::Y, PLANAR ? 0 : (tile / (ntx * nty)) * S::Z};
     const int dim[3] = {min(S::X, N - t0[0]), min(S::Y, N - t0[1]), PLANAR ? 1 : min(S::Z, N - t0[2])};
     const double cm = __longlong_as_double((long long)maxima[0]), sm = __longlong_as_double((long long)maxima[1]);
@@ -1085,12 +1085,6 @@ hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool
         hipLaunchKernelGGL(fixed_sum_kernel<T>, dim3(unsigned(std::min<int64_t>((2 * G + 255) / 256, 4096))), dim3(256),
                            0, s, reinterpret_cast<const T*>(part), int(ranges), 2 * G, static_cast<T*>(grad_f));
     return hipGetLastError();
-}
-
-int64_t tile_step(int64_t n) {
-    int64_t step = std::max<int64_t>(1, int64_t(0.6180339887498949 * double(n)));
-    while (std::gcd(step, n) != 1) ++step;
-    return step % std::max<int64_t>(n, 1);
 }
 
 hipError_t launch_pose_chain(const double* gp, const double* scale, int64_t B, double* out, hipStream_t s) {

@@ -50,6 +50,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "block_order.hpp"
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -836,17 +837,28 @@ __device__ __forceinline__ BrickNode brick_node(const GridDesc& g, int64_t blk, 
 // Pass 1 of the adjoint on its own: the nearest sample of every node in brick
 // order (squared distance, place in tree order or -1), one wave per 16 nodes,
 // and the nodes' xi sums cleared.
-__global__ __launch_bounds__(64) void adjoint_nearest_kernel(const double* __restrict__ qs,
-                                                             const int* __restrict__ js,
-                                                             const TreeNode* __restrict__ nodes, SampleTree tr,
-                                                             int64_t ns, GridDesc g, int64_t turn, NearData near) {
-    const int64_t grp = int64_t(blockIdx.x) * turn % gridDim.x;
-    const int lane = int(threadIdx.x);
+template <int WPB>
+__global__ __launch_bounds__(64 * WPB) void adjoint_nearest_kernel(const double* __restrict__ qs,
+                                                                   const int* __restrict__ js,
+                                                                   const TreeNode* __restrict__ nodes, SampleTree tr,
+                                                                   int64_t ns, GridDesc g, int64_t turn,
+                                                                   NearData near) {
+    __shared__ double sh_best[WPB == 4 ? 256 : 1];
+    __shared__ int sh_idx[WPB == 4 ? 256 : 1];
+    const int64_t grp = scattered_tile(blockIdx.x, gridDim.x, turn);
+    const int lane = int(threadIdx.x) & 63, sub = WPB == 1 ? 0 : uniform(int(threadIdx.x) >> 6);
     const BrickNode b = brick_node(g, grp >> 4, int(grp & 15) * 16 + (lane & 15));
     double best;
     int sbest;
-    wave_nearest<1>(qs, js, nodes, tr, ns, b.x, b.y, b.z, b.valid, 0, best, sbest, nullptr);
-    if (lane < 16) {
+    wave_nearest<WPB>(qs, js, nodes, tr, ns, b.x, b.y, b.z, b.valid, sub, best, sbest, nullptr);
+    if constexpr (WPB == 4) {
+        sh_best[threadIdx.x] = best;
+        sh_idx[threadIdx.x] = sbest;
+        __syncthreads();
+#pragma unroll
+        for (int wv = 0; wv < 4; ++wv) nearer(sh_best[64 * wv + lane], sh_idx[64 * wv + lane], js, best, sbest);
+    }
+    if (sub == 0 && lane < 16) {
         near.d2[16 * grp + lane] = best;
         near.at[16 * grp + lane] = sbest;
         near.sum[16 * grp + lane] = 0.0;
@@ -907,7 +919,8 @@ __global__ __launch_bounds__(kSdfBlock) void adjoint_xi_kernel(const double* __r
 // on small grids by how evenly the pairs fall: bricks at the surface hold many
 // times the mean.  There the leaves are split over more blocks than run at a
 // time, which needs pass 1 done once, by itself: 3.9k samples on 64^3 nodes
-// 2.2 ms with one block a brick, 1.85 so (the three kernels), 5.2 before all of this.
+// 2.2 ms with one block a brick, 1.85 in the bricks' order, 1.25 in a scattered one
+// (the three kernels), 5.2 before all of this.
 template <typename T, bool NEAR>
 __global__ __launch_bounds__(kSdfBlock) void sdf_adjoint_kernel(const double* __restrict__ q,
                                                                 const double* __restrict__ nrm,
@@ -926,7 +939,7 @@ __global__ __launch_bounds__(kSdfBlock) void sdf_adjoint_kernel(const double* __
     __shared__ int nnear[kSdfBlock];
     __shared__ double red[kSdfBlock / 64];
 
-    const int64_t blk = int64_t(blockIdx.x) * turn % gridDim.x;
+    const int64_t blk = scattered_tile(blockIdx.x, gridDim.x, turn);
     const int lane = int(threadIdx.x) & 63, wave = uniform(int(threadIdx.x) >> 6);
     const double sig2inv = 1.0 / (prm.sigma * prm.sigma);
 
@@ -1654,6 +1667,10 @@ namespace {
 // Leaf ranges per brick of the adjoint: about kAdjointBlocks blocks in all, at
 // least a leaf for each wave.  Larger grids have bricks enough to even out.
 constexpr int64_t kAdjointBlocks = 8192;
+// Groups of 16 nodes up to which four waves look for their nearest samples, as
+// the build's bricks (shape gradients: 630 / 670 us at 2048 groups, 1445 / 1455
+// at 6912, 1875 / 1855 at 15360, 2830 / 2805 at 16384).
+constexpr int64_t kShareNearest = 10000;
 struct AdjointSplit {
     int64_t bricks, splits;
 };
@@ -1728,8 +1745,12 @@ hipError_t launch_sdf_adjoint(const double* q, const double* n, const double* w,
     if (sp.splits > 1 && ws_bytes >= sdf_adjoint_bytes(ns, g)) {
         auto* d2 = reinterpret_cast<double*>(static_cast<char*>(ws) + sdf_ws_layout(ns).total);
         const NearData near{d2, d2 + slots, reinterpret_cast<int*>(d2 + 2 * slots)};
-        hipLaunchKernelGGL(adjoint_nearest_kernel, dim3(unsigned(16 * sp.bricks)), dim3(64), 0, s, P.st.qs, P.st.js,
-                           P.node, P.tr, ns, g, tile_step(16 * sp.bricks), near);
+        auto nearest = [&](auto kernel, int waves) {
+            hipLaunchKernelGGL(kernel, dim3(unsigned(16 * sp.bricks)), dim3(64 * waves), 0, s, P.st.qs, P.st.js, P.node,
+                               P.tr, ns, g, tile_step(16 * sp.bricks), near);
+        };
+        if (16 * sp.bricks <= kShareNearest) nearest(adjoint_nearest_kernel<4>, 4);
+        else nearest(adjoint_nearest_kernel<1>, 1);
         run(sdf_adjoint_kernel<T, true>, sp.splits, near);
         hipLaunchKernelGGL(adjoint_xi_kernel, dim3(unsigned(sp.bricks)), dim3(kSdfBlock), 0, s, q, P.st.js, g, near,
                            grad_q);

@@ -260,11 +260,4 @@ hipError_t launch_score_grad(const void* rho_f, int N, bool planar, const void* 
                              const double* poses, int64_t B, T* score, double* grad_pose, T* grad_w, T* grad_c,
                              const double* grad_scale, void* ws, size_t ws_bytes, hipStream_t s);
 
-// Step of a walk over n tiles (a bijection i -> i step mod n): near n over the
-// golden ratio, without a common divisor.  Consecutive blocks go to the XCDs
-// and their shader engines in turn, and neighbouring tiles have much the same
-// work; the walk gives each engine, and each stretch of the launch, tiles from
-// all over the grid.
-int64_t tile_step(int64_t n);
-
 }  // namespace sdf
