@@ -272,8 +272,8 @@ constexpr int kFusedBlock = 512;
 // XCDs and their shader engines in turn, and a row of 32 tiles gave each engine
 // the same y of every row and rotation, the body's middle to a few of them.
 // Rows and rotations start at other columns: with the fused x pass, 2N = 256,
-// 24 rotations of a 64^3 body's octree samples take 1430 us, 2450 before, when a
-// CU held a block two thirds of the time.
+// 24 rotations of 151k octree samples take 1430 us, 2450 before, when a CU held a
+// block two thirds of the time.
 __device__ __forceinline__ int turned_tile(int tile, int tbz, int rot, int nty) {
     return (tile + 5 * tbz + 11 * rot) % nty;
 }
@@ -335,13 +335,18 @@ __global__ __launch_bounds__(256) void nfft_bin_kernel(const T* __restrict__ pos
     const int lane = int(threadIdx.x & 63);
     const int rot = int(blockIdx.y);
     cplx<T> ck = mk(T(0), T(0));
-    if (k < m) ck = c[k];
+    T px = T(0), py = T(0), pz = T(0);
+    if (k < m) {  // issued together
+        ck = c[k];
+        px = pos[3 * k];
+        py = pos[3 * k + 1];
+        if (DIM == 3) pz = pos[3 * k + 2];
+    }
     const bool active = k < m && (ck.re != T(0) || ck.im != T(0));
     T v[3] = {T(0), T(0), T(0)};
-    int64_t bin = -1;
+    int bin = -1;  // within the rotation
     if (active) {
         const T* r = R + 9 * rot;
-        const T px = pos[3 * k], py = pos[3 * k + 1], pz = DIM == 3 ? pos[3 * k + 2] : T(0);
         const T fn = T(nf), half = T(0.5 * w);
         int b[3] = {0, 0, 0};
 #pragma unroll
@@ -351,28 +356,32 @@ __global__ __launch_bounds__(256) void nfft_bin_kernel(const T* __restrict__ pos
             const int l0 = first_node(v[a], half);  // in [-w/2, nf)
             b[a] = l0 < 0 ? l0 + nf : l0;
         }
-        const int nbins = ts.ntx * ts.nty * ts.ntz;
-        bin = int64_t(rot) * nbins + (b[2] / ts.tz * ts.nty + b[1] / ts.ty) * ts.ntx + b[0] / ts.tx;
+        bin = (b[2] / ts.tz * ts.nty + b[1] / ts.ty) * ts.ntx + b[0] / ts.tx;
     }
     // Samples are in Morton order, so a wave's lanes share few bins: each
     // group of lanes with one bin makes one atomic, issued by its lowest lane.
+    // The groups are found first, without memory, so that a wave waits for its
+    // atomics once (24 rotations of 151k octree samples, count and scatter:
+    // 118 + 155 us with a wait per group, 94 + 119 so).
     unsigned long long pending = __ballot(active);
-    int64_t slot = 0;
+    int leader = 0, rank = 0, cnt = 0;
     while (pending) {
-        const int leader = __ffsll((long long)pending) - 1;
-        const int64_t lbin = __shfl(bin, leader);
-        const unsigned long long grp = __ballot(active && bin == lbin);
-        const int cnt = __popcll(grp);
-        if (!SCATTER) {
-            if (lane == leader) atomicAdd(&counts[lbin], cnt);
-        } else {
-            int base = 0;
-            if (lane == leader) base = offsets[lbin] + atomicAdd(&cursor[lbin], cnt);
-            base = __shfl(base, leader);
-            if ((grp >> lane) & 1ull) slot = int64_t(base) + __popcll(grp & ((1ull << lane) - 1ull));
+        const int first = uniform(__ffsll((long long)pending) - 1);
+        const unsigned long long grp = __ballot(active && bin == __builtin_amdgcn_readlane(bin, first));
+        if ((grp >> lane) & 1ull) {
+            leader = first;
+            rank = __popcll(grp & ((1ull << lane) - 1ull));
+            cnt = __popcll(grp);
         }
         pending &= ~grp;
     }
+    int base = 0;
+    if (active && lane == leader) {
+        const int64_t at = int64_t(rot) * ts.ntx * ts.nty * ts.ntz + bin;
+        if (SCATTER) base = offsets[at] + atomicAdd(&cursor[at], cnt);
+        else atomicAdd(&counts[at], cnt);
+    }
+    const int64_t slot = int64_t(__shfl(base, leader)) + rank;
     if (SCATTER && active) {
         vbuf[4 * slot] = v[0];
         vbuf[4 * slot + 1] = v[1];
@@ -609,6 +618,76 @@ __global__ __launch_bounds__(256) void nfft_tile_kernel(const T* __restrict__ vb
 
 // j-th of the N kept modes (FFT order) on the 2N grid
 __device__ __forceinline__ int fine_mode(int j, int N) { return j < N / 2 ? j : j + N; }
+
+// FFT of LINES lines of NF points by BS threads, line l's element e at
+// buf[l NF + e]: the passes of lds_fft_lines (the same butterflies on the same
+// values), but the first takes its points from load(line, e), which may read
+// what buf overlays, and the last gives its outputs to store(line, j, r, value),
+// so that the values cross LDS once less at either end and outputs that store
+// drops are never computed.  A thread takes all its lines in one round, so a
+// pass has two barriers however many lines there are.
+template <int NF, int LINES, int BS, int STRIDE, typename T, typename L, typename S, int R, int... Rest>
+__device__ __forceinline__ void fft_through(cplx<T>* __restrict__ buf, const cplx<T>* __restrict__ tw, L&& load,
+                                            S&& store, Radices<R, Rest...>) {
+    constexpr int TPL = FFTShape<NF>::TPL, CONC = BS / TPL, LP = (LINES + CONC - 1) / CONC;
+    constexpr int NB = NF / R, PER = (NB + TPL - 1) / TPL;
+    constexpr bool FIRST = STRIDE == 1, LAST = sizeof...(Rest) == 0;
+    const int ll = int(threadIdx.x) / TPL, t = int(threadIdx.x) % TPL;
+    const bool on = ll < CONC;
+    cplx<T> v[LP][PER][R];
+#pragma unroll
+    for (int p = 0; p < LP; ++p)
+#pragma unroll
+        for (int b = 0; b < PER; ++b) {
+            const int line = ll + p * CONC, j = t + b * TPL;
+            if (on && (LP * CONC == LINES || line < LINES) && (PER * TPL == NB || j < NB)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if constexpr (FIRST) v[p][b][r] = load(line, j + r * NB);
+                    else v[p][b][r] = buf[line * NF + j + r * NB];
+                }
+            }
+        }
+    if constexpr (!LAST) __syncthreads();
+#pragma unroll
+    for (int p = 0; p < LP; ++p)
+#pragma unroll
+        for (int b = 0; b < PER; ++b) {
+            const int line = ll + p * CONC, j = t + b * TPL;
+            if (on && (LP * CONC == LINES || line < LINES) && (PER * TPL == NB || j < NB)) {
+                const int k = STRIDE == 1 ? 0 : j % STRIDE;
+                if constexpr (STRIDE > 1) {
+#pragma unroll
+                    for (int r = 1; r < R; ++r) v[p][b][r] = v[p][b][r] * tw[r * k * (NF / (STRIDE * R))];
+                }
+                dftR<T, -1, R>(v[p][b]);
+                const int o = (j - k) * R + k;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if constexpr (LAST) store(line, j, r, v[p][b][r]);
+                    else buf[line * NF + o + r * STRIDE] = v[p][b][r];
+                }
+            }
+        }
+    if constexpr (!LAST) {
+        __syncthreads();
+        fft_through<NF, LINES, BS, STRIDE * R>(buf, tw, load, store, Radices<Rest...>{});
+    }
+}
+
+template <int... R>
+constexpr int last_radix(Radices<R...>) {
+    constexpr int r[] = {R...};
+    return r[sizeof...(R) - 1];
+}
+
+// kept mode (its place among the N) of the last pass's output j + r NF / R, or
+// -1; r is a constant where the pass is unrolled, so whole outputs drop out
+template <int NF, int R>
+__device__ __forceinline__ int kept_mode(int j, int r) {
+    const int k = j + r * (NF / R), N = NF / 2;
+    return k < N / 2 ? k : (k >= NF - N / 2 ? k - N : -1);
+}
 
 template <typename T, int NF>
 __global__ __launch_bounds__(256) void nfft_rows_pruned_kernel(const cplx<T>* __restrict__ in,
@@ -897,6 +976,9 @@ void launch_line_tile(const float* vbuf, const cplx<float>* cbuf, const int* cou
 // in the same LDS, transformed there (2N points), and only the N kept modes
 // of each line are stored, into the x-pruned buffer [b][z][y][N] that the y
 // pass reads.  The oversampled grid itself is never written to memory.
+// Bound by VALU issue, half of it the transform (2N = 256, 24 rotations of 151k
+// samples: 1430 us with the values converted into LDS, transformed there and
+// copied out, 1320 with the first pass converting and the last one storing).
 constexpr int kFusedRows = kLineRows * kFusedRowsZ;
 constexpr int kFusedLds = kFusedRows * (256 + 11);  // ints per plane at nf = 256
 
@@ -908,7 +990,6 @@ __global__ __launch_bounds__(kFusedBlock) void nfft_line_fft_kernel(const float*
                                                                     cplx<float>* __restrict__ half_buf) {
     constexpr int nf = NF, N = NF / 2, msk = NF - 1, RY = kLineRows, RZ = kFusedRowsZ, ROWS = kFusedRows;
     constexpr int BS = kFusedBlock;
-    constexpr int PER = ROWS * NF / BS;  // converted values per thread
     constexpr int NBZ = 1 + (W - 1 + RZ - 1) / RZ, NB = 2 * NBZ;
     static_assert(ROWS * NF * sizeof(cplx<float>) <= 2 * kFusedLds * sizeof(int), "complex rows exceed the LDS");
     __shared__ __align__(16) int acc[2 * kFusedLds];
@@ -1142,30 +1223,28 @@ __global__ __launch_bounds__(kFusedBlock) void nfft_line_fft_kernel(const float*
         spread(vbuf[4 * at], vbuf[4 * at + 1], vbuf[4 * at + 2], cbuf[at]);
     }
     __syncthreads();
-    // integer rows (with their wrap slots folded) -> complex lines in the same LDS
+    // integer rows (with their wrap slots folded) -> complex lines in the same
+    // LDS -> kept modes
     const float inv = S / float(TileAcc<float>::kOne);
-    cplx<float> val[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = int(threadIdx.x) + k * BS;
-        const int x = e % NF, row = e / NF;
-        int ar = lre[row * px + x], ai = lim[row * px + x];
-        if (x < 8) {
-            ar += lre[row * px + nf + x];
-            ai += lim[row * px + nf + x];
-        }
-        val[k] = mk(float(ar) * inv, float(ai) * inv);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PER; ++k) cb[int(threadIdx.x) + k * BS] = val[k];
-    __syncthreads();
-    lds_fft_lines<float, NF, -1, false>(cb, 1, NF, ROWS, tw);
-    __syncthreads();
-    for (int e = int(threadIdx.x); e < ROWS * N; e += BS) {
-        const int r = e / N, j = e % N;
-        hrow(r)[j] = cb[r * NF + fine_mode(j, N)];
-    }
+    using Plan = typename DefaultPlan<NF>::type;
+    fft_through<NF, ROWS, BS, 1>(
+        cb, tw,
+        [=](int row, int x) __attribute__((always_inline)) {
+            int ar = lre[row * px + x], ai = lim[row * px + x];
+            if (x < 8) {
+                ar += lre[row * px + nf + x];
+                ai += lim[row * px + nf + x];
+            }
+            // rounded before the butterflies, as through LDS: not fused into their sums
+            float re = float(ar) * inv, im = float(ai) * inv;
+            asm("" : "+v"(re), "+v"(im));
+            return mk(re, im);
+        },
+        [=](int row, int j, int r, cplx<float> v) __attribute__((always_inline)) {
+            const int m = kept_mode<NF, last_radix(Plan{})>(j, r);
+            if (m >= 0) hrow(row)[m] = v;
+        },
+        Plan{});
 }
 
 template <int NF>
