@@ -1461,6 +1461,10 @@ __global__ __launch_bounds__(slab_block(N)) void islab_peak_kernel(const cf* __r
 //   h_j(ky)  = sum_kx P(kx, ky) e^{2 pi i kx x_j / N},  x_j in t_x + {-1, 0, 1}
 //   g(x_j, y_i) = sum_ky h_j(ky) e^{2 pi i ky y_i / N}
 // Re g belongs to the even rotation of the pair, Im g to the odd one.
+// Bound by the latency of a dozen dependent steps: with two threads a row at
+// N = 64 (half the block idle), the twiddles before the partials' loads and
+// eight barriers in the argmax 9 rotations of 64^3 took 10.6 us, 9.3 so (192 of
+// 128^3: 31 either way).
 template <int N>
 __global__ __launch_bounds__(kFinishBlock) void finish_slab_kernel(const cf* __restrict__ packed, int nz,
                                                                    const float* __restrict__ pval,
@@ -1468,19 +1472,14 @@ __global__ __launch_bounds__(kFinishBlock) void finish_slab_kernel(const cf* __r
                                                                    double* __restrict__ nbbuf,
                                                                    const FusedRot* __restrict__ rots,
                                                                    const FusedJob* __restrict__ jobs) {
-    __shared__ float sv[kFinishBlock];
-    __shared__ int si[kFinishBlock];
+    constexpr int SPLIT = N == 64 ? 4 : 2;  // threads per row ky
+    __shared__ float sv[kFinishBlock / 64];
+    __shared__ int si[kFinishBlock / 64];
     __shared__ double twr[N], twi[N];
-    __shared__ double hre[N][2][3], him[N][2][3];
+    __shared__ double hre[N][SPLIT][3], him[N][SPLIT][3];
     __shared__ double red[kFinishBlock / 64][9];
     const int rot = blockIdx.y;
     const int dzi = gridDim.x == 1 ? 1 : blockIdx.x;
-    for (int m = threadIdx.x; m < N; m += kFinishBlock) {
-        double sn, cs;
-        sincospi(2.0 * double(m) / double(N), &sn, &cs);
-        twr[m] = cs;
-        twi[m] = sn;
-    }
     float bv = -INFINITY;
     int bi = 0x7fffffff;
     constexpr int NW = islab_waves(N);
@@ -1503,39 +1502,44 @@ __global__ __launch_bounds__(kFinishBlock) void finish_slab_kernel(const cf* __r
                 ii[p] = pi[i];
             }
         }
+        for (int m = threadIdx.x; m < N; m += kFinishBlock) {
+            double sn, cs;
+            sincospi(2.0 * double(m) / double(N), &sn, &cs);
+            twr[m] = cs;
+            twi[m] = sn;
+        }
 #pragma unroll
         for (int p = 0; p < PB; ++p)
             if (better(vv[p], ii[p], bv, bi)) { bv = vv[p]; bi = ii[p]; }
     }
-    sv[threadIdx.x] = bv;
-    si[threadIdx.x] = bi;
-    __syncthreads();
-    for (int off = kFinishBlock / 2; off > 0; off >>= 1) {
-        if (int(threadIdx.x) < off && better(sv[threadIdx.x + off], si[threadIdx.x + off], sv[threadIdx.x], si[threadIdx.x])) {
-            sv[threadIdx.x] = sv[threadIdx.x + off];
-            si[threadIdx.x] = si[threadIdx.x + off];
-        }
-        __syncthreads();
+    const int lane = threadIdx.x % warpSize, wid = threadIdx.x / warpSize;
+    wave_argmax(bv, bi);
+    if (lane == 0) {
+        sv[wid] = bv;
+        si[wid] = bi;
     }
+    __syncthreads();
     bv = sv[0];
     bi = si[0];
+    for (int w = 1; w < kFinishBlock / 64; ++w)
+        if (better(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
     const int tx = bi % N, ty = (bi / N) % N, tz = bi / (N * N);
     const int zz = wrap(tz + dzi - 1, nz);
     const cf* sl = packed + (int64_t(rot / 2) * nz + zz) * N * N;
     const bool imag = rot & 1;
     const int xs[3] = {(tx + N - 1) % N, tx, (tx + 1) % N};
     const int ys[3] = {(ty + N - 1) % N, ty, (ty + 1) % N};
-    // inner sums along x: two threads per row ky, each half of the row's
+    // inner sums along x: SPLIT threads per row ky, each its share of the row's
     // stored positions
     const bool grouped = nz == N && (N == 64 || N == 128);
     // (the loads of HB positions are issued together: one at a time, each
     // waited on before the next, the loop ran at cache latency)
-    constexpr int HB = N / 2 >= 16 ? 16 : N / 2;
-    static_assert((N / 2) % HB == 0, "whole batches of positions");
-    for (int w = threadIdx.x; w < 2 * N; w += kFinishBlock) {
-        const int ky = w >> 1, half = w & 1;
+    constexpr int HP = N / SPLIT, HB = HP >= 16 ? 16 : HP;
+    static_assert(HP % HB == 0, "whole batches of positions");
+    for (int w = threadIdx.x; w < SPLIT * N; w += kFinishBlock) {
+        const int ky = w / SPLIT, share = w % SPLIT;
         double ar[3] = {0, 0, 0}, ai[3] = {0, 0, 0};
-        for (int p0 = half * (N / 2); p0 < (half + 1) * (N / 2); p0 += HB) {
+        for (int p0 = share * HP; p0 < (share + 1) * HP; p0 += HB) {
             cf vb[HB];
 #pragma unroll
             for (int q = 0; q < HB; ++q) vb[q] = sl[ky * N + p0 + q];
@@ -1554,8 +1558,8 @@ __global__ __launch_bounds__(kFinishBlock) void finish_slab_kernel(const cf* __r
         }
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            hre[ky][half][j] = ar[j];
-            him[ky][half][j] = ai[j];
+            hre[ky][share][j] = ar[j];
+            him[ky][share][j] = ai[j];
         }
     }
     __syncthreads();
@@ -1565,8 +1569,12 @@ __global__ __launch_bounds__(kFinishBlock) void finish_slab_kernel(const cf* __r
     for (int ky = threadIdx.x; ky < N; ky += kFinishBlock) {
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const double hr = hre[ky][0][j] + hre[ky][1][j];
-            const double hi = him[ky][0][j] + him[ky][1][j];
+            double hr = hre[ky][0][j], hi = him[ky][0][j];
+#pragma unroll
+            for (int p = 1; p < SPLIT; ++p) {
+                hr += hre[ky][p][j];
+                hi += him[ky][p][j];
+            }
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 const int m = (ky * ys[i]) % N;
@@ -1574,7 +1582,6 @@ __global__ __launch_bounds__(kFinishBlock) void finish_slab_kernel(const cf* __r
             }
         }
     }
-    const int lane = threadIdx.x % warpSize, wid = threadIdx.x / warpSize;
 #pragma unroll
     for (int a = 0; a < 9; ++a) {
         double v = part[a];
