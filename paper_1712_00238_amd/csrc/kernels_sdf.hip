@@ -118,7 +118,7 @@ struct TreeNode {
     double lo[3], hi[3];  // box of the node's samples (infinite if one is not finite)
     double c[3];          // grid-lattice point nearest the box centre: origin of the node's FP32 records
     float reach2;         // square of the distance and xi from which its interpolation points stand in; < 0: none
-    float qmax2;          // leaves: largest squared sample distance from c
+    float qmax2;          // leaves: largest squared sample distance from c; infinite where a sample is not finite
     int px;               // first 16-point record group of the interpolation points
     int order;            // their orders per axis, 4 bits each
 };
@@ -1229,7 +1229,8 @@ __global__ __launch_bounds__(kSdfBlock) void leaf_kernel(const double* __restric
         const double mid = 0.5 * (lo + hi);
         const double o = a == 0 ? g.ox : (a == 1 ? g.oy : g.oz);
         c[a] = fabs(mid) < INFINITY ? lattice(mid, o, g.h) : 0.0;
-        // a sample that is not finite never counts: the leaf is then always visited and tested pair by pair
+        // a sample that is not finite never counts: the leaf is then always visited, and its infinite qmax2
+        // has it tested pair by pair
         t.lo[a] = all ? lo : -INFINITY;
         t.hi[a] = all ? hi : INFINITY;
         t.c[a] = c[a];
@@ -1240,7 +1241,7 @@ __global__ __launch_bounds__(kSdfBlock) void leaf_kernel(const double* __restric
     const double m2 = wave_max(finite ? double(x) * x + double(y) * y + double(z) * z : 0.0);
     if (lane == 0) {
         t.reach2 = -1.f;
-        t.qmax2 = float(m2 * 1.0001);
+        t.qmax2 = all ? float(m2 * 1.0001) : INFINITY;
         t.px = 0;
         t.order = 0x111;
         node[leaf] = t;

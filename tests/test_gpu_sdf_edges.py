@@ -1,0 +1,69 @@
+"""sdf_build at the edges of its inputs: samples that are not finite."""
+
+import numpy as np
+import pytest
+
+from helpers import flush_print
+from workloads import configs as C
+from workloads import shapes
+
+pytestmark = pytest.mark.gpu
+
+PARAMS = C.SDFParams(xi_floor=0.25)
+GRID = C.GridSpec((14, 13, 12), (-6.5, -6.0, -5.5), 1.0)
+
+
+@pytest.fixture(scope="module")
+def ctxs():
+    from paper_1712_00238_amd.api import Context
+    c32, c64 = Context(0, "f32"), Context(0, "f64")
+    yield {"f32": c32, "f64": c64}
+    c32.close()
+    c64.close()
+
+
+def sphere(count, radius=4.0, seed=2):
+    v = np.random.default_rng(seed).normal(size=(count, 3))
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    return shapes.PointSamples(radius * v + 0.3, v.copy(), np.full(count, 4 * np.pi * radius ** 2 / count))
+
+
+def join(s, q, n=(1.0, 0.0, 0.0), w=1.0):
+    q = np.asarray(q, dtype=np.float64).reshape(-1, 3)
+    return shapes.PointSamples(np.concatenate([s.q, q]), np.concatenate([s.n, np.tile(n, (len(q), 1))]),
+                               np.concatenate([s.w, np.full(len(q), w)]))
+
+
+def build(ctx, s, grid=GRID, params=PARAMS, phi=None):
+    return ctx.sdf_build(s.q, s.n, s.w, grid, params, phi=phi).cpu().numpy().reshape(-1)
+
+
+INF, NAN = np.inf, np.nan
+# samples that fill a leaf of their own: NaN points share the first place
+# of the order and (+inf, NaN, NaN) has the last: 64 and more of the first, and
+# one of the last where it falls alone into the last leaf
+ALL_BAD = [(640, [[NAN, NAN, NAN]] * 64), (576, [[INF, NAN, NAN]]), (700, [[NAN, NAN, NAN]] * 200),
+           (64, [[INF, NAN, NAN]] * 3)]
+
+
+@pytest.mark.parametrize("phi", [None, "inverse_square"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("count,bad", ALL_BAD)
+def test_leaf_without_a_finite_sample_counts_nowhere(ctxs, dtype, phi, count, bad):
+    """The sums are those without the bad samples, in another order."""
+    s = sphere(count)
+    flush_print("bad leaf", dtype, phi, count, len(bad))
+    a, b = build(ctxs[dtype], s, phi=phi), build(ctxs[dtype], join(s, bad), phi=phi)
+    tol = 1e-12 if dtype == "f64" else 1e-5
+    assert np.max(np.abs(a - b)) <= tol * np.abs(a).max()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_leaf_of_a_node_and_samples_that_are_not_finite(ctxs, dtype):
+    """63 NaN samples and one finite sample, four cells below the grid's corner and
+    so of the lowest key, fill the first leaf, whose centre it is."""
+    s = join(sphere(640), [[x - 4.0 * GRID.h for x in GRID.origin]], n=(-1.0, 0.0, 0.0), w=0.5)
+    flush_print("node and NaNs", dtype)
+    a, b = build(ctxs[dtype], s), build(ctxs[dtype], join(s, [[NAN, NAN, NAN]] * 63))
+    tol = 1e-12 if dtype == "f64" else 1e-5
+    assert np.max(np.abs(a - b)) <= tol * np.abs(a).max()
