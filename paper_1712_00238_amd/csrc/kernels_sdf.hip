@@ -118,7 +118,8 @@ struct TreeNode {
     double lo[3], hi[3];  // box of the node's samples (infinite if one is not finite)
     double c[3];          // grid-lattice point nearest the box centre: origin of the node's FP32 records
     float reach2;         // square of the distance and xi from which its interpolation points stand in; < 0: none
-    float qmax2;          // leaves: largest squared sample distance from c; infinite where a sample is not finite
+    float qmax2;          // leaves: largest squared sample distance from c; infinite for a node with a sample whose
+                          // position is not finite or whose record is not plain
     int px;               // first 16-point record group of the interpolation points
     int order;            // their orders per axis, 4 bits each
 };
@@ -1179,18 +1180,26 @@ __device__ __forceinline__ double wave_max(double v) {
 __device__ __forceinline__ double lattice(double v, double o, double h) { return o + h * rint((v - o) / h); }
 
 // MFMA records of a point: rec1 = (-2 q, |q|^2), rec2 = (w, -q.w), stored per
-// 16 points component by component, so a wave's operand is one 256-byte load
-__device__ __forceinline__ void put_record(float* __restrict__ rec1, float* __restrict__ rec2, int64_t at, float x,
+// 16 points component by component, so a wave's operand is one 256-byte load.
+// A node that is not concerned multiplies them by zero, so records of matrix
+// items have to be finite (true: all values are, with room for the sums of 2^30
+// samples in the interpolation points).
+constexpr float kRecordMax = 1e18f;
+__device__ __forceinline__ bool put_record(float* __restrict__ rec1, float* __restrict__ rec2, int64_t at, float x,
                                            float y, float z, float wx, float wy, float wz) {
     const int64_t o = (at >> 4) * 64 + (at & 15);
     rec1[o] = -2.f * x;
     rec1[o + 16] = -2.f * y;
     rec1[o + 32] = -2.f * z;
-    rec1[o + 48] = float(double(x) * x + double(y) * y + double(z) * z);
+    const float q2 = float(double(x) * x + double(y) * y + double(z) * z);
+    const float qw = -float(double(x) * wx + double(y) * wy + double(z) * wz);
+    rec1[o + 48] = q2;
     rec2[o] = wx;
     rec2[o + 16] = wy;
     rec2[o + 32] = wz;
-    rec2[o + 48] = -float(double(x) * wx + double(y) * wy + double(z) * wz);
+    rec2[o + 48] = qw;
+    // (a comparison with NaN is false)
+    return q2 <= kRecordMax && fabsf(wx) + fabsf(wy) + fabsf(wz) + fabsf(qw) <= kRecordMax;
 }
 
 // One wave per leaf: samples gathered in Hilbert order, the leaf's box, and
@@ -1230,18 +1239,19 @@ __global__ __launch_bounds__(kSdfBlock) void leaf_kernel(const double* __restric
         const double o = a == 0 ? g.ox : (a == 1 ? g.oy : g.oz);
         c[a] = fabs(mid) < INFINITY ? lattice(mid, o, g.h) : 0.0;
         // a sample that is not finite never counts: the leaf is then always visited, and its infinite qmax2
-        // has it tested pair by pair
+        // has it tested pair by pair (below)
         t.lo[a] = all ? lo : -INFINITY;
         t.hi[a] = all ? hi : INFINITY;
         t.c[a] = c[a];
     }
     const float x = float(p[0] - c[0]), y = float(p[1] - c[1]), z = float(p[2] - c[2]);
+    bool plain = all;
     if constexpr (FAST)
-        put_record(rec1, rec2, ix, x, y, z, float(v[0]), float(v[1]), float(v[2]));
+        plain &= __ballot(!put_record(rec1, rec2, ix, x, y, z, float(v[0]), float(v[1]), float(v[2]))) == 0;
     const double m2 = wave_max(finite ? double(x) * x + double(y) * y + double(z) * z : 0.0);
     if (lane == 0) {
         t.reach2 = -1.f;
-        t.qmax2 = all ? float(m2 * 1.0001) : INFINITY;
+        t.qmax2 = plain ? float(m2 * 1.0001) : INFINITY;
         t.px = 0;
         t.order = 0x111;
         node[leaf] = t;
@@ -1306,7 +1316,10 @@ __global__ __launch_bounds__(kSdfBlock) void tree_up_kernel(TreeNode* __restrict
             const bool own = i < tr.cnt[l];
             TreeNode t;
             double half[3], hmax = 0.0;
-            bool ok = own;
+            t.qmax2 = 0.f;
+            for (int c = kFan * i; c < kFan * (i + 1) && c < tr.cnt[l - 1]; ++c)
+                if (node[tr.off[l - 1] + c].qmax2 == INFINITY) t.qmax2 = INFINITY;
+            bool ok = own && t.qmax2 == 0.f;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 double lo = INFINITY, hi = -INFINITY;
@@ -1320,11 +1333,10 @@ __global__ __launch_bounds__(kSdfBlock) void tree_up_kernel(TreeNode* __restrict
                 const double o = a == 0 ? g.ox : (a == 1 ? g.oy : g.oz);
                 t.c[a] = fabs(mid) < INFINITY ? lattice(mid, o, g.h) : 0.0;
                 half[a] = 0.5 * (hi - lo);
-                ok &= half[a] < INFINITY;
+                ok &= half[a] * half[a] < double(kRecordMax) / 4.0;  // the points' records are plain too
                 hmax = fmax(hmax, half[a]);
             }
             t.reach2 = -1.f;
-            t.qmax2 = 0.f;
             t.px = 0;
             t.order = 0x111;
             int pick = 0;

@@ -1,7 +1,8 @@
-"""sdf_build at the edges of its inputs: samples that are not finite."""
+"""sdf_build at the edges of its inputs: samples and weights that are not finite."""
 
 import numpy as np
 import pytest
+from scipy.spatial import cKDTree
 
 from helpers import flush_print
 from workloads import configs as C
@@ -67,3 +68,35 @@ def test_leaf_of_a_node_and_samples_that_are_not_finite(ctxs, dtype):
     a, b = build(ctxs[dtype], s), build(ctxs[dtype], join(s, [[NAN, NAN, NAN]] * 63))
     tol = 1e-12 if dtype == "f64" else 1e-5
     assert np.max(np.abs(a - b)) <= tol * np.abs(a).max()
+
+
+def ball_edges(s, grid, j):
+    """For every node: is sample j inside its ball, and the ball's relative margin."""
+    pts = grid.node_positions()
+    xi = cKDTree(s.q).query(pts)[0]
+    return np.linalg.norm(pts - s.q[j], axis=1) / ((1 + PARAMS.eps) * xi) - 1.0
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("bad", [NAN, INF, 1e300])
+@pytest.mark.parametrize("count,grid", [(640, GRID), (30000, C.GridSpec((18, 17, 16), (-8.5, -8.0, -7.5), 1.0))])
+def test_weight_that_is_not_finite_reaches_its_own_nodes_only(ctxs, dtype, bad, count, grid):
+    """Nodes with the sample outside their ball have the sums of the part without
+    it, those with it inside are not finite (1e300 is infinite in 32 bits).  30000
+    samples on 4900 nodes are enough pairs for interpolated clusters."""
+    s = sphere(count)
+    j = count // 3
+    w = s.w.copy()
+    w[j] = 0.0
+    ref = build(ctxs[dtype], shapes.PointSamples(s.q, s.n, w), grid)
+    w[j] = bad
+    flush_print("bad weight", dtype, bad, count)
+    got = build(ctxs[dtype], shapes.PointSamples(s.q, s.n, w), grid)
+    margin = ball_edges(s, grid, j)
+    out, inside = margin > 1e-9, margin < -1e-9
+    assert out.sum() > 100 and inside.sum() > 100
+    tol = 1e-12 if dtype == "f64" else 1e-5
+    assert np.max(np.abs(got - ref)[out]) <= tol * np.abs(ref).max()
+    if dtype == "f32" or not np.isfinite(bad):
+        live = inside & (ref != 0)
+        assert not np.isfinite(got[live]).any()
