@@ -676,7 +676,7 @@ __global__ void rho_from_c_kernel(const T* __restrict__ w_m, const T* __restrict
 __global__ void fixed_pose_kernel(const double* __restrict__ poses, int64_t B, double* __restrict__ out,
                                   unsigned long long* __restrict__ maxima) {
     const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b < 2) maxima[b] = 0;
+    if (b < 3) maxima[b] = 0;
     if (b >= B) return;
     double r[9];
     quat_rot(poses + 7 * b + 3, r);
@@ -685,7 +685,7 @@ __global__ void fixed_pose_kernel(const double* __restrict__ poses, int64_t B, d
 }
 
 // maxima[0] = largest finite |Re c_k| or |Im c_k|, maxima[1] = largest finite |s_b|, as the bits of
-// non-negative doubles (which order like integers)
+// non-negative doubles (which order like integers); maxima[2] = 1 if some rho_M or w_M is not finite
 template <typename T>
 __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restrict__ rho_m, const T* __restrict__ w_m,
                                                         int64_t K, const double* __restrict__ gscale, int64_t B,
@@ -693,8 +693,12 @@ __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restric
     __shared__ unsigned long long sh[2][4];
     const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, step = int64_t(gridDim.x) * 256;
     double m[2] = {0.0, 0.0};
+    bool odd = false;
     for (int64_t k = i0; k < K; k += step) {
-        const cplx<T> c = rho_m[k] * w_m[k];
+        const cplx<T> r = rho_m[k];
+        const T w = w_m[k];
+        odd |= !((r.re - r.re) + (r.im - r.im) + (w - w) == T(0));
+        const cplx<T> c = r * w;
         const double a = fabs(double(c.re)), b = fabs(double(c.im));
         if (a < INFINITY) m[0] = fmax(m[0], a);
         if (b < INFINITY) m[0] = fmax(m[0], b);
@@ -708,7 +712,7 @@ __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restric
         for (int off = 32; off > 0; off >>= 1) m[q] = fmax(m[q], __shfl_xor(m[q], off));
         if ((threadIdx.x & 63) == 0) sh[q][threadIdx.x >> 6] = __double_as_longlong(m[q]);
     }
-    __syncthreads();
+    if (__syncthreads_or(odd) && threadIdx.x == 0) atomicMax(maxima + 2, 1ull);
     if (threadIdx.x < 2) {
         const unsigned long long* v = sh[threadIdx.x];
         atomicMax(maxima + threadIdx.x, max(max(v[0], v[1]), max(v[2], v[3])));
@@ -724,7 +728,7 @@ __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restric
 // Sums are 64-bit integers, so runs repeat bit for bit.  FP32 terms are rounded
 // to 2^-30 of the largest c_k s_b, FP64 ones to at most 2^-55 of it with the
 // sums moved to FP64 registers every kFixedFlush poses.  A term that is not
-// finite, and a pose that is not, leaves NaN at the nodes it reaches.
+// finite, and one of a pose that is not, leaves NaN at the nodes it reaches.
 constexpr int kFixedFlush = 16;
 template <typename T, bool PLANAR>
 __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* __restrict__ rho_m,
@@ -802,8 +806,33 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                 yhi[a] += fmaxf(-h * rf[3 * a + q], e * rf[3 * a + q]);
             }
         }
-        if (!finite) {  // uniform
-            for (int i = int(threadIdx.x); i < S::X * S::Y * S::Z / 32; i += kTileBlock) atomicOr(bad + i, ~0u);
+        if (!finite) {  // uniform: every weight of a sample's stencil is NaN, and the stencil lies where the
+                        // conversions put it; a sample without a term (a pose of scale zero) reaches nothing
+            const int64_t K = sb == T(0) && !maxima[2] ? 0 : int64_t(n_m) * n_m * (PLANAR ? 1 : n_m);
+            for (int64_t kk = int64_t(threadIdx.x); kk < K; kk += kTileBlock) {
+                const cplx<T> ck = rho_m[kk] * (w_m[kk] * sb);
+                if (ck.re == T(0) && ck.im == T(0)) continue;
+                const int64_t row = kk / n_m;
+                const T xb[3] = {T(int(kk - row * n_m)) - half_box, T(int(row % n_m)) - half_box,
+                                 PLANAR ? T(0) : T(int(row / n_m)) - half_box};
+                unsigned first[3] = {0, 0, 0};  // sums of large conversions wrap
+#pragma unroll
+                for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
+                    const double ti = floor(pose[a]);
+                    const T y = T(pose[a] - ti) + r[3 * a] * xb[0] + r[3 * a + 1] * xb[1] + r[3 * a + 2] * xb[2];
+                    first[a] = unsigned(int(dev_floor(y))) + unsigned(int(ti)) - 1u;
+                }
+                for (int tap = 0; tap < (PLANAR ? 16 : 64); ++tap) {
+                    const int ix = wrap(int(first[0] + (tap & 3)), N) - t0[0],
+                              iy = wrap(int(first[1] + ((tap >> 2) & 3)), N) - t0[1],
+                              iz = PLANAR ? 0 : wrap(int(first[2] + (tap >> 4)), N) - t0[2];
+                    if (unsigned(ix) >= unsigned(dim[0]) || unsigned(iy) >= unsigned(dim[1]) ||
+                        unsigned(iz) >= unsigned(dim[2]))
+                        continue;
+                    const int nd = (iz * S::Y + iy) * S::X + ix;
+                    atomicOr(bad + nd / 32, 1u << (nd % 32));
+                }
+            }
             continue;
         }
         int m0[3] = {0, 0, 0}, m1[3] = {0, 0, 0};
@@ -905,8 +934,9 @@ int64_t fixed_tiles(int N, bool planar) {
                   : up(SpreadTile<false>::X) * up(SpreadTile<false>::Y) * up(SpreadTile<false>::Z);
 }
 
-// R of every pose, then the two maxima in the last 16 bytes
-size_t fixed_table_bytes(int64_t B) { return (sizeof(double) * 9 * size_t(B) + 15) / 16 * 16 + 16; }
+// R of every pose, then the maxima in the last 32 bytes
+constexpr size_t kFixedTail = 32;
+size_t fixed_table_bytes(int64_t B) { return (sizeof(double) * 9 * size_t(B) + 15) / 16 * 16 + kFixedTail; }
 
 }  // namespace
 
@@ -1056,7 +1086,7 @@ hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool
     const int64_t K = planar ? int64_t(n_m) * n_m : int64_t(n_m) * n_m * n_m;
     const int64_t G = planar ? int64_t(N) * N : int64_t(N) * N * N;
     double* rot = static_cast<double*>(ws);
-    auto* maxima = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + fixed_table_bytes(B) - 16);
+    auto* maxima = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + fixed_table_bytes(B) - kFixedTail);
     auto* part = reinterpret_cast<cplx<T>*>(static_cast<char*>(ws) + fixed_table_bytes(B));
     const auto* rm = static_cast<const cplx<T>*>(rho_m);
     hipLaunchKernelGGL(fixed_pose_kernel, dim3(unsigned((B + 127) / 128)), dim3(128), 0, s, poses, B, rot, maxima);

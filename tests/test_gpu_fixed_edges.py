@@ -1,0 +1,99 @@
+"""score_grad_fixed at the edges of its inputs: poses that are not finite."""
+
+import numpy as np
+import pytest
+
+from helpers import flush_print
+from oracle import correlate as oc
+from oracle import grad as og
+from oracle import rotation
+from oracle import spread as osp
+from workloads import configs as C
+from workloads import rotations as wr
+
+pytestmark = pytest.mark.gpu
+
+INF, NAN = np.inf, np.nan
+
+
+@pytest.fixture(scope="module")
+def ctxs():
+    from paper_1712_00238_amd.api import Context
+    c32, c64 = Context(0, "f32"), Context(0, "f64")
+    yield {"f32": c32, "f64": c64}
+    c32.close()
+    c64.close()
+
+
+def case(n, nm, planar, count, seed):
+    rng = np.random.default_rng(seed)
+    gf = C.GridSpec((n, n, 1 if planar else n), (0, 0, 0), 1.0)
+    gm = C.GridSpec((nm, nm, 1 if planar else nm), (0, 0, 0), 1.0)
+    rho_m = rng.normal(size=gm.n[::-1]) + 1j * rng.normal(size=gm.n[::-1])
+    w = rng.uniform(0.5, 1.5, size=gm.n[::-1])
+    t = rng.uniform(-3 * n, 4 * n, size=(count, 3))
+    q = wr.planar_rotations(41.0, count) if planar else wr.uniform_quaternions(count, seed)
+    if planar:
+        t[:, 2] = 0.0
+    return gf, gm, rho_m, w, np.concatenate([t, q], axis=1), rng.normal(size=count)
+
+
+def fixed(ctx, gf, rho_m, w, gm, poses, s):
+    return ctx.score_grad_fixed(gf, rho_m, w, gm, poses, grad_scale=s).cpu().numpy()
+
+
+def reached(shape, nm, planar, pose):
+    """Nodes of the samples' stencils; a coordinate that is not a number has floor 0."""
+    with np.errstate(invalid="ignore"):
+        ti = np.floor(pose[:3])
+        y = (pose[:3] - ti) + osp.body_positions(nm, planar) @ rotation.quat_to_matrix(pose[3:]).T
+    base = (np.nan_to_num(np.floor(y), nan=0.0) + np.nan_to_num(ti, nan=0.0) - 1).astype(int)
+    mask = np.zeros(shape, dtype=bool)
+    for cz in range(1 if planar else 4):
+        for cy in range(4):
+            for cx in range(4):
+                mask[(base[:, 2] + cz) % shape[0] if not planar else 0, (base[:, 1] + cy) % shape[1],
+                     (base[:, 0] + cx) % shape[2]] = True
+    return mask
+
+
+# the entries of a pose that are not finite: one translation, the rotation, both
+BAD_POSES = [{0: NAN}, {1: NAN}, {3: NAN, 4: NAN, 5: NAN, 6: NAN}, {a: NAN for a in range(7)}, {3: INF}]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,nm,planar", [(37, 7, False), (20, 9, False), (70, 21, True)])
+@pytest.mark.parametrize("bad", BAD_POSES)
+def test_pose_that_is_not_finite_reaches_its_stencils_only(ctxs, dtype, n, nm, planar, bad):
+    """NaN at the nodes of its samples' stencils, the other poses' sums elsewhere;
+    with a scale of zero it adds nothing."""
+    gf, gm, rho_m, w, poses, s = case(n, nm, planar, 5, n + nm)
+    c = oc.moving_coefficients(rho_m, w)
+    for a, v in bad.items():
+        poses[2, a] = v
+    flush_print("bad pose", dtype, n, nm, planar, bad)
+    keep = [0, 1, 3, 4]
+    shape = gf.n[::-1]
+    ref = og.fixed_cotangent(c, osp.body_positions(nm, planar), poses[keep], s[keep], shape)
+    tol = (1e-12 if dtype == "f64" else 1e-5) * np.abs(ref).max()
+    hit = reached(shape, nm, planar, poses[2])
+    got = fixed(ctxs[dtype], gf, rho_m, w, gm, poses, s).reshape(shape)
+    assert np.array_equal(np.isnan(got.real), hit) and np.array_equal(np.isnan(got.imag), hit)
+    assert np.max(np.abs(got - ref)[~hit]) <= tol
+    s[2] = 0.0
+    got = fixed(ctxs[dtype], gf, rho_m, w, gm, poses, s).reshape(shape)
+    assert np.max(np.abs(got - ref)) <= tol
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_masked_pose_in_the_backward_call(ctxs, dtype):
+    """score_grad_backward's rho_fixed cotangent with a NaN pose of cotangent zero."""
+    gf, gm, rho_m, w, poses, s = case(20, 9, False, 4, 5)
+    poses[1] = NAN
+    s[1] = 0.0
+    flush_print("masked pose", dtype)
+    got = ctxs[dtype].score_grad_backward(None, gf, rho_m, w, gm, poses, s, want_pose=False, want_fixed=True)[3]
+    keep = [0, 2, 3]
+    ref = og.fixed_cotangent(oc.moving_coefficients(rho_m, w), osp.body_positions(9, False), poses[keep], s[keep],
+                             gf.n[::-1])
+    assert np.max(np.abs(got.cpu().numpy() - ref)) <= (1e-12 if dtype == "f64" else 1e-5) * np.abs(ref).max()
