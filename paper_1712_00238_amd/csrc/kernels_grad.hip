@@ -728,8 +728,18 @@ __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restric
 // Sums are 64-bit integers, so runs repeat bit for bit.  FP32 terms are rounded
 // to 2^-30 of the largest c_k s_b, FP64 ones to at most 2^-55 of it with the
 // sums moved to FP64 registers every kFixedFlush poses.  A term that is not
-// finite, and one of a pose that is not, leaves NaN at the nodes it reaches.
+// finite is a flag of its node, for an infinity of either sign or, as both, NaN.
 constexpr int kFixedFlush = 16;
+template <typename T>
+__device__ __forceinline__ void flag_term(unsigned* flags, int words, int node, T v) {
+    const unsigned bit = 1u << (node % 32);
+    if (!(v < T(0))) atomicOr(flags + node / 32, bit);
+    if (!(v > T(0))) atomicOr(flags + words + node / 32, bit);
+}
+__device__ __forceinline__ double flagged(const unsigned* flags, int words, int node) {
+    const bool up = (flags[node / 32] >> (node % 32)) & 1, down = (flags[words + node / 32] >> (node % 32)) & 1;
+    return up ? (down ? NAN : INFINITY) : (down ? -INFINITY : 0.0);
+}
 template <typename T, bool PLANAR>
 __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* __restrict__ rho_m,
                                                                 const T* __restrict__ w_m, int n_m,
@@ -743,7 +753,8 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
     constexpr bool WIDE = std::is_same<T, double>::value;
     constexpr int OWN = S::X * S::Y * S::Z / kTileBlock;  // nodes a thread stores
     __shared__ unsigned long long acc[S::WORDS];
-    __shared__ unsigned bad[S::X * S::Y * S::Z / 32];
+    constexpr int FLAGS = S::X * S::Y * S::Z / 32;  // words per sign and part
+    __shared__ unsigned bad[4 * FLAGS];
     const int ntx = (N + S::X - 1) / S::X, nty = (N + S::Y - 1) / S::Y;
     const int range = int(blockIdx.x % unsigned(ranges));
     const int tile = int(scattered_tile(int64_t(blockIdx.x / unsigned(ranges)), tiles, step));
@@ -755,7 +766,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
     const double pow2 = some ? pow2_below(fmin(top / (cm * sm), WIDE ? 1e300 : 1e37)) : 0.0;
     const double inv = some ? 1.0 / pow2 : 0.0;
     for (int i = int(threadIdx.x); i < S::WORDS; i += kTileBlock) acc[i] = 0;
-    for (int i = int(threadIdx.x); i < S::X * S::Y * S::Z / 32; i += kTileBlock) bad[i] = 0;
+    for (int i = int(threadIdx.x); i < 4 * FLAGS; i += kTileBlock) bad[i] = 0;
     double sr[OWN], si[OWN];
 #pragma unroll
     for (int o = 0; o < OWN; ++o) sr[o] = si[o] = 0.0;
@@ -830,7 +841,8 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                         unsigned(iz) >= unsigned(dim[2]))
                         continue;
                     const int nd = (iz * S::Y + iy) * S::X + ix;
-                    atomicOr(bad + nd / 32, 1u << (nd % 32));
+                    flag_term(bad, FLAGS, nd, T(NAN));
+                    flag_term(bad + 2 * FLAGS, FLAGS, nd, T(NAN));
                 }
             }
             continue;
@@ -858,8 +870,8 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                         const int kk = (k * n_m + j) * n_m + i;
                         cplx<T> ck = rho_m[kk] * (w_m[kk] * sb);
                         if (ck.re == T(0) && ck.im == T(0)) return;
-                        const bool fin = (ck.re - ck.re) + (ck.im - ck.im) == T(0);
-                        const double vr = double(ck.re) * pow2, vi = double(ck.im) * pow2;
+                        const bool fin_re = ck.re - ck.re == T(0), fin_im = ck.im - ck.im == T(0);
+                        const double vr = fin_re ? double(ck.re) * pow2 : 0.0, vi = fin_im ? double(ck.im) * pow2 : 0.0;
                         const T xb[3] = {T(i) - half_box, T(j) - half_box, PLANAR ? T(0) : T(k) - half_box};
                         int b3[3] = {0, 0, 0};
                         T wgt[3][4];
@@ -887,10 +899,12 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                                     if (unsigned(ix) >= unsigned(dim[0])) continue;
                                     const T wt = wgt[0][cx] * wyz;
                                     unsigned long long* a = acc + row * S::PITCH + ix;
-                                    if (!fin) {
+                                    if (!(fin_re && fin_im)) {
                                         const int nd = row * S::X + ix;
-                                        atomicOr(bad + nd / 32, 1u << (nd % 32));
-                                    } else if constexpr (WIDE) {
+                                        if (!fin_re) flag_term(bad, FLAGS, nd, ck.re * wt);
+                                        if (!fin_im) flag_term(bad + 2 * FLAGS, FLAGS, nd, ck.im * wt);
+                                    }
+                                    if constexpr (WIDE) {
                                         atomicAdd(a, fixed(cr * wt));
                                         atomicAdd(a + S::IMAG, fixed(ci * wt));
                                     } else {
@@ -911,9 +925,8 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
         const int nd = o * kTileBlock + int(threadIdx.x);
         const int ix = nd % S::X, iy = (nd / S::X) % S::Y, iz = nd / (S::X * S::Y);
         if (ix >= dim[0] || iy >= dim[1] || iz >= dim[2]) continue;
-        const bool poison = (bad[nd / 32] >> (nd % 32)) & 1;
-        const double f = poison ? NAN : 0.0;
-        dst[(int64_t(t0[2] + iz) * N + t0[1] + iy) * N + t0[0] + ix] = mk(T(sr[o] + f), T(si[o] + f));
+        dst[(int64_t(t0[2] + iz) * N + t0[1] + iy) * N + t0[0] + ix] =
+            mk(T(sr[o] + flagged(bad, FLAGS, nd)), T(si[o] + flagged(bad + 2 * FLAGS, FLAGS, nd)));
     }
 }
 

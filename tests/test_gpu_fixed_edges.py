@@ -1,4 +1,4 @@
-"""score_grad_fixed at the edges of its inputs: poses that are not finite."""
+"""score_grad_fixed at the edges of its inputs: poses and terms that are not finite."""
 
 import numpy as np
 import pytest
@@ -97,3 +97,45 @@ def test_masked_pose_in_the_backward_call(ctxs, dtype):
     ref = og.fixed_cotangent(oc.moving_coefficients(rho_m, w), osp.body_positions(9, False), poses[keep], s[keep],
                              gf.n[::-1])
     assert np.max(np.abs(got.cpu().numpy() - ref)) <= (1e-12 if dtype == "f64" else 1e-5) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("planar", [False, True])
+def test_infinite_terms_add_as_numbers_do(ctxs, dtype, planar):
+    """An infinite part leaves its infinity at its sample's nodes, infinities of
+    opposite signs NaN where they meet, and the other part is as without them."""
+    n, nm = (30, 9) if not planar else (50, 13)
+    gf, gm, rho_m, w, poses, s = case(n, nm, planar, 3, n)
+    s[:] = [1.0, -0.5, 2.0]
+    at = [(0, 3, 4), (0, 5, 6)] if planar else [(2, 3, 4), (3, 5, 4)]
+    zeroed = rho_m.copy()
+    for j in at:
+        zeroed[j] = 1j * rho_m[j].imag
+    c = oc.moving_coefficients(zeroed, w)
+    shape = gf.n[::-1]
+    ref = og.fixed_cotangent(c, osp.body_positions(nm, planar), poses, s, shape)
+    up, down = np.zeros(shape, dtype=bool), np.zeros(shape, dtype=bool)
+    for j, sign in zip(at, (1.0, -1.0)):
+        one = np.zeros(rho_m.shape)
+        one[j] = 1.0
+        for b in range(3):
+            hit = np.abs(og.fixed_cotangent(one.ravel(), osp.body_positions(nm, planar), poses[b:b + 1], np.ones(1),
+                                            shape)) > 0
+            (up if sign * s[b] > 0 else down)[hit] = True
+        rho_m[j] = complex(sign * INF, rho_m[j].imag)
+    expect = np.where(up & down, NAN, np.where(up, INF, np.where(down, -INF, ref.real)))
+    flush_print("infinite terms", dtype, planar)
+    got = fixed(ctxs[dtype], gf, rho_m, w, gm, poses, s).reshape(shape)
+    tol = (1e-12 if dtype == "f64" else 1e-5) * np.abs(ref).max()
+    plain = np.isfinite(expect)
+    assert np.array_equal(got.real[~plain], expect[~plain], equal_nan=True)
+    assert (up & down).any() and up.any() and down.any()
+    assert np.max(np.abs(got.real - expect)[plain]) <= tol
+    assert np.max(np.abs(got.imag - ref.imag)) <= tol
+    # an infinite scale: every node of its pose
+    s[2] = INF
+    got = fixed(ctxs[dtype], gf, zeroed, w, gm, poses, s).reshape(shape)
+    hit = reached(shape, nm, planar, poses[2])
+    assert not np.isfinite(got.imag[hit]).any()
+    two = og.fixed_cotangent(c, osp.body_positions(nm, planar), poses[:2], s[:2], shape)
+    assert np.max(np.abs(got - two)[~hit]) <= tol
