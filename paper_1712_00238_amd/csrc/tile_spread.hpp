@@ -27,8 +27,8 @@ struct SpreadTile {
 constexpr int kTileBlock = 256;
 
 // Calls f(i, j, k) for every body sample x = (i, j, k) - n_m / 2 whose position
-// R x (r: FP32 rows of R) lies in the box [lo, hi), and for a few within 0.02
-// outside it (f tests exactly).  A wave takes 64 body lines along i at a time
+// R x (r: FP32 rows of R) lies in the box [lo, hi), and for a few outside it
+// (within 0.02, or on a line that an edge of the box nearly runs along: f tests exactly).  A wave takes 64 body lines along i at a time
 // (every waves-th line, so that all of a block's waves share few lines); the
 // box cuts each line to one run of samples, and the runs are laid end to end
 // over the lanes, so f runs with full waves.  No barrier.
@@ -64,8 +64,9 @@ __device__ __forceinline__ void box_samples(const float r[9], int n_m, const flo
 #pragma unroll
         for (int c = 0; c < D; ++c) {
             const float y0 = r[3 * c + 1] * bj + r[3 * c + 2] * bk - r[3 * c] * half, s = r[3 * c];
-            if (fabsf(s) < 1e-4f) {  // the line moves by less than 0.02 along this axis
-                ok &= y0 >= lo[c] - 0.04f && y0 <= hi[c] + 0.04f;
+            if (fabsf(s) < 1e-4f) {  // all of the line or nothing: its samples lie between y0 and y0 + s n_m
+                const float y1 = y0 + s * float(n_m);
+                ok &= fmaxf(y0, y1) >= lo[c] - 0.04f && fminf(y0, y1) <= hi[c] + 0.04f;
             } else {
                 const float inv = 1.f / s;
                 const float q1 = (lo[c] - 0.02f - y0) * inv, q2 = (hi[c] + 0.02f - y0) * inv;

@@ -1,4 +1,5 @@
-"""score_grad_fixed at the edges of its inputs: poses and terms that are not finite."""
+"""score_grad_fixed at the edges of its inputs: poses and terms that are not
+finite, and long body lines almost along the grid's axes."""
 
 import numpy as np
 import pytest
@@ -139,3 +140,15 @@ def test_infinite_terms_add_as_numbers_do(ctxs, dtype, planar):
     assert not np.isfinite(got.imag[hit]).any()
     two = og.fixed_cotangent(c, osp.body_positions(nm, planar), poses[:2], s[:2], shape)
     assert np.max(np.abs(got - two)[~hit]) <= tol
+
+
+@pytest.mark.parametrize("n,nm,angle,t", [(1100, 1024, 9e-5, (3.3, 40.0)), (1600, 1500, -9.9e-5, (0.7, 2.026)),
+                                          (520, 500, 9.9e-5, (5.25, 7.98))])
+def test_long_lines_almost_along_an_axis(ctxs, n, nm, angle, t):
+    """Lines of a wide planar body that drift across a tile's edge over their length."""
+    gf, gm, rho_m, w, poses, s = case(n, nm, True, 1, n)
+    poses[0] = [t[0], t[1], 0.0, np.cos(0.5 * angle), 0.0, 0.0, np.sin(0.5 * angle)]
+    flush_print("long lines", n, nm, angle)
+    got = fixed(ctxs["f64"], gf, rho_m, w, gm, poses, s).reshape(gf.n[::-1])
+    ref = og.fixed_cotangent(oc.moving_coefficients(rho_m, w), osp.body_positions(nm, True), poses, s, gf.n[::-1])
+    assert np.max(np.abs(got - ref)) <= 1e-12 * np.abs(ref).max()
