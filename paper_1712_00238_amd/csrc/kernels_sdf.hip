@@ -304,13 +304,13 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
                                                               const float* __restrict__ rec1,
                                                               const float* __restrict__ rec2, int64_t ns, GridDesc g,
                                                               ParamDesc prm, cplx<T>* __restrict__ out,
-                                                              unsigned long long* __restrict__ stats) {
+                                                              unsigned long long* __restrict__ stats, int64_t brick0) {
     static_assert(WPB == 1 || WPB == 4, "waves per brick");
     __shared__ double sh_best[WPB == 4 ? 256 : 1];
     __shared__ __align__(8) int sh_idx[WPB == 4 ? 256 : 2];
     const int lane = int(threadIdx.x) & 63, sub = WPB == 1 ? 0 : uniform(int(threadIdx.x) >> 6);
     const int n = lane & 15, gq = lane >> 4;
-    const int64_t brick = blockIdx.x;
+    const int64_t brick = brick0 + blockIdx.x;
     const BrickGrid bg = wave_bricks(g.nx, g.ny, g.nz);
     // Consecutive blocks go to the XCDs and their shader engines in turn, so a
     // row of bricks as long as a multiple of their number would give each
@@ -1624,6 +1624,8 @@ hipError_t prepare_samples(const double* q, const double* n, const double* w, in
     return hipGetLastError();
 }
 
+// a launch has fewer than 2^32 threads along x: more go into several
+constexpr int64_t kLaunchThreads = int64_t(1) << 31;
 // node-sample pairs from which interpolation repays its own launches
 constexpr double kInterpPairs = 1e8;
 // Grids of at most this many bricks give each brick's samples to four waves,
@@ -1656,12 +1658,15 @@ void enqueue_build(const double* q, const double* n, const Prepared& P, int64_t 
                    const ParamDesc& p, cplx<T>* out, unsigned long long* stats, hipStream_t s) {
     const BrickGrid bg = wave_bricks(g.nx, g.ny, g.nz);
     const int64_t bricks = int64_t(bg.nx) * bg.ny * bg.nz;
-    if (bricks <= kShareBricks<FAST>)
-        hipLaunchKernelGGL((sdf_build_kernel<T, PHI, FAST, 4, STATS>), dim3(unsigned(bricks)), dim3(kSdfBlock), 0, s, q,
-                           n, P.st.qs, P.st.wn, P.st.js, P.node, P.tr, P.rec1, P.rec2, ns, g, p, out, stats);
-    else
-        hipLaunchKernelGGL((sdf_build_kernel<T, PHI, FAST, 1, STATS>), dim3(unsigned(bricks)), dim3(64), 0, s, q, n,
-                           P.st.qs, P.st.wn, P.st.js, P.node, P.tr, P.rec1, P.rec2, ns, g, p, out, stats);
+    auto run = [&](auto kernel, int waves) {
+        for (int64_t b0 = 0; b0 < bricks; b0 += kLaunchThreads / (64 * waves)) {
+            const int64_t count = std::min<int64_t>(bricks - b0, kLaunchThreads / (64 * waves));
+            hipLaunchKernelGGL(kernel, dim3(unsigned(count)), dim3(64 * waves), 0, s, q, n, P.st.qs, P.st.wn, P.st.js,
+                               P.node, P.tr, P.rec1, P.rec2, ns, g, p, out, stats, b0);
+        }
+    };
+    if (bricks <= kShareBricks<FAST>) run(sdf_build_kernel<T, PHI, FAST, 4, STATS>, 4);
+    else run(sdf_build_kernel<T, PHI, FAST, 1, STATS>, 1);
 }
 
 }  // namespace

@@ -1,4 +1,5 @@
-"""sdf_build at the edges of its inputs: samples and weights that are not finite."""
+"""sdf_build at the edges of its inputs: samples and weights that are not finite,
+and calls past the size of one launch."""
 
 import numpy as np
 import pytest
@@ -100,3 +101,26 @@ def test_weight_that_is_not_finite_reaches_its_own_nodes_only(ctxs, dtype, bad, 
     if dtype == "f32" or not np.isfinite(bad):
         live = inside & (ref != 0)
         assert not np.isfinite(got[live]).any()
+
+
+@pytest.mark.parametrize("n", [(1024, 1024, 1024), (32768, 32768, 1)])
+def test_grid_past_one_launch(ctxs, n):
+    """2^30 and more threads' worth of 16-node bricks: the nodes of both ends and of
+    the middle are those of a small grid there."""
+    import torch
+    s = sphere(50, 30.0)
+    h = 0.5
+    centre = [0.5 * h * m if m > 3 else 0.0 for m in n]
+    s = shapes.PointSamples(s.q + np.array(centre), s.n, s.w)
+    flush_print("large grid", n)
+    out = ctxs["f32"].sdf_build(s.q, s.n, s.w, C.GridSpec(n, (0.0, 0.0, 0.0), h), PARAMS)
+    for share in (0.0, 0.5, 1.0):
+        m = tuple(min(x, 24) for x in n)
+        at = [int(share * (x - y)) for x, y in zip(n, m)]
+        part = C.GridSpec(m, tuple(h * a for a in at), h)
+        ref = ctxs["f64"].sdf_build(s.q, s.n, s.w, part, PARAMS)
+        got = out[at[2]:at[2] + m[2], at[1]:at[1] + m[1], at[0]:at[0] + m[0]].to(torch.complex128)
+        # far from the part its terms cancel some hundredfold
+        assert float((got - ref).abs().max()) <= 1e-4 * float(ref.abs().max())
+    del out
+    torch.cuda.empty_cache()
