@@ -1375,13 +1375,14 @@ __global__ __launch_bounds__(kSdfBlock) void tree_up_kernel(TreeNode* __restrict
 __global__ __launch_bounds__(kSdfBlock) void interp_sum_kernel(const TreeNode* __restrict__ node, SampleTree tr,
                                                                InterpLayout lay, const double* __restrict__ qs,
                                                                const double* __restrict__ wn, int64_t n,
-                                                               double* __restrict__ part) {
+                                                               double* __restrict__ part, int64_t blk0) {
     __shared__ double tab[4][16][3][kInterpMax];
     __shared__ double sums[4][64][3];
+    const int64_t blk = blk0 + blockIdx.x;
     int l = 1;
-    while (l + 1 < tr.levels && int64_t(blockIdx.x) >= lay.blk[l + 1]) ++l;
+    while (l + 1 < tr.levels && blk >= lay.blk[l + 1]) ++l;
     const int chunks = (lay.cap[l] + 63) / 64;
-    const int64_t b = int64_t(blockIdx.x) - lay.blk[l];
+    const int64_t b = blk - lay.blk[l];
     const int chunk = int(b % chunks), split = int((b / chunks) % lay.split[l]);
     const int i = int(b / (int64_t(chunks) * lay.split[l]));
     const TreeNode t = node[tr.off[l] + i];
@@ -1552,6 +1553,9 @@ struct Prepared {
     const float *rec1, *rec2;
 };
 
+// a launch has fewer than 2^32 threads along x: more go into several
+constexpr int64_t kLaunchThreads = int64_t(1) << 31;
+
 // Hilbert order, sorted copies, sample tree; with `fast` the records of the FP32
 // sum, with `interp` its interpolation points, with `tiles` the 256-sample tile boxes
 hipError_t prepare_samples(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g, void* ws,
@@ -1610,8 +1614,13 @@ hipError_t prepare_samples(const double* q, const double* n, const double* w, in
         l = l1;
     }
     if (fast && interp && tr.levels > 1) {
-        hipLaunchKernelGGL(interp_sum_kernel, dim3(unsigned(L.lay.blk[tr.levels])), dim3(kSdfBlock), 0, s, node, tr,
-                           L.lay, qs, wn, ns, part);
+        for (int64_t b0 = 0; b0 < L.lay.blk[tr.levels]; b0 += kLaunchThreads / kSdfBlock) {
+            const int64_t count = std::min(L.lay.blk[tr.levels] - b0, kLaunchThreads / kSdfBlock);
+            hipLaunchKernelGGL(interp_sum_kernel, dim3(unsigned(count)), dim3(kSdfBlock), 0, s, node, tr, L.lay, qs, wn,
+                               ns, part, b0);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
         int64_t pts = 0;
         for (int lv = 1; lv < tr.levels; ++lv) pts = std::max(pts, int64_t(tr.cnt[lv]) * L.lay.cap[lv]);
         const dim3 rg{unsigned((pts + kSdfBlock - 1) / kSdfBlock), unsigned(tr.levels - 1), 1u};
@@ -1624,8 +1633,6 @@ hipError_t prepare_samples(const double* q, const double* n, const double* w, in
     return hipGetLastError();
 }
 
-// a launch has fewer than 2^32 threads along x: more go into several
-constexpr int64_t kLaunchThreads = int64_t(1) << 31;
 // node-sample pairs from which interpolation repays its own launches
 constexpr double kInterpPairs = 1e8;
 // Grids of at most this many bricks give each brick's samples to four waves,

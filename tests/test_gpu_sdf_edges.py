@@ -124,3 +124,28 @@ def test_grid_past_one_launch(ctxs, n):
         assert float((got - ref).abs().max()) <= 1e-4 * float(ref.abs().max())
     del out
     torch.cuda.empty_cache()
+
+
+def test_samples_past_one_launch_of_the_interpolation_sums(ctxs):
+    """1.4e8 samples: more than 2^32 threads in the sums of all interpolation points
+    (without the last of them the field is off by its own size).  A ball of radius
+    10 holds 1.4e6 samples, a quarter of them to a lane: sqrt(3.5e5) roundings of
+    6e-8, and terms that cancel threefold."""
+    import torch
+    torch.cuda.empty_cache()
+    count, radius = 140_000_000, 50.0
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    n = torch.randn((count, 3), generator=gen, device="cuda", dtype=torch.float64)
+    n /= n.norm(dim=1, keepdim=True)
+    q = radius * n
+    w = torch.full((count,), 4 * np.pi * radius ** 2 / count, dtype=torch.float64, device="cuda")
+    # nodes 1 to 4 above the surface, whose balls reach up to 10
+    grid = C.GridSpec((4, 3, 4), (0.0, 0.0, radius + 1.0), 1.0)
+    flush_print("samples", count)
+    got = ctxs["f32"].sdf_build(q, n, w, grid, PARAMS)
+    ref = ctxs["f64"].sdf_build(q, n, w, grid, PARAMS)
+    err = float((got.to(torch.complex128) - ref).abs().max()) / float(ref.abs().max())
+    flush_print("relative error", err)
+    assert err <= 1e-4
+    del q, n, w
+    torch.cuda.empty_cache()
