@@ -284,6 +284,28 @@ int ensure_ws(sdf_ctx ctx, size_t bytes) {
     return SDF_OK;
 }
 
+// A workspace of `want` bytes or, where the cap or the device's memory does not
+// hold that many, of `least`; *got says which.  A stream that is being captured
+// takes what the workspace holds already.
+int ensure_either(sdf_ctx ctx, size_t want, size_t least, hipStream_t s, size_t* got) {
+    *got = want;
+    if (want <= ctx->ws_bytes) return SDF_OK;
+    if (want > least && (!ctx->cap || want <= ctx->cap)) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
+        size_t room = 0, all = 0;
+        if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
+            hipMemGetInfo(&room, &all) == hipSuccess && want <= room + ctx->ws_bytes) {
+            const std::string ctx_err = ctx->err, last_err = g_err;
+            if (ensure_ws(ctx, want) == SDF_OK) return SDF_OK;
+            ctx->err = ctx_err;
+            g_err = last_err;
+        }
+        (void)hipGetLastError();
+    }
+    *got = least;
+    return ensure_ws(ctx, least);
+}
+
 sdf::GridDesc desc(const sdf_grid* g) {
     return sdf::GridDesc{g->n[0], g->n[1], g->n[2], g->origin[0], g->origin[1], g->origin[2], g->h};
 }
@@ -291,35 +313,24 @@ sdf::GridDesc desc(const sdf_grid* g) {
 int64_t gsize(const sdf_grid* g) { return int64_t(g->n[0]) * g->n[1] * g->n[2]; }
 
 // workspace of one sdf_build: with the FP32 sum's records and interpolation
-// points where they apply and fit the cap, else the least that it needs
+// points where they apply
 size_t build_ws_bytes(sdf_ctx ctx, int64_t ns, int kind) {
-    if (ctx->dtype == SDF_F32 && (kind == sdf::kPhiSkeletal || kind == sdf::kPhiInverseSquare)) {
-        const size_t fast = sdf::sdf_build_fast_bytes(ns);
-        if (!ctx->cap || fast <= ctx->cap) return fast;
-    }
+    if (ctx->dtype == SDF_F32 && (kind == sdf::kPhiSkeletal || kind == sdf::kPhiInverseSquare))
+        return sdf::sdf_build_fast_bytes(ns);
     return sdf::sdf_build_workspace_bytes(ns, kind);
 }
 
-// workspace of one fixed-field cotangent: with partial grids for the pose
-// ranges where the cap allows
-size_t fixed_ws_bytes(sdf_ctx ctx, int64_t B, int N, bool planar) {
-    const bool wide = ctx->dtype == SDF_F64;
-    const size_t split = wide ? sdf::fixed_cotangent_bytes<double>(B, N, planar, true)
-                              : sdf::fixed_cotangent_bytes<float>(B, N, planar, true);
-    if (!ctx->cap || split <= ctx->cap) return split;
-    return wide ? sdf::fixed_cotangent_bytes<double>(B, N, planar, false)
-                : sdf::fixed_cotangent_bytes<float>(B, N, planar, false);
+// workspace of one fixed-field cotangent, with partial grids for the pose
+// ranges (split) or without
+size_t fixed_ws_bytes(sdf_ctx ctx, int64_t B, int N, bool planar, bool split) {
+    return ctx->dtype == SDF_F64 ? sdf::fixed_cotangent_bytes<double>(B, N, planar, split)
+                                 : sdf::fixed_cotangent_bytes<float>(B, N, planar, split);
 }
 
-// workspace of the pose kernels: the finer split's where `limit` (0: none)
-// leaves room for it beside `other` bytes
-size_t pose_ws_bytes(sdf_ctx ctx, int64_t B, int N, int nm, bool planar, int wmode, size_t limit, size_t other) {
-    auto bytes = [&](bool fine) {
-        return ctx->dtype == SDF_F64 ? sdf::grad_workspace_bytes<double>(B, N, nm, planar, wmode, fine)
-                                     : sdf::grad_workspace_bytes<float>(B, N, nm, planar, wmode, fine);
-    };
-    const size_t fine = bytes(true);
-    return !limit || align_up(fine) + other <= limit ? fine : bytes(false);
+// workspace of the pose kernels, for the finer split or the least
+size_t pose_ws_bytes(sdf_ctx ctx, int64_t B, int N, int nm, bool planar, int wmode, bool fine) {
+    return ctx->dtype == SDF_F64 ? sdf::grad_workspace_bytes<double>(B, N, nm, planar, wmode, fine)
+                                 : sdf::grad_workspace_bytes<float>(B, N, nm, planar, wmode, fine);
 }
 
 void drop_graph(sdf_ctx ctx) {
@@ -378,12 +389,11 @@ int plain_pair(sdf_ctx ctx, const PairIn& pr, Mode mode, void* vol_out, hipStrea
         const size_t room = ctx->cap > one ? (ctx->cap - one) / per : 0;
         B = std::max<int64_t>(1, std::min<int64_t>(B, 1 + int64_t(room)));
     }
-    int rc = ensure_ws(ctx, carve(nullptr, B, &qd, &RT, &cmax, &c, &grid));
-    if (rc && B > 1) {
-        B = 1;
-        rc = ensure_ws(ctx, carve(nullptr, B, &qd, &RT, &cmax, &c, &grid));
-    }
+    const size_t want = carve(nullptr, B, &qd, &RT, &cmax, &c, &grid);
+    size_t got = 0;
+    int rc = ensure_either(ctx, want, carve(nullptr, 1, &qd, &RT, &cmax, &c, &grid), s, &got);
     if (rc) return rc;
+    if (got < want) B = 1;
     carve(static_cast<char*>(ctx->ws), B, &qd, &RT, &cmax, &c, &grid);
     SDF_TRY_HIP(ctx, hipMemcpyAsync(qd, pr.quats, sizeof(double) * 4 * n_rot, hipMemcpyHostToDevice, s),
                 "quaternion upload");
@@ -808,10 +818,11 @@ int direct_impl(sdf_ctx ctx, const void* spec, const sdf_grid* gf, const double*
     cv.take(sizeof(double) * 3 * ns);
     cv.take(2 * sizeof(T) * K);
     cv.take(2 * sizeof(T) * G);
-    if (ctx->cap && cv.off + sdf_ws > ctx->cap) sdf_ws = sdf::sdf_build_workspace_bytes(ns);
-    cv.take(sdf_ws);
-    int rc = ensure_ws(ctx, cv.off);
+    const size_t least_ws = sdf::sdf_build_workspace_bytes(ns);
+    size_t got = 0;
+    int rc = ensure_either(ctx, cv.off + align_up(sdf_ws), cv.off + align_up(least_ws), s, &got);
     if (rc) return rc;
+    if (got < cv.off + align_up(sdf_ws)) sdf_ws = least_ws;
     Carve c2{static_cast<char*>(ctx->ws)};
     double* qd = static_cast<double*>(c2.take(sizeof(double) * 4 * n_rot));
     double* r64 = static_cast<double*>(c2.take(sizeof(double) * 9 * n_rot));
@@ -1103,8 +1114,8 @@ static int sdf_build_impl(sdf_ctx ctx, const void* q, const void* nrm, const voi
     const double* nd = static_cast<const double*>(nrm);
     const double* wd = static_cast<const double*>(w);
     ctx->fused_cache_valid = false;  // the ordered samples share the workspace
-    const size_t ws_bytes = build_ws_bytes(ctx, n, kind);
-    rc = ensure_ws(ctx, ws_bytes);
+    size_t ws_bytes = 0;
+    rc = ensure_either(ctx, build_ws_bytes(ctx, n, kind), sdf::sdf_build_workspace_bytes(n, kind), s, &ws_bytes);
     if (rc) return rc;
     unsigned long long* stats = nullptr;
     if (ctx->opt_sdf_stats && kind == SDF_PHI_SKELETAL) {
@@ -1153,9 +1164,8 @@ int sdf_build_adjoint(sdf_ctx ctx, const void* q, const void* nrm, const void* w
     const double* nd = static_cast<const double*>(nrm);
     const double* wd = static_cast<const double*>(w);
     ctx->fused_cache_valid = false;  // the ordered samples share the workspace
-    size_t bytes = sdf::sdf_adjoint_bytes(n, desc(g));
-    if (ctx->cap && bytes > ctx->cap) bytes = sdf::sdf_build_workspace_bytes(n);
-    rc = ensure_ws(ctx, bytes);
+    size_t bytes = 0;
+    rc = ensure_either(ctx, sdf::sdf_adjoint_bytes(n, desc(g)), sdf::sdf_build_workspace_bytes(n), s, &bytes);
     if (rc) return rc;
     hipError_t e = ctx->dtype == SDF_F64
                        ? sdf::launch_sdf_adjoint<double>(qd, nd, wd, n, desc(g), pd, cot, grad_q, grad_n, grad_w,
@@ -1391,17 +1401,18 @@ static int score_grad_impl(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g
     const bool planar = g_fixed->n[2] == 1;
     const int N = g_fixed->n[0], nm = g_moving->n[0];
     const int wmode = grad_c ? 2 : (grad_w ? 1 : 0);
-    const size_t need =
-        pose_ws_bytes(ctx, B, N, nm, planar, wmode, scratch_buf ? kScratchBytes : ctx->cap, 0);
+    const size_t least = pose_ws_bytes(ctx, B, N, nm, planar, wmode, false);
+    size_t need = pose_ws_bytes(ctx, B, N, nm, planar, wmode, true);
     void* ws = scratch_buf;
     if (scratch_buf) {
+        if (need > kScratchBytes) need = least;
         if (need > kScratchBytes)
             return fail(ctx, SDF_ENOMEM, "score_grad_noalloc needs " + std::to_string(need) +
                                              " bytes of scratch, more than its fixed " +
                                              std::to_string(kScratchBytes) + " (fewer poses per call, or no grad_w)");
     } else {
         ctx->fused_cache_valid = false;
-        rc = ensure_ws(ctx, need);
+        rc = ensure_either(ctx, need, least, s, &need);
         if (rc) return rc;
         ws = ctx->ws;
     }
@@ -1468,18 +1479,20 @@ int score_grad_backward(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g_fi
     const int64_t K = gsize(g_moving);
     const size_t el = esize(ctx);
     const int wmode = grad_rho_moving ? 2 : (grad_w ? 1 : 0);
-    const size_t gws = pose_ws_bytes(ctx, B, N, nm, planar, wmode, ctx->cap,
-                                     align_up(el * size_t(B)) + align_up(2 * el * size_t(K)));
     // workspace: the gradient kernels' scratch, the per-pose scores (not
     // returned), the moving coefficients' cotangent; the fixed cotangent's
     // pose table reuses the front once those kernels are done (stream order)
-    Carve cv{nullptr};
-    cv.take(gws);
-    cv.take(el * size_t(B));
-    cv.take(2 * el * size_t(K));
-    const size_t fixed_bytes = grad_rho_fixed ? fixed_ws_bytes(ctx, B, N, planar) : 0;
-    rc = ensure_ws(ctx, std::max(cv.off, fixed_bytes));
+    const size_t rest = align_up(el * size_t(B)) + align_up(2 * el * size_t(K));
+    auto moving_bytes = [&](bool fine) { return align_up(pose_ws_bytes(ctx, B, N, nm, planar, wmode, fine)) + rest; };
+    auto fixed_side = [&](bool split) { return grad_rho_fixed ? fixed_ws_bytes(ctx, B, N, planar, split) : 0; };
+    bool fine = !ctx->cap || moving_bytes(true) <= ctx->cap, split = !ctx->cap || fixed_side(true) <= ctx->cap;
+    const size_t want = std::max(moving_bytes(fine), fixed_side(split));
+    const size_t least = std::max(moving_bytes(false), fixed_side(false));
+    size_t got = 0;
+    rc = ensure_either(ctx, want, least, s, &got);
     if (rc) return rc;
+    if (got < want) fine = split = false;
+    const size_t gws = pose_ws_bytes(ctx, B, N, nm, planar, wmode, fine), fixed_bytes = fixed_side(split);
     Carve c2{static_cast<char*>(ctx->ws)};
     void* gw_ws = c2.take(gws);
     void* score_ws = c2.take(el * size_t(B));
@@ -1541,8 +1554,9 @@ int score_grad_fixed(sdf_ctx ctx, const sdf_grid* g_fixed, const void* rho_movin
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool planar = g_fixed->n[2] == 1;
     const int N = g_fixed->n[0], nm = g_moving->n[0];
-    const size_t ws_bytes = fixed_ws_bytes(ctx, B, N, planar);
-    rc = ensure_ws(ctx, ws_bytes);
+    size_t ws_bytes = 0;
+    rc = ensure_either(ctx, fixed_ws_bytes(ctx, B, N, planar, true), fixed_ws_bytes(ctx, B, N, planar, false), s,
+                       &ws_bytes);
     if (rc) return rc;
     hipError_t e = ctx->dtype == SDF_F64
                        ? sdf::launch_fixed_cotangent<double>(rho_moving, static_cast<const double*>(w_moving), nm,

@@ -149,3 +149,37 @@ def test_samples_past_one_launch_of_the_interpolation_sums(ctxs):
     assert err <= 1e-4
     del q, n, w
     torch.cuda.empty_cache()
+
+
+def test_build_where_memory_holds_only_the_least_workspace():
+    """With 1.5 GiB left on the device 1e7 samples have room for their order (0.7 GB)
+    but not for the FP32 sum's records (2.6 GB): the build runs pair by pair."""
+    import torch
+    from paper_1712_00238_amd.api import Context
+    torch.cuda.empty_cache()
+    count, radius = 10_000_000, 20.0
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    n = torch.randn((count, 3), generator=gen, device="cuda", dtype=torch.float64)
+    n /= n.norm(dim=1, keepdim=True)
+    q = radius * n
+    w = torch.full((count,), 4 * np.pi * radius ** 2 / count, dtype=torch.float64, device="cuda")
+    grid = C.GridSpec((4, 3, 4), (0.0, 0.0, radius + 1.0), 1.0)
+    torch.cuda.empty_cache()
+    with Context(0, "f64") as ctx:
+        ref = ctx.sdf_build(q, n, w, grid, PARAMS).clone()
+    left, held = 3 << 29, []
+    with Context(0, "f32") as ctx:
+        ctx.sdf_build(q[:100], n[:100], w[:100], grid, PARAMS)
+        torch.cuda.synchronize()
+        flush_print("free before", torch.cuda.mem_get_info()[0])
+        while torch.cuda.mem_get_info()[0] > left + (16 << 20):
+            held.append(torch.empty(min(torch.cuda.mem_get_info()[0] - left, 16 << 30), dtype=torch.uint8, device="cuda"))
+        flush_print("free", torch.cuda.mem_get_info()[0])
+        try:
+            got = ctx.sdf_build(q, n, w, grid, PARAMS)
+            torch.cuda.synchronize()
+        finally:
+            held.clear()
+            torch.cuda.empty_cache()
+    # sequential FP32 sums of up to 1.6e5 terms a lane
+    assert float((got.to(torch.complex128) - ref).abs().max()) <= 1e-3 * float(ref.abs().max())
