@@ -77,7 +77,7 @@ constexpr double kInterpXi = 1.2;
 constexpr int kInterpSplit = 2048;  // samples per block of the weight sums
 
 // relative half-width of the band around the ball's squared radius that is
-// decided in FP64.  FP32 squared distances are nearer than that: differences
+// decided in FP64.  FP32 squared distances are nearer than that: FP64 differences
 // give them to 4e-7; the matrix form sums |p|^2, -2 p.q and |q|^2, at most (|p| + |q|)^2
 // <= 9 d^2 where it is used (|q| <= d), in five roundings of 6e-8.
 constexpr double kBallBand = 4e-6;
@@ -436,31 +436,17 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
             terms(da, wa, gr);
         }
     };
-    // the pairs of a leaf by differences
-    auto plain_leaf = [&](const double c[3], int leaf) {
+    // the pairs of a leaf by differences, taken in FP64: a leaf may be as wide as
+    // the part (sparse samples, a window of a larger part), and rounded about its
+    // centre the positions would carry 6e-8 of its radius into a short distance
+    auto plain_leaf = [&](int leaf) {
         const int64_t s0 = int64_t(leaf) * kLeaf;
         const int cnt = int(ns - s0 < kLeaf ? ns - s0 : kLeaf);
         if (!live) return;
-        const T cx = T(px - c[0]), cy = T(py - c[1]), cz = T(pz - c[2]);
         for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) {
             const int64_t s = s0 + a;
-            T dx, dy, dz, wx, wy, wz;
-            if constexpr (FAST) {
-                const int64_t o = (s >> 4) * 64 + (s & 15);
-                dx = cx + T(0.5f * rec1[o]);
-                dy = cy + T(0.5f * rec1[o + 16]);
-                dz = cz + T(0.5f * rec1[o + 32]);
-                wx = T(rec2[o]);
-                wy = T(rec2[o + 16]);
-                wz = T(rec2[o + 32]);
-            } else {
-                dx = T(px - qs[3 * s]);
-                dy = T(py - qs[3 * s + 1]);
-                dz = T(pz - qs[3 * s + 2]);
-                wx = T(wn[3 * s]);
-                wy = T(wn[3 * s + 1]);
-                wz = T(wn[3 * s + 2]);
-            }
+            const T dx = T(px - qs[3 * s]), dy = T(py - qs[3 * s + 1]), dz = T(pz - qs[3 * s + 2]);
+            const T wx = T(wn[3 * s]), wy = T(wn[3 * s + 1]), wz = T(wn[3 * s + 2]);
             const T d2 = dx * dx + dy * dy + dz * dz;
             if (STATS) ++vis2;
             if (d2 <= r2hi) {
@@ -519,7 +505,7 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
                     if (STATS && !ce && mine)
                         for (int a = 4 * sub + gq; a < cnt_s; a += 4 * WPB) ++inball;
                 } else {
-                    plain_leaf(te.c, w.base + e);
+                    plain_leaf(w.base + e);
                 }
             }
             w.pend |= uint64_t(later) << (4 * w.l);

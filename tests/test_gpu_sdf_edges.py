@@ -183,3 +183,33 @@ def test_build_where_memory_holds_only_the_least_workspace():
             torch.cuda.empty_cache()
     # sequential FP32 sums of up to 1.6e5 terms a lane
     assert float((got.to(torch.complex128) - ref).abs().max()) <= 1e-3 * float(ref.abs().max())
+
+
+def test_window_of_a_much_larger_part(ctxs):
+    """Samples off the grid share a few keys, so their leaves are as wide as the part
+    (8000 cells about a 64-cell window).  FP32 terms carry up to 3e-5 each, the
+    sums of a node's terms cancel some threefold."""
+    near, far = sphere(2000, 30.0, 5), sphere(2000, 8000.0, 6)
+    mix = np.random.default_rng(1).permutation(4000)
+    s = shapes.PointSamples(np.concatenate([near.q, far.q])[mix], np.concatenate([near.n, far.n])[mix],
+                            np.concatenate([near.w, far.w])[mix])
+    grid = C.GridSpec((33, 32, 31), (-8.0, -8.0, -7.5), 0.5)
+    a, b = build(ctxs["f32"], s, grid), build(ctxs["f64"], s, grid)
+    err = np.abs(a - b)
+    flush_print("window: max rel", (err / np.abs(b)).max(), "2-norm", np.linalg.norm(err) / np.linalg.norm(b))
+    assert np.all(err <= 1e-4 * np.abs(b) + 1e-6 * np.abs(b).max())
+
+
+@pytest.mark.parametrize("outlier", [50.0, 2000.0, 8000.0, 80000.0])
+def test_ball_edges_in_a_wide_leaf(ctxs, outlier):
+    """Three samples in one leaf: the nearest (of next to no weight), one that some
+    balls hold and some do not, and an outlier.  Whether the second counts is
+    decided in FP64."""
+    s = shapes.PointSamples(np.array([[0.3, 0.2, -0.1], [7.9, 0.4, 0.7], [outlier, 0.5 * outlier, 0.3 * outlier]]),
+                            np.array([[1.0, 0.0, 0.0], [0.6, 0.0, 0.8], [1.0, 0.0, 0.0]]), np.array([1e-12, 1.0, 1e-12]))
+    grid = C.GridSpec((96, 96, 96), (-4.03, -4.01, -4.02), 0.0837)
+    a, b = (np.abs(build(ctxs[d], s, grid)) for d in ("f32", "f64"))
+    in_a, in_b = a > 1e-6 * a.max(), b > 1e-6 * b.max()
+    flush_print("ball edges", outlier, int((in_a != in_b).sum()), int(in_b.sum()))
+    assert 1000 < in_b.sum() < in_b.size - 1000
+    assert np.array_equal(in_a, in_b)
