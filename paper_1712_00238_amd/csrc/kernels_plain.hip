@@ -7,7 +7,6 @@
 //   then y with the product, then x).
 // The FP64 search, full score volumes and the windowless reference run here;
 // it is also what the fused FP32 kernels are compared with.
-#include <type_traits>
 
 #include "common.hpp"
 #include "fft.hpp"
@@ -145,31 +144,20 @@ __global__ void spread_atomic_kernel(const cplx<T>* __restrict__ c, int n_m, int
 // The samples that reach the tile come wave by wave with full lanes
 // (box_samples): each lane forms its sample's weights and adds the taps that
 // lie in the tile to LDS.
-// Sums are integers (their order does not matter, runs repeat bit for bit):
-// 64 bits for FP64, in units of at most 16 max|c| / 2^60, finer than the rounding of an
-// FP64 sum; 32 bits for FP32, in units of at most 16 max|c| / 2^31.  The weights at a node of a unit-density lattice sum to about 1, so
-// no sum leaves the range.  Nodes are centred coordinates [-N/2, N/2): the fit
-// rule keeps every stencil inside, so no index wraps before the store.
+// Sums are 64-bit integers in both precisions (their order does not matter, runs
+// repeat bit for bit), in units of at most 2^-61 max|c|: finer than the rounding
+// of an FP64 sum at nodes of 1/500 of the largest value and more, and of an FP32
+// sum at any node that a coefficient of 2^-37 of the largest reaches (32-bit sums
+// in units of 16 max|c| / 2^31 lost two digits on fields with one coefficient a
+// hundred times the rest).  The B-splines of a whole lattice of unit density sum
+// to at most 1.01 at any point, those of a part of it to less, so no sum reaches
+// 2^63.  Nodes are centred coordinates [-N/2, N/2): the fit rule keeps every
+// stencil inside, so no index wraps before the store.
 // Bound by VALU issue (6 instructions per FP64 sum besides its LDS add).  FP64,
 // 8 rotations of 96^3 / 48^3: the whole search 6212 -> 413 us, 180 of them here;
 // 36 rotations of 128^2 / 64^2: 1930 -> 65 us (with the batched and fused
 // transform passes).
-template <typename T>
-struct TileSum;
-template <>
-struct TileSum<float> {
-    using type = int;
-    static constexpr double top = 2147483648.0;  // 2^31
-    struct Fixed {
-        __device__ __forceinline__ int operator()(float v) const { return __float2int_rn(v); }
-    };
-};
-template <>
-struct TileSum<double> {
-    using type = unsigned long long;
-    static constexpr double top = 1152921504606846976.0;  // 2^60
-    using Fixed = Fixed64;
-};
+constexpr double kTileTop = 4611686018427387904.0;  // 2^62: |c| in units
 
 // The r-th tile from the middle of the grid outwards.  The body's tiles take
 // nearly all of the time; launched first, over all rotations, they spread over
@@ -221,8 +209,7 @@ __global__ __launch_bounds__(BLOCK) void spread_tile_kernel(const cplx<T>* __res
                                                                  const unsigned long long* __restrict__ cmax,
                                                                  cplx<T>* __restrict__ out) {
     using S = SpreadTile<PLANAR>;
-    using A = typename TileSum<T>::type;
-    __shared__ A acc[S::WORDS];
+    __shared__ unsigned long long acc[S::WORDS];
     const int sx = min(S::X, N), sy = min(S::Y, N), sz = PLANAR ? 1 : min(S::Z, N);
     const int ntx = N / sx, nty = N / sy;
     int tile[3];
@@ -234,13 +221,12 @@ __global__ __launch_bounds__(BLOCK) void spread_tile_kernel(const cplx<T>* __res
     const T* r = R + 9 * int64_t(blockIdx.x);
     const double cm = __longlong_as_double((long long)*cmax);
     const bool finite = cm < INFINITY;
-    const double pow2 = pow2_below(fmin(TileSum<T>::top / (8.0 * cm), std::is_same<T, float>::value ? 1e37 : 1e300));
-    const T scale = cm > 0.0 && finite ? T(pow2) : T(0);
-    const T inv = cm > 0.0 ? T(1.0 / pow2) : T(0);
+    const double pow2 = pow2_below(fmin(kTileTop / cm, 1e300));
+    const double scale = cm > 0.0 && finite ? pow2 : 0.0, inv = cm > 0.0 ? 1.0 / pow2 : 0.0;
     for (int i = int(threadIdx.x); i < S::WORDS; i += BLOCK) acc[i] = 0;
     __syncthreads();
     const T half_box = T(0.5) * T(n_m);
-    const typename TileSum<T>::Fixed fixed;
+    const Fixed64 fixed;
     float rf[9], lo[3], hi[3];
 #pragma unroll
     for (int a = 0; a < 9; ++a) rf[a] = float(sign * r[a]);
@@ -250,9 +236,8 @@ __global__ __launch_bounds__(BLOCK) void spread_tile_kernel(const cplx<T>* __res
         hi[a] = float(t0[a] + dim[a] + 1);
     }
     box_samples<PLANAR>(rf, n_m, lo, hi, uniform(int(threadIdx.x) >> 6), BLOCK / 64, [&](int i, int j, int k) {
-        cplx<T> v = c[(k * n_m + j) * n_m + i];
-        v.re *= scale;
-        v.im *= scale;
+        const cplx<T> v = c[(k * n_m + j) * n_m + i];
+        const double v_re = double(v.re) * scale, v_im = double(v.im) * scale;
         const T bx = T(i) - half_box, by = T(j) - half_box, bz = PLANAR ? T(0) : T(k) - half_box;
         T wt[3][4];
         int b[3];
@@ -271,15 +256,15 @@ __global__ __launch_bounds__(BLOCK) void spread_tile_kernel(const cplx<T>* __res
             for (int cy = 0; cy < 4; ++cy) {
                 const int iy = b[1] + cy;
                 if (unsigned(iy) >= unsigned(sy)) continue;
-                const T wyz = PLANAR ? wt[1][cy] : wt[1][cy] * wt[2][cz];
-                const T row_re = v.re * wyz, row_im = v.im * wyz;
-                A* row = acc + (iz * S::Y + iy) * S::PITCH;
+                const double wyz = PLANAR ? double(wt[1][cy]) : double(wt[1][cy] * wt[2][cz]);
+                const double row_re = v_re * wyz, row_im = v_im * wyz;
+                unsigned long long* row = acc + (iz * S::Y + iy) * S::PITCH;
 #pragma unroll
                 for (int cx = 0; cx < 4; ++cx) {
                     const int ix = b[0] + cx;
                     if (unsigned(ix) >= unsigned(sx)) continue;
-                    atomicAdd(row + ix, fixed(row_re * wt[0][cx]));
-                    atomicAdd(row + S::IMAG + ix, fixed(row_im * wt[0][cx]));
+                    atomicAdd(row + ix, fixed(row_re * double(wt[0][cx])));
+                    atomicAdd(row + S::IMAG + ix, fixed(row_im * double(wt[0][cx])));
                 }
             }
         }
@@ -287,10 +272,9 @@ __global__ __launch_bounds__(BLOCK) void spread_tile_kernel(const cplx<T>* __res
     __syncthreads();
     for (int i = int(threadIdx.x); i < sx * sy * sz; i += BLOCK) {
         const int ix = i % sx, iy = (i / sx) % sy, iz = i / (sx * sy);
-        const A* a = acc + (iz * S::Y + iy) * S::PITCH + ix;
+        const unsigned long long* a = acc + (iz * S::Y + iy) * S::PITCH + ix;
         const int ux = (t0[0] + ix + N) % N, uy = (t0[1] + iy + N) % N, uz = PLANAR ? 0 : (t0[2] + iz + N) % N;
-        using I = typename std::conditional<std::is_same<T, double>::value, long long, int>::type;
-        cplx<T> v = mk(T(I(a[0])) * inv, T(I(a[S::IMAG])) * inv);
+        cplx<T> v = mk(T(double((long long)a[0]) * inv), T(double((long long)a[S::IMAG]) * inv));
         // a transform of any value that is not finite is NaN everywhere
         if (!finite) v = mk(T(NAN), T(NAN));
         g[(int64_t(uz) * N + uy) * N + ux] = v;
