@@ -15,6 +15,7 @@
 // quaternion chain rule in FP64.  Per-sample weight gradients stay in
 // registers across the pose tile and are written once per tile.
 #include <algorithm>
+#include <limits>
 #include <type_traits>
 
 #include "block_order.hpp"
@@ -676,7 +677,7 @@ __global__ void rho_from_c_kernel(const T* __restrict__ w_m, const T* __restrict
 __global__ void fixed_pose_kernel(const double* __restrict__ poses, int64_t B, double* __restrict__ out,
                                   unsigned long long* __restrict__ maxima) {
     const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b < 3) maxima[b] = 0;
+    if (b < 2) maxima[b] = 0;
     if (b >= B) return;
     double r[9];
     quat_rot(poses + 7 * b + 3, r);
@@ -684,39 +685,26 @@ __global__ void fixed_pose_kernel(const double* __restrict__ poses, int64_t B, d
     for (int a = 0; a < 9; ++a) out[9 * b + a] = r[a];
 }
 
-// maxima[0] = largest finite |Re c_k| or |Im c_k|, maxima[1] = largest finite |s_b|, as the bits of
-// non-negative doubles (which order like integers); maxima[2] = 1 if some rho_M or w_M is not finite
+// maxima[0] = largest |Re c_k| or |Im c_k| of the finite rho_M and w_M (infinite where their product
+// overflows), as the bits of a non-negative double (which order like integers); maxima[1] = 1 if some
+// rho_M or w_M is not finite
 template <typename T>
 __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restrict__ rho_m, const T* __restrict__ w_m,
-                                                        int64_t K, const double* __restrict__ gscale, int64_t B,
-                                                        unsigned long long* __restrict__ maxima) {
-    __shared__ unsigned long long sh[2][4];
-    const int64_t i0 = int64_t(blockIdx.x) * 256 + threadIdx.x, step = int64_t(gridDim.x) * 256;
-    double m[2] = {0.0, 0.0};
+                                                        int64_t K, unsigned long long* __restrict__ maxima) {
+    __shared__ unsigned long long sh[4];
+    double m = 0.0;
     bool odd = false;
-    for (int64_t k = i0; k < K; k += step) {
+    for (int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x; k < K; k += int64_t(gridDim.x) * 256) {
         const cplx<T> r = rho_m[k];
         const T w = w_m[k];
-        odd |= !((r.re - r.re) + (r.im - r.im) + (w - w) == T(0));
-        const cplx<T> c = r * w;
-        const double a = fabs(double(c.re)), b = fabs(double(c.im));
-        if (a < INFINITY) m[0] = fmax(m[0], a);
-        if (b < INFINITY) m[0] = fmax(m[0], b);
+        const bool plain = (r.re - r.re) + (r.im - r.im) + (w - w) == T(0);
+        odd |= !plain;
+        if (plain) m = fmax(m, fmax(fabs(double(r.re) * double(w)), fabs(double(r.im) * double(w))));
     }
-    for (int64_t b = i0; b < B; b += step) {
-        const double s = fabs(gscale ? gscale[b] : 1.0);
-        if (s < INFINITY) m[1] = fmax(m[1], s);
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        for (int off = 32; off > 0; off >>= 1) m[q] = fmax(m[q], __shfl_xor(m[q], off));
-        if ((threadIdx.x & 63) == 0) sh[q][threadIdx.x >> 6] = __double_as_longlong(m[q]);
-    }
-    if (__syncthreads_or(odd) && threadIdx.x == 0) atomicMax(maxima + 2, 1ull);
-    if (threadIdx.x < 2) {
-        const unsigned long long* v = sh[threadIdx.x];
-        atomicMax(maxima + threadIdx.x, max(max(v[0], v[1]), max(v[2], v[3])));
-    }
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = __double_as_longlong(m);
+    if (__syncthreads_or(odd) && threadIdx.x == 0) atomicMax(maxima + 1, 1ull);
+    if (threadIdx.x == 0) atomicMax(maxima, max(max(sh[0], sh[1]), max(sh[2], sh[3])));
 }
 
 // A block owns a tile of the fixed grid and a range of poses: for every pose
@@ -725,11 +713,16 @@ __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restric
 // pose range) or to its range's partial grid.  It replaces one global atomic
 // pair per tap, at 23 billion a second: 32 poses of a 32^3 box on 64^3 nodes
 // 5.9 -> 0.33 ms.  Bound by LDS adds and VALU issue.
-// Sums are 64-bit integers, so runs repeat bit for bit.  FP32 terms are rounded
-// to 2^-30 of the largest c_k s_b, FP64 ones to at most 2^-55 of it with the
-// sums moved to FP64 registers every kFixedFlush poses.  A term that is not
-// finite is a flag of its node, for an infinity of either sign or, as both, NaN.
-constexpr int kFixedFlush = 16;
+// Sums of a pose are 64-bit integers in units of at most 2^-57 max|c_k| |s_b|, and
+// move to FP64 registers after each pose, in order: runs repeat bit for bit, and
+// poses of any scale keep their digits beside larger ones (one scale for all
+// poses left three of a pose at 1e-6 of the largest, in FP32).  Moving costs 200
+// instructions a wave, a pose's samples some thousands.  On the torus at most 8
+// images of the body meet, the splines of each sum to little over 1, and 2^58 an
+// image leaves room for 32 before a sum reaches 2^63.
+// A term that is not finite is a flag of its node, for an infinity of either sign
+// or, as both, NaN.
+constexpr double kFixedTop = 288230376151711744.0;  // 2^58
 template <typename T>
 __device__ __forceinline__ void flag_term(unsigned* flags, int words, int node, T v) {
     const unsigned bit = 1u << (node % 32);
@@ -750,7 +743,6 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                                                                 const unsigned long long* __restrict__ maxima,
                                                                 cplx<T>* __restrict__ out) {
     using S = SpreadTile<PLANAR>;
-    constexpr bool WIDE = std::is_same<T, double>::value;
     constexpr int OWN = S::X * S::Y * S::Z / kTileBlock;  // nodes a thread stores
     __shared__ unsigned long long acc[S::WORDS];
     constexpr int FLAGS = S::X * S::Y * S::Z / 32;  // words per sign and part
@@ -760,18 +752,14 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
     const int tile = int(scattered_tile(int64_t(blockIdx.x / unsigned(ranges)), tiles, step));
     const int t0[3] = {(tile % ntx) * S::X, ((tile / ntx) % nty) * S::Y, PLANAR ? 0 : (tile / (ntx * nty)) * S::Z};
     const int dim[3] = {min(S::X, N - t0[0]), min(S::Y, N - t0[1]), PLANAR ? 1 : min(S::Z, N - t0[2])};
-    const double cm = __longlong_as_double((long long)maxima[0]), sm = __longlong_as_double((long long)maxima[1]);
-    const double top = WIDE ? 1152921504606846976.0 / (8.0 * kFixedFlush) : 1073741824.0;  // 2^60, 2^30
-    const bool some = cm > 0.0 && sm > 0.0;
-    const double pow2 = some ? pow2_below(fmin(top / (cm * sm), WIDE ? 1e300 : 1e37)) : 0.0;
-    const double inv = some ? 1.0 / pow2 : 0.0;
+    const double cm = __longlong_as_double((long long)maxima[0]);
     for (int i = int(threadIdx.x); i < S::WORDS; i += kTileBlock) acc[i] = 0;
     for (int i = int(threadIdx.x); i < 4 * FLAGS; i += kTileBlock) bad[i] = 0;
     double sr[OWN], si[OWN];
 #pragma unroll
     for (int o = 0; o < OWN; ++o) sr[o] = si[o] = 0.0;
     __syncthreads();
-    auto flush = [&]() {
+    auto flush = [&](double inv) {
         __syncthreads();
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
@@ -788,7 +776,6 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
     const T half_box = T(0.5) * T(n_m);
     const int64_t b0 = int64_t(range) * per, b1 = b0 + per < B ? b0 + per : B;
     for (int64_t b = b0; b < b1; ++b) {
-        if (WIDE && b > b0 && (b - b0) % kFixedFlush == 0) flush();
         const double* P = rot + 9 * b;
         const double* pose = poses + 7 * b;
         T r[9], tfr[3];
@@ -819,7 +806,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
         }
         if (!finite) {  // uniform: every weight of a sample's stencil is NaN, and the stencil lies where the
                         // conversions put it; a sample without a term (a pose of scale zero) reaches nothing
-            const int64_t K = sb == T(0) && !maxima[2] ? 0 : int64_t(n_m) * n_m * (PLANAR ? 1 : n_m);
+            const int64_t K = sb == T(0) && !maxima[1] ? 0 : int64_t(n_m) * n_m * (PLANAR ? 1 : n_m);
             for (int64_t kk = int64_t(threadIdx.x); kk < K; kk += kTileBlock) {
                 const cplx<T> ck = rho_m[kk] * (w_m[kk] * sb);
                 if (ck.re == T(0) && ck.im == T(0)) continue;
@@ -847,6 +834,10 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
             }
             continue;
         }
+        // (terms that are finite are at most the largest finite T)
+        const double most = fmin(cm * fabs(double(sb)), double(std::numeric_limits<T>::max()));
+        const double pow2 = pow2_below(fmin(kFixedTop / most, 1e300));
+        bool touched = false;  // uniform
         int m0[3] = {0, 0, 0}, m1[3] = {0, 0, 0};
 #pragma unroll
         for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
@@ -866,7 +857,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                         lo[a] = float(o[a] - 2) - f;
                         hi[a] = float(o[a] + dim[a] + 1) - f;
                     }
-                    box_samples<PLANAR>(rf, n_m, lo, hi, wave, kTileBlock / 64, [&](int i, int j, int k) {
+                    touched |= box_samples<PLANAR>(rf, n_m, lo, hi, wave, kTileBlock / 64, [&](int i, int j, int k) {
                         const int kk = (k * n_m + j) * n_m + i;
                         cplx<T> ck = rho_m[kk] * (w_m[kk] * sb);
                         if (ck.re == T(0) && ck.im == T(0)) return;
@@ -882,7 +873,6 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                             b3[a] = int(fl) - 1 - o[a];
                             bspline3_weights(y - fl, wgt[a]);
                         }
-                        const T cr = T(vr), ci = T(vi);  // exact: a power of two apart
 #pragma unroll
                         for (int cz = 0; cz < (PLANAR ? 1 : 4); ++cz) {
                             const int iz = PLANAR ? 0 : b3[2] + cz;
@@ -892,32 +882,29 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
                                 const int iy = b3[1] + cy;
                                 if (unsigned(iy) >= unsigned(dim[1])) continue;
                                 const T wyz = PLANAR ? wgt[1][cy] : wgt[1][cy] * wgt[2][cz];
+                                const double row_re = vr * double(wyz), row_im = vi * double(wyz);
                                 const int row = iz * S::Y + iy;
 #pragma unroll
                                 for (int cx = 0; cx < 4; ++cx) {
                                     const int ix = b3[0] + cx;
                                     if (unsigned(ix) >= unsigned(dim[0])) continue;
-                                    const T wt = wgt[0][cx] * wyz;
                                     unsigned long long* a = acc + row * S::PITCH + ix;
                                     if (!(fin_re && fin_im)) {
+                                        const T wt = wgt[0][cx] * wyz;
                                         const int nd = row * S::X + ix;
                                         if (!fin_re) flag_term(bad, FLAGS, nd, ck.re * wt);
                                         if (!fin_im) flag_term(bad + 2 * FLAGS, FLAGS, nd, ck.im * wt);
                                     }
-                                    if constexpr (WIDE) {
-                                        atomicAdd(a, fixed(cr * wt));
-                                        atomicAdd(a + S::IMAG, fixed(ci * wt));
-                                    } else {
-                                        atomicAdd(a, (unsigned long long)(long long)__float2int_rn(cr * wt));
-                                        atomicAdd(a + S::IMAG, (unsigned long long)(long long)__float2int_rn(ci * wt));
-                                    }
+                                    atomicAdd(a, fixed(row_re * double(wgt[0][cx])));
+                                    atomicAdd(a + S::IMAG, fixed(row_im * double(wgt[0][cx])));
                                 }
                             }
                         }
                     });
                 }
+        if (touched) flush(1.0 / pow2);
     }
-    flush();
+    __syncthreads();  // flags of a pose that is not finite
     const int64_t G = PLANAR ? int64_t(N) * N : int64_t(N) * N * N;
     cplx<T>* dst = out + int64_t(range) * G;
 #pragma unroll
@@ -947,8 +934,8 @@ int64_t fixed_tiles(int N, bool planar) {
                   : up(SpreadTile<false>::X) * up(SpreadTile<false>::Y) * up(SpreadTile<false>::Z);
 }
 
-// R of every pose, then the maxima in the last 32 bytes
-constexpr size_t kFixedTail = 32;
+// R of every pose, then the maxima in the last 16 bytes
+constexpr size_t kFixedTail = 16;
 size_t fixed_table_bytes(int64_t B) { return (sizeof(double) * 9 * size_t(B) + 15) / 16 * 16 + kFixedTail; }
 
 }  // namespace
@@ -1103,9 +1090,8 @@ hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool
     auto* part = reinterpret_cast<cplx<T>*>(static_cast<char*>(ws) + fixed_table_bytes(B));
     const auto* rm = static_cast<const cplx<T>*>(rho_m);
     hipLaunchKernelGGL(fixed_pose_kernel, dim3(unsigned((B + 127) / 128)), dim3(128), 0, s, poses, B, rot, maxima);
-    const int64_t longest = std::max(K, B);
-    hipLaunchKernelGGL(fixed_max_kernel<T>, dim3(unsigned(std::min<int64_t>((longest + 255) / 256, 256))), dim3(256), 0,
-                       s, rm, w_m, K, grad_scale, B, maxima);
+    hipLaunchKernelGGL(fixed_max_kernel<T>, dim3(unsigned(std::min<int64_t>((K + 255) / 256, 256))), dim3(256), 0, s, rm,
+                       w_m, K, maxima);
     const int64_t tiles = fixed_tiles(N, planar);
     int64_t ranges = 1;
     if (ws_bytes >= fixed_cotangent_bytes<T>(B, N, planar, true))

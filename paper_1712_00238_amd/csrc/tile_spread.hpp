@@ -4,8 +4,6 @@
 // and by the fixed field's cotangent (all poses per tile).
 #pragma once
 
-#include <type_traits>
-
 #include "common.hpp"
 
 namespace sdf {
@@ -28,12 +26,14 @@ constexpr int kTileBlock = 256;
 
 // Calls f(i, j, k) for every body sample x = (i, j, k) - n_m / 2 whose position
 // R x (r: FP32 rows of R) lies in the box [lo, hi), and for a few outside it
-// (within 0.02, or on a line that an edge of the box nearly runs along: f tests exactly).  A wave takes 64 body lines along i at a time
+// (within 0.02, or on a line that an edge of the box nearly runs along: f tests
+// exactly).  A wave takes 64 body lines along i at a time
 // (every waves-th line, so that all of a block's waves share few lines); the
 // box cuts each line to one run of samples, and the runs are laid end to end
-// over the lanes, so f runs with full waves.  No barrier.
+// over the lanes, so f runs with full waves.  No barrier.  False (for all waves
+// alike) if the box holds no line.
 template <bool PLANAR, typename F>
-__device__ __forceinline__ void box_samples(const float r[9], int n_m, const float lo[3], const float hi[3], int wave,
+__device__ __forceinline__ bool box_samples(const float r[9], int n_m, const float lo[3], const float hi[3], int wave,
                                             int waves, F&& f) {
     constexpr int D = PLANAR ? 2 : 3;
     const float half = 0.5f * float(n_m);
@@ -52,7 +52,7 @@ __device__ __forceinline__ void box_samples(const float r[9], int n_m, const flo
         }
         first[a] = max(0, int(ceilf(mid - ext)));
         last[a] = min(n_m - 1, int(floorf(mid + ext)));
-        if (last[a] < first[a]) return;  // uniform
+        if (last[a] < first[a]) return false;  // uniform
     }
     const int nj = last[1] - first[1] + 1, lines = nj * (last[2] - first[2] + 1);
     const int lane = int(threadIdx.x) & 63;
@@ -95,6 +95,7 @@ __device__ __forceinline__ void box_samples(const float r[9], int n_m, const flo
             if (p < total) f(i, first[1] + ql % nj, first[2] + ql / nj);
         }
     }
+    return true;
 }
 
 // 64-bit integer nearest v, |v| < 2^62, in two exact steps: adding m = 1.5 2^52

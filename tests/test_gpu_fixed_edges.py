@@ -1,5 +1,6 @@
 """score_grad_fixed at the edges of its inputs: poses and terms that are not
-finite, and long body lines almost along the grid's axes."""
+finite, long body lines almost along the grid's axes, scales and coefficients of
+uneven size."""
 
 import numpy as np
 import pytest
@@ -152,3 +153,44 @@ def test_long_lines_almost_along_an_axis(ctxs, n, nm, angle, t):
     got = fixed(ctxs["f64"], gf, rho_m, w, gm, poses, s).reshape(gf.n[::-1])
     ref = og.fixed_cotangent(oc.moving_coefficients(rho_m, w), osp.body_positions(nm, True), poses, s, gf.n[::-1])
     assert np.max(np.abs(got - ref)) <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("small", [1e-3, 1e-6, 1e-12, 1e-24])
+@pytest.mark.parametrize("nm,planar", [(9, False), (13, True)])
+def test_poses_of_small_scale_keep_their_digits(ctxs, dtype, small, nm, planar):
+    """Softmax-like scales on poses that do not meet: each pose's nodes are as
+    accurate as if it were alone (positions of 40 cells and weights rounded once
+    each: 1e-5 and 1e-13 of the pose's largest sum)."""
+    gf, gm, rho_m, w, poses, s = case(80, nm, planar, 20, nm)
+    poses[:, :3] = [10.3, 20.6, 0.0 if planar else 30.2]
+    poses[1::2, 0] += 40.0  # 0 and 40 apart, 9 sqrt 3 + 4 and 13 sqrt 2 + 4 reach 20
+    s = np.where(np.arange(20) % 2, small * s, s)
+    xb, shape = osp.body_positions(nm, planar), gf.n[::-1]
+    flush_print("small scales", dtype, small, nm, planar)
+    got = fixed(ctxs[dtype], gf, rho_m, w, gm, poses, s).reshape(shape)
+    c = oc.moving_coefficients(rho_m, w)
+    for part in (0, 1):
+        ref = og.fixed_cotangent(c, xb, poses[part::2], s[part::2], shape)
+        on = np.zeros(shape, dtype=bool)
+        on[..., 40 * part:40 * part + 40] = True
+        assert np.max(np.abs(got - ref)[on]) <= (1e-13 if dtype == "f64" else 1e-5) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_one_large_coefficient_leaves_the_others_theirs(ctxs, dtype):
+    """A coefficient 1e4 (FP64: 1e2) times the rest: nodes away from it are as accurate
+    as without it."""
+    gf, gm, rho_m, w, poses, s = case(40, 15, False, 6, 4)
+    poses[:, :3] = 20.0
+    large = 1e4 if dtype == "f32" else 1e2
+    rho_m[0, 0, 0] = large * (1 + 1j)
+    one = np.zeros(rho_m.shape)
+    one[0, 0, 0] = 1.0
+    xb, shape = osp.body_positions(15, False), gf.n[::-1]
+    away = og.fixed_cotangent(one.ravel(), xb, poses, np.ones(6), shape) == 0
+    ref = og.fixed_cotangent(oc.moving_coefficients(rho_m, w), xb, poses, s, shape)
+    flush_print("one large coefficient", dtype)
+    err = np.abs(fixed(ctxs[dtype], gf, rho_m, w, gm, poses, s).reshape(shape) - ref)[away].max()
+    flush_print("error", err / np.abs(ref[away]).max())
+    assert err <= (1e-13 if dtype == "f64" else 1e-5) * np.abs(ref[away]).max()
