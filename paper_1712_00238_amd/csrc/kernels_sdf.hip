@@ -219,6 +219,7 @@ __device__ __forceinline__ void wave_nearest(const double* __restrict__ qs, cons
     best = INFINITY;          // over the samples this lane has seen
     double bound = INFINITY;  // over those its node's four lanes have seen
     sbest = -1;
+    int first = -1;  // the leaf of the first bound
     auto leaf_nearest = [&](int leaf) {
         const int64_t s0 = int64_t(leaf) * kLeaf;
         const int cnt = int(ns - s0 < kLeaf ? ns - s0 : kLeaf);
@@ -251,7 +252,7 @@ __device__ __forceinline__ void wave_nearest(const double* __restrict__ qs, cons
                 }
             }
             id = __builtin_amdgcn_readfirstlane(id);
-            if (l == 0) leaf_nearest(id);
+            if (l == 0) leaf_nearest(first = id);
             else at = kFan * id;
         }
     }
@@ -268,7 +269,7 @@ __device__ __forceinline__ void wave_nearest(const double* __restrict__ qs, cons
         while (w.climb(tr.levels)) {
             const int c = w.take();
             if (w.l == 0) {
-                leaf_nearest(c);
+                if (c != first) leaf_nearest(c);  // that one is seen
             } else {
                 w.down(c);
                 test();
@@ -282,6 +283,58 @@ __device__ __forceinline__ void wave_nearest(const double* __restrict__ qs, cons
         nearer(d1, s1, js, best, sbest);
     }
 }
+
+// eq. 3a: lambda1 gb(xi / R - 1) + i lambda2 gb(xi / R + 1), FP64, defined on the
+// boundary too (no floor); gb truncates at |x| > eps
+template <typename T>
+__device__ __forceinline__ cplx<T> dsl_value(double xi, const ParamDesc& prm) {
+    const double x1 = xi / prm.radius - 1.0, x2 = xi / prm.radius + 1.0;
+    const double c = 1.0 / (2.5066282746310002 * prm.sigma);
+    const double h = -0.5 / (prm.sigma * prm.sigma);
+    const double re = fabs(x1) <= prm.eps ? prm.lambda1 * c * exp(h * x1 * x1) : 0.0;
+    const double im = fabs(x2) <= prm.eps ? prm.lambda2 * c * exp(h * x2 * x2) : 0.0;
+    return mk(T(re), T(im));
+}
+// membership of p from its nearest sample j
+__device__ __forceinline__ int side_of(const double* __restrict__ q, const double* __restrict__ nrm, int64_t j,
+                                       double px, double py, double pz) {
+    const double dot =
+        (px - q[3 * j]) * nrm[3 * j] + (py - q[3 * j + 1]) * nrm[3 * j + 1] + (pz - q[3 * j + 2]) * nrm[3 * j + 2];
+    return dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
+}
+// The kernel sum of a node at squared distance `best` from its nearest sample:
+// exp(-(r - 1)^2 / (2 sigma^2)) = 2^(-u^2) with u = (r - 1) gs,
+// gs = sqrt(log2(e) / 2) / sigma, and u = eta (gs / xi) - gs
+template <typename T, int PHI>
+struct NodeSum {
+    T inv_xi2, gs, inv_xi_gs;
+    T re = T(0), im = T(0);  // sums of coef (1 - r^2) and of coef eta
+    __device__ __forceinline__ NodeSum(double best, double xi, double sigma) {
+        const double gs64 = std::sqrt(0.5 * 1.4426950408889634) / sigma;
+        inv_xi2 = T(1.0 / best);
+        gs = T(gs64);
+        inv_xi_gs = T(gs64 / xi);
+    }
+    __device__ __forceinline__ void add(T d2, T wdot) {
+        const T inv_eta = fast_rsqrt(d2);
+        const T eta = d2 * inv_eta;
+        T coef = wdot * inv_eta;
+        if constexpr (PHI == kPhiSkeletal) {
+            const T u = eta * inv_xi_gs - gs;
+            coef *= dev_exp2(-u * u);
+        }
+        const T den = T(1) + d2 * inv_xi2;
+        coef *= dev_rcp(den * den);
+        re += coef * (T(1) - d2 * inv_xi2);
+        im += coef * eta;
+    }
+    __device__ __forceinline__ cplx<T> value(int side, double best, double xi, const ParamDesc& prm) const {
+        const double lam = side > 0 ? prm.lambda1 : -prm.lambda2;
+        const T scale = T(lam / (2.0 * 3.14159265358979323846 * prm.sigma * best));
+        const T im_sign = side > 0 ? T(-2) : T(2);  // P = (1 - r^2) -+ 2 i r, applied once per node
+        return mk(re * scale, im * (im_sign * (T(1.0 / xi) * scale)));
+    }
+};
 
 // PHI: the kernel of eq. 13 (kPhi* in launch.hpp): skeletal (eq. 15),
 // inverse-square (eq. 15 with the medial Gaussian at its peak: the pair
@@ -337,24 +390,12 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
         __syncthreads();
     }
     const int64_t jb = sbest >= 0 ? js[sbest] : 0;
-    const double dot = (px - q[3 * jb]) * nrm[3 * jb] + (py - q[3 * jb + 1]) * nrm[3 * jb + 1] +
-                       (pz - q[3 * jb + 2]) * nrm[3 * jb + 2];
-    const int pmc = dot > 0.0 ? 1 : (dot < 0.0 ? -1 : 0);
+    const int pmc = side_of(q, nrm, jb, px, py, pz);
     const double xi_abs64 = sqrt(best);
     const bool writer = valid && gq == 0 && sub == 0;
     cplx<T>* dst = out + (int64_t(k) * g.ny + j) * g.nx + i;
     if constexpr (PHI == kPhiDsl) {
-        // eq. 3a: lambda1 gb(xi / R - 1) + i lambda2 gb(xi / R + 1), FP64, defined
-        // on the boundary too (no floor); gb truncates at |x| > eps
-        if (writer) {
-            const double xi = pmc * xi_abs64;
-            const double x1 = xi / prm.radius - 1.0, x2 = xi / prm.radius + 1.0;
-            const double c = 1.0 / (2.5066282746310002 * prm.sigma);
-            const double h = -0.5 / (prm.sigma * prm.sigma);
-            const double re = fabs(x1) <= prm.eps ? prm.lambda1 * c * exp(h * x1 * x1) : 0.0;
-            const double im = fabs(x2) <= prm.eps ? prm.lambda2 * c * exp(h * x2 * x2) : 0.0;
-            *dst = mk(T(re), T(im));
-        }
+        if (writer) *dst = dsl_value<T>(pmc * xi_abs64, prm);
         return;
     }
     const bool live = valid && pmc != 0 && xi_abs64 >= prm.xi_floor;
@@ -363,25 +404,7 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
     const double r2max64 = (1.0 + prm.eps) * (1.0 + prm.eps) * best;
     const T r2lo = T(r2max64 * (1.0 - kBallBand)), r2hi = T(r2max64 * (1.0 + kBallBand));
     const float r2mid = float(r2max64), r2gap = float(r2max64 * kBallBand), r2above = r2mid * (1.f + 2.4e-7f);
-    const T inv_xi = T(1.0 / xi_abs64), inv_xi2 = T(1.0 / best);
-    // exp(-(r - 1)^2 / (2 sigma^2)) = 2^(-u^2) with u = (r - 1) gs,
-    // gs = sqrt(log2(e) / 2) / sigma, and u = eta (gs / xi) - gs
-    const double gs64 = std::sqrt(0.5 * 1.4426950408889634) / prm.sigma;
-    const T gs = T(gs64), inv_xi_gs = T(gs64 / xi_abs64);
-    T acc_re = T(0), acc_im = T(0);  // sums of coef (1 - r^2) and of coef eta
-    auto pair_term = [&](T d2, T wdot) {
-        const T inv_eta = fast_rsqrt(d2);
-        const T eta = d2 * inv_eta;
-        T coef = wdot * inv_eta;
-        if constexpr (PHI == kPhiSkeletal) {
-            const T u = eta * inv_xi_gs - gs;
-            coef *= dev_exp2(-u * u);
-        }
-        const T den = T(1) + d2 * inv_xi2;
-        coef *= dev_rcp(den * den);
-        acc_re += coef * (T(1) - d2 * inv_xi2);
-        acc_im += coef * eta;
-    };
+    NodeSum<T, PHI> acc(best, xi_abs64, prm.sigma);
     auto edge_in = [&](int64_t s) {  // the ball test of sample s in FP64
         return dist2(px - qs[3 * s], py - qs[3 * s + 1], pz - qs[3 * s + 2]) <= r2max64;
     };
@@ -424,7 +447,7 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
             }
             if (STATS && mine) vis2 += 4;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) pair_term(T(d2[r]), T(wd[r]));
+            for (int r = 0; r < 4; ++r) acc.add(T(d2[r]), T(wd[r]));
         };
         // the next group's operands load under this group's terms; seven waves per SIMD hide the rest
         float u0 = load1(sub), v0 = load2(sub);
@@ -446,14 +469,24 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
         for (int a = 4 * sub + gq; a < cnt; a += 4 * WPB) {
             const int64_t s = s0 + a;
             const T dx = T(px - qs[3 * s]), dy = T(py - qs[3 * s + 1]), dz = T(pz - qs[3 * s + 2]);
-            const T wx = T(wn[3 * s]), wy = T(wn[3 * s + 1]), wz = T(wn[3 * s + 2]);
+            T wx, wy, wz;
+            if constexpr (FAST) {
+                const int64_t o = (s >> 4) * 64 + (s & 15);
+                wx = T(rec2[o]);
+                wy = T(rec2[o + 16]);
+                wz = T(rec2[o + 32]);
+            } else {
+                wx = T(wn[3 * s]);
+                wy = T(wn[3 * s + 1]);
+                wz = T(wn[3 * s + 2]);
+            }
             const T d2 = dx * dx + dy * dy + dz * dz;
             if (STATS) ++vis2;
             if (d2 <= r2hi) {
                 const bool in = d2 <= r2lo || edge_in(s);
                 if (in) {
                     if (STATS) ++inball;
-                    pair_term(d2, dx * wx + dy * wy + dz * wz);
+                    acc.add(d2, dx * wx + dy * wy + dz * wz);
                 }
             }
         }
@@ -520,22 +553,22 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
     }
 #pragma unroll
     for (int off = 16; off <= 32; off <<= 1) {
-        acc_re += __shfl_xor(acc_re, off);
-        acc_im += __shfl_xor(acc_im, off);
+        acc.re += __shfl_xor(acc.re, off);
+        acc.im += __shfl_xor(acc.im, off);
     }
     if constexpr (WPB == 4) {
         double* sh_im = reinterpret_cast<double*>(sh_idx);  // 64 sums fit
         if (gq == 0) {
-            sh_best[16 * sub + n] = double(acc_re);
-            sh_im[16 * sub + n] = double(acc_im);
+            sh_best[16 * sub + n] = double(acc.re);
+            sh_im[16 * sub + n] = double(acc.im);
         }
         __syncthreads();
-        acc_re = T(sh_best[n]);
-        acc_im = T(sh_im[n]);
+        acc.re = T(sh_best[n]);
+        acc.im = T(sh_im[n]);
 #pragma unroll
         for (int wv = 1; wv < 4; ++wv) {
-            acc_re += T(sh_best[16 * wv + n]);
-            acc_im += T(sh_im[16 * wv + n]);
+            acc.re += T(sh_best[16 * wv + n]);
+            acc.im += T(sh_im[16 * wv + n]);
         }
     }
     if constexpr (STATS) {
@@ -546,16 +579,7 @@ __global__ __launch_bounds__(64 * WPB, STATS ? 3 : (FAST ? 7 : 4)) void sdf_buil
             if (lane == 0) atomicAdd(stats + a, c[a]);
         }
     }
-    if (writer) {
-        cplx<T> res = mk(T(0), T(0));
-        if (live) {
-            const double lam = pmc > 0 ? prm.lambda1 : -prm.lambda2;
-            const T scale = T(lam / (2.0 * 3.14159265358979323846 * prm.sigma * best));
-            const T im_sign = pmc > 0 ? T(-2) : T(2);  // P = (1 - r^2) -+ 2 i r, applied once per node
-            res = mk(acc_re * scale, acc_im * (im_sign * (inv_xi * scale)));
-        }
-        *dst = res;
-    }
+    if (writer) *dst = live ? acc.value(pmc, best, xi_abs64, prm) : mk(T(0), T(0));
 }
 
 // brick of nodes handled by one block
@@ -563,6 +587,68 @@ struct Brick {
     int bx, by, bz;
 };
 __host__ __device__ inline Brick brick_shape(int nz) { return nz == 1 ? Brick{16, 16, 1} : Brick{8, 8, 4}; }
+
+// Few samples, many nodes: a thread per node walks all samples in their given
+// order, with no sort and no tree (both passes' decisions are those of the tree
+// kernels: FP64, the lowest index on ties).  Sample indices are uniform, so
+// positions come through the scalar cache; w n goes through LDS.  Bound by VALU
+// issue, some 30 instructions a pair; on small grids a chain of one sample after
+// the other.
+constexpr int kFewMax = 576;
+template <typename T, int PHI>
+__global__ __launch_bounds__(kSdfBlock) void sdf_few_kernel(const double* __restrict__ q,
+                                                            const double* __restrict__ nrm,
+                                                            const double* __restrict__ w, int ns, GridDesc g,
+                                                            ParamDesc prm, cplx<T>* __restrict__ out, int64_t brick0) {
+    __shared__ v4<T> wn[kFewMax];
+    if constexpr (PHI != kPhiDsl) {
+        for (int a = int(threadIdx.x); a < ns; a += kSdfBlock)
+            wn[a] = v4<T>{T(w[a] * nrm[3 * a]), T(w[a] * nrm[3 * a + 1]), T(w[a] * nrm[3 * a + 2]), T(0)};
+        __syncthreads();
+    }
+    const Brick br = brick_shape(g.nz);
+    const int64_t nbx = (g.nx + br.bx - 1) / br.bx, nby = (g.ny + br.by - 1) / br.by, blk = brick0 + blockIdx.x;
+    const int t = int(threadIdx.x);
+    const int i = int(blk % nbx) * br.bx + t % br.bx, j = int(blk / nbx % nby) * br.by + t / br.bx % br.by,
+              k = int(blk / (nbx * nby)) * br.bz + t / (br.bx * br.by);
+    if (i >= g.nx || j >= g.ny || k >= g.nz) return;
+    const double px = g.ox + g.h * i, py = g.oy + g.h * j, pz = g.oz + g.h * k;
+    double best = INFINITY;
+    int jb = 0;
+#pragma unroll 4
+    for (int a = 0; a < ns; ++a) {
+        const double d2 = dist2(px - q[3 * a], py - q[3 * a + 1], pz - q[3 * a + 2]);
+        if (d2 < best) {
+            best = d2;
+            jb = a;
+        }
+    }
+    const int side = side_of(q, nrm, jb, px, py, pz);
+    const double xi = sqrt(best);
+    cplx<T>* dst = out + (int64_t(k) * g.ny + j) * g.nx + i;
+    if constexpr (PHI == kPhiDsl) {
+        *dst = dsl_value<T>(side * xi, prm);
+        return;
+    }
+    if (!(side != 0 && xi >= prm.xi_floor)) {
+        *dst = mk(T(0), T(0));
+        return;
+    }
+    const double r2max = (1.0 + prm.eps) * (1.0 + prm.eps) * best;
+    const T r2lo = T(r2max * (1.0 - kBallBand)), r2hi = T(r2max * (1.0 + kBallBand));
+    NodeSum<T, PHI> acc(best, xi, prm.sigma);
+#pragma unroll 2
+    for (int a = 0; a < ns; ++a) {
+        const double ex = px - q[3 * a], ey = py - q[3 * a + 1], ez = pz - q[3 * a + 2];
+        const T dx = T(ex), dy = T(ey), dz = T(ez);
+        const T d2 = dx * dx + dy * dy + dz * dz;
+        if (d2 <= r2hi && (d2 <= r2lo || dist2(ex, ey, ez) <= r2max)) {
+            const v4<T> m = wn[a];
+            acc.add(d2, dx * m.x + dy * m.y + dz * m.z);
+        }
+    }
+    *dst = acc.value(side, best, xi, prm);
+}
 
 // Samples in Hilbert order with per-tile bounding boxes.
 struct SampleTiles {
@@ -1646,6 +1732,31 @@ __global__ void zero_grads_kernel(double* __restrict__ gq, double* __restrict__ 
     }
 }
 
+template <typename T, int PHI>
+void enqueue_few(const double* q, const double* n, const double* w, int64_t ns, const GridDesc& g, const ParamDesc& p,
+                 cplx<T>* out, hipStream_t s) {
+    const int64_t bricks = brick_count(g);
+    for (int64_t b0 = 0; b0 < bricks; b0 += kLaunchThreads / kSdfBlock) {
+        const int64_t count = std::min(bricks - b0, kLaunchThreads / kSdfBlock);
+        hipLaunchKernelGGL((sdf_few_kernel<T, PHI>), dim3(unsigned(count)), dim3(kSdfBlock), 0, s, q, n, w, int(ns), g, p,
+                           out, b0);
+    }
+}
+// Up to how many samples that is the faster way.  On small grids it is a serial
+// chain of 0.25 us a sample: 64 samples on 32^3 nodes 20.6 us (the tree 33.5), 200
+// 57 (45).  On large ones the tree's walk costs a wave of 16 nodes as much as some
+// hundred pairs of each: on 128^3 nodes 1 sample takes 19 us (the tree 169), 64 142
+// (393), 300 610 (900), 500 1006 (1079); FP64 64 340 (483), 300 1536 (1543), 400
+// 2040 (1916); on 64^3 300 116 (150), 500 190 (190).  The signed distance alone
+// (double skin layer): 500 on 8^3 32 (32), on 128^3 315 (440).
+bool few_samples(int64_t ns, const GridDesc& g, int phi, bool wide) {
+    const int64_t nodes = int64_t(g.nx) * g.ny * g.nz;
+    if (brick_count(g) * kSdfBlock > 2 * nodes) return ns <= 64 && nodes <= 4096;  // thin grids fill few lanes
+    if (phi == kPhiDsl) return ns <= 512;
+    if (nodes < (1 << 18)) return ns <= 64;
+    return ns <= (wide || nodes < (1 << 20) ? 300 : kFewMax);
+}
+
 template <typename T, int PHI, bool FAST, bool STATS = false>
 void enqueue_build(const double* q, const double* n, const Prepared& P, int64_t ns, const GridDesc& g,
                    const ParamDesc& p, cplx<T>* out, unsigned long long* stats, hipStream_t s) {
@@ -1714,6 +1825,12 @@ hipError_t launch_sdf_build(const double* q, const double* n, const double* w, i
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(sdf_radial_kernel<T>, dim3(unsigned(brick_count(g))), dim3(kSdfBlock), 0, s, P.st, 2 * ns,
                            g, p, out);
+        return hipGetLastError();
+    }
+    if (!stats && few_samples(ns, g, phi, std::is_same<T, double>::value)) {
+        if (phi == kPhiDsl) enqueue_few<T, kPhiDsl>(q, n, w, ns, g, p, out, s);
+        else if (phi == kPhiInverseSquare) enqueue_few<T, kPhiInverseSquare>(q, n, w, ns, g, p, out, s);
+        else enqueue_few<T, kPhiSkeletal>(q, n, w, ns, g, p, out, s);
         return hipGetLastError();
     }
     const bool sums = phi == kPhiSkeletal || phi == kPhiInverseSquare;
