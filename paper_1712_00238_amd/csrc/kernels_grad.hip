@@ -217,18 +217,25 @@ __global__ __launch_bounds__(kGBlock) void grad_tile_kernel(const cplx<T>* __res
                 }
             }
         }
-        // block reduction of the per-pose sums (FP64): rows of 16 lanes, then the rows
+        // block reduction of the per-pose sums (FP64): rows of 16 lanes, then the rows;
+        // a single sum over the wave (FP64, 4096 poses of 32^3: values alone 12.4 ms, with
+        // the rows, where the compiler gathers with other registers, 14.3)
         constexpr int nacc = GRAD ? kNAcc : 1;
 #pragma unroll
         for (int a = 0; a < nacc; ++a) {
-            const double v = row16_sum(acc[a]);
-            if ((threadIdx.x & 15) == 0) red[threadIdx.x >> 4][a] = v;
+            if constexpr (GRAD) {
+                const double v = row16_sum(acc[a]);
+                if ((threadIdx.x & 15) == 0) red[threadIdx.x >> 4][a] = v;
+            } else {
+                const double v = warp_sum(acc[a]);
+                if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][a] = v;
+            }
         }
         __syncthreads();
         if (threadIdx.x < nacc) {
             double v = 0.0;
 #pragma unroll
-            for (int rw = 0; rw < kGBlock / 16; ++rw) v += red[rw][threadIdx.x];
+            for (int rw = 0; rw < kGBlock / (GRAD ? 16 : 64); ++rw) v += red[rw][threadIdx.x];
             part[(b * nsb + sb) * kNAcc + threadIdx.x] = v;
         }
         __syncthreads();
@@ -968,12 +975,14 @@ GradSplit grad_split(int64_t B, int N, int n_m, bool planar, int wmode, bool fin
     auto tiles = [&](int spt) { return box ? nt * nt * nt : (K + kGBlock * spt - 1) / (kGBlock * spt); };
     GradSplit g{tiles(kSPT), 0, kSPT, kPosesPerBlock};
     if (fine) {
-        const int64_t least = wmode ? (B + kFewGroups - 1) / kFewGroups : 1;
-        const int64_t per = std::max(g.nsb * B / kFewBlocks, least);
-        if (per < kPosesPerBlock) g.per = int(per);
-        if (g.nsb * ((B + g.per - 1) / g.per) < kFewBlocks) {
+        const int64_t least = std::min<int64_t>(wmode ? (B + kFewGroups - 1) / kFewGroups : 1, kPosesPerBlock);
+        if (g.nsb * ((B + least - 1) / least) < kFewBlocks) {
+            g.per = int(least);
             g.spt = 1;
             g.nsb = tiles(1);
+        } else {  // at most kFewBlocks: four a CU and no fifth to wait for
+            const int64_t per = (g.nsb * B + kFewBlocks - 1) / kFewBlocks;
+            g.per = int(std::min<int64_t>(std::max(per, least), kPosesPerBlock));
         }
     }
     g.npb = (B + g.per - 1) / g.per;
