@@ -322,9 +322,9 @@ size_t build_ws_bytes(sdf_ctx ctx, int64_t ns, int kind) {
 
 // workspace of one fixed-field cotangent, with partial grids for the pose
 // ranges (split) or without
-size_t fixed_ws_bytes(sdf_ctx ctx, int64_t B, int N, bool planar, bool split) {
-    return ctx->dtype == SDF_F64 ? sdf::fixed_cotangent_bytes<double>(B, N, planar, split)
-                                 : sdf::fixed_cotangent_bytes<float>(B, N, planar, split);
+size_t fixed_ws_bytes(sdf_ctx ctx, int64_t B, int N, int nm, bool planar, bool split) {
+    return ctx->dtype == SDF_F64 ? sdf::fixed_cotangent_bytes<double>(B, N, nm, planar, split)
+                                 : sdf::fixed_cotangent_bytes<float>(B, N, nm, planar, split);
 }
 
 // workspace of the pose kernels, for the finer split or the least
@@ -1484,7 +1484,7 @@ int score_grad_backward(sdf_ctx ctx, const void* rho_fixed, const sdf_grid* g_fi
     // pose table reuses the front once those kernels are done (stream order)
     const size_t rest = align_up(el * size_t(B)) + align_up(2 * el * size_t(K));
     auto moving_bytes = [&](bool fine) { return align_up(pose_ws_bytes(ctx, B, N, nm, planar, wmode, fine)) + rest; };
-    auto fixed_side = [&](bool split) { return grad_rho_fixed ? fixed_ws_bytes(ctx, B, N, planar, split) : 0; };
+    auto fixed_side = [&](bool split) { return grad_rho_fixed ? fixed_ws_bytes(ctx, B, N, nm, planar, split) : 0; };
     bool fine = !ctx->cap || moving_bytes(true) <= ctx->cap, split = !ctx->cap || fixed_side(true) <= ctx->cap;
     const size_t want = std::max(moving_bytes(fine), fixed_side(split));
     const size_t least = std::max(moving_bytes(false), fixed_side(false));
@@ -1555,7 +1555,7 @@ int score_grad_fixed(sdf_ctx ctx, const sdf_grid* g_fixed, const void* rho_movin
     const bool planar = g_fixed->n[2] == 1;
     const int N = g_fixed->n[0], nm = g_moving->n[0];
     size_t ws_bytes = 0;
-    rc = ensure_either(ctx, fixed_ws_bytes(ctx, B, N, planar, true), fixed_ws_bytes(ctx, B, N, planar, false), s,
+    rc = ensure_either(ctx, fixed_ws_bytes(ctx, B, N, nm, planar, true), fixed_ws_bytes(ctx, B, N, nm, planar, false), s,
                        &ws_bytes);
     if (rc) return rc;
     hipError_t e = ctx->dtype == SDF_F64

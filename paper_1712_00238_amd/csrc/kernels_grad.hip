@@ -680,28 +680,32 @@ __global__ void rho_from_c_kernel(const T* __restrict__ w_m, const T* __restrict
 
 // ---- cotangent of the scores with respect to rho_F (the adjoint of the
 // gather): G(p) = sum_b s_b sum_k c_k B3(p - y_kb), periodic, y_kb = R_b x_k + t_b.
-// Per pose: R (FP64).  Also clears the maxima of fixed_max_kernel.
-__global__ void fixed_pose_kernel(const double* __restrict__ poses, int64_t B, double* __restrict__ out,
-                                  unsigned long long* __restrict__ maxima) {
-    const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b < 2) maxima[b] = 0;
-    if (b >= B) return;
+// Per pose: R (FP64).
+__device__ __forceinline__ void put_rotation(const double* __restrict__ poses, int64_t b, double* __restrict__ out) {
     double r[9];
     quat_rot(poses + 7 * b + 3, r);
 #pragma unroll
     for (int a = 0; a < 9; ++a) out[9 * b + a] = r[a];
 }
+// Rotations, and the maxima of fixed_max_kernel cleared.
+__global__ void fixed_pose_kernel(const double* __restrict__ poses, int64_t B, double* __restrict__ out,
+                                  unsigned long long* __restrict__ maxima) {
+    const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (b < 2) maxima[b] = 0;
+    if (b < B) put_rotation(poses, b, out);
+}
 
 // maxima[0] = largest |Re c_k| or |Im c_k| of the finite rho_M and w_M (infinite where their product
 // overflows), as the bits of a non-negative double (which order like integers); maxima[1] = 1 if some
-// rho_M or w_M is not finite
-template <typename T>
-__global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restrict__ rho_m, const T* __restrict__ w_m,
-                                                        int64_t K, unsigned long long* __restrict__ maxima) {
-    __shared__ unsigned long long sh[4];
+// rho_M or w_M is not finite.  Small calls do the rotations and both maxima in one block and launch.
+template <typename T, int BLOCK>
+__device__ __forceinline__ void coefficient_maxima(const cplx<T>* __restrict__ rho_m, const T* __restrict__ w_m,
+                                                   int64_t K, unsigned long long* __restrict__ maxima) {
+    __shared__ double sh[BLOCK / 64];
     double m = 0.0;
     bool odd = false;
-    for (int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x; k < K; k += int64_t(gridDim.x) * 256) {
+#pragma unroll 4
+    for (int64_t k = int64_t(blockIdx.x) * BLOCK + threadIdx.x; k < K; k += int64_t(gridDim.x) * BLOCK) {
         const cplx<T> r = rho_m[k];
         const T w = w_m[k];
         const bool plain = (r.re - r.re) + (r.im - r.im) + (w - w) == T(0);
@@ -709,15 +713,37 @@ __global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restric
         if (plain) m = fmax(m, fmax(fabs(double(r.re) * double(w)), fabs(double(r.im) * double(w))));
     }
     for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = __double_as_longlong(m);
-    if (__syncthreads_or(odd) && threadIdx.x == 0) atomicMax(maxima + 1, 1ull);
-    if (threadIdx.x == 0) atomicMax(maxima, max(max(sh[0], sh[1]), max(sh[2], sh[3])));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+    const bool any = __syncthreads_or(odd);
+    if (threadIdx.x != 0) return;
+    for (int wv = 1; wv < BLOCK / 64; ++wv) m = fmax(m, sh[wv]);
+    const unsigned long long bits = __double_as_longlong(m);
+    if (gridDim.x == 1) {
+        maxima[0] = bits;
+        maxima[1] = any;
+    } else {
+        atomicMax(maxima, bits);
+        if (any) atomicMax(maxima + 1, 1ull);
+    }
+}
+template <typename T>
+__global__ __launch_bounds__(256) void fixed_max_kernel(const cplx<T>* __restrict__ rho_m, const T* __restrict__ w_m,
+                                                        int64_t K, unsigned long long* __restrict__ maxima) {
+    coefficient_maxima<T, 256>(rho_m, w_m, K, maxima);
+}
+template <typename T>
+__global__ __launch_bounds__(1024) void fixed_prep_kernel(const cplx<T>* __restrict__ rho_m, const T* __restrict__ w_m,
+                                                          int64_t K, const double* __restrict__ poses, int64_t B,
+                                                          double* __restrict__ out,
+                                                          unsigned long long* __restrict__ maxima) {
+    for (int64_t b = threadIdx.x; b < B; b += 1024) put_rotation(poses, b, out);
+    coefficient_maxima<T, 1024>(rho_m, w_m, K, maxima);
 }
 
 // A block owns a tile of the fixed grid and a range of poses: for every pose
 // and every periodic image of the tile that the turned box reaches, the samples
-// in reach add their taps to LDS sums; each node is stored once, to out (one
-// pose range) or to its range's partial grid.  It replaces one global atomic
+// in reach (DENSE: all samples, or a part of them, wrapped) add their taps to LDS
+// sums; each node is stored once, to out or to a partial grid.  It replaces one global atomic
 // pair per tap, at 23 billion a second: 32 poses of a 32^3 box on 64^3 nodes
 // 5.9 -> 0.33 ms.  Bound by LDS adds and VALU issue.
 // Sums of a pose are 64-bit integers in units of at most 2^-57 max|c_k| |s_b|, and
@@ -740,28 +766,29 @@ __device__ __forceinline__ double flagged(const unsigned* flags, int words, int 
     const bool up = (flags[node / 32] >> (node % 32)) & 1, down = (flags[words + node / 32] >> (node % 32)) & 1;
     return up ? (down ? NAN : INFINITY) : (down ? -INFINITY : 0.0);
 }
-template <typename T, bool PLANAR>
-__global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* __restrict__ rho_m,
+template <typename T, bool PLANAR, int BLOCK, bool DENSE>
+__global__ __launch_bounds__(BLOCK, BLOCK == kTileBlock ? 3 : 1) void fixed_tile_kernel(const cplx<T>* __restrict__ rho_m,
                                                                 const T* __restrict__ w_m, int n_m,
                                                                 const double* __restrict__ rot,
                                                                 const double* __restrict__ poses,
                                                                 const double* __restrict__ gscale, int64_t B,
-                                                                int64_t per, int ranges, int N, int64_t tiles, int64_t step,
+                                                                int64_t per, int grids, int parts, int N,
+                                                                int64_t tiles, int64_t step,
                                                                 const unsigned long long* __restrict__ maxima,
                                                                 cplx<T>* __restrict__ out) {
     using S = SpreadTile<PLANAR>;
-    constexpr int OWN = S::X * S::Y * S::Z / kTileBlock;  // nodes a thread stores
+    constexpr int OWN = S::X * S::Y * S::Z / BLOCK;  // nodes a thread stores
     __shared__ unsigned long long acc[S::WORDS];
     constexpr int FLAGS = S::X * S::Y * S::Z / 32;  // words per sign and part
     __shared__ unsigned bad[4 * FLAGS];
     const int ntx = (N + S::X - 1) / S::X, nty = (N + S::Y - 1) / S::Y;
-    const int range = int(blockIdx.x % unsigned(ranges));
-    const int tile = int(scattered_tile(int64_t(blockIdx.x / unsigned(ranges)), tiles, step));
+    const int grid = int(blockIdx.x % unsigned(grids)), range = grid / parts;
+    const int tile = int(scattered_tile(int64_t(blockIdx.x / unsigned(grids)), tiles, step));
     const int t0[3] = {(tile % ntx) * S::X, ((tile / ntx) % nty) * S::Y, PLANAR ? 0 : (tile / (ntx * nty)) * S::Z};
     const int dim[3] = {min(S::X, N - t0[0]), min(S::Y, N - t0[1]), PLANAR ? 1 : min(S::Z, N - t0[2])};
     const double cm = __longlong_as_double((long long)maxima[0]);
-    for (int i = int(threadIdx.x); i < S::WORDS; i += kTileBlock) acc[i] = 0;
-    for (int i = int(threadIdx.x); i < 4 * FLAGS; i += kTileBlock) bad[i] = 0;
+    for (int i = int(threadIdx.x); i < S::WORDS; i += BLOCK) acc[i] = 0;
+    for (int i = int(threadIdx.x); i < 4 * FLAGS; i += BLOCK) bad[i] = 0;
     double sr[OWN], si[OWN];
 #pragma unroll
     for (int o = 0; o < OWN; ++o) sr[o] = si[o] = 0.0;
@@ -770,7 +797,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
         __syncthreads();
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
-            const int nd = o * kTileBlock + int(threadIdx.x);
+            const int nd = o * BLOCK + int(threadIdx.x);
             unsigned long long* a = acc + (nd / S::X) * S::PITCH + nd % S::X;
             sr[o] += double((long long)a[0]) * inv;
             si[o] += double((long long)a[S::IMAG]) * inv;
@@ -779,7 +806,6 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
         __syncthreads();
     };
     const Fixed64 fixed;
-    const int wave = uniform(int(threadIdx.x) >> 6);
     const T half_box = T(0.5) * T(n_m);
     const int64_t b0 = int64_t(range) * per, b1 = b0 + per < B ? b0 + per : B;
     for (int64_t b = b0; b < b1; ++b) {
@@ -814,7 +840,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
         if (!finite) {  // uniform: every weight of a sample's stencil is NaN, and the stencil lies where the
                         // conversions put it; a sample without a term (a pose of scale zero) reaches nothing
             const int64_t K = sb == T(0) && !maxima[1] ? 0 : int64_t(n_m) * n_m * (PLANAR ? 1 : n_m);
-            for (int64_t kk = int64_t(threadIdx.x); kk < K; kk += kTileBlock) {
+            for (int64_t kk = int64_t(threadIdx.x); kk < K; kk += BLOCK) {
                 const cplx<T> ck = rho_m[kk] * (w_m[kk] * sb);
                 if (ck.re == T(0) && ck.im == T(0)) continue;
                 const int64_t row = kk / n_m;
@@ -845,78 +871,92 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
         const double most = fmin(cm * fabs(double(sb)), double(std::numeric_limits<T>::max()));
         const double pow2 = pow2_below(fmin(kFixedTop / most, 1e300));
         bool touched = false;  // uniform
-        int m0[3] = {0, 0, 0}, m1[3] = {0, 0, 0};
+        // a tap's node within the tile: on the torus where the sample's stencil was
+        // wrapped as a whole, else that of its image
+        auto tap = [&](int a, int at) { return DENSE && at >= N - t0[a] ? at - N : at; };
+        auto add_sample = [&](int i, int j, int k, const int o[3]) {
+            const int kk = (k * n_m + j) * n_m + i;
+            cplx<T> ck = rho_m[kk] * (w_m[kk] * sb);
+            if (ck.re == T(0) && ck.im == T(0)) return;
+            const bool fin_re = ck.re - ck.re == T(0), fin_im = ck.im - ck.im == T(0);
+            const double vr = fin_re ? double(ck.re) * pow2 : 0.0, vi = fin_im ? double(ck.im) * pow2 : 0.0;
+            const T xb[3] = {T(i) - half_box, T(j) - half_box, PLANAR ? T(0) : T(k) - half_box};
+            int b3[3] = {0, 0, 0};
+            T wgt[3][4];
 #pragma unroll
-        for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
-            const float base = float(t0[a] - tw[a]);
-            m0[a] = uniform(int(ceilf((ylo[a] - 0.05f - (base + float(dim[a] + 1))) / float(N))));
-            m1[a] = uniform(int(floorf((yhi[a] + 0.05f - (base - 2.f)) / float(N))));
-        }
-        for (int mz = m0[2]; mz <= m1[2]; ++mz)
-            for (int my = m0[1]; my <= m1[1]; ++my)
-                for (int mx = m0[0]; mx <= m1[0]; ++mx) {
-                    const int o[3] = {t0[0] - tw[0] + mx * N, t0[1] - tw[1] + my * N,
-                                      PLANAR ? 0 : t0[2] - tw[2] + mz * N};
-                    float lo[3], hi[3];
+            for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
+                const T y = tfr[a] + r[3 * a] * xb[0] + r[3 * a + 1] * xb[1] + r[3 * a + 2] * xb[2];
+                const T fl = dev_floor(y);
+                b3[a] = int(fl) - 1 - o[a];
+                if constexpr (DENSE) b3[a] = wrap(b3[a] + t0[a], N) - t0[a];
+                bspline3_weights(y - fl, wgt[a]);
+            }
 #pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        const float f = PLANAR && a == 2 ? 0.f : float(tfr[a]);
-                        lo[a] = float(o[a] - 2) - f;
-                        hi[a] = float(o[a] + dim[a] + 1) - f;
+            for (int cz = 0; cz < (PLANAR ? 1 : 4); ++cz) {
+                const int iz = PLANAR ? 0 : tap(2, b3[2] + cz);
+                if (unsigned(iz) >= unsigned(dim[2])) continue;
+#pragma unroll
+                for (int cy = 0; cy < 4; ++cy) {
+                    const int iy = tap(1, b3[1] + cy);
+                    if (unsigned(iy) >= unsigned(dim[1])) continue;
+                    const T wyz = PLANAR ? wgt[1][cy] : wgt[1][cy] * wgt[2][cz];
+                    const double row_re = vr * double(wyz), row_im = vi * double(wyz);
+                    const int row = iz * S::Y + iy;
+#pragma unroll
+                    for (int cx = 0; cx < 4; ++cx) {
+                        const int ix = tap(0, b3[0] + cx);
+                        if (unsigned(ix) >= unsigned(dim[0])) continue;
+                        unsigned long long* a = acc + row * S::PITCH + ix;
+                        if (!(fin_re && fin_im)) {
+                            const T wt = wgt[0][cx] * wyz;
+                            const int nd = row * S::X + ix;
+                            if (!fin_re) flag_term(bad, FLAGS, nd, ck.re * wt);
+                            if (!fin_im) flag_term(bad + 2 * FLAGS, FLAGS, nd, ck.im * wt);
+                        }
+                        atomicAdd(a, fixed(row_re * double(wgt[0][cx])));
+                        atomicAdd(a + S::IMAG, fixed(row_im * double(wgt[0][cx])));
                     }
-                    touched |= box_samples<PLANAR>(rf, n_m, lo, hi, wave, kTileBlock / 64, [&](int i, int j, int k) {
-                        const int kk = (k * n_m + j) * n_m + i;
-                        cplx<T> ck = rho_m[kk] * (w_m[kk] * sb);
-                        if (ck.re == T(0) && ck.im == T(0)) return;
-                        const bool fin_re = ck.re - ck.re == T(0), fin_im = ck.im - ck.im == T(0);
-                        const double vr = fin_re ? double(ck.re) * pow2 : 0.0, vi = fin_im ? double(ck.im) * pow2 : 0.0;
-                        const T xb[3] = {T(i) - half_box, T(j) - half_box, PLANAR ? T(0) : T(k) - half_box};
-                        int b3[3] = {0, 0, 0};
-                        T wgt[3][4];
-#pragma unroll
-                        for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
-                            const T y = tfr[a] + r[3 * a] * xb[0] + r[3 * a + 1] * xb[1] + r[3 * a + 2] * xb[2];
-                            const T fl = dev_floor(y);
-                            b3[a] = int(fl) - 1 - o[a];
-                            bspline3_weights(y - fl, wgt[a]);
-                        }
-#pragma unroll
-                        for (int cz = 0; cz < (PLANAR ? 1 : 4); ++cz) {
-                            const int iz = PLANAR ? 0 : b3[2] + cz;
-                            if (unsigned(iz) >= unsigned(dim[2])) continue;
-#pragma unroll
-                            for (int cy = 0; cy < 4; ++cy) {
-                                const int iy = b3[1] + cy;
-                                if (unsigned(iy) >= unsigned(dim[1])) continue;
-                                const T wyz = PLANAR ? wgt[1][cy] : wgt[1][cy] * wgt[2][cz];
-                                const double row_re = vr * double(wyz), row_im = vi * double(wyz);
-                                const int row = iz * S::Y + iy;
-#pragma unroll
-                                for (int cx = 0; cx < 4; ++cx) {
-                                    const int ix = b3[0] + cx;
-                                    if (unsigned(ix) >= unsigned(dim[0])) continue;
-                                    unsigned long long* a = acc + row * S::PITCH + ix;
-                                    if (!(fin_re && fin_im)) {
-                                        const T wt = wgt[0][cx] * wyz;
-                                        const int nd = row * S::X + ix;
-                                        if (!fin_re) flag_term(bad, FLAGS, nd, ck.re * wt);
-                                        if (!fin_im) flag_term(bad + 2 * FLAGS, FLAGS, nd, ck.im * wt);
-                                    }
-                                    atomicAdd(a, fixed(row_re * double(wgt[0][cx])));
-                                    atomicAdd(a + S::IMAG, fixed(row_im * double(wgt[0][cx])));
-                                }
-                            }
-                        }
-                    });
                 }
+            }
+        };
+        if constexpr (DENSE) {  // every sample of the body reaches the tile, or nearly
+            const int o[3] = {t0[0] - tw[0], t0[1] - tw[1], PLANAR ? 0 : t0[2] - tw[2]};
+            const int K = n_m * n_m * (PLANAR ? 1 : n_m);
+            for (int kk = grid % parts * BLOCK + int(threadIdx.x); kk < K; kk += parts * BLOCK)
+                add_sample(kk % n_m, kk / n_m % n_m, PLANAR ? 0 : kk / (n_m * n_m), o);
+            touched = true;
+        } else {
+            int m0[3] = {0, 0, 0}, m1[3] = {0, 0, 0};
+#pragma unroll
+            for (int a = 0; a < (PLANAR ? 2 : 3); ++a) {
+                const float base = float(t0[a] - tw[a]);
+                m0[a] = uniform(int(ceilf((ylo[a] - 0.05f - (base + float(dim[a] + 1))) / float(N))));
+                m1[a] = uniform(int(floorf((yhi[a] + 0.05f - (base - 2.f)) / float(N))));
+            }
+            for (int mz = m0[2]; mz <= m1[2]; ++mz)
+                for (int my = m0[1]; my <= m1[1]; ++my)
+                    for (int mx = m0[0]; mx <= m1[0]; ++mx) {
+                        const int o[3] = {t0[0] - tw[0] + mx * N, t0[1] - tw[1] + my * N,
+                                          PLANAR ? 0 : t0[2] - tw[2] + mz * N};
+                        float lo[3], hi[3];
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            const float f = PLANAR && a == 2 ? 0.f : float(tfr[a]);
+                            lo[a] = float(o[a] - 2) - f;
+                            hi[a] = float(o[a] + dim[a] + 1) - f;
+                        }
+                        touched |= box_samples<PLANAR>(rf, n_m, lo, hi, uniform(int(threadIdx.x) >> 6), BLOCK / 64,
+                                                       [&](int i, int j, int k) { add_sample(i, j, k, o); });
+                    }
+        }
         if (touched) flush(1.0 / pow2);
     }
     __syncthreads();  // flags of a pose that is not finite
     const int64_t G = PLANAR ? int64_t(N) * N : int64_t(N) * N * N;
-    cplx<T>* dst = out + int64_t(range) * G;
+    cplx<T>* dst = out + int64_t(grid) * G;
 #pragma unroll
     for (int o = 0; o < OWN; ++o) {
-        const int nd = o * kTileBlock + int(threadIdx.x);
+        const int nd = o * BLOCK + int(threadIdx.x);
         const int ix = nd % S::X, iy = (nd / S::X) % S::Y, iz = nd / (S::X * S::Y);
         if (ix >= dim[0] || iy >= dim[1] || iz >= dim[2]) continue;
         dst[(int64_t(t0[2] + iz) * N + t0[1] + iy) * N + t0[0] + ix] =
@@ -924,7 +964,7 @@ __global__ __launch_bounds__(kTileBlock) void fixed_tile_kernel(const cplx<T>* _
     }
 }
 
-// out = sum of the pose ranges' partial grids, in order
+// out = sum of the partial grids, in order
 template <typename T>
 __global__ void fixed_sum_kernel(const T* __restrict__ part, int ranges, int64_t count, T* __restrict__ out) {
     for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < count; i += int64_t(gridDim.x) * blockDim.x) {
@@ -1074,18 +1114,40 @@ hipError_t launch_score_grad(const void* rho_f, int N, bool planar, const void* 
     return hipGetLastError();
 }
 
-// Pose ranges of the fixed cotangent: grids of few tiles split the poses so
-// that about 4096 blocks run (the tiles a small box reaches are few, so one
-// range per resident block leaves some CUs with two busy tiles and most with
-// none); each range then has a partial grid.
-int64_t fixed_ranges(int64_t B, int N, bool planar) {
-    return std::max<int64_t>(1, std::min<int64_t>(4096 / fixed_tiles(N, planar), std::min<int64_t>(B, 64)));
+// How the fixed cotangent's work is cut.  Grids of few tiles split the poses into
+// ranges so that about 4096 blocks run (the tiles a small box reaches are few, so
+// one range per resident block leaves some CUs with two busy tiles and most with
+// none).  Where a tile with its stencils is half of the torus or more, or few
+// blocks would run at all, a block walks all samples, wrapped: the many images of
+// a small torus each cost a search of the body's lines.  With few blocks it walks
+// a part of them.  Each pose range and part has a partial grid.  FP32 calls: one
+// pose of a 16^3 body on 16^3 nodes 154 us by images, 63 by samples, 27 in four
+// parts; 3 of 17^3 on 17^3 158, 95, 47; one of 8^3 on 8^3 87, 22; but 25 of 16^3 on
+// 32^3 65, 116.
+constexpr int kDenseBlock = 1024;
+struct FixedSplit {
+    int64_t ranges, per, parts;  // per: poses of a range
+    bool dense;
+    int64_t grids() const { return ranges * parts; }
+};
+FixedSplit fixed_split(int64_t B, int N, int n_m, bool planar, bool split) {
+    const int64_t tiles = fixed_tiles(N, planar), K = int64_t(n_m) * n_m * (planar ? 1 : n_m);
+    FixedSplit f{1, B, 1, N <= (planar ? 48 : 20)};
+    if (!split) return f;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(4096 / tiles, std::min<int64_t>(B, 64)));
+    f.per = (B + most - 1) / most;
+    f.ranges = (B + f.per - 1) / f.per;
+    const int64_t blocks = tiles * f.ranges;
+    f.dense |= blocks <= 64 && N <= (planar ? 64 : 48);
+    // a part of 1024 samples (planar, a quarter of the taps: 4096) repays its sum
+    if (f.dense) f.parts = std::max<int64_t>(1, std::min(K / (planar ? 4 * kDenseBlock : kDenseBlock), 256 / blocks));
+    return f;
 }
 template <typename T>
-size_t fixed_cotangent_bytes(int64_t B, int N, bool planar, bool split) {
+size_t fixed_cotangent_bytes(int64_t B, int N, int n_m, bool planar, bool split) {
     const size_t G = size_t(N) * N * (planar ? 1 : N);
-    const int64_t r = split ? fixed_ranges(B, N, planar) : 1;
-    return fixed_table_bytes(B) + (r > 1 ? size_t(r) * G * 2 * sizeof(T) : 0);
+    const int64_t g = fixed_split(B, N, n_m, planar, split).grids();
+    return fixed_table_bytes(B) + (g > 1 ? size_t(g) * G * 2 * sizeof(T) : 0);
 }
 
 template <typename T>
@@ -1098,30 +1160,35 @@ hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool
     auto* maxima = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + fixed_table_bytes(B) - kFixedTail);
     auto* part = reinterpret_cast<cplx<T>*>(static_cast<char*>(ws) + fixed_table_bytes(B));
     const auto* rm = static_cast<const cplx<T>*>(rho_m);
-    hipLaunchKernelGGL(fixed_pose_kernel, dim3(unsigned((B + 127) / 128)), dim3(128), 0, s, poses, B, rot, maxima);
-    hipLaunchKernelGGL(fixed_max_kernel<T>, dim3(unsigned(std::min<int64_t>((K + 255) / 256, 256))), dim3(256), 0, s, rm,
-                       w_m, K, maxima);
+    if (K <= 16384 && B <= 2048) {  // one launch of a chain of three or four
+        hipLaunchKernelGGL(fixed_prep_kernel<T>, dim3(1), dim3(1024), 0, s, rm, w_m, K, poses, B, rot, maxima);
+    } else {
+        hipLaunchKernelGGL(fixed_pose_kernel, dim3(unsigned((B + 127) / 128)), dim3(128), 0, s, poses, B, rot, maxima);
+        hipLaunchKernelGGL(fixed_max_kernel<T>, dim3(unsigned(std::min<int64_t>((K + 255) / 256, 256))), dim3(256), 0, s,
+                           rm, w_m, K, maxima);
+    }
     const int64_t tiles = fixed_tiles(N, planar);
-    int64_t ranges = 1;
-    if (ws_bytes >= fixed_cotangent_bytes<T>(B, N, planar, true))
-        ranges = fixed_ranges(B, N, planar);
-    const int64_t per = (B + ranges - 1) / ranges;
-    ranges = (B + per - 1) / per;
-    cplx<T>* dst = ranges > 1 ? part : static_cast<cplx<T>*>(grad_f);
+    const FixedSplit f =
+        fixed_split(B, N, n_m, planar, ws_bytes >= fixed_cotangent_bytes<T>(B, N, n_m, planar, true));
+    cplx<T>* dst = f.grids() > 1 ? part : static_cast<cplx<T>*>(grad_f);
     // the ranges of a tile side by side and the tiles scattered, so that every
     // CU gets its share of the body's tiles (64^3 field, 32 poses of a 32^3
     // body: 334 us with the tiles in order, 213 so)
-    const dim3 grid{unsigned(ranges * tiles), 1u, 1u};
     const int64_t step = tile_step(tiles);
-    if (planar)
-        hipLaunchKernelGGL((fixed_tile_kernel<T, true>), grid, dim3(kTileBlock), 0, s, rm, w_m, n_m, rot, poses,
-                           grad_scale, B, per, int(ranges), N, tiles, step, maxima, dst);
-    else
-        hipLaunchKernelGGL((fixed_tile_kernel<T, false>), grid, dim3(kTileBlock), 0, s, rm, w_m, n_m, rot, poses,
-                           grad_scale, B, per, int(ranges), N, tiles, step, maxima, dst);
-    if (ranges > 1)
+    auto run = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(f.grids() * tiles)), dim3(threads), 0, s, rm, w_m, n_m, rot, poses,
+                           grad_scale, B, f.per, int(f.grids()), int(f.parts), N, tiles, step, maxima, dst);
+    };
+    if (f.dense) {
+        if (planar) run(fixed_tile_kernel<T, true, kDenseBlock, true>, kDenseBlock);
+        else run(fixed_tile_kernel<T, false, kDenseBlock, true>, kDenseBlock);
+    } else {
+        if (planar) run(fixed_tile_kernel<T, true, kTileBlock, false>, kTileBlock);
+        else run(fixed_tile_kernel<T, false, kTileBlock, false>, kTileBlock);
+    }
+    if (f.grids() > 1)
         hipLaunchKernelGGL(fixed_sum_kernel<T>, dim3(unsigned(std::min<int64_t>((2 * G + 255) / 256, 4096))), dim3(256),
-                           0, s, reinterpret_cast<const T*>(part), int(ranges), 2 * G, static_cast<T*>(grad_f));
+                           0, s, reinterpret_cast<const T*>(part), int(f.grids()), 2 * G, static_cast<T*>(grad_f));
     return hipGetLastError();
 }
 
@@ -1139,8 +1206,8 @@ hipError_t launch_rho_from_c(const T* w_m, const void* grad_c, int64_t K, void* 
 template hipError_t launch_rho_from_c<float>(const float*, const void*, int64_t, void*, hipStream_t);
 template hipError_t launch_rho_from_c<double>(const double*, const void*, int64_t, void*, hipStream_t);
 
-template size_t fixed_cotangent_bytes<float>(int64_t, int, bool, bool);
-template size_t fixed_cotangent_bytes<double>(int64_t, int, bool, bool);
+template size_t fixed_cotangent_bytes<float>(int64_t, int, int, bool, bool);
+template size_t fixed_cotangent_bytes<double>(int64_t, int, int, bool, bool);
 template hipError_t launch_fixed_cotangent<float>(const void*, const float*, int, bool, int, const double*, int64_t,
                                                   const double*, void*, void*, size_t, hipStream_t);
 template hipError_t launch_fixed_cotangent<double>(const void*, const double*, int, bool, int, const double*, int64_t,

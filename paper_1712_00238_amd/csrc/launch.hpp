@@ -241,9 +241,9 @@ template <typename T>
 size_t grad_workspace_bytes(int64_t B, int N, int n_m, bool planar, int wmode, bool fine);
 // cotangent of sum_b s_b f_b with respect to rho_F (complex, every node
 // written); ws: fixed_cotangent_bytes, with `split` so much that grids of few
-// tiles can divide the poses over more blocks
+// tiles can divide the poses, and calls of few blocks the samples, over more blocks
 template <typename T>
-size_t fixed_cotangent_bytes(int64_t B, int N, bool planar, bool split);
+size_t fixed_cotangent_bytes(int64_t B, int N, int n_m, bool planar, bool split);
 template <typename T>
 hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool planar, int N, const double* poses,
                                   int64_t B, const double* grad_scale, void* grad_f, void* ws, size_t ws_bytes,

@@ -194,3 +194,16 @@ def test_one_large_coefficient_leaves_the_others_theirs(ctxs, dtype):
     err = np.abs(fixed(ctxs[dtype], gf, rho_m, w, gm, poses, s).reshape(shape) - ref)[away].max()
     flush_print("error", err / np.abs(ref[away]).max())
     assert err <= (1e-13 if dtype == "f64" else 1e-5) * np.abs(ref[away]).max()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,nm,planar,count", [(4, 3, False, 70), (8, 8, False, 1), (20, 20, False, 9), (21, 21, False, 9),
+                                               (48, 48, True, 9), (49, 49, True, 9), (5, 5, True, 2)])
+def test_small_tori(ctxs, dtype, n, nm, planar, count):
+    """Fields on either side of the rule that walks all samples for every tile, with
+    the largest boxes, against the oracle (positions and weights rounded once each)."""
+    gf, gm, rho_m, w, poses, s = case(n, nm, planar, count, n + count)
+    flush_print("small torus", dtype, n, nm, planar, count)
+    got = fixed(ctxs[dtype], gf, rho_m, w, gm, poses, s).reshape(gf.n[::-1])
+    ref = og.fixed_cotangent(oc.moving_coefficients(rho_m, w), osp.body_positions(nm, planar), poses, s, gf.n[::-1])
+    assert np.max(np.abs(got - ref)) <= (1e-12 if dtype == "f64" else 1e-5) * np.abs(ref).max()
