@@ -1744,7 +1744,7 @@ void enqueue_few(const double* q, const double* n, const double* w, int64_t ns, 
 }
 // Up to how many samples that is the faster way.  On small grids it is a serial
 // chain of 0.25 us a sample: 64 samples on 32^3 nodes 20.6 us (the tree 33.5), 200
-// 57 (45).  On large ones the tree's walk costs a wave of 16 nodes as much as some
+// 57 (45), on 8^3 64 19 (20), FP64 24 (18).  On large ones the tree's walk costs a wave of 16 nodes as much as some
 // hundred pairs of each: on 128^3 nodes 1 sample takes 19 us (the tree 169), 64 142
 // (393), 300 610 (900), 500 1006 (1079); FP64 64 340 (483), 300 1536 (1543), 400
 // 2040 (1916); on 64^3 300 116 (150), 500 190 (190).  The signed distance alone
@@ -1753,7 +1753,7 @@ bool few_samples(int64_t ns, const GridDesc& g, int phi, bool wide) {
     const int64_t nodes = int64_t(g.nx) * g.ny * g.nz;
     if (brick_count(g) * kSdfBlock > 2 * nodes) return ns <= 64 && nodes <= 4096;  // thin grids fill few lanes
     if (phi == kPhiDsl) return ns <= 512;
-    if (nodes < (1 << 18)) return ns <= 64;
+    if (nodes < (1 << 18)) return ns <= (wide ? 32 : 64);
     return ns <= (wide || nodes < (1 << 20) ? 300 : kFewMax);
 }
 
