@@ -165,8 +165,10 @@ int sdf_ctx_stats_reset(sdf_ctx ctx);
  * g->n[0]*n[1]*n[2].  g, p: host structs.  Any grid shape is accepted.
  * The samples are put in Hilbert order in the context's workspace (about
  * 70 bytes per sample), which the next call of any entry point may reuse.
- * The FP32 sum uses about 200 bytes per sample more where the workspace cap
- * allows; below that it sums pair by pair.
+ * The FP32 sum uses about 200 bytes per sample more where the workspace cap and
+ * the device's memory allow; below that it sums pair by pair.  A sample whose
+ * position is not finite counts nowhere, one whose weight or normal is not makes
+ * the nodes with it in their ball not finite, and no others.
  * Errors: SDF_EINVAL (null pointer, n <= 0 or n > 2^30, bad grid, invalid
  * params), SDF_ENOMEM (workspace). */
 int sdf_build(sdf_ctx ctx, const void *q, const void *nrm, const void *w, int64_t n,
@@ -423,10 +425,14 @@ int score_grad_coef(sdf_ctx ctx, const void *rho_fixed, const sdf_grid *g_fixed,
  *   grad_f(p) = sum_b s_b sum_k c_k B3(p - R_b x_k / h - t_b),   periodic,
  * with c_k = w_k rho_M(x_k) and s_b = grad_scale[b] (or 1): complex, the fixed
  * grid's size and layout, context precision, overwritten.  With
- * sdf_build_adjoint it gives the fixed part's shape gradients.  Sums are
- * integers and taken in a fixed order (runs repeat bit for bit).  Same
- * constraints as score_grad; rho_fixed is not needed.  Small grids use a partial
- * grid per range of poses (up to 64 of them) where the workspace cap allows.
+ * sdf_build_adjoint it gives the fixed part's shape gradients.  A pose's sums are
+ * integers, in units of at most 2^-57 of its largest |c_k s_b|, and the poses are
+ * added in a fixed order (runs repeat bit for bit).  Terms that are not finite, and
+ * those of a pose that is not, leave infinities and NaN at the nodes they reach; a
+ * pose with s_b = 0 adds nothing, whatever it holds.  Same constraints as
+ * score_grad; rho_fixed is not needed.  Small grids use partial grids (per range of
+ * poses or part of the samples) where the workspace cap and the device's memory
+ * allow.
  * Errors: SDF_EINVAL, SDF_ENOMEM, SDF_EHIP. */
 int score_grad_fixed(sdf_ctx ctx, const sdf_grid *g_fixed, const void *rho_moving, const void *w_moving,
                      const sdf_grid *g_moving, const double *poses, int64_t B, const double *grad_scale,

@@ -1464,7 +1464,7 @@ __global__ __launch_bounds__(slab_block(N)) void islab_peak_kernel(const cf* __r
 // Bound by the latency of a dozen dependent steps: with two threads a row at
 // N = 64 (half the block idle), the twiddles before the partials' loads and
 // eight barriers in the argmax 9 rotations of 64^3 took 10.6 us, 9.3 so (192 of
-// 128^3: 31 either way).
+// 128^3: 31 either way).  Smaller sizes were not timed and keep two threads a row.
 template <int N>
 __global__ __launch_bounds__(kFinishBlock) void finish_slab_kernel(const cf* __restrict__ packed, int nz,
                                                                    const float* __restrict__ pval,

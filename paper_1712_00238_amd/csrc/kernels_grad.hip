@@ -745,7 +745,7 @@ __global__ __launch_bounds__(1024) void fixed_prep_kernel(const cplx<T>* __restr
 // in reach (DENSE: all samples, or a part of them, wrapped) add their taps to LDS
 // sums; each node is stored once, to out or to a partial grid.  It replaces one global atomic
 // pair per tap, at 23 billion a second: 32 poses of a 32^3 box on 64^3 nodes
-// 5.9 -> 0.33 ms.  Bound by LDS adds and VALU issue.
+// 5.9 -> 0.26 ms.  Bound by LDS adds and VALU issue.
 // Sums of a pose are 64-bit integers in units of at most 2^-57 max|c_k| |s_b|, and
 // move to FP64 registers after each pose, in order: runs repeat bit for bit, and
 // poses of any scale keep their digits beside larger ones (one scale for all
@@ -1173,7 +1173,8 @@ hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool
     cplx<T>* dst = f.grids() > 1 ? part : static_cast<cplx<T>*>(grad_f);
     // the ranges of a tile side by side and the tiles scattered, so that every
     // CU gets its share of the body's tiles (64^3 field, 32 poses of a 32^3
-    // body: 334 us with the tiles in order, 213 so)
+    // body: 334 us with the tiles in order, 213 so, of FP32 terms rounded to one
+    // word; 265 with the two-word ones)
     const int64_t step = tile_step(tiles);
     auto run = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(unsigned(f.grids() * tiles)), dim3(threads), 0, s, rm, w_m, n_m, rot, poses,

@@ -153,8 +153,8 @@ __global__ void spread_atomic_kernel(const cplx<T>* __restrict__ c, int n_m, int
 // to at most 1.01 at any point, those of a part of it to less, so no sum reaches
 // 2^63.  Nodes are centred coordinates [-N/2, N/2): the fit rule keeps every
 // stencil inside, so no index wraps before the store.
-// Bound by VALU issue (6 instructions per FP64 sum besides its LDS add).  FP64,
-// 8 rotations of 96^3 / 48^3: the whole search 6212 -> 413 us, 180 of them here;
+// Bound by VALU issue (6 instructions per sum besides its LDS add).  FP64, 8
+// rotations of 96^3 / 48^3: the whole search 6212 -> 461 us, 217 of them here;
 // 36 rotations of 128^2 / 64^2: 1930 -> 65 us (with the batched and fused
 // transform passes).
 constexpr double kTileTop = 4611686018427387904.0;  // 2^62: |c| in units
@@ -162,7 +162,8 @@ constexpr double kTileTop = 4611686018427387904.0;  // 2^62: |c| in units
 // The r-th tile from the middle of the grid outwards.  The body's tiles take
 // nearly all of the time; launched first, over all rotations, they spread over
 // the CUs evenly and none is left for the end (FP64, 96^3, 8 rotations of a 48^3
-// body: 420 us for the search in row order, 413 so; 12 of 128^3: 1300 and 1215).
+// body: 420 us for the search in row order, 413 so, repeated on the same buffers;
+// 12 of 128^3: 1300 and 1215).
 // 3D tiles are half as thick as wide, and
 // shell k of the nested boxes of 2k x 2k x 4k tiles holds its two lowest and two
 // highest layers, then the rings of the layers between; grids of less than two
@@ -768,8 +769,8 @@ hipError_t launch_spread_tiles(const void* c, int n_m, bool planar, const T* R, 
         const unsigned tx = unsigned(N / (S::X < N ? S::X : N)), ty = unsigned(N / (S::Y < N ? S::Y : N)),
                        tz = unsigned(N / (S::Z < N ? S::Z : N));
         // A call of few tiles ends with its slowest: eight waves a tile halve
-        // that, where many tiles keep every CU busy with four (FP64: 413 / 455 us
-        // for a search of 8 rotations at 96^3, 3456 tiles; 1214 / 1191 for 12 at
+        // that, where many tiles keep every CU busy with four (FP64, repeated: 413 /
+        // 455 us for a search of 8 rotations at 96^3, 3456 tiles; 1214 / 1191 for 12 at
         // 128^3, 12288).
         const dim3 grid{unsigned(n_rot), tx * ty * tz, 1u};
         if (int64_t(n_rot) * tx * ty * tz <= 8192)

@@ -40,7 +40,9 @@
 //     relative to the cluster's centre, |p - q|^2 = |p|^2 + (-2 q, |q|^2).(p, 1) and
 //     (p - q).wn = (wn, -q.wn).(p, 1): two 16 x 16 x 4 FP32 MFMAs give 16 nodes x 16
 //     samples of each, 9 of the 23 vector instructions of a pair.  Clusters
-//     closer than their own radius cancel too much and take differences.
+//     closer than their own radius cancel too much, and those with a record that
+//     is not finite would reach nodes that they do not concern: these take FP64
+//     differences, sample by sample.
 // Bound by VALU issue (88% busy): about 60 instructions per 16 x 16 pairs beyond
 // the 14 of each pair's term.  Measured, whole builds on 128^3 nodes: 242k samples
 // of a union of 2000 spheres 322 -> 64 ms, 15.7k samples of a box with a bore 23.0
@@ -1619,7 +1621,7 @@ inline SdfWs sdf_ws_layout(int64_t n) {
 }
 
 struct Prepared {
-    SampleTiles st;       // 256-sample tiles (radial and adjoint kernels)
+    SampleTiles st;       // sorted samples, and 256-sample tiles (radial kernel)
     SampleTree tr;
     const TreeNode* node;
     const float *rec1, *rec2;
