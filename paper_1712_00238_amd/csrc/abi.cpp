@@ -82,6 +82,7 @@ struct sdf_ctx_s {
     size_t cap = 0;
     void* ws = nullptr;
     size_t ws_bytes = 0;
+    size_t ws_refused = SIZE_MAX;  // the least size that the device has refused
     std::string err;
     int64_t opt_path = 0;
     int64_t opt_batch = 64;
@@ -293,12 +294,15 @@ int ensure_either(sdf_ctx ctx, size_t want, size_t least, hipStream_t s, size_t*
     if (want > least && (!ctx->cap || want <= ctx->cap)) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
         size_t room = 0, all = 0;
+        // after a refusal the device is asked first: an attempt gives the workspace back
         if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
-            hipMemGetInfo(&room, &all) == hipSuccess && want <= room + ctx->ws_bytes) {
+            (want < ctx->ws_refused ||
+             (hipMemGetInfo(&room, &all) == hipSuccess && want <= room + ctx->ws_bytes))) {
             const std::string ctx_err = ctx->err, last_err = g_err;
             if (ensure_ws(ctx, want) == SDF_OK) return SDF_OK;
             ctx->err = ctx_err;
             g_err = last_err;
+            ctx->ws_refused = std::min(ctx->ws_refused, want);
         }
         (void)hipGetLastError();
     }

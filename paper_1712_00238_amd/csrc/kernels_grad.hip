@@ -767,15 +767,12 @@ __device__ __forceinline__ double flagged(const unsigned* flags, int words, int 
     return up ? (down ? NAN : INFINITY) : (down ? -INFINITY : 0.0);
 }
 template <typename T, bool PLANAR, int BLOCK, bool DENSE>
-__global__ __launch_bounds__(BLOCK, BLOCK == kTileBlock ? 3 : 1) void fixed_tile_kernel(const cplx<T>* __restrict__ rho_m,
-                                                                const T* __restrict__ w_m, int n_m,
-                                                                const double* __restrict__ rot,
-                                                                const double* __restrict__ poses,
-                                                                const double* __restrict__ gscale, int64_t B,
-                                                                int64_t per, int grids, int parts, int N,
-                                                                int64_t tiles, int64_t step,
-                                                                const unsigned long long* __restrict__ maxima,
-                                                                cplx<T>* __restrict__ out) {
+__global__ __launch_bounds__(BLOCK, BLOCK == kTileBlock ? 3 : 1)
+void fixed_tile_kernel(const cplx<T>* __restrict__ rho_m, const T* __restrict__ w_m, int n_m,
+                       const double* __restrict__ rot, const double* __restrict__ poses,
+                       const double* __restrict__ gscale, int64_t B, int64_t per, int grids, int parts, int N,
+                       int64_t tiles, int64_t step, const unsigned long long* __restrict__ maxima,
+                       cplx<T>* __restrict__ out) {
     using S = SpreadTile<PLANAR>;
     constexpr int OWN = S::X * S::Y * S::Z / BLOCK;  // nodes a thread stores
     __shared__ unsigned long long acc[S::WORDS];
@@ -1164,8 +1161,8 @@ hipError_t launch_fixed_cotangent(const void* rho_m, const T* w_m, int n_m, bool
         hipLaunchKernelGGL(fixed_prep_kernel<T>, dim3(1), dim3(1024), 0, s, rm, w_m, K, poses, B, rot, maxima);
     } else {
         hipLaunchKernelGGL(fixed_pose_kernel, dim3(unsigned((B + 127) / 128)), dim3(128), 0, s, poses, B, rot, maxima);
-        hipLaunchKernelGGL(fixed_max_kernel<T>, dim3(unsigned(std::min<int64_t>((K + 255) / 256, 256))), dim3(256), 0, s,
-                           rm, w_m, K, maxima);
+        const unsigned blocks = unsigned(std::min<int64_t>((K + 255) / 256, 256));
+        hipLaunchKernelGGL(fixed_max_kernel<T>, dim3(blocks), dim3(256), 0, s, rm, w_m, K, maxima);
     }
     const int64_t tiles = fixed_tiles(N, planar);
     const FixedSplit f =

@@ -197,8 +197,9 @@ def test_one_large_coefficient_leaves_the_others_theirs(ctxs, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("n,nm,planar,count", [(4, 3, False, 70), (8, 8, False, 1), (20, 20, False, 9), (21, 21, False, 9),
-                                               (48, 48, True, 9), (49, 49, True, 9), (5, 5, True, 2)])
+@pytest.mark.parametrize("n,nm,planar,count", [(4, 3, False, 70), (8, 8, False, 1), (20, 20, False, 9),
+                                               (21, 21, False, 9), (48, 48, True, 9), (49, 49, True, 9),
+                                               (5, 5, True, 2), (30, 30, False, 1), (64, 64, True, 3)])
 def test_small_tori(ctxs, dtype, n, nm, planar, count):
     """Fields on either side of the rule that walks all samples for every tile, with
     the largest boxes, against the oracle (positions and weights rounded once each)."""

@@ -173,14 +173,17 @@ def test_build_where_memory_holds_only_the_least_workspace():
         torch.cuda.synchronize()
         flush_print("free before", torch.cuda.mem_get_info()[0])
         while torch.cuda.mem_get_info()[0] > left + (16 << 20):
-            held.append(torch.empty(min(torch.cuda.mem_get_info()[0] - left, 16 << 30), dtype=torch.uint8, device="cuda"))
+            size = min(torch.cuda.mem_get_info()[0] - left, 16 << 30)
+            held.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
         flush_print("free", torch.cuda.mem_get_info()[0])
         try:
             got = ctx.sdf_build(q, n, w, grid, PARAMS)
+            again = ctx.sdf_build(q, n, w, grid, PARAMS)
             torch.cuda.synchronize()
         finally:
             held.clear()
             torch.cuda.empty_cache()
+    assert torch.equal(got, again)
     # sequential FP32 sums of up to 1.6e5 terms a lane
     assert float((got.to(torch.complex128) - ref).abs().max()) <= 1e-3 * float(ref.abs().max())
 
@@ -206,7 +209,8 @@ def test_ball_edges_in_a_wide_leaf(ctxs, outlier):
     balls hold and some do not, and an outlier.  Whether the second counts is
     decided in FP64."""
     s = shapes.PointSamples(np.array([[0.3, 0.2, -0.1], [7.9, 0.4, 0.7], [outlier, 0.5 * outlier, 0.3 * outlier]]),
-                            np.array([[1.0, 0.0, 0.0], [0.6, 0.0, 0.8], [1.0, 0.0, 0.0]]), np.array([1e-12, 1.0, 1e-12]))
+                            np.array([[1.0, 0.0, 0.0], [0.6, 0.0, 0.8], [1.0, 0.0, 0.0]]),
+                            np.array([1e-12, 1.0, 1e-12]))
     grid = C.GridSpec((96, 96, 96), (-4.03, -4.01, -4.02), 0.0837)
     a, b = (np.abs(build(ctxs[d], s, grid)) for d in ("f32", "f64"))
     in_a, in_b = a > 1e-6 * a.max(), b > 1e-6 * b.max()

@@ -38,7 +38,8 @@ def grid(n, extent=14.0):
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("n", [(9, 10, 11), (33, 1, 1), (1, 1, 70), (30, 31, 1), (64, 64, 64), (128, 90, 91), (1024, 1024, 1)])
+@pytest.mark.parametrize("n", [(9, 10, 11), (33, 1, 1), (1, 1, 70), (30, 31, 1), (64, 64, 64), (128, 90, 91),
+                               (1024, 1024, 1)])
 @pytest.mark.parametrize("count", [1, 32, 33, 64, 65, 300, 301, 576, 577])
 def test_against_the_tree(ctxs, dtype, n, count):
     """The decisions are the same FP64 ones; sums differ by their order and form (3e-5
